@@ -131,24 +131,125 @@ __device__ __forceinline__ int32_t quantise_hi(float v, float inv, float s0, uin
     return apply_sign((T >> 16) + (hi16 < th ? 1u : 0u), v);
 }
 
-// The same decision for two coordinates at once in the 16-bit lanes of one
-// register (packed integer ops): T0, T1 as above, r01 their high random
-// halves (coordinate 0 in the low lane).  Returns the two codes as 16-bit
-// two's complement lanes.  one2 holds 1 in both lanes; it is passed in so
-// that the packed min is not rewritten as two compares and selects.
-__device__ __forceinline__ uint32_t pair_codes(uint32_t T0, uint32_t T1, float v0, float v1, uint32_t r01,
-                                               uint32_t one2)
+// The Philox blocks of one lane for several rows of a tile.  A tile's lanes
+// share the counter's high word and each row's worker id, so the products of
+// the first two rounds split into a part that depends on the row alone
+// (RowKey: scalar arithmetic) and one that depends on the lane alone
+// (LaneKey: once for all rows); a row then costs 16 products instead of 19.
+struct RowKey {
+    uint32_t n0, n1;      // counter words 0 and 1 after round 1
+    uint32_t p_hi, p_lo;  // round 2's product of word 0
+};
+struct LaneKey {
+    uint32_t n3;          // counter word 3 after round 1
+    uint32_t p_hi, p_lo;  // round 2's product of word 2
+};
+
+__device__ __forceinline__ RowKey row_key(uint32_t c1, uint32_t worker, uint32_t key0)
 {
-    const u16x2 lev = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(T1, T0, 0x07060302u));
-    const u16x2 th = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(T1, T0, 0x05040100u));
-    // max(th - r, 0) > 0 exactly when r < th
-    const u16x2 up = __builtin_elementwise_min(__builtin_elementwise_sub_sat(th, __builtin_bit_cast(u16x2, r01)),
-                                               __builtin_bit_cast(u16x2, one2));
-    const u16x2 mag = lev + up;
+    const uint64_t pb = static_cast<uint64_t>(0xCD9E8D57u) * worker;
+    RowKey r;
+    r.n0 = static_cast<uint32_t>(pb >> 32) ^ c1 ^ key0;
+    r.n1 = static_cast<uint32_t>(pb);
+    const uint64_t pa = static_cast<uint64_t>(0xD2511F53u) * r.n0;
+    r.p_hi = static_cast<uint32_t>(pa >> 32);
+    r.p_lo = static_cast<uint32_t>(pa);
+    return r;
+}
+
+__device__ __forceinline__ LaneKey lane_key(uint32_t c0, uint32_t c3, uint32_t key1)
+{
+    const uint64_t pa = static_cast<uint64_t>(0xD2511F53u) * c0;
+    LaneKey l;
+    l.n3 = static_cast<uint32_t>(pa);
+    const uint64_t pb = static_cast<uint64_t>(0xCD9E8D57u) * (static_cast<uint32_t>(pa >> 32) ^ c3 ^ key1);
+    l.p_hi = static_cast<uint32_t>(pb >> 32);
+    l.p_lo = static_cast<uint32_t>(pb);
+    return l;
+}
+
+// The complement of philox4x32_10(c0, c1, worker, c3, key) from its row and
+// lane parts (words 0 and 2 are complemented by the last round's
+// three-operand xors: truth table 0x69).
+__device__ __forceinline__ uint4 philox_tail_not(const RowKey& r, const LaneKey& l, uint32_t key0, uint32_t key1)
+{
+    uint32_t k0 = key0 + 0x9E3779B9u, k1 = key1 + 0xBB67AE85u;
+    uint32_t c0 = __builtin_amdgcn_bitop3_b32(l.p_hi, r.n1, k0, 0x96);
+    uint32_t c1 = l.p_lo;
+    uint32_t c2 = __builtin_amdgcn_bitop3_b32(r.p_hi, l.n3, k1, 0x96);
+    uint32_t c3 = r.p_lo;
+#pragma unroll
+    for (int round = 2; round < 10; ++round) {
+        k0 += 0x9E3779B9u;
+        k1 += 0xBB67AE85u;
+        const uint64_t pa = static_cast<uint64_t>(0xD2511F53u) * c0;
+        const uint64_t pb = static_cast<uint64_t>(0xCD9E8D57u) * c2;
+        if (round < 9) {
+            c0 = __builtin_amdgcn_bitop3_b32(static_cast<uint32_t>(pb >> 32), c1, k0, 0x96);
+            c2 = __builtin_amdgcn_bitop3_b32(static_cast<uint32_t>(pa >> 32), c3, k1, 0x96);
+            c1 = static_cast<uint32_t>(pb);
+            c3 = static_cast<uint32_t>(pa);
+        } else {
+            c0 = __builtin_amdgcn_bitop3_b32(static_cast<uint32_t>(pb >> 32), c1, k0, 0x69);
+            c2 = __builtin_amdgcn_bitop3_b32(static_cast<uint32_t>(pa >> 32), c3, k1, 0x69);
+            c1 = ~static_cast<uint32_t>(pb);
+            c3 = ~static_cast<uint32_t>(pa);
+        }
+    }
+    return make_uint4(c0, c1, c2, c3);
+}
+
+// v_cvt_u32_f32: truncates, with 0 for NaN and for negative values and
+// 0xFFFFFFFF for values of 2^32 and above (a C++ conversion leaves those
+// undefined).
+__device__ __forceinline__ uint32_t cvt_u32_sat(float x)
+{
+    uint32_t r;
+    __asm__("v_cvt_u32_f32_e32 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
+// The largest of the low 16 bits of a, b and c, in the low 16 bits (the high
+// half of the result is not defined).
+__device__ __forceinline__ uint32_t max3_lo16(uint32_t a, uint32_t b, uint32_t c)
+{
+    uint32_t r;
+    __asm__("v_max3_u16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// Adds half `half` (0: low, 1: high) of `halves` to t.
+template <int HALF>
+__device__ __forceinline__ uint32_t add_half(uint32_t t, uint32_t halves)
+{
+    return t + (HALF ? halves >> 16 : halves & 0xFFFFu);
+}
+
+// Signs of two coordinates as 16-bit lanes: 1 or -1 (by the sign bits).
+__device__ __forceinline__ u16x2 pair_signs(float v0, float v1)
+{
     // 0xFFFF in the lane of a negative v (replicated sign bits of the top bytes)
-    const u16x2 neg = __builtin_bit_cast(
-        u16x2, __builtin_amdgcn_perm(__float_as_uint(v1), __float_as_uint(v0), 0x0B0B0909u));
-    return __builtin_bit_cast(uint32_t, static_cast<u16x2>((mag ^ neg) - neg));
+    const uint32_t neg = __builtin_amdgcn_perm(__float_as_uint(v1), __float_as_uint(v0), 0x0B0B0909u);
+    return __builtin_bit_cast(u16x2, neg | 0x00010001u);
+}
+
+// |code| of one coordinate from its whole uniform word (hi16, lo16):
+// l + [r < t], 0 for a NaN or infinite v.  inv and s0x carry a factor of
+// 2^16 when PRE (the products are then finite for finite v, up to overflow
+// to infinity, which the minimum takes to s0); else inv may be infinite and
+// the factor is applied after the minimum.
+template <bool PRE>
+__device__ __forceinline__ uint32_t exact_magnitude(float v, float inv, float s0x, uint32_t hi16, uint32_t lo16)
+{
+    float xs;
+    if (PRE)
+        xs = __builtin_amdgcn_classf(v, kNonFinite) ? 0.0f : fminf(fabsf(v) * inv, s0x);
+    else
+        xs = scaled_magnitude(v, inv, s0x) * 65536.0f;
+    const uint32_t T = static_cast<uint32_t>(xs);
+    const uint32_t th = T & 0xFFFFu;
+    const uint32_t t_lo = static_cast<uint32_t>((xs - floorf(xs)) * 65536.0f);
+    return (T >> 16) + ((hi16 < th || (hi16 == th && lo16 < t_lo)) ? 1u : 0u);
 }
 
 // The tied case: [r < t] decided by the low halves of r and t.
@@ -157,14 +258,6 @@ __device__ __forceinline__ int32_t quantise_tie(float v, float x, uint32_t lo16)
     const float lf = floorf(x);
     const uint32_t t = static_cast<uint32_t>((x - lf) * 4294967296.0f);
     return apply_sign(static_cast<uint32_t>(lf) + (lo16 < (t & 0xFFFFu) ? 1u : 0u), v);
-}
-
-// The tied case from xs = x * 2^16 and T = floor(xs): the low half of t is
-// floor((xs - T) * 2^16).
-__device__ __forceinline__ int32_t quantise_tie_scaled(float v, float xs, uint32_t T, uint32_t lo16)
-{
-    const uint32_t t_lo = static_cast<uint32_t>((xs - floorf(xs)) * 65536.0f);
-    return apply_sign((T >> 16) + (lo16 < t_lo ? 1u : 0u), v);
 }
 
 // Deterministic wave64 sum of a double (fixed butterfly order).

@@ -905,12 +905,6 @@ __device__ __forceinline__ void tile_halves(uint4 w, bool odd, uint32_t* a01, ui
     *b23 = odd ? keep23 : recv23;
 }
 
-__device__ __forceinline__ uint32_t half16(uint32_t packed01, uint32_t packed23, int j)
-{
-    const uint32_t w = j < 2 ? packed01 : packed23;
-    return (j & 1) ? (w >> 16) : (w & 0xFFFFu);
-}
-
 // BITS = 8: int8 codes.  BITS = 4 or 2: codes packed low bits first, two or
 // four to a byte (every |code| <= s_0 fits the field; checked on the host).
 template <int BITS>
@@ -957,13 +951,6 @@ __device__ __forceinline__ void store_pairs(uint8_t* row, int64_t coord, uint32_
     }
 }
 
-// Replaces 16-bit lane (j & 1) of *p with code c.
-__device__ __forceinline__ void set_lane16(uint32_t* p, int j, int32_t c)
-{
-    const uint32_t u = static_cast<uint32_t>(c) & 0xFFFFu;
-    *p = (j & 1) ? ((*p & 0xFFFFu) | (u << 16)) : ((*p & 0xFFFF0000u) | u);
-}
-
 // One tile's inputs for one lane: its A and B gradient quads and, with
 // several scales, their four scale indices each.
 struct TileIn {
@@ -1005,68 +992,98 @@ __device__ __forceinline__ TileIn load_tile(const float* __restrict__ row, const
     return in;
 }
 
-// The eight codes of one lane for tile T of worker `worker`, as four 16-bit
-// lane pairs (A0 A1, A2 A3, B0 B1, B2 B3).  v: the lane's coordinates;
-// inv: their s_k / W, times 2^16 when PRE (then s0x = s0 * 2^16).  Every lane
-// of the wave must call it (DPP exchange, wave-uniform branches).
+// This lane's Philox counter word 0 in tile T (and the tile's word 1): block
+// 64 T + u for even lane 2u, 64 T + 32 + u for odd lane 2u + 1.
+__device__ __forceinline__ uint32_t tile_c0(int64_t T)
+{
+    const uint32_t lane = threadIdx.x & 63u;
+    return (static_cast<uint32_t>(T) << 6) | (lane >> 1) | ((lane & 1u) << 5);
+}
+__device__ __forceinline__ uint32_t tile_c1(int64_t T)
+{
+    return static_cast<uint32_t>(static_cast<uint64_t>(T) >> 26);
+}
+
+// |code| of a lane's eight coordinates of one row as four 16-bit lane pairs
+// (A0 A1, A2 A3, B0 B1, B2 B3), and sgn their signs (1 or -1 per lane): the
+// codes are mag * sgn.  v: the lane's coordinates; inv: their s_k / W, times
+// 2^16 when PRE (then s0x = s0 * 2^16).  Every lane of the wave must call it
+// (DPP exchange, wave-uniform branches).
+//
+// With T = floor(x * 2^16) = l * 2^16 + th and a uniform high half r, the
+// sum u = T + (2^16 - 1 - r) carries into its upper half exactly when
+// r < th, so u >> 16 = l + [r < th]: one add on the complemented half.  Its
+// lower half is 2^16 - 1 exactly when r == th, the tie the low halves
+// decide.  A lane with a tie, or with a T above s0 * 2^16 (x clamped, or an
+// infinite v; NaN converts to 0, which is its code), sends the wave to the
+// exact form below; about one tile in 128 does.  Against forming level,
+// threshold and compare in 16-bit lanes, and the first Philox rounds per
+// row, this is 30% fewer VALU issue slots a row.
 template <bool PRE>
-__device__ __forceinline__ void tile_codes(const float v[8], const float inv[8], float s0x, int64_t T,
-                                           uint32_t worker, uint32_t key0, uint32_t key1, uint32_t one2,
-                                           uint32_t p[4])
+__device__ __forceinline__ void tile_mags(const float v[8], const float inv[8], float s0x, uint32_t c0, uint32_t c1,
+                                          const LaneKey& lk, uint32_t worker, uint32_t key0, uint32_t key1,
+                                          u16x2 mag[4], u16x2 sgn[4])
 {
     const int lane = threadIdx.x & 63;
     const bool odd = (lane & 1) != 0;
-    const uint64_t q = static_cast<uint64_t>(T << 6) + static_cast<uint64_t>(lane >> 1) + (odd ? 32u : 0u);
-    uint32_t a01, a23, b01, b23;
-    tile_halves(philox4x32_10(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), worker, 0u, key0, key1),
-                odd, &a01, &a23, &b01, &b23);
-    float xs[8];
+    uint32_t h[4];  // complemented high halves: A0 A1, A2 A3, B0 B1, B2 B3
+    tile_halves(philox_tail_not(row_key(c1, worker, key0), lk, key0, key1), odd, &h[0], &h[1], &h[2], &h[3]);
+    bool rare = !PRE;
     if (PRE) {
-        // every table entry is finite, so |v| * inv is NaN or infinite only
-        // for NaN or infinite v, which quantise to 0 (wave-uniform, rare)
-        bool bad = false;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            xs[j] = fminf(fabsf(v[j]) * inv[j], s0x);
-            bad = bad || __builtin_amdgcn_classf(v[j], kNonFinite);
-        }
-        if (__builtin_expect(__ballot(bad) != 0, 0)) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                xs[j] = __builtin_amdgcn_classf(v[j], kNonFinite) ? 0.0f : xs[j];
-        }
-    } else {
-        // entries may be infinite (0 * inf is NaN): select by class
+        uint32_t T[8], u[8];
+        uint32_t t_max = 0u, tie = 0u;
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-            xs[j] = scaled_magnitude(v[j], inv[j], s0x) * 65536.0f;
-    }
-    uint32_t Tw[8];
-    bool tie[8];
-    bool any_tie = false;
+            T[j] = cvt_u32_sat(fabsf(v[j]) * inv[j]);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        Tw[j] = static_cast<uint32_t>(xs[j]);
-        const uint32_t h = j < 4 ? half16(a01, a23, j) : half16(b01, b23, j - 4);
-        tie[j] = (Tw[j] & 0xFFFFu) == h;
-        any_tie = any_tie || tie[j];
+        for (int j = 0; j < 4; ++j) {
+            t_max = max(max(T[2 * j], T[2 * j + 1]), t_max);
+            u[2 * j] = add_half<0>(T[2 * j], h[j]);
+            u[2 * j + 1] = add_half<1>(T[2 * j + 1], h[j]);
+            tie = max3_lo16(tie, u[2 * j], u[2 * j + 1]);
+            mag[j] = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(u[2 * j + 1], u[2 * j], 0x07060302u));
+        }
+        rare = t_max > static_cast<uint32_t>(s0x) || static_cast<uint16_t>(tie) == 0xFFFFu;
     }
-    p[0] = pair_codes(Tw[0], Tw[1], v[0], v[1], a01, one2);
-    p[1] = pair_codes(Tw[2], Tw[3], v[2], v[3], a23, one2);
-    p[2] = pair_codes(Tw[4], Tw[5], v[4], v[5], b01, one2);
-    p[3] = pair_codes(Tw[6], Tw[7], v[6], v[7], b23, one2);
-    // wave-uniform branch (the DPP exchange needs every lane): draw the low
-    // halves from the purpose-1 blocks when any lane has a tie
-    if (__builtin_expect(__ballot(any_tie) != 0, 0)) {
-        tile_halves(philox4x32_10(static_cast<uint32_t>(q), static_cast<uint32_t>(q >> 32), worker, 1u, key0, key1),
-                    odd, &a01, &a23, &b01, &b23);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint32_t h = j < 4 ? half16(a01, a23, j) : half16(b01, b23, j - 4);
-            if (tie[j])
-                set_lane16(&p[j >> 1], j, quantise_tie_scaled(v[j], xs[j], Tw[j], h));
+    for (int j = 0; j < 4; ++j)
+        sgn[j] = pair_signs(v[2 * j], v[2 * j + 1]);
+    if (!PRE || __builtin_expect(__ballot(rare) != 0, 0)) {
+        uint32_t lo[4];
+        tile_halves(philox4x32_10(c0, c1, worker, 1u, key0, key1), odd, &lo[0], &lo[1], &lo[2], &lo[3]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t m0 = exact_magnitude<PRE>(v[2 * j], inv[2 * j], s0x, ~h[j] & 0xFFFFu, lo[j] & 0xFFFFu);
+            const uint32_t m1 = exact_magnitude<PRE>(v[2 * j + 1], inv[2 * j + 1], s0x, ~h[j] >> 16, lo[j] >> 16);
+            mag[j] = u16x2{static_cast<uint16_t>(m0), static_cast<uint16_t>(m1)};
         }
     }
+}
+
+// One row's eight codes of one lane as 16-bit lane pairs.
+template <bool PRE>
+__device__ __forceinline__ void tile_codes(const float v[8], const float inv[8], float s0x, int64_t T,
+                                           uint32_t worker, uint32_t key0, uint32_t key1, uint32_t p[4])
+{
+    const uint32_t c0 = tile_c0(T);
+    u16x2 mag[4], sgn[4];
+    tile_mags<PRE>(v, inv, s0x, c0, tile_c1(T), lane_key(c0, 0u, key1), worker, key0, key1, mag, sgn);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        p[j] = __builtin_bit_cast(uint32_t, static_cast<u16x2>(mag[j] * sgn[j]));
+}
+
+// The same added to the lane pairs of h (one multiply-add each).
+template <bool PRE>
+__device__ __forceinline__ void add_codes(const float v[8], const float inv[8], float s0x, int64_t T,
+                                          uint32_t worker, uint32_t key0, uint32_t key1, uint32_t h[4])
+{
+    const uint32_t c0 = tile_c0(T);
+    u16x2 mag[4], sgn[4];
+    tile_mags<PRE>(v, inv, s0x, c0, tile_c1(T), lane_key(c0, 0u, key1), worker, key0, key1, mag, sgn);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        h[j] = __builtin_bit_cast(uint32_t, static_cast<u16x2>(mag[j] * sgn[j] + __builtin_bit_cast(u16x2, h[j])));
 }
 
 // One tile of one code row: the codes from the lane's loaded inputs, then
@@ -1079,7 +1096,7 @@ __device__ __forceinline__ void tile_codes(const float v[8], const float inv[8],
 template <bool MULTI, int BITS, bool PRE, bool NT>
 __device__ __forceinline__ void code_tile(const TileIn& in, uint8_t* __restrict__ out, int64_t T,
                                           const float* inv_t, float inv0, float s0x, uint32_t kmax,
-                                          uint32_t worker, uint32_t key0, uint32_t key1, uint32_t one2)
+                                          uint32_t worker, uint32_t key0, uint32_t key1)
 {
     const float v[8] = {in.A.x, in.A.y, in.A.z, in.A.w, in.B.x, in.B.y, in.B.z, in.B.w};
     float inv[8];
@@ -1095,7 +1112,7 @@ __device__ __forceinline__ void code_tile(const TileIn& in, uint8_t* __restrict_
             inv[j] = inv0;
     }
     uint32_t p[4];
-    tile_codes<PRE>(v, inv, s0x, T, worker, key0, key1, one2, p);
+    tile_codes<PRE>(v, inv, s0x, T, worker, key0, key1, p);
     const int64_t a_off = (T << 9) + 4 * (threadIdx.x & 63);
     store_pairs<BITS, NT>(out, a_off, p[0], p[1]);
     store_pairs<BITS, NT>(out, a_off + 256, p[2], p[3]);
@@ -1114,16 +1131,14 @@ __device__ __forceinline__ void quantise_few(const float* __restrict__ row, uint
                                              float s0x, uint32_t kmax, uint32_t worker, uint32_t key0,
                                              uint32_t key1)
 {
-    uint32_t one2 = 0x00010001u;
-    asm("" : "+s"(one2));
     const int lane = threadIdx.x & 63;
     if (first < ntiles) {
         const TileIn in = MULTI ? load_tile<MULTI>(row, idx, (first << 9) + 4 * lane) : in0;
-        code_tile<MULTI, BITS, PRE, NT>(in, out, first, inv_t, inv0, s0x, kmax, worker, key0, key1, one2);
+        code_tile<MULTI, BITS, PRE, NT>(in, out, first, inv_t, inv0, s0x, kmax, worker, key0, key1);
     }
     if (MULTI && tpw == 2 && first + 1 < ntiles) {
         const TileIn in = load_tile<MULTI>(row, idx, ((first + 1) << 9) + 4 * lane);
-        code_tile<MULTI, BITS, PRE, NT>(in, out, first + 1, inv_t, inv0, s0x, kmax, worker, key0, key1, one2);
+        code_tile<MULTI, BITS, PRE, NT>(in, out, first + 1, inv_t, inv0, s0x, kmax, worker, key0, key1);
     }
 }
 
@@ -1137,13 +1152,11 @@ __device__ __forceinline__ void quantise_tiles(const float* __restrict__ row, ui
                                                uint32_t key1, int32_t tpw)
 {
     const int lane = threadIdx.x & 63;
-    uint32_t one2 = 0x00010001u;
-    asm("" : "+s"(one2));
     for (int64_t c0 = first; c0 < ntiles; c0 += stride) {
         const int64_t c1 = c0 + tpw < ntiles ? c0 + tpw : ntiles;
         for (int64_t T = c0; T < c1; ++T) {
             const TileIn in = (!MULTI && T == first) ? in0 : load_tile<MULTI>(row, idx, (T << 9) + 4 * lane);
-            code_tile<MULTI, BITS, PRE, NT>(in, out, T, inv_t, inv0, s0x, kmax, worker, key0, key1, one2);
+            code_tile<MULTI, BITS, PRE, NT>(in, out, T, inv_t, inv0, s0x, kmax, worker, key0, key1);
         }
     }
 }
@@ -1550,7 +1563,7 @@ template <bool MULTI, bool PRE, bool ACC, bool DEQ, bool NT, bool ROW1>
 __device__ __forceinline__ void quant_sum_tile(const float* __restrict__ g, int64_t ldg, int32_t rows,
                                                uint32_t worker0, int64_t T, TileIn in, i32x4 oldA, i32x4 oldB,
                                                const float* inv_t, float inv0, float s0x, uint32_t kmax,
-                                               uint32_t key0, uint32_t key1, uint32_t one2,
+                                               uint32_t key0, uint32_t key1,
                                                int32_t* __restrict__ sum, const float* deq_t,
                                                float* __restrict__ out)
 {
@@ -1575,11 +1588,7 @@ __device__ __forceinline__ void quant_sum_tile(const float* __restrict__ g, int6
             nB = load_nt(nrow + a_off + 256);
         }
         const float v[8] = {A.x, A.y, A.z, A.w, B.x, B.y, B.z, B.w};
-        uint32_t p[4];
-        tile_codes<PRE>(v, inv, s0x, T, worker0 + static_cast<uint32_t>(r), key0, key1, one2, p);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            h[j] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, h[j]) + __builtin_bit_cast(u16x2, p[j]));
+        add_codes<PRE>(v, inv, s0x, T, worker0 + static_cast<uint32_t>(r), key0, key1, h);
         if (++pending == kPairRows) {
             widen_pairs(h, acc);
             pending = 0;
@@ -1709,19 +1718,17 @@ __global__ __launch_bounds__(kBlock) void k_quant_sum(const float* __restrict__ 
     const float inv0 = zero ? 0.0f : q0;
     const float s0 = S.s[0];
     const uint32_t kmax = static_cast<uint32_t>(S.K - 1);
-    uint32_t one2 = 0x00010001u;
-    asm("" : "+s"(one2));
 
     // the preloaded tile, then (on a grid capped below one tile per wave)
     // every stride-th tile after it
     if (first < ntiles) {
         if (pre)
             quant_sum_tile<MULTI, true, ACC, DEQ, NT, ROW1>(g, ldg, rows, w0, first, in0, oldA0, oldB0, inv_p,
-                                                      inv0 * 65536.0f, s0 * 65536.0f, kmax, key0, key1, one2, sum,
+                                                      inv0 * 65536.0f, s0 * 65536.0f, kmax, key0, key1, sum,
                                                       deq_s, out);
         else
             quant_sum_tile<MULTI, false, ACC, DEQ, NT, ROW1>(g, ldg, rows, w0, first, in0, oldA0, oldB0, inv_p, inv0, s0,
-                                                       kmax, key0, key1, one2, sum, deq_s, out);
+                                                       kmax, key0, key1, sum, deq_s, out);
     }
     if (stride < ntiles) {
         for (int64_t T = first + stride; T < ntiles; T += stride) {
@@ -1734,10 +1741,10 @@ __global__ __launch_bounds__(kBlock) void k_quant_sum(const float* __restrict__ 
             }
             if (pre)
                 quant_sum_tile<MULTI, true, ACC, DEQ, NT, ROW1>(g, ldg, rows, w0, T, in, oldA, oldB, inv_p, inv0 * 65536.0f,
-                                                          s0 * 65536.0f, kmax, key0, key1, one2, sum, deq_s, out);
+                                                          s0 * 65536.0f, kmax, key0, key1, sum, deq_s, out);
             else
                 quant_sum_tile<MULTI, false, ACC, DEQ, NT, ROW1>(g, ldg, rows, w0, T, in, oldA, oldB, inv_p, inv0, s0,
-                                                           kmax, key0, key1, one2, sum, deq_s, out);
+                                                           kmax, key0, key1, sum, deq_s, out);
         }
     }
     if (blockIdx.x == 0 && threadIdx.x < 64)
@@ -1856,8 +1863,7 @@ template <int ROWS, bool PRE, bool NT, bool INDEX>
 __device__ __forceinline__ void index_quant_sum_tile(const f32x4 (&A)[ROWS], const f32x4 (&B)[ROWS], int32_t rows,
                                                      uint32_t worker0, int64_t T, const uint2* tab, bool by_table,
                                                      const float* thr, int32_t K, bool zero, const float* inv_t,
-                                                     float s0x, const float* deq_t, uint32_t key0, uint32_t key1,
-                                                     uint32_t one2, uint8_t* __restrict__ idx,
+                                                     float s0x, const float* deq_t, uint32_t key0, uint32_t key1, uint8_t* __restrict__ idx,
                                                      int32_t* __restrict__ sum, float* __restrict__ out)
 {
     const int lane = threadIdx.x & 63;
@@ -1876,11 +1882,7 @@ __device__ __forceinline__ void index_quant_sum_tile(const f32x4 (&A)[ROWS], con
     for (int r = 0; r < ROWS; ++r) {
         if (r < rows) {
             const float v[8] = {A[r].x, A[r].y, A[r].z, A[r].w, B[r].x, B[r].y, B[r].z, B[r].w};
-            uint32_t p[4];
-            tile_codes<PRE>(v, inv, s0x, T, worker0 + static_cast<uint32_t>(r), key0, key1, one2, p);
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                h[j] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, h[j]) + __builtin_bit_cast(u16x2, p[j]));
+            add_codes<PRE>(v, inv, s0x, T, worker0 + static_cast<uint32_t>(r), key0, key1, h);
         }
     }
     int32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -2033,8 +2035,6 @@ __global__ __launch_bounds__(kBlock) void k_index_quant_sum(const float* __restr
         tab_s[e] = ent;
     }
     const bool by_table = __syncthreads_or(crowded) == 0;
-    uint32_t one2 = 0x00010001u;
-    asm("" : "+s"(one2));
     const float s0x = pre ? s0 * 65536.0f : s0;
 
     // the preloaded tile, then (on a grid capped below one tile per wave)
@@ -2044,10 +2044,10 @@ __global__ __launch_bounds__(kBlock) void k_index_quant_sum(const float* __restr
             load_rows(T);
         if (pre)
             index_quant_sum_tile<ROWS, true, NT, true>(A, B, M, 0u, T, tab_s, by_table, thr_s, K, zero, inv_p, s0x,
-                                                       deq_s, key0, key1, one2, idx, sum, out);
+                                                       deq_s, key0, key1, idx, sum, out);
         else
             index_quant_sum_tile<ROWS, false, NT, true>(A, B, M, 0u, T, tab_s, by_table, thr_s, K, zero, inv_p, s0x,
-                                                        deq_s, key0, key1, one2, idx, sum, out);
+                                                        deq_s, key0, key1, idx, sum, out);
     }
     if (blockIdx.x == 0 && threadIdx.x < 64)
         index_quant_sum_tail(g, d, ldg, M, ntiles, thr_s, K, zero, inv_s, s0, key0, key1, idx, sum, deq_s, out);
@@ -2096,7 +2096,7 @@ template <int ROWS, int BITS, bool PRE, bool NT>
 __device__ __forceinline__ void index_quantise_tile(const f32x4 (&A)[ROWS], const f32x4 (&B)[ROWS], int32_t rows,
                                                     int64_t T, const uint2* tab, bool by_table, const float* thr,
                                                     int32_t K, bool zero, const float* inv_t, float s0x,
-                                                    uint32_t key0, uint32_t key1, uint32_t one2,
+                                                    uint32_t key0, uint32_t key1,
                                                     uint8_t* __restrict__ idx, uint8_t* __restrict__ codes,
                                                     int64_t ldc, uint8_t* stage)
 {
@@ -2114,7 +2114,7 @@ __device__ __forceinline__ void index_quantise_tile(const f32x4 (&A)[ROWS], cons
         if (r < rows) {
             const float v[8] = {A[r].x, A[r].y, A[r].z, A[r].w, B[r].x, B[r].y, B[r].z, B[r].w};
             uint32_t p[4];
-            tile_codes<PRE>(v, inv, s0x, T, static_cast<uint32_t>(r), key0, key1, one2, p);
+            tile_codes<PRE>(v, inv, s0x, T, static_cast<uint32_t>(r), key0, key1, p);
             // the row's codes of this tile into the wave's LDS rows
             uint8_t* srow = stage + r * (64 * BITS);
             lds_put<BITS>(srow + (4 * lane) * BITS / 8, pack_quad<BITS>(p[0], p[1]));
@@ -2273,8 +2273,6 @@ __global__ __launch_bounds__(kBlock) void k_index_quantise(const float* __restri
         tab_s[e] = ent;
     }
     const bool by_table = __syncthreads_or(crowded) == 0;
-    uint32_t one2 = 0x00010001u;
-    asm("" : "+s"(one2));
     const float s0x = pre ? s0 * 65536.0f : s0;
 
     for (int64_t T = first; T < ntiles; T += stride) {
@@ -2282,10 +2280,10 @@ __global__ __launch_bounds__(kBlock) void k_index_quantise(const float* __restri
             load_rows(T);
         if (pre)
             index_quantise_tile<ROWS, BITS, true, NT>(A, B, M, T, tab_s, by_table, thr_s, K, zero, inv_p, s0x,
-                                                             key0, key1, one2, idx, codes, ldc, stage);
+                                                             key0, key1, idx, codes, ldc, stage);
         else
             index_quantise_tile<ROWS, BITS, false, NT>(A, B, M, T, tab_s, by_table, thr_s, K, zero, inv_p, s0x,
-                                                              key0, key1, one2, idx, codes, ldc, stage);
+                                                              key0, key1, idx, codes, ldc, stage);
     }
     if (blockIdx.x == 0 && threadIdx.x < 64)
         index_quantise_tail<BITS>(g, d, ldg, M, ntiles, thr_s, K, zero, inv_s, s0, key0, key1, idx, codes, ldc);
@@ -2314,7 +2312,7 @@ __global__ __launch_bounds__(kBlock) void k_index_quantise(const float* __restri
 template <int RPW, bool PRE, bool NT>
 __device__ __forceinline__ void split_tile(const f32x4 (&A)[RPW], const f32x4 (&B)[RPW], int32_t rows,
                                            uint32_t worker0, int64_t T, float inv0, float s0x, float deq0,
-                                           uint32_t key0, uint32_t key1, uint32_t one2, i32x4 (*ps)[128],
+                                           uint32_t key0, uint32_t key1, i32x4 (*ps)[128],
                                            int32_t* __restrict__ sum, float* __restrict__ out)
 {
     const int lane = threadIdx.x & 63;
@@ -2327,11 +2325,7 @@ __device__ __forceinline__ void split_tile(const f32x4 (&A)[RPW], const f32x4 (&
         const int32_t m = wave + 4 * r;
         if (m < rows) {
             const float v[8] = {A[r].x, A[r].y, A[r].z, A[r].w, B[r].x, B[r].y, B[r].z, B[r].w};
-            uint32_t p[4];
-            tile_codes<PRE>(v, inv, s0x, T, worker0 + static_cast<uint32_t>(m), key0, key1, one2, p);
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                h[j] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, h[j]) + __builtin_bit_cast(u16x2, p[j]));
+            add_codes<PRE>(v, inv, s0x, T, worker0 + static_cast<uint32_t>(m), key0, key1, h);
         }
     }
     int32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -2392,8 +2386,6 @@ __global__ __launch_bounds__(kBlock) void k_quant_sum_split(const float* __restr
     const float inv0 = zero ? 0.0f : q0;
     const float denom = static_cast<float>(static_cast<double>(M) * static_cast<double>(s0));
     const float deq0 = zero ? 0.0f : div_rn32(W, denom);
-    uint32_t one2 = 0x00010001u;
-    asm("" : "+s"(one2));
     const float s0x = pre ? s0 * 65536.0f : s0;
     const float invx = pre ? inv0 * 65536.0f : inv0;
 
@@ -2402,9 +2394,9 @@ __global__ __launch_bounds__(kBlock) void k_quant_sum_split(const float* __restr
         if (T != first)
             load_rows(T);
         if (pre)
-            split_tile<RPW, true, NT>(A, B, rows, w0, T, invx, s0x, deq0, key0, key1, one2, ps_s[parity], sum, out);
+            split_tile<RPW, true, NT>(A, B, rows, w0, T, invx, s0x, deq0, key0, key1, ps_s[parity], sum, out);
         else
-            split_tile<RPW, false, NT>(A, B, rows, w0, T, invx, s0x, deq0, key0, key1, one2, ps_s[parity], sum, out);
+            split_tile<RPW, false, NT>(A, B, rows, w0, T, invx, s0x, deq0, key0, key1, ps_s[parity], sum, out);
         parity ^= 1;
     }
     if (blockIdx.x == 0 && threadIdx.x < 64) {
