@@ -47,6 +47,31 @@ __device__ __forceinline__ void store_nt(float* p, f32x4 v)
     __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(p));
 }
 
+// Stores that write through the caches (cache policy sc0 sc1: every level
+// passes the line on at once, in the order of the stores) instead of leaving
+// dirty lines in the XCD's L2 to be evicted later, out of order; NT adds the
+// nontemporal hint.  Work-free passes on MI355X with 256-thread blocks and
+// nontemporal, plain or write-through stores: 4 bytes in and 1 out at 2^27
+// coordinates 99.6, 94.7 and 89.7 us; the accumulating pass (8.5 in, 4 out)
+// at 25.6 M 45.9, 44 and 38.5 us.  Beyond the 256 MB Infinity Cache the
+// accumulating pass, whose next call reads the sums back, is faster with
+// both (2.03 against 2.15 ms at 2^30).  `base` is wave-uniform.
+template <bool NT, typename V>
+__device__ __forceinline__ void store_through(void* base, uint32_t byte_off, V v)
+{
+    constexpr int kSc0 = 1, kNt = 2, kSc1 = 16;
+    constexpr int policy = kSc0 | kSc1 | (NT ? kNt : 0);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(base, 0, -1, 0x00027000);
+    if constexpr (sizeof(V) == 16)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, byte_off, 0, policy);
+    else if constexpr (sizeof(V) == 4)
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, byte_off, 0, policy);
+    else if constexpr (sizeof(V) == 2)
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, v), r, byte_off, 0, policy);
+    else
+        __builtin_amdgcn_raw_buffer_store_b8(__builtin_bit_cast(uint8_t, v), r, byte_off, 0, policy);
+}
+
 // Scale set passed by value in the kernel arguments.
 struct ScaleSet {
     float s[kMaxScales];
@@ -235,14 +260,14 @@ __device__ __forceinline__ u16x2 pair_signs(float v0, float v1)
 
 // |code| of one coordinate from its whole uniform word (hi16, lo16):
 // l + [r < t], 0 for a NaN or infinite v.  inv and s0x carry a factor of
-// 2^16 when PRE (the products are then finite for finite v, up to overflow
+// 2^16 when pre (the products are then finite for finite v, up to overflow
 // to infinity, which the minimum takes to s0); else inv may be infinite and
 // the factor is applied after the minimum.
-template <bool PRE>
-__device__ __forceinline__ uint32_t exact_magnitude(float v, float inv, float s0x, uint32_t hi16, uint32_t lo16)
+__device__ __forceinline__ uint32_t exact_magnitude(float v, float inv, float s0x, bool pre, uint32_t hi16,
+                                                    uint32_t lo16)
 {
     float xs;
-    if (PRE)
+    if (pre)
         xs = __builtin_amdgcn_classf(v, kNonFinite) ? 0.0f : fminf(fabsf(v) * inv, s0x);
     else
         xs = scaled_magnitude(v, inv, s0x) * 65536.0f;

@@ -22,9 +22,8 @@
 //   k_index_quant_sum  all of up to 16 rows held at once: the     (Eq. (11) +
 //                shared index from their exact maxima, then        sharing, (12),
 //                k_quant_sum's codes, sums and reconstruction      sum, (13))
-//   k_quant_sum_split  one scale, 5 to 16 rows: a tile's rows     (Eq. (8),
-//                split over a block's waves, their sums meeting    sum, (9))
-//                in LDS
+//   k_quant_sum_split  one scale, 5 to 16 rows: the same with     (Eq. (8),
+//                no index                                          sum, (9))
 //   k_dequant    int32 (+ index) -> fp32                          (Eq. (9)/(13))
 //
 // Every per-coordinate result is a pure function of its inputs and the
@@ -1016,48 +1015,61 @@ __device__ __forceinline__ uint32_t tile_c1(int64_t T)
 // lower half is 2^16 - 1 exactly when r == th, the tie the low halves
 // decide.  A lane with a tie, or with a T above s0 * 2^16 (x clamped, or an
 // infinite v; NaN converts to 0, which is its code), sends the wave to the
-// exact form below; about one tile in 128 does.  Against forming level,
+// exact form below; about one tile in 128 does.  Without pre every tile
+// goes there.  Against forming level,
 // threshold and compare in 16-bit lanes, and the first Philox rounds per
 // row, this is 30% fewer VALU issue slots a row.
-template <bool PRE>
-__device__ __forceinline__ void tile_mags(const float v[8], const float inv[8], float s0x, uint32_t c0, uint32_t c1,
-                                          const LaneKey& lk, uint32_t worker, uint32_t key0, uint32_t key1,
+// Returns whether the wave needs the exact form; h: the complemented high
+// halves (A0 A1, A2 A3, B0 B1, B2 B3), kept for it.
+__device__ __forceinline__ bool fast_mags(const float v[8], const float inv[8], float s0x, const LaneKey& lk,
+                                          const RowKey& rk, uint32_t key0, uint32_t key1, uint32_t h[4],
                                           u16x2 mag[4], u16x2 sgn[4])
 {
-    const int lane = threadIdx.x & 63;
-    const bool odd = (lane & 1) != 0;
-    uint32_t h[4];  // complemented high halves: A0 A1, A2 A3, B0 B1, B2 B3
-    tile_halves(philox_tail_not(row_key(c1, worker, key0), lk, key0, key1), odd, &h[0], &h[1], &h[2], &h[3]);
-    bool rare = !PRE;
-    if (PRE) {
-        uint32_t T[8], u[8];
-        uint32_t t_max = 0u, tie = 0u;
+    const bool odd = (threadIdx.x & 1) != 0;
+    tile_halves(philox_tail_not(rk, lk, key0, key1), odd, &h[0], &h[1], &h[2], &h[3]);
+    uint32_t T[8], u[8];
+    uint32_t t_max = 0u, tie = 0u;
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            T[j] = cvt_u32_sat(fabsf(v[j]) * inv[j]);
+    for (int j = 0; j < 8; ++j)
+        T[j] = cvt_u32_sat(fabsf(v[j]) * inv[j]);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            t_max = max(max(T[2 * j], T[2 * j + 1]), t_max);
-            u[2 * j] = add_half<0>(T[2 * j], h[j]);
-            u[2 * j + 1] = add_half<1>(T[2 * j + 1], h[j]);
-            tie = max3_lo16(tie, u[2 * j], u[2 * j + 1]);
-            mag[j] = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(u[2 * j + 1], u[2 * j], 0x07060302u));
-        }
-        rare = t_max > static_cast<uint32_t>(s0x) || static_cast<uint16_t>(tie) == 0xFFFFu;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 4; ++j) {
+        t_max = max(max(T[2 * j], T[2 * j + 1]), t_max);
+        u[2 * j] = add_half<0>(T[2 * j], h[j]);
+        u[2 * j + 1] = add_half<1>(T[2 * j + 1], h[j]);
+        tie = max3_lo16(tie, u[2 * j], u[2 * j + 1]);
+        mag[j] = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(u[2 * j + 1], u[2 * j], 0x07060302u));
         sgn[j] = pair_signs(v[2 * j], v[2 * j + 1]);
-    if (!PRE || __builtin_expect(__ballot(rare) != 0, 0)) {
-        uint32_t lo[4];
-        tile_halves(philox4x32_10(c0, c1, worker, 1u, key0, key1), odd, &lo[0], &lo[1], &lo[2], &lo[3]);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t m0 = exact_magnitude<PRE>(v[2 * j], inv[2 * j], s0x, ~h[j] & 0xFFFFu, lo[j] & 0xFFFFu);
-            const uint32_t m1 = exact_magnitude<PRE>(v[2 * j + 1], inv[2 * j + 1], s0x, ~h[j] >> 16, lo[j] >> 16);
-            mag[j] = u16x2{static_cast<uint16_t>(m0), static_cast<uint16_t>(m1)};
-        }
     }
+    return __ballot(t_max > static_cast<uint32_t>(s0x) || static_cast<uint16_t>(tie) == 0xFFFFu) != 0;
+}
+
+// The exact magnitudes: the low halves drawn too, from the block of counter
+// (c0, c1, worker, 1).
+__device__ __forceinline__ void exact_mags(const float v[8], const float inv[8], float s0x, bool pre, uint32_t c0,
+                                           uint32_t c1, uint32_t worker, uint32_t key0, uint32_t key1,
+                                           const uint32_t h[4], u16x2 mag[4])
+{
+    const bool odd = (threadIdx.x & 1) != 0;
+    uint32_t lo[4];
+    tile_halves(philox4x32_10(c0, c1, worker, 1u, key0, key1), odd, &lo[0], &lo[1], &lo[2], &lo[3]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t m0 = exact_magnitude(v[2 * j], inv[2 * j], s0x, pre, ~h[j] & 0xFFFFu, lo[j] & 0xFFFFu);
+        const uint32_t m1 = exact_magnitude(v[2 * j + 1], inv[2 * j + 1], s0x, pre, ~h[j] >> 16, lo[j] >> 16);
+        mag[j] = u16x2{static_cast<uint16_t>(m0), static_cast<uint16_t>(m1)};
+    }
+}
+
+// Both for one row.
+__device__ __forceinline__ void tile_mags(const float v[8], const float inv[8], float s0x, bool pre, int64_t T,
+                                          uint32_t worker, uint32_t key0, uint32_t key1, u16x2 mag[4], u16x2 sgn[4])
+{
+    const uint32_t c0 = tile_c0(T), c1 = tile_c1(T);
+    uint32_t h[4];
+    const bool rare = fast_mags(v, inv, s0x, lane_key(c0, 0u, key1), row_key(c1, worker, key0), key0, key1, h, mag, sgn);
+    if (__builtin_expect(!pre || rare, 0))
+        exact_mags(v, inv, s0x, pre, c0, c1, worker, key0, key1, h, mag);
 }
 
 // One row's eight codes of one lane as 16-bit lane pairs.
@@ -1065,9 +1077,8 @@ template <bool PRE>
 __device__ __forceinline__ void tile_codes(const float v[8], const float inv[8], float s0x, int64_t T,
                                            uint32_t worker, uint32_t key0, uint32_t key1, uint32_t p[4])
 {
-    const uint32_t c0 = tile_c0(T);
     u16x2 mag[4], sgn[4];
-    tile_mags<PRE>(v, inv, s0x, c0, tile_c1(T), lane_key(c0, 0u, key1), worker, key0, key1, mag, sgn);
+    tile_mags(v, inv, s0x, PRE, T, worker, key0, key1, mag, sgn);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
         p[j] = __builtin_bit_cast(uint32_t, static_cast<u16x2>(mag[j] * sgn[j]));
@@ -1078,9 +1089,8 @@ template <bool PRE>
 __device__ __forceinline__ void add_codes(const float v[8], const float inv[8], float s0x, int64_t T,
                                           uint32_t worker, uint32_t key0, uint32_t key1, uint32_t h[4])
 {
-    const uint32_t c0 = tile_c0(T);
     u16x2 mag[4], sgn[4];
-    tile_mags<PRE>(v, inv, s0x, c0, tile_c1(T), lane_key(c0, 0u, key1), worker, key0, key1, mag, sgn);
+    tile_mags(v, inv, s0x, PRE, T, worker, key0, key1, mag, sgn);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
         h[j] = __builtin_bit_cast(uint32_t, static_cast<u16x2>(mag[j] * sgn[j] + __builtin_bit_cast(u16x2, h[j])));
@@ -1859,198 +1869,303 @@ __device__ __forceinline__ void store_index(uint8_t* __restrict__ idx, int64_t a
     }
 }
 
-template <int ROWS, bool PRE, bool NT, bool INDEX>
-__device__ __forceinline__ void index_quant_sum_tile(const f32x4 (&A)[ROWS], const f32x4 (&B)[ROWS], int32_t rows,
-                                                     uint32_t worker0, int64_t T, const uint2* tab, bool by_table,
-                                                     const float* thr, int32_t K, bool zero, const float* inv_t,
-                                                     float s0x, const float* deq_t, uint32_t key0, uint32_t key1, uint8_t* __restrict__ idx,
-                                                     int32_t* __restrict__ sum, float* __restrict__ out)
+// ---------------------------------------------------------------------------
+// All of up to kFuseRows resident rows quantised, summed and reconstructed in
+// one call (one scale, or several with the shared index formed here).  One
+// wave per block and 256-coordinate tile: lane t holds quad 4t .. 4t + 3 of
+// every row (ROWS, the row count rounded up to even; a row past the last
+// re-reads it and is not counted), all loads issued before W is read.  Rows
+// are coded two at a time: the lanes of a pair share the Philox block of their
+// eight coordinates, so even lanes compute it for row 2p and odd lanes for row
+// 2p + 1, and tile_halves' exchange hands each lane its halves for both rows
+// (its "A" quad is row 2p's, its "B" quad row 2p + 1's).
+//
+// What bounds it is the memory system, and the launch shape decides how well
+// it streams: with sixteen rows of VGG-16 size, reading them and storing two
+// words per coordinate without any work took 1.86 ms with four-wave blocks
+// and nontemporal stores, 1.61 ms with one-wave blocks, and 1.59 ms with
+// those and write-through stores (1.25 ms for the reads alone).  One quad per
+// lane and row keeps 16 rows in 64 registers, so four waves share a SIMD (two
+// with 512-coordinate tiles).  The tables are formed by the wave's first K
+// lanes and kept in LDS; a one-wave block has no barrier to wait at.
+// ---------------------------------------------------------------------------
+struct RowTables {
+    float inv[kMaxScales];  // s_k / W, times 2^16 when pre
+    float deq[kMaxScales];  // RN32(W / (M s_k))
+    RowKey key[kFuseRows];  // each row's part of its Philox blocks
+};
+
+// The call's constants in one wave: lane k < K forms scale k's entries.
+struct WaveScale {
+    float s0x;       // s_0 * 2^16 when pre, else s_0
+    bool pre;
+    float inv, deq;  // lane k's s_k / W (times 2^16 when pre) and RN32(W / (M s_k)); 0 on the zero path
+};
+
+__device__ __forceinline__ float lane_value(float x, int32_t lane)
 {
-    const int lane = threadIdx.x & 63;
-    const int64_t a_off = (T << 9) + 4 * lane;
-    uint32_t k[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
-    if (INDEX) {
-        tile_index<ROWS>(A, B, tab, by_table, thr, K, zero, k);
-        store_index<NT>(idx, a_off, k);
-    }
-    float inv[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        inv[j] = inv_t[k[j]];
-    uint32_t h[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-        if (r < rows) {
-            const float v[8] = {A[r].x, A[r].y, A[r].z, A[r].w, B[r].x, B[r].y, B[r].z, B[r].w};
-            add_codes<PRE>(v, inv, s0x, T, worker0 + static_cast<uint32_t>(r), key0, key1, h);
-        }
-    }
-    int32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    widen_pairs(h, acc);
-    const i32x4 sa = {acc[0], acc[1], acc[2], acc[3]};
-    const i32x4 sb = {acc[4], acc[5], acc[6], acc[7]};
-    store_sum4<NT>(sum + a_off, sa);
-    store_sum4<NT>(sum + a_off + 256, sb);
-    f32x4 oa, ob;
-    oa.x = static_cast<float>(sa.x) * deq_t[k[0]];
-    oa.y = static_cast<float>(sa.y) * deq_t[k[1]];
-    oa.z = static_cast<float>(sa.z) * deq_t[k[2]];
-    oa.w = static_cast<float>(sa.w) * deq_t[k[3]];
-    ob.x = static_cast<float>(sb.x) * deq_t[k[4]];
-    ob.y = static_cast<float>(sb.y) * deq_t[k[5]];
-    ob.z = static_cast<float>(sb.z) * deq_t[k[6]];
-    ob.w = static_cast<float>(sb.w) * deq_t[k[7]];
-    store_nt(out + a_off, oa);
-    store_nt(out + a_off + 256, ob);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }
 
-// The coordinates past the last whole tile (fewer than 512): lane t of one
-// wave takes the 8 contiguous coordinates of group ntiles * 64 + t, forms
-// their indices from the rows' maxima (threshold counts), then quantises and
-// sums every row.  inv_s holds s_k / W (not scaled).
-__device__ __forceinline__ void index_quant_sum_tail(const float* __restrict__ g, int64_t d, int64_t ldg, int32_t M,
-                                                     int64_t ntiles, const float* thr, int32_t K, bool zero,
-                                                     const float* inv_s, float s0, uint32_t key0, uint32_t key1,
-                                                     uint8_t* __restrict__ idx, int32_t* __restrict__ sum,
-                                                     const float* deq_t, float* __restrict__ out)
+// The scales come to their lanes through scalar loads: a vector load of them
+// here would be waited for behind the rows' loads, which the counter of
+// outstanding loads retires in order, and so would everything formed from
+// it (measured on 4 rows of 25.6 M coordinates with four scales: 113.7 us against 108.1; 8 rows of 11.2 M: 79.5 against 73.3).
+template <bool MULTI>
+__device__ __forceinline__ WaveScale wave_scale(const float* __restrict__ wptr, const ScaleSet& S, int32_t M)
 {
-    const int64_t q = (ntiles << 6) + (threadIdx.x & 63);
-    const int64_t base = q << 3;
-    if (base >= d)
-        return;
-    float a[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    for (int32_t r = 0; r < M; ++r) {
-        const float* row = g + static_cast<int64_t>(r) * ldg;
+    WaveScale c;
+    const float W = *wptr;
+    float s = S.s[0];
+    if (MULTI) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            a[j] = fmaxf(a[j], usable_or_zero(base + j < d ? row[base + j] : 0.0f));
+        for (int k = 1; k < kMaxScales; ++k)
+            __asm__("v_writelane_b32 %0, %1, %2" : "+v"(s) : "s"(S.s[k]), "n"(k));
     }
-    uint32_t kk[8];
-    float inv[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        int32_t count = 0;
-        for (int k = 0; k < K; ++k)
-            count += a[j] <= thr[k] ? 1 : 0;
-        kk[j] = index_from_count(a[j], count, K, zero);
-        inv[j] = inv_s[kk[j]];
-    }
-    int32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int32_t r = 0; r < M; ++r) {
-        const float* row = g + static_cast<int64_t>(r) * ldg;
-        float v[8];
-        int32_t code[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            v[j] = base + j < d ? row[base + j] : 0.0f;
-        quantise_group(v, inv, s0, static_cast<uint64_t>(q), static_cast<uint32_t>(r), key0, key1, code);
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            acc[j] += code[j];
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        if (base + j < d) {
-            idx[base + j] = static_cast<uint8_t>(kk[j]);
-            sum[base + j] = acc[j];
-            out[base + j] = static_cast<float>(acc[j]) * deq_t[kk[j]];
-        }
-    }
+    const float q = div_rn32(s, W);
+    const float s0 = S.s[0];
+    const bool zero = zero_path(W, lane_value(q, 0));
+    // the largest entry is the last scale's; 2^16 times it stays finite
+    c.pre = zero || lane_value(q, MULTI ? S.K - 1 : 0) <= 0x1p100f;
+    const float inv = zero ? 0.0f : q;
+    c.inv = c.pre ? inv * 65536.0f : inv;
+    c.s0x = c.pre ? s0 * 65536.0f : s0;
+    // M * s_k is exactly representable in binary32 (checked on the host)
+    c.deq = zero ? 0.0f : div_rn32(W, static_cast<float>(static_cast<double>(M) * static_cast<double>(s)));
+    return c;
 }
 
-template <int ROWS, bool NT>
-__global__ __launch_bounds__(kBlock) void k_index_quant_sum(const float* __restrict__ g, int64_t d, int32_t M,
-                                                            int64_t ldg, const float* __restrict__ wptr, ScaleSet S,
-                                                            uint32_t key0, uint32_t key1, uint8_t* __restrict__ idx,
-                                                            int32_t* __restrict__ sum, float* __restrict__ out)
+// The shared index of a lane's four coordinates from the largest usable |g|
+// over the ROWS rows it holds: two rows per instruction with the NaN- and
+// infinity-propagating maximum; a result that is not finite means some value
+// was not usable (infinite or NaN), and then the lane forms the largest
+// usable |g| value by value.  Then the rule itself, #{k : a s_k / W <= s_0}
+// - 1, the table's entries broadcast from their lanes.  Written as "not
+// above", it also gives K - 1 for a = 0 (0 times an infinite entry is not
+// above) and on the zero path (every entry 0).  Against comparing a with
+// each scale's threshold this is one multiply more per scale and coordinate
+// and saves forming the thresholds in every wave.
+template <int ROWS>
+__device__ __forceinline__ void quad_index(const f32x4 (&A)[ROWS], const WaveScale& c, int32_t K, uint32_t k[4])
 {
-    __shared__ float inv_s[kMaxScales];  // s_k / W
-    __shared__ float inv_p[kMaxScales];  // s_k / W * 2^16 when pre
-    __shared__ float deq_s[kMaxScales];  // RN32(W / (M s_k))
-    __shared__ float thr_s[kMaxScales];  // T_k
-    __shared__ uint2 tab_s[256];
-    const int lane = threadIdx.x & 63;
-    const int64_t ntiles = d >> 9;
-    const int32_t wave_in_block = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(threadIdx.x >> 6));
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * (kBlock / 64) + wave_in_block;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * (kBlock / 64);
-
-    // every row of the first tile goes out before W is read and the tables
-    // are formed
-    f32x4 A[ROWS], B[ROWS];
-    const auto load_rows = [&](int64_t T) {
-        const int64_t a_off = (T << 9) + 4 * lane;
+    static_assert(ROWS % 2 == 0, "rows are taken in pairs");
+    float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int r = 0; r < ROWS; r += 2) {
+        a[0] = max3_abs(a[0], A[r].x, A[r + 1].x);
+        a[1] = max3_abs(a[1], A[r].y, A[r + 1].y);
+        a[2] = max3_abs(a[2], A[r].z, A[r + 1].z);
+        a[3] = max3_abs(a[3], A[r].w, A[r + 1].w);
+    }
+    const uint32_t worst = max(max(__float_as_uint(a[0]), __float_as_uint(a[1])),
+                               max(__float_as_uint(a[2]), __float_as_uint(a[3])));
+    if (__builtin_expect(worst >= 0x7F800000u, 0)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            a[j] = 0.0f;
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            const float* row = g + static_cast<int64_t>(r < M ? r : M - 1) * ldg;
-            A[r] = load_nt(row + a_off);
-            B[r] = load_nt(row + a_off + 256);
+            a[0] = fmaxf(a[0], usable_or_zero(A[r].x));
+            a[1] = fmaxf(a[1], usable_or_zero(A[r].y));
+            a[2] = fmaxf(a[2], usable_or_zero(A[r].z));
+            a[3] = fmaxf(a[3], usable_or_zero(A[r].w));
         }
-    };
-    if (first < ntiles)
-        load_rows(first);
+    }
+    uint32_t count[4] = {0u, 0u, 0u, 0u};
+    for (int32_t q = 0; q < K; ++q) {
+        const float inv = lane_value(c.inv, q);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            count[j] += !(a[j] * inv > c.s0x) ? 1u : 0u;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        k[j] = __builtin_elementwise_sub_sat(count[j], 1u);
+}
 
-    const float W = *wptr;
-    const float s0 = S.s[0];
-    const int32_t K = S.K;
-    const float q0 = div_rn32(s0, W);
-    const bool zero = zero_path(W, q0);
-    const bool pre = zero || div_rn32(S.s_last, W) <= 0x1p100f;
-    if (threadIdx.x < K) {
-        const float inv = zero ? 0.0f : div_rn32(S.s[threadIdx.x], W);
-        inv_s[threadIdx.x] = inv;
-        inv_p[threadIdx.x] = pre ? inv * 65536.0f : inv;
-        const float denom = static_cast<float>(static_cast<double>(M) * static_cast<double>(S.s[threadIdx.x]));
-        deq_s[threadIdx.x] = zero ? 0.0f : div_rn32(W, denom);
-        thr_s[threadIdx.x] = zero ? 0.0f : index_threshold(inv, s0);
+// Loads quad 4t .. 4t + 3 of tile T of every row; with TAIL only the
+// coordinates below d, zeros past them.
+template <int ROWS, bool TAIL>
+__device__ __forceinline__ void load_quads(const float* __restrict__ g, int64_t ldg, int32_t rows, int64_t T,
+                                           int64_t d, f32x4 (&A)[ROWS])
+{
+    const int lane = threadIdx.x & 63;
+    const float* tile = g + (T << 8);
+    const int64_t left = TAIL ? d - (T << 8) - 4 * lane : 4;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const float* p = tile + static_cast<int64_t>(r < rows ? r : rows - 1) * ldg + 4 * lane;
+        if (left >= 4) {
+            A[r] = load_nt(p);
+        } else {
+            A[r].x = left > 0 ? p[0] : 0.0f;
+            A[r].y = left > 1 ? p[1] : 0.0f;
+            A[r].z = left > 2 ? p[2] : 0.0f;
+            A[r].w = 0.0f;
+        }
+    }
+}
+
+// Philox counter words 0 and 1 of this lane in 256-coordinate tile T.
+__device__ __forceinline__ uint32_t quad_c0(int64_t T)
+{
+    return (static_cast<uint32_t>(T) << 5) | ((threadIdx.x & 63u) >> 1);
+}
+__device__ __forceinline__ uint32_t quad_c1(int64_t T)
+{
+    return static_cast<uint32_t>(static_cast<uint64_t>(T) >> 27);
+}
+
+// Adds mag * sgn of rows 2p ([0], [1]) and, unless it is past the last row,
+// 2p + 1 ([2], [3]) to the quad's sums.
+__device__ __forceinline__ void add_pair(const u16x2 mag[4], const u16x2 sgn[4], bool both, u16x2& h0, u16x2& h1)
+{
+    h0 = mag[0] * sgn[0] + h0;
+    h1 = mag[1] * sgn[1] + h1;
+    if (both) {
+        h0 = mag[2] * sgn[2] + h0;
+        h1 = mag[3] * sgn[3] + h1;
+    }
+}
+
+template <int ROWS, bool MULTI, bool NT, bool TAIL>
+__device__ __forceinline__ void rows_tile(const f32x4 (&A)[ROWS], const float* __restrict__ g, int64_t ldg,
+                                          int32_t rows, uint32_t worker0, int64_t T, int64_t d, const WaveScale& c, int32_t K, const RowTables& tab,
+                                          uint32_t key0, uint32_t key1, uint8_t* __restrict__ idx,
+                                          int32_t* __restrict__ sum, float* __restrict__ out)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t a_off = T << 8;
+    const int64_t left = TAIL ? d - a_off - 4 * lane : 4;
+    uint32_t k[4] = {0u, 0u, 0u, 0u};
+    float inv[4];
+    if (MULTI) {
+        quad_index<ROWS>(A, c, K, k);
+        const uint32_t word = k[0] | (k[1] << 8) | (k[2] << 16) | (k[3] << 24);
+        if (left >= 4) {
+            store_through<false>(idx + a_off, 4 * lane, word);
+        } else {
+            for (int j = 0; j < left; ++j)
+                idx[a_off + 4 * lane + j] = static_cast<uint8_t>(word >> (8 * j));
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        inv[j] = MULTI ? tab.inv[k[j]] : lane_value(c.inv, 0);
+    const uint32_t c0 = quad_c0(T), c1 = quad_c1(T);
+    const uint32_t odd = threadIdx.x & 1u;
+    const LaneKey lk = lane_key(c0, 0u, key1);
+    const float inv8[8] = {inv[0], inv[1], inv[2], inv[3], inv[0], inv[1], inv[2], inv[3]};
+    u16x2 h0 = {0, 0}, h1 = {0, 0};
+    u16x2 mag[4], sgn[4];
+    uint32_t bits[4];
+    uint32_t redo = 0u;  // row pairs that need the exact form (wave-uniform)
+#pragma unroll
+    for (int p = 0; p < ROWS / 2; ++p) {
+        if (2 * p < rows) {
+            // the pair's row keys are read when its turn comes (the index
+            // depends on the sums so far): read ahead for every pair, they
+            // take 8 registers each and cost waves on the SIMD (8 rows at
+            // 11.2 M coordinates, four scales: 78.7 us against 73.3)
+            uint32_t row = 2 * p + odd;
+            __asm__ volatile("" : "+v"(row) : "v"(h0));
+            const float v[8] = {A[2 * p].x,     A[2 * p].y,     A[2 * p].z,     A[2 * p].w,
+                                A[2 * p + 1].x, A[2 * p + 1].y, A[2 * p + 1].z, A[2 * p + 1].w};
+            const bool rare = fast_mags(v, inv8, c.s0x, lk, tab.key[row], key0, key1, bits, mag, sgn);
+            redo |= rare || !c.pre ? 1u << p : 0u;
+            add_pair(mag, sgn, 2 * p + 1 < rows, h0, h1);
+        }
+    }
+    // the pairs that need it once more, from memory: the exact magnitudes in
+    // place of the fast ones (a loop here instead of a branch per pair keeps
+    // the tile's code straight and a third of the size)
+    while (__builtin_expect(redo != 0u, 0)) {
+        const int p = __builtin_ctz(redo);
+        redo &= redo - 1u;
+        f32x4 B[2];
+        const int32_t r0 = 2 * p;
+        load_quads<2, TAIL>(g + static_cast<int64_t>(r0) * ldg, ldg, rows - r0 < 2 ? 1 : 2, T, d, B);
+        const float v[8] = {B[0].x, B[0].y, B[0].z, B[0].w, B[1].x, B[1].y, B[1].z, B[1].w};
+        fast_mags(v, inv8, c.s0x, lk, tab.key[2 * p + odd], key0, key1, bits, mag, sgn);
+        u16x2 ex[4];
+        exact_mags(v, inv8, c.s0x, c.pre, c0, c1, worker0 + 2u * p + odd, key0, key1, bits, ex);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            ex[j] -= mag[j];
+        add_pair(ex, sgn, r0 + 1 < rows, h0, h1);
+    }
+    const i32x4 s = {static_cast<int16_t>(h0.x), static_cast<int16_t>(h0.y), static_cast<int16_t>(h1.x),
+                     static_cast<int16_t>(h1.y)};
+    const float deq0 = lane_value(c.deq, 0);
+    f32x4 o;
+    o.x = static_cast<float>(s.x) * (MULTI ? tab.deq[k[0]] : deq0);
+    o.y = static_cast<float>(s.y) * (MULTI ? tab.deq[k[1]] : deq0);
+    o.z = static_cast<float>(s.z) * (MULTI ? tab.deq[k[2]] : deq0);
+    o.w = static_cast<float>(s.w) * (MULTI ? tab.deq[k[3]] : deq0);
+    if (left >= 4) {
+        store_through<NT>(sum + a_off, 16 * lane, s);
+        store_through<NT>(out + a_off, 16 * lane, o);
+    } else {
+        const int64_t i = a_off + 4 * lane;
+        if (left > 0) { sum[i] = s.x; out[i] = o.x; }
+        if (left > 1) { sum[i + 1] = s.y; out[i + 1] = o.y; }
+        if (left > 2) { sum[i + 2] = s.z; out[i + 2] = o.z; }
+    }
+}
+
+// Block b takes tile tile0 + b; the tile past the whole ones holds the last
+// coordinates.  There is no loop over tiles: with one, the compiler kept the
+// rows' keys and other loop invariants in registers (155 instead of 101 at 16
+// rows); a call with more tiles than the grid cap is several launches.
+template <int ROWS, bool MULTI, bool NT>
+__device__ __forceinline__ void rows_block(const float* __restrict__ g, int64_t d, int32_t rows, int64_t ldg,
+                                           int32_t worker0, const float* __restrict__ wptr, const ScaleSet& S,
+                                           uint32_t key0, uint32_t key1, int64_t tile0, uint8_t* __restrict__ idx,
+                                           int32_t* __restrict__ sum, int32_t M, float* __restrict__ out)
+{
+    __shared__ RowTables tab;
+    const int64_t T = tile0 + blockIdx.x;
+    const bool whole = T < d >> 8;
+    f32x4 A[ROWS];
+    if (whole)
+        load_quads<ROWS, false>(g, ldg, rows, T, d, A);
+    if (threadIdx.x < ROWS)
+        tab.key[threadIdx.x] = row_key(quad_c1(T), static_cast<uint32_t>(worker0) + threadIdx.x, key0);
+    const WaveScale c = wave_scale<MULTI>(wptr, S, M);
+    if (MULTI && threadIdx.x < kMaxScales) {
+        tab.inv[threadIdx.x] = c.inv;
+        tab.deq[threadIdx.x] = c.deq;
     }
     __syncthreads();
-    // thread e forms the table's entry e (the rule of k_index_max with the
-    // thresholds' full bits): x + [bits(a) <= y] is the index of a value a > 0
-    // of binade e; a binade without a threshold inside holds y = 0xFFFFFFFF
-    // with x lowered by one; on the zero path every value gets K - 1
-    int crowded = 0;
-    {
-        const uint32_t e = threadIdx.x;
-        int32_t above = 0, inside = 0;
-        uint32_t tin = 0u;
-        for (int k = 0; k < K; ++k) {
-            const uint32_t tb = __float_as_uint(thr_s[k]);
-            above += (tb >> 23) > e ? 1 : 0;
-            if ((tb >> 23) == e) {
-                ++inside;
-                tin = tb;
-            }
-        }
-        uint2 ent;
-        if (zero) {
-            ent.x = static_cast<uint32_t>(K - 2);
-            ent.y = 0xFFFFFFFFu;
-        } else {
-            crowded = inside > 1 ? 1 : 0;
-            const bool limit = inside > 0 && above > 0;
-            ent.x = static_cast<uint32_t>(above > 0 ? above - 1 : 0) - (limit ? 0u : 1u);
-            ent.y = limit ? tin : 0xFFFFFFFFu;
-        }
-        tab_s[e] = ent;
+    if (whole) {
+        rows_tile<ROWS, MULTI, NT, false>(A, g, ldg, rows, static_cast<uint32_t>(worker0), T, d, c, S.K, tab, key0, key1,
+                                      idx, sum, out);
+    } else {
+        load_quads<ROWS, true>(g, ldg, rows, T, d, A);
+        rows_tile<ROWS, MULTI, NT, true>(A, g, ldg, rows, static_cast<uint32_t>(worker0), T, d, c, S.K, tab, key0, key1,
+                                     idx, sum, out);
     }
-    const bool by_table = __syncthreads_or(crowded) == 0;
-    const float s0x = pre ? s0 * 65536.0f : s0;
+}
 
-    // the preloaded tile, then (on a grid capped below one tile per wave)
-    // every stride-th tile after it
-    for (int64_t T = first; T < ntiles; T += stride) {
-        if (T != first)
-            load_rows(T);
-        if (pre)
-            index_quant_sum_tile<ROWS, true, NT, true>(A, B, M, 0u, T, tab_s, by_table, thr_s, K, zero, inv_p, s0x,
-                                                       deq_s, key0, key1, idx, sum, out);
-        else
-            index_quant_sum_tile<ROWS, false, NT, true>(A, B, M, 0u, T, tab_s, by_table, thr_s, K, zero, inv_p, s0x,
-                                                        deq_s, key0, key1, idx, sum, out);
-    }
-    if (blockIdx.x == 0 && threadIdx.x < 64)
-        index_quant_sum_tail(g, d, ldg, M, ntiles, thr_s, K, zero, inv_s, s0, key0, key1, idx, sum, deq_s, out);
+// One scale.
+template <int ROWS, bool NT>
+__global__ __launch_bounds__(64) void k_quant_sum_split(const float* __restrict__ g, int64_t d, int32_t rows,
+                                                        int64_t ldg, int32_t worker0, const float* __restrict__ wptr,
+                                                        ScaleSet S, uint32_t key0, uint32_t key1, int64_t tile0,
+                                                        int32_t* __restrict__ sum, int32_t M, float* __restrict__ out)
+{
+    rows_block<ROWS, false, NT>(g, d, rows, ldg, worker0, wptr, S, key0, key1, tile0, nullptr, sum, M, out);
+}
+
+// Several scales, the shared index formed and stored: all M rows, as workers
+// 0 .. M - 1.
+template <int ROWS, bool NT>
+__global__ __launch_bounds__(64) void k_index_quant_sum(const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg,
+                                                        const float* __restrict__ wptr, ScaleSet S, uint32_t key0,
+                                                        uint32_t key1, int64_t tile0, uint8_t* __restrict__ idx,
+                                                        int32_t* __restrict__ sum, float* __restrict__ out)
+{
+    rows_block<ROWS, true, NT>(g, d, M, ldg, 0, wptr, S, key0, key1, tile0, idx, sum, M, out);
 }
 
 // ---------------------------------------------------------------------------
@@ -2290,123 +2405,6 @@ __global__ __launch_bounds__(kBlock) void k_index_quantise(const float* __restri
 }
 
 // ---------------------------------------------------------------------------
-// One scale, 5 to 16 rows set and reconstructed in one call, the rows of a
-// tile split over the block's four waves: wave w holds rows w, w + 4, ...
-// (RPW of them) of the block's 512-coordinate tile in k_quantise's lane
-// layout, codes them (the codes and draws of k_quantise for that row and
-// tile) and sums them in the 16-bit lanes of the pair registers; the waves'
-// int32 sums meet in LDS, and waves 0 and 1 add them and store the tile's A
-// and B quads of sums and of the reconstruction.  The integer sums are exact
-// in any order.  Against one wave holding every row of a tile (the layout
-// k_index_quant_sum keeps for several scales), a wave needs about a third of
-// the registers (86 against 217 for 16 rows), so five waves share a SIMD
-// instead of two and hide each other's loads: measured on MI355X, 1.76 ->
-// 1.62 ms at VGG-16 size (16 rows) and 72.9 -> 69.6 us at ResNet-18 size
-// (8 rows, against k_quant_sum's row loop).  The same split with the shared
-// index formed in the pass (the waves' maxima meeting in LDS first) was
-// slower with several scales: each tile then waits at two barriers and each
-// block forms the thresholds and the exponent table again (ResNet-50 size,
-// 8 rows: 0.237 against 0.175 ms; VGG-16, four scales: 1.94 against 1.79 ms;
-// 0.209 and 1.82 ms with four tiles per block).
-// ---------------------------------------------------------------------------
-template <int RPW, bool PRE, bool NT>
-__device__ __forceinline__ void split_tile(const f32x4 (&A)[RPW], const f32x4 (&B)[RPW], int32_t rows,
-                                           uint32_t worker0, int64_t T, float inv0, float s0x, float deq0,
-                                           uint32_t key0, uint32_t key1, i32x4 (*ps)[128],
-                                           int32_t* __restrict__ sum, float* __restrict__ out)
-{
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(threadIdx.x >> 6));
-    const int64_t a_off = (T << 9) + 4 * lane;
-    const float inv[8] = {inv0, inv0, inv0, inv0, inv0, inv0, inv0, inv0};
-    uint32_t h[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int r = 0; r < RPW; ++r) {
-        const int32_t m = wave + 4 * r;
-        if (m < rows) {
-            const float v[8] = {A[r].x, A[r].y, A[r].z, A[r].w, B[r].x, B[r].y, B[r].z, B[r].w};
-            add_codes<PRE>(v, inv, s0x, T, worker0 + static_cast<uint32_t>(m), key0, key1, h);
-        }
-    }
-    int32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    widen_pairs(h, acc);
-    ps[wave][lane] = i32x4{acc[0], acc[1], acc[2], acc[3]};
-    ps[wave][64 + lane] = i32x4{acc[4], acc[5], acc[6], acc[7]};
-    __syncthreads();
-    if (wave < 2) {
-        // wave 0: the A quad of every lane, wave 1: the B quad
-        const int q = 64 * wave + lane;
-        const i32x4 s = (ps[0][q] + ps[1][q]) + (ps[2][q] + ps[3][q]);
-        const int64_t off = a_off + 256 * wave;
-        store_sum4<NT>(sum + off, s);
-        f32x4 o;
-        o.x = static_cast<float>(s.x) * deq0;
-        o.y = static_cast<float>(s.y) * deq0;
-        o.z = static_cast<float>(s.z) * deq0;
-        o.w = static_cast<float>(s.w) * deq0;
-        store_nt(out + off, o);
-    }
-}
-
-// One block per tile (blocks stride over the tiles on a capped grid).
-template <int RPW, bool NT>
-__global__ __launch_bounds__(kBlock) void k_quant_sum_split(const float* __restrict__ g, int64_t d, int32_t rows,
-                                                            int64_t ldg, int32_t worker0,
-                                                            const float* __restrict__ wptr, ScaleSet S, uint32_t key0,
-                                                            uint32_t key1, int32_t* __restrict__ sum, int32_t M,
-                                                            float* __restrict__ out)
-{
-    __shared__ i32x4 ps_s[2][4][128];  // by tile parity: the next tile's sums never overwrite ones being read
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(threadIdx.x >> 6));
-    const int64_t ntiles = d >> 9;
-    const uint32_t w0 = static_cast<uint32_t>(worker0);
-    const int64_t first = blockIdx.x;
-
-    // the first tile's rows go out before W is read
-    f32x4 A[RPW], B[RPW];
-    const auto load_rows = [&](int64_t T) {
-        const int64_t a_off = (T << 9) + 4 * lane;
-#pragma unroll
-        for (int r = 0; r < RPW; ++r) {
-            const int32_t m = wave + 4 * r;
-            const float* row = g + static_cast<int64_t>(m < rows ? m : rows - 1) * ldg;
-            A[r] = load_nt(row + a_off);
-            B[r] = load_nt(row + a_off + 256);
-        }
-    };
-    if (first < ntiles)
-        load_rows(first);
-
-    const float W = *wptr;
-    const float s0 = S.s[0];
-    const float q0 = div_rn32(s0, W);
-    const bool zero = zero_path(W, q0);
-    const bool pre = zero || q0 <= 0x1p100f;
-    const float inv0 = zero ? 0.0f : q0;
-    const float denom = static_cast<float>(static_cast<double>(M) * static_cast<double>(s0));
-    const float deq0 = zero ? 0.0f : div_rn32(W, denom);
-    const float s0x = pre ? s0 * 65536.0f : s0;
-    const float invx = pre ? inv0 * 65536.0f : inv0;
-
-    int parity = 0;
-    for (int64_t T = first; T < ntiles; T += gridDim.x) {
-        if (T != first)
-            load_rows(T);
-        if (pre)
-            split_tile<RPW, true, NT>(A, B, rows, w0, T, invx, s0x, deq0, key0, key1, ps_s[parity], sum, out);
-        else
-            split_tile<RPW, false, NT>(A, B, rows, w0, T, invx, s0x, deq0, key0, key1, ps_s[parity], sum, out);
-        parity ^= 1;
-    }
-    if (blockIdx.x == 0 && threadIdx.x < 64) {
-        const float inv_t[1] = {inv0}, deq_t[1] = {deq0};
-        quant_sum_tail<false, false, true>(g, d, ldg, rows, w0, nullptr, ntiles, inv_t, inv0, s0, 0u, key0, key1, sum,
-                                           deq_t, out);
-    }
-}
-
-// ---------------------------------------------------------------------------
 // Host-side launchers (called by the ABI layer after validation).
 // ---------------------------------------------------------------------------
 // Tiles per wave for the quantiser.  Launch-shape sweeps on MI355X with cold
@@ -2582,6 +2580,50 @@ hipError_t launch_quantise(const float* g, int64_t d, int32_t rows, int64_t ldg,
     return hipGetLastError();
 }
 
+// Write-through stores also carry the nontemporal hint when the sums exceed
+// this many bytes, the Infinity Cache's size (work-free passes): the sums and
+// outputs of 16 rows at VGG-16 size, with the index, 1.64 against 1.72 ms;
+// at ResNet-50 size (102 MB) 167 us with the hint, 157 without.
+constexpr int64_t kThroughNontemporalBytes = int64_t(256) << 20;
+
+// One scale, 5 <= rows <= kFuseRows rows set and reconstructed in one call:
+// one block per 256-coordinate tile (the last one partial), one instance per
+// row pair count.
+#define UQ_ROW_PAIRS_3_TO_8(LAUNCH, NT) \
+    LAUNCH(3, NT);                      \
+    LAUNCH(4, NT);                      \
+    LAUNCH(5, NT);                      \
+    LAUNCH(6, NT);                      \
+    LAUNCH(7, NT);                      \
+    LAUNCH(8, NT)
+#define UQ_ROW_PAIRS_1_TO_8(LAUNCH, NT) \
+    LAUNCH(1, NT);                      \
+    LAUNCH(2, NT);                      \
+    UQ_ROW_PAIRS_3_TO_8(LAUNCH, NT)
+
+static hipError_t launch_quant_sum_split(const float* g, int64_t d, int32_t rows, int64_t ldg, int32_t worker0,
+                                         const float* w, const ScaleSet& S, uint32_t key0, uint32_t key1,
+                                         int32_t* sum, int32_t M, float* out, hipStream_t stream)
+{
+    const int64_t ntiles = (d + 255) >> 8;
+    const bool nt = 4 * d > kThroughNontemporalBytes;
+    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
+        const dim3 grid(one_shot(ntiles - tile0, 1));
+#define UQ_LAUNCH_SPLIT(PAIRS, NT)                                                                                 \
+    case PAIRS:                                                                                                    \
+        hipLaunchKernelGGL((k_quant_sum_split<2 * PAIRS, NT>), grid, dim3(64), 0, stream, g, d, rows, ldg,         \
+                           worker0, w, S, key0, key1, tile0, sum, M, out);                                         \
+        break
+        if (nt) {
+            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_3_TO_8(UQ_LAUNCH_SPLIT, true); }
+        } else {
+            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_3_TO_8(UQ_LAUNCH_SPLIT, false); }
+        }
+#undef UQ_LAUNCH_SPLIT
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_quant_sum(const float* g, int64_t d, int32_t rows, int64_t ldg, int32_t worker0, const float* w,
                             const ScaleSet& S, const uint8_t* idx, uint64_t seed, int32_t accumulate, int32_t* sum,
                             int32_t M, float* out, hipStream_t stream, int32_t idx_bits)
@@ -2598,27 +2640,8 @@ hipError_t launch_quant_sum(const float* g, int64_t d, int32_t rows, int64_t ldg
     const bool multi = S.K > 1;
     const bool acc = accumulate != 0;
     const bool deq = out != nullptr;
-    if (!multi && !acc && deq && rows > 4 && rows <= kFuseRows) {
-        // one scale, 5 to 16 rows set and reconstructed: the rows of a tile
-        // split over the block's waves, one block per tile
-        const dim3 sgrid(one_shot(d >> 9, 1));
-#define UQ_LAUNCH_SPLIT(RPW, NT)                                                                                  \
-    hipLaunchKernelGGL((k_quant_sum_split<RPW, NT>), sgrid, dim3(kBlock), 0, stream, g, d, rows, ldg, worker0, w,   \
-                       S, key0, key1, sum, M, out)
-        if (rows <= 8) {
-            if (nt)
-                UQ_LAUNCH_SPLIT(2, true);
-            else
-                UQ_LAUNCH_SPLIT(2, false);
-        } else {
-            if (nt)
-                UQ_LAUNCH_SPLIT(4, true);
-            else
-                UQ_LAUNCH_SPLIT(4, false);
-        }
-#undef UQ_LAUNCH_SPLIT
-        return hipGetLastError();
-    }
+    if (!multi && !acc && deq && rows > 4 && rows <= kFuseRows)
+        return launch_quant_sum_split(g, d, rows, ldg, worker0, w, S, key0, key1, sum, M, out, stream);
 #define UQ_LAUNCH_QSUM_(MULTI, ACC, DEQ, NT, NIB)                                                                   \
     do {                                                                                                           \
         if (rows == 1)                                                                                             \
@@ -2671,26 +2694,24 @@ hipError_t launch_index_quant_sum(const float* g, int64_t d, int32_t M, int64_t 
         return hipSuccess;
     const uint32_t key0 = static_cast<uint32_t>(seed);
     const uint32_t key1 = static_cast<uint32_t>(seed >> 32);
-    const dim3 grid(one_shot(d >> 9, kBlock / 64));
-    const bool nt = 4 * d > kSumNontemporalBytes;
-#define UQ_LAUNCH_IQS(ROWS)                                                                                        \
-    do {                                                                                                           \
-        if (nt)                                                                                                    \
-            hipLaunchKernelGGL((k_index_quant_sum<ROWS, true>), grid, dim3(kBlock), 0, stream, g, d, M, ldg, w, S, \
-                               key0, key1, idx, sum, out);                                                         \
-        else                                                                                                       \
-            hipLaunchKernelGGL((k_index_quant_sum<ROWS, false>), grid, dim3(kBlock), 0, stream, g, d, M, ldg, w,   \
-                               S, key0, key1, idx, sum, out);                                                      \
-    } while (0)
-    if (M <= 2)
-        UQ_LAUNCH_IQS(2);
-    else if (M <= 4)
-        UQ_LAUNCH_IQS(4);
-    else if (M <= 8)
-        UQ_LAUNCH_IQS(8);
-    else
-        UQ_LAUNCH_IQS(16);
+    // one block per 256-coordinate tile (the last one partial), one instance
+    // per row pair count
+    const int64_t ntiles = (d + 255) >> 8;
+    const bool nt = 4 * d > kThroughNontemporalBytes;
+    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
+        const dim3 grid(one_shot(ntiles - tile0, 1));
+#define UQ_LAUNCH_IQS(PAIRS, NT)                                                                                   \
+    case PAIRS:                                                                                                    \
+        hipLaunchKernelGGL((k_index_quant_sum<2 * PAIRS, NT>), grid, dim3(64), 0, stream, g, d, M, ldg, w, S,      \
+                           key0, key1, tile0, idx, sum, out);                                                      \
+        break
+        if (nt) {
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, true); }
+        } else {
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, false); }
+        }
 #undef UQ_LAUNCH_IQS
+    }
     return hipGetLastError();
 }
 
