@@ -917,36 +917,40 @@ __device__ __forceinline__ uint32_t pack_field(const int32_t c[4])
     return w;
 }
 
-// Stores four consecutive codes held as 16-bit lanes of p01 (codes 0, 1) and
-// p23 (codes 2, 3) at coordinate `coord` of a code row.
-template <int BITS, bool NT>
-__device__ __forceinline__ void store_pairs(uint8_t* row, int64_t coord, uint32_t p01, uint32_t p23)
+// Four consecutive codes (16-bit lanes of p01, p23) in the code row's layout:
+// 4, 2 or 1 bytes.
+template <int BITS>
+__device__ __forceinline__ uint32_t pack_quad(uint32_t p01, uint32_t p23)
 {
-    // the low byte of each lane: codes 0..3 in bytes 0..3
     const uint32_t w = __builtin_amdgcn_perm(p23, p01, 0x06040200u);
-    if (BITS == 8) {
-        uint32_t* p = reinterpret_cast<uint32_t*>(row + coord);
-        if (NT)
-            __builtin_nontemporal_store(w, p);
-        else
-            *p = w;
-    } else if (BITS == 4) {
+    if (BITS == 8)
+        return w;
+    if (BITS == 4) {
         const uint32_t x = w & 0x0F0F0F0Fu;
-        const uint32_t y = x | (x >> 4);  // byte 0: codes 0, 1; byte 2: codes 2, 3
-        const uint16_t v = static_cast<uint16_t>(__builtin_amdgcn_perm(0u, y, 0x0C0C0200u));
-        uint16_t* p = reinterpret_cast<uint16_t*>(row + coord / 2);
-        if (NT)
-            __builtin_nontemporal_store(v, p);
-        else
-            *p = v;
+        const uint32_t y = x | (x >> 4);
+        return __builtin_amdgcn_perm(0u, y, 0x0C0C0200u);
+    }
+    const uint32_t x = w & 0x03030303u;
+    const uint32_t y = x | (x >> 6);
+    return (y | (y >> 12)) & 0xFFu;
+}
+
+// Stores a lane's A and B quads of codes of one tile (pairs p[0], p[1] and
+// p[2], p[3]) to the tile's bytes of a code row.
+template <int BITS, bool NT>
+__device__ __forceinline__ void store_quads(uint8_t* tile, const uint32_t p[4])
+{
+    const uint32_t a = pack_quad<BITS>(p[0], p[1]), b = pack_quad<BITS>(p[2], p[3]);
+    const uint32_t at = (threadIdx.x & 63u) * (BITS / 2);
+    if (BITS == 8) {
+        store_through<NT>(tile, at, a);
+        store_through<NT>(tile, at + 256, b);
+    } else if (BITS == 4) {
+        store_through<NT>(tile, at, static_cast<uint16_t>(a));
+        store_through<NT>(tile, at + 128, static_cast<uint16_t>(b));
     } else {
-        const uint32_t x = w & 0x03030303u;
-        const uint32_t y = x | (x >> 6);  // byte 0: codes 0, 1; byte 2: codes 2, 3
-        const uint8_t v = static_cast<uint8_t>(y | (y >> 12));
-        if (NT)
-            __builtin_nontemporal_store(v, row + coord / 4);
-        else
-            row[coord / 4] = v;
+        store_through<NT>(tile, at, static_cast<uint8_t>(a));
+        store_through<NT>(tile, at + 64, static_cast<uint8_t>(b));
     }
 }
 
@@ -1072,102 +1076,58 @@ __device__ __forceinline__ void tile_mags(const float v[8], const float inv[8], 
         exact_mags(v, inv, s0x, pre, c0, c1, worker, key0, key1, h, mag);
 }
 
-// One row's eight codes of one lane as 16-bit lane pairs.
-template <bool PRE>
-__device__ __forceinline__ void tile_codes(const float v[8], const float inv[8], float s0x, int64_t T,
-                                           uint32_t worker, uint32_t key0, uint32_t key1, uint32_t p[4])
+// The call's constants in one wave: lane k < K forms scale k's entries.
+struct WaveScale {
+    float s0x;       // s_0 * 2^16 when pre, else s_0
+    bool pre;
+    // lane k's s_k / W, the same times 2^16 when pre, and RN32(W / (M s_k));
+    // 0 on the zero path
+    float raw, inv, deq;
+};
+
+__device__ __forceinline__ float lane_value(float x, int32_t lane)
 {
-    u16x2 mag[4], sgn[4];
-    tile_mags(v, inv, s0x, PRE, T, worker, key0, key1, mag, sgn);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        p[j] = __builtin_bit_cast(uint32_t, static_cast<u16x2>(mag[j] * sgn[j]));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
 }
 
-// The same added to the lane pairs of h (one multiply-add each).
-template <bool PRE>
-__device__ __forceinline__ void add_codes(const float v[8], const float inv[8], float s0x, int64_t T,
-                                          uint32_t worker, uint32_t key0, uint32_t key1, uint32_t h[4])
+// The scales come to their lanes through scalar loads: a vector load of them
+// here would be waited for behind the rows' loads, which the counter of
+// outstanding loads retires in order, and so would everything formed from
+// it (measured on 4 rows of 25.6 M coordinates with four scales: 113.7 us against 108.1; 8 rows of 11.2 M: 79.5 against 73.3).
+template <bool MULTI>
+__device__ __forceinline__ WaveScale wave_scale(const float* __restrict__ wptr, const ScaleSet& S, int32_t M)
 {
-    u16x2 mag[4], sgn[4];
-    tile_mags(v, inv, s0x, PRE, T, worker, key0, key1, mag, sgn);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        h[j] = __builtin_bit_cast(uint32_t, static_cast<u16x2>(mag[j] * sgn[j] + __builtin_bit_cast(u16x2, h[j])));
-}
-
-// One tile of one code row: the codes from the lane's loaded inputs, then
-// the stores.  inv_t / inv0 hold s_k / W, multiplied by 2^16 when PRE (then
-// s0x = s0 * 2^16 too), so that xs = x * 2^16 comes out of one multiply and
-// one min; without PRE (an entry is above 2^100, or infinite) the 2^16 is
-// applied after the min.  Both give xs = RN(|v| s_k / W) * 2^16 exactly
-// whenever |v| s_k / W is a normal number, and T = floor(xs) = 0 with a zero
-// threshold low half otherwise, so the codes do not depend on PRE.
-template <bool MULTI, int BITS, bool PRE, bool NT>
-__device__ __forceinline__ void code_tile(const TileIn& in, uint8_t* __restrict__ out, int64_t T,
-                                          const float* inv_t, float inv0, float s0x, uint32_t kmax,
-                                          uint32_t worker, uint32_t key0, uint32_t key1)
-{
-    const float v[8] = {in.A.x, in.A.y, in.A.z, in.A.w, in.B.x, in.B.y, in.B.z, in.B.w};
-    float inv[8];
+    WaveScale c;
+    const float W = *wptr;
+    float s = S.s[0];
     if (MULTI) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            inv[j] = inv_t[min((in.ka >> (8 * j)) & 0xFFu, kmax)];
-            inv[j + 4] = inv_t[min((in.kb >> (8 * j)) & 0xFFu, kmax)];
-        }
-    } else {
+        for (int k = 1; k < kMaxScales; ++k)
+            __asm__("v_writelane_b32 %0, %1, %2" : "+v"(s) : "s"(S.s[k]), "n"(k));
+    }
+    const float q = div_rn32(s, W);
+    const float s0 = S.s[0];
+    const bool zero = zero_path(W, lane_value(q, 0));
+    // the largest entry is the last scale's; 2^16 times it stays finite
+    c.pre = zero || lane_value(q, MULTI ? S.K - 1 : 0) <= 0x1p100f;
+    c.raw = zero ? 0.0f : q;
+    c.inv = c.pre ? c.raw * 65536.0f : c.raw;
+    c.s0x = c.pre ? s0 * 65536.0f : s0;
+    // M * s_k is exactly representable in binary32 (checked on the host)
+    c.deq = zero ? 0.0f : div_rn32(W, static_cast<float>(static_cast<double>(M) * static_cast<double>(s)));
+    return c;
+}
+
+// One tile's scale entries for one lane: its A and B quads' entries of `inv`
+// (LDS, several scales) or the one scale's.
+template <bool MULTI>
+__device__ __forceinline__ void tile_scales(const TileIn& in, const float* inv_t, float inv0, uint32_t kmax,
+                                            float inv[8])
+{
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            inv[j] = inv0;
-    }
-    uint32_t p[4];
-    tile_codes<PRE>(v, inv, s0x, T, worker, key0, key1, p);
-    const int64_t a_off = (T << 9) + 4 * (threadIdx.x & 63);
-    store_pairs<BITS, NT>(out, a_off, p[0], p[1]);
-    store_pairs<BITS, NT>(out, a_off + 256, p[2], p[3]);
-}
-
-// The whole tiles of one code row when the grid covers them all at once: the
-// wave's tile `first` and, with several scales and tpw = 2, first + 1, as
-// straight-line code.  With one scale (tpw = 1) the tile arrives already
-// loaded in `in0`.  The loop form below, run with the same tiles, measured
-// 9% slower with one scale and 1% slower with several (its 64-bit tile
-// bounds are compared on the vector unit).
-template <bool MULTI, int BITS, bool PRE, bool NT>
-__device__ __forceinline__ void quantise_few(const float* __restrict__ row, uint8_t* __restrict__ out,
-                                             const uint8_t* __restrict__ idx, int64_t ntiles, int64_t first,
-                                             int32_t tpw, const TileIn& in0, const float* inv_t, float inv0,
-                                             float s0x, uint32_t kmax, uint32_t worker, uint32_t key0,
-                                             uint32_t key1)
-{
-    const int lane = threadIdx.x & 63;
-    if (first < ntiles) {
-        const TileIn in = MULTI ? load_tile<MULTI>(row, idx, (first << 9) + 4 * lane) : in0;
-        code_tile<MULTI, BITS, PRE, NT>(in, out, first, inv_t, inv0, s0x, kmax, worker, key0, key1);
-    }
-    if (MULTI && tpw == 2 && first + 1 < ntiles) {
-        const TileIn in = load_tile<MULTI>(row, idx, ((first + 1) << 9) + 4 * lane);
-        code_tile<MULTI, BITS, PRE, NT>(in, out, first + 1, inv_t, inv0, s0x, kmax, worker, key0, key1);
-    }
-}
-
-// The whole tiles of one code row on a capped grid: each wave takes `tpw`
-// consecutive tiles from `first`, then strides by the grid.
-template <bool MULTI, int BITS, bool PRE, bool NT>
-__device__ __forceinline__ void quantise_tiles(const float* __restrict__ row, uint8_t* __restrict__ out,
-                                               const uint8_t* __restrict__ idx, int64_t ntiles, int64_t first,
-                                               int64_t stride, const TileIn& in0, const float* inv_t, float inv0,
-                                               float s0x, uint32_t kmax, uint32_t worker, uint32_t key0,
-                                               uint32_t key1, int32_t tpw)
-{
-    const int lane = threadIdx.x & 63;
-    for (int64_t c0 = first; c0 < ntiles; c0 += stride) {
-        const int64_t c1 = c0 + tpw < ntiles ? c0 + tpw : ntiles;
-        for (int64_t T = c0; T < c1; ++T) {
-            const TileIn in = (!MULTI && T == first) ? in0 : load_tile<MULTI>(row, idx, (T << 9) + 4 * lane);
-            code_tile<MULTI, BITS, PRE, NT>(in, out, T, inv_t, inv0, s0x, kmax, worker, key0, key1);
-        }
+    for (int j = 0; j < 4; ++j) {
+        inv[j] = MULTI ? inv_t[min((in.ka >> (8 * j)) & 0xFFu, kmax)] : inv0;
+        inv[j + 4] = MULTI ? inv_t[min((in.kb >> (8 * j)) & 0xFFu, kmax)] : inv0;
     }
 }
 
@@ -1210,76 +1170,50 @@ __device__ __forceinline__ void quantise_tail(const float* __restrict__ row, uin
 }
 
 // The quantiser: MULTI with a per-coordinate scale index, BITS the code
-// width (8, or 4 / 2 packed), NT codes stored nontemporally (the launcher sets
-// it for launches that write more than kCodesNontemporalBytes).
+// width (8, or 4 / 2 packed), NT codes stored nontemporally too (launches that
+// write more than kThroughNontemporalBytes).  One wave per block and tile
+// (x: tiles from tile0, the one past the whole tiles the row's last
+// coordinates; y: rows), the tile's loads issued before the tables are formed.
 template <bool MULTI, int BITS, bool NT>
-__global__ __launch_bounds__(kBlock) void k_quantise(const float* __restrict__ g, int64_t d, int64_t ldg,
-                                                     int32_t worker0, const float* __restrict__ wptr,
-                                                     ScaleSet S, const uint8_t* __restrict__ idx,
-                                                     uint32_t key0, uint32_t key1,
-                                                     uint8_t* __restrict__ codes, int64_t ldc, int32_t tpw)
+__global__ __launch_bounds__(64) void k_quantise(const float* __restrict__ g, int64_t d, int64_t ldg, int32_t worker0,
+                                                 const float* __restrict__ wptr, ScaleSet S,
+                                                 const uint8_t* __restrict__ idx, uint32_t key0, uint32_t key1,
+                                                 int64_t tile0, uint8_t* __restrict__ codes, int64_t ldc)
 {
-    __shared__ float inv_s[kMaxScales];   // s_k / W
-    __shared__ float inv_p[kMaxScales];   // s_k / W * 2^16 when pre
-
-    // 2-D grid: tile blocks in x, worker rows in y; each wave takes `tpw`
-    // consecutive tiles (on a one-shot grid, only those), then strides by
-    // the grid
+    __shared__ float inv_s[kMaxScales];  // s_k / W
+    __shared__ float inv_p[kMaxScales];  // s_k / W * 2^16 when pre
     const int32_t r = blockIdx.y;
     const uint32_t worker = static_cast<uint32_t>(worker0) + static_cast<uint32_t>(r);
     const float* row = g + static_cast<int64_t>(r) * ldg;
     uint8_t* out = codes + static_cast<int64_t>(r) * ldc;
     const int64_t ntiles = d >> 9;
-    const int32_t wave_in_block = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(threadIdx.x >> 6));
-    const int64_t first = (static_cast<int64_t>(blockIdx.x) * (kBlock / 64) + wave_in_block) * tpw;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * (kBlock / 64) * tpw;
-
-    // with one scale the first tile's loads go out before the tables are
-    // formed, so that their latency covers the load of W and the division
-    // (with several scales this measured slower, so there they stay in the
-    // tile loop)
-    TileIn in0 = {};
-    if (!MULTI && first < ntiles)
-        in0 = load_tile<MULTI>(row, idx, (first << 9) + 4 * (threadIdx.x & 63));
-
-    const float W = *wptr;
-    // tables; on the zero path every entry is 0, which makes every code 0
-    const float q0 = div_rn32(S.s[0], W);
-    const bool zero = zero_path(W, q0);
-    // the largest entry is the last scale's; 2^16 times it stays finite
-    const bool pre = zero || (MULTI ? div_rn32(S.s_last, W) : q0) <= 0x1p100f;
-    float inv0 = 0.0f;
-    if (MULTI) {
-        if (threadIdx.x < S.K) {
-            const float inv = zero ? 0.0f : div_rn32(S.s[threadIdx.x], W);
-            inv_s[threadIdx.x] = inv;
-            inv_p[threadIdx.x] = pre ? inv * 65536.0f : inv;
-        }
-        __syncthreads();
-    } else {
-        inv0 = zero ? 0.0f : q0;
-    }
-    const float s0 = S.s[0];
+    const int64_t T = tile0 + blockIdx.x;
+    const int lane = threadIdx.x;
+    TileIn in = {};
+    if (T < ntiles)
+        in = load_tile<MULTI>(row, idx, (T << 9) + 4 * lane);
+    const WaveScale c = wave_scale<MULTI>(wptr, S, 1);
     const uint32_t kmax = static_cast<uint32_t>(S.K - 1);
-
-    if (stride >= ntiles && tpw <= (MULTI ? 2 : 1)) {
-        if (pre)
-            quantise_few<MULTI, BITS, true, NT>(row, out, idx, ntiles, first, tpw, in0, inv_p, inv0 * 65536.0f,
-                                                s0 * 65536.0f, kmax, worker, key0, key1);
-        else
-            quantise_few<MULTI, BITS, false, NT>(row, out, idx, ntiles, first, tpw, in0, inv_p, inv0, s0, kmax,
-                                                 worker, key0, key1);
-    } else if (pre)
-        quantise_tiles<MULTI, BITS, true, NT>(row, out, idx, ntiles, first, stride, in0, inv_p, inv0 * 65536.0f,
-                                              s0 * 65536.0f, kmax, worker, key0, key1, tpw);
-    else
-        quantise_tiles<MULTI, BITS, false, NT>(row, out, idx, ntiles, first, stride, in0, inv_p, inv0, s0, kmax,
-                                               worker, key0, key1, tpw);
-
-    // Coordinates past the last whole tile (fewer than 512): groups of 8
-    // contiguous coordinates, one per lane of the first wave of block x = 0.
-    if (blockIdx.x == 0 && threadIdx.x < 64)
-        quantise_tail<MULTI, BITS>(row, out, idx, d, ntiles, inv_s, inv0, s0, kmax, worker, key0, key1);
+    if (MULTI && lane < kMaxScales) {
+        inv_s[lane] = c.raw;
+        inv_p[lane] = c.inv;
+    }
+    __syncthreads();
+    if (T < ntiles) {
+        const float v[8] = {in.A.x, in.A.y, in.A.z, in.A.w, in.B.x, in.B.y, in.B.z, in.B.w};
+        float inv[8];
+        tile_scales<MULTI>(in, inv_p, lane_value(c.inv, 0), kmax, inv);
+        u16x2 mag[4], sgn[4];
+        tile_mags(v, inv, c.s0x, c.pre, T, worker, key0, key1, mag, sgn);
+        uint32_t p[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            p[j] = __builtin_bit_cast(uint32_t, static_cast<u16x2>(mag[j] * sgn[j]));
+        store_quads<BITS, NT>(out + T * (64 * BITS), p);
+    } else {
+        quantise_tail<MULTI, BITS>(row, out, idx, d, ntiles, inv_s, lane_value(c.raw, 0), S.s[0], kmax, worker, key0,
+                                   key1);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1450,71 +1384,49 @@ __global__ __launch_bounds__(kBlock) void k_sum(const uint8_t* __restrict__ code
 // ---------------------------------------------------------------------------
 // Reconstruction: out_i = RN32(sum_i * deq_k), deq_k = RN32(W / (M s_k)).
 // ---------------------------------------------------------------------------
+// One wave per block and 512 coordinates (the last block: fewer).
 template <bool MULTI>
-__global__ __launch_bounds__(kBlock) void k_dequant(const int32_t* __restrict__ sum, int64_t d, int32_t M,
-                                                    const float* __restrict__ wptr, ScaleSet S,
-                                                    const uint8_t* __restrict__ idx, float* __restrict__ out)
+__global__ __launch_bounds__(64) void k_dequant(const int32_t* __restrict__ sum, int64_t d, int32_t M,
+                                                const float* __restrict__ wptr, ScaleSet S,
+                                                const uint8_t* __restrict__ idx, int64_t tile0,
+                                                float* __restrict__ out)
 {
     __shared__ float deq_s[kMaxScales];
-    const int64_t nquad = d >> 2;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    // the first quad's loads go out before the tables are formed
-    i32x4 s_first = {0, 0, 0, 0};
-    uint32_t k_first = 0u;
-    if (first < nquad) {
-        s_first = load_nt(sum + (first << 2));
-        if (MULTI)
-            k_first = *reinterpret_cast<const uint32_t*>(idx + (first << 2));
-    }
-
-    const float W = *wptr;
-    const float inv0 = div_rn32(S.s[0], W);
-    const bool zero = zero_path(W, inv0);
-    if (threadIdx.x < S.K) {
-        // M * s_k is exactly representable in binary32 (checked on the host)
-        const float denom = static_cast<float>(static_cast<double>(M) * static_cast<double>(S.s[threadIdx.x]));
-        deq_s[threadIdx.x] = zero ? 0.0f : div_rn32(W, denom);
-    }
-    __syncthreads();
-    const int32_t kmax = S.K - 1;
-    const float deq0 = deq_s[0];
-
-    for (int64_t q = first; q < nquad; q += stride) {
-        i32x4 s;
-        uint32_t kk = 0u;
-        if (q == first) {
-            s = s_first;
-            kk = k_first;
-        } else {
-            s = load_nt(sum + (q << 2));
+    const int lane = threadIdx.x;
+    const int64_t T = tile0 + blockIdx.x;
+    const int64_t t_off = T << 9;
+    const bool whole = T < d >> 9;
+    i32x4 s[2] = {};
+    uint32_t kk[2] = {0u, 0u};
+    if (whole) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int64_t i = t_off + 256 * h + 4 * lane;
+            s[h] = load_nt(sum + i);
             if (MULTI)
-                kk = *reinterpret_cast<const uint32_t*>(idx + (q << 2));
+                kk[h] = *reinterpret_cast<const uint32_t*>(idx + i);
         }
-        f32x4 o;
-        if (MULTI) {
-            const int32_t k0 = min(static_cast<int32_t>(kk & 0xFFu), kmax);
-            const int32_t k1 = min(static_cast<int32_t>((kk >> 8) & 0xFFu), kmax);
-            const int32_t k2 = min(static_cast<int32_t>((kk >> 16) & 0xFFu), kmax);
-            const int32_t k3 = min(static_cast<int32_t>(kk >> 24), kmax);
-            o.x = static_cast<float>(s.x) * deq_s[k0];
-            o.y = static_cast<float>(s.y) * deq_s[k1];
-            o.z = static_cast<float>(s.z) * deq_s[k2];
-            o.w = static_cast<float>(s.w) * deq_s[k3];
-        } else {
-            o.x = static_cast<float>(s.x) * deq0;
-            o.y = static_cast<float>(s.y) * deq0;
-            o.z = static_cast<float>(s.z) * deq0;
-            o.w = static_cast<float>(s.w) * deq0;
-        }
-        store_nt(out + (q << 2), o);
     }
-    const int64_t t = (nquad << 2) + static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (blockIdx.x == 0 && t < d) {
-        int32_t k = 0;
-        if (MULTI)
-            k = min(static_cast<int32_t>(idx[t]), kmax);
-        out[t] = static_cast<float>(sum[t]) * deq_s[k];
+    const WaveScale c = wave_scale<MULTI>(wptr, S, M);
+    const float deq0 = lane_value(c.deq, 0);
+    const uint32_t kmax = static_cast<uint32_t>(S.K - 1);
+    if (MULTI && lane < kMaxScales)
+        deq_s[lane] = c.deq;
+    __syncthreads();
+    if (whole) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const auto f = [&](int j) { return MULTI ? deq_s[min((kk[h] >> (8 * j)) & 0xFFu, kmax)] : deq0; };
+            f32x4 o;
+            o.x = static_cast<float>(s[h].x) * f(0);
+            o.y = static_cast<float>(s[h].y) * f(1);
+            o.z = static_cast<float>(s[h].z) * f(2);
+            o.w = static_cast<float>(s[h].w) * f(3);
+            store_through<false>(out + t_off, 1024 * h + 16 * lane, o);
+        }
+    } else {
+        for (int64_t i = t_off + lane; i < d; i += 64)
+            out[i] = static_cast<float>(sum[i]) * (MULTI ? deq_s[min(static_cast<uint32_t>(idx[i]), kmax)] : deq0);
     }
 }
 
@@ -1545,15 +1457,6 @@ __device__ __forceinline__ i32x4 load_sum4(const int32_t* p)
     return *reinterpret_cast<const i32x4*>(p);
 }
 
-template <bool NT>
-__device__ __forceinline__ void store_sum4(int32_t* p, i32x4 v)
-{
-    if (NT)
-        __builtin_nontemporal_store(v, reinterpret_cast<i32x4*>(p));
-    else
-        *reinterpret_cast<i32x4*>(p) = v;
-}
-
 // Adds the 16-bit lane sums of h[4] (codes A0 A1, A2 A3, B0 B1, B2 B3) to the
 // int32 sums acc[8] and clears h.
 __device__ __forceinline__ void widen_pairs(uint32_t h[4], int32_t acc[8])
@@ -1563,72 +1466,6 @@ __device__ __forceinline__ void widen_pairs(uint32_t h[4], int32_t acc[8])
         acc[2 * j] += __builtin_amdgcn_sbfe(static_cast<int32_t>(h[j]), 0, 16);
         acc[2 * j + 1] += __builtin_amdgcn_sbfe(static_cast<int32_t>(h[j]), 16, 16);
         h[j] = 0u;
-    }
-}
-
-// One tile of every row: `in` holds row 0's quads and the tile's index words,
-// oldA / oldB the sums already stored (when ACC).  inv_t / inv0 / s0x as for
-// code_tile.
-template <bool MULTI, bool PRE, bool ACC, bool DEQ, bool NT, bool ROW1>
-__device__ __forceinline__ void quant_sum_tile(const float* __restrict__ g, int64_t ldg, int32_t rows,
-                                               uint32_t worker0, int64_t T, TileIn in, i32x4 oldA, i32x4 oldB,
-                                               const float* inv_t, float inv0, float s0x, uint32_t kmax,
-                                               uint32_t key0, uint32_t key1,
-                                               int32_t* __restrict__ sum, const float* deq_t,
-                                               float* __restrict__ out)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t a_off = (T << 9) + 4 * lane;
-    float inv[8];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        inv[j] = MULTI ? inv_t[min((in.ka >> (8 * j)) & 0xFFu, kmax)] : inv0;
-        inv[j + 4] = MULTI ? inv_t[min((in.kb >> (8 * j)) & 0xFFu, kmax)] : inv0;
-    }
-    int32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    uint32_t h[4] = {0u, 0u, 0u, 0u};
-    int32_t pending = 0;
-    f32x4 A = in.A, B = in.B;
-    const int32_t nrows = ROW1 ? 1 : rows;
-    for (int32_t r = 0; r < nrows; ++r) {
-        f32x4 nA = A, nB = B;
-        if (!ROW1 && r + 1 < nrows) {
-            const float* nrow = g + static_cast<int64_t>(r + 1) * ldg;
-            nA = load_nt(nrow + a_off);
-            nB = load_nt(nrow + a_off + 256);
-        }
-        const float v[8] = {A.x, A.y, A.z, A.w, B.x, B.y, B.z, B.w};
-        add_codes<PRE>(v, inv, s0x, T, worker0 + static_cast<uint32_t>(r), key0, key1, h);
-        if (++pending == kPairRows) {
-            widen_pairs(h, acc);
-            pending = 0;
-        }
-        A = nA;
-        B = nB;
-    }
-    widen_pairs(h, acc);
-    i32x4 sa = {acc[0], acc[1], acc[2], acc[3]};
-    i32x4 sb = {acc[4], acc[5], acc[6], acc[7]};
-    if (ACC) {
-        sa += oldA;
-        sb += oldB;
-    }
-    store_sum4<NT>(sum + a_off, sa);
-    store_sum4<NT>(sum + a_off + 256, sb);
-    if (DEQ) {
-        // the index words again (two registers live instead of eight indices)
-        const auto k = [&](uint32_t word, int j) { return MULTI ? min((word >> (8 * j)) & 0xFFu, kmax) : 0u; };
-        f32x4 oa, ob;
-        oa.x = static_cast<float>(sa.x) * deq_t[k(in.ka, 0)];
-        oa.y = static_cast<float>(sa.y) * deq_t[k(in.ka, 1)];
-        oa.z = static_cast<float>(sa.z) * deq_t[k(in.ka, 2)];
-        oa.w = static_cast<float>(sa.w) * deq_t[k(in.ka, 3)];
-        ob.x = static_cast<float>(sb.x) * deq_t[k(in.kb, 0)];
-        ob.y = static_cast<float>(sb.y) * deq_t[k(in.kb, 1)];
-        ob.z = static_cast<float>(sb.z) * deq_t[k(in.kb, 2)];
-        ob.w = static_cast<float>(sb.w) * deq_t[k(in.kb, 3)];
-        store_nt(out + a_off, oa);
-        store_nt(out + a_off + 256, ob);
     }
 }
 
@@ -1680,86 +1517,99 @@ __device__ __forceinline__ void quant_sum_tail(const float* __restrict__ g, int6
 }
 
 // ROW1: the one-row form (a streamed worker), compiled apart so that it does
-// not carry the row loop's registers.  NIB: the index as 4-bit fields.
+// not carry the row loop's registers.  NIB: the index as 4-bit fields.  NT:
+// the old sums loaded, and the sums and outputs stored, nontemporally too.
+// One wave per block and tile; tile d >> 9 holds the last coordinates.
 template <bool MULTI, bool ACC, bool DEQ, bool NT, bool ROW1, bool NIB>
-__global__ __launch_bounds__(kBlock) void k_quant_sum(const float* __restrict__ g, int64_t d, int32_t rows,
-                                                      int64_t ldg, int32_t worker0, const float* __restrict__ wptr,
-                                                      ScaleSet S, const uint8_t* __restrict__ idx, uint32_t key0,
-                                                      uint32_t key1, int32_t* __restrict__ sum, int32_t M,
-                                                      float* __restrict__ out)
+__global__ __launch_bounds__(64) void k_quant_sum(const float* __restrict__ g, int64_t d, int32_t rows, int64_t ldg,
+                                                  int32_t worker0, const float* __restrict__ wptr, ScaleSet S,
+                                                  const uint8_t* __restrict__ idx, uint32_t key0, uint32_t key1,
+                                                  int64_t tile0, int32_t* __restrict__ sum, int32_t M,
+                                                  float* __restrict__ out)
 {
     __shared__ float inv_s[kMaxScales];  // s_k / W
     __shared__ float inv_p[kMaxScales];  // s_k / W * 2^16 when pre
     __shared__ float deq_s[kMaxScales];  // RN32(W / (M s_k))
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x;
     const int64_t ntiles = d >> 9;
-    const int32_t wave_in_block = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(threadIdx.x >> 6));
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * (kBlock / 64) + wave_in_block;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * (kBlock / 64);
+    const int64_t T = tile0 + blockIdx.x;
+    const int64_t t_off = T << 9;
+    const int64_t a_off = t_off + 4 * lane;
     const uint32_t w0 = static_cast<uint32_t>(worker0);
 
-    // the first tile's loads (row 0, its index words, the old sums) go out
-    // before W is read and the tables are formed
-    TileIn in0 = {};
-    i32x4 oldA0 = {0, 0, 0, 0}, oldB0 = {0, 0, 0, 0};
-    if (first < ntiles) {
-        const int64_t a_off = (first << 9) + 4 * lane;
-        in0 = load_tile<MULTI, NIB>(g, idx, a_off);
+    // the tile's loads (row 0, its index words, the old sums) go out before
+    // W is read and the tables are formed
+    TileIn in = {};
+    i32x4 sa = {0, 0, 0, 0}, sb = {0, 0, 0, 0};
+    if (T < ntiles) {
+        in = load_tile<MULTI, NIB>(g, idx, a_off);
         if (ACC) {
-            oldA0 = load_sum4<NT>(sum + a_off);
-            oldB0 = load_sum4<NT>(sum + a_off + 256);
+            sa = load_sum4<NT>(sum + a_off);
+            sb = load_sum4<NT>(sum + a_off + 256);
         }
     }
-
-    const float W = *wptr;
-    const float q0 = div_rn32(S.s[0], W);
-    const bool zero = zero_path(W, q0);
-    const bool pre = zero || (MULTI ? div_rn32(S.s_last, W) : q0) <= 0x1p100f;
-    if (threadIdx.x < S.K) {
-        const float inv = zero ? 0.0f : div_rn32(S.s[threadIdx.x], W);
-        inv_s[threadIdx.x] = inv;
-        inv_p[threadIdx.x] = pre ? inv * 65536.0f : inv;
-        if (DEQ) {
-            const float denom = static_cast<float>(static_cast<double>(M) * static_cast<double>(S.s[threadIdx.x]));
-            deq_s[threadIdx.x] = zero ? 0.0f : div_rn32(W, denom);
-        }
+    const WaveScale c = wave_scale<MULTI>(wptr, S, M);
+    const uint32_t kmax = static_cast<uint32_t>(S.K - 1);
+    const float inv0 = lane_value(c.inv, 0), raw0 = lane_value(c.raw, 0), deq0 = DEQ ? lane_value(c.deq, 0) : 0.0f;
+    if (lane < kMaxScales) {
+        inv_s[lane] = c.raw;
+        inv_p[lane] = c.inv;
+        if (DEQ)
+            deq_s[lane] = c.deq;
     }
     __syncthreads();
-    const float inv0 = zero ? 0.0f : q0;
-    const float s0 = S.s[0];
-    const uint32_t kmax = static_cast<uint32_t>(S.K - 1);
-
-    // the preloaded tile, then (on a grid capped below one tile per wave)
-    // every stride-th tile after it
-    if (first < ntiles) {
-        if (pre)
-            quant_sum_tile<MULTI, true, ACC, DEQ, NT, ROW1>(g, ldg, rows, w0, first, in0, oldA0, oldB0, inv_p,
-                                                      inv0 * 65536.0f, s0 * 65536.0f, kmax, key0, key1, sum,
-                                                      deq_s, out);
-        else
-            quant_sum_tile<MULTI, false, ACC, DEQ, NT, ROW1>(g, ldg, rows, w0, first, in0, oldA0, oldB0, inv_p, inv0, s0,
-                                                       kmax, key0, key1, sum, deq_s, out);
+    if (T >= ntiles) {
+        quant_sum_tail<MULTI, ACC, DEQ, NIB>(g, d, ldg, rows, w0, idx, ntiles, inv_s, raw0, S.s[0], kmax, key0, key1,
+                                             sum, deq_s, out);
+        return;
     }
-    if (stride < ntiles) {
-        for (int64_t T = first + stride; T < ntiles; T += stride) {
-            const int64_t a_off = (T << 9) + 4 * lane;
-            const TileIn in = load_tile<MULTI, NIB>(g, idx, a_off);
-            i32x4 oldA = {0, 0, 0, 0}, oldB = {0, 0, 0, 0};
-            if (ACC) {
-                oldA = load_sum4<NT>(sum + a_off);
-                oldB = load_sum4<NT>(sum + a_off + 256);
-            }
-            if (pre)
-                quant_sum_tile<MULTI, true, ACC, DEQ, NT, ROW1>(g, ldg, rows, w0, T, in, oldA, oldB, inv_p, inv0 * 65536.0f,
-                                                          s0 * 65536.0f, kmax, key0, key1, sum, deq_s, out);
-            else
-                quant_sum_tile<MULTI, false, ACC, DEQ, NT, ROW1>(g, ldg, rows, w0, T, in, oldA, oldB, inv_p, inv0, s0,
-                                                           kmax, key0, key1, sum, deq_s, out);
+    float inv[8];
+    tile_scales<MULTI>(in, inv_p, inv0, kmax, inv);
+    int32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    uint32_t h[4] = {0u, 0u, 0u, 0u};
+    int32_t pending = 0;
+    f32x4 A = in.A, B = in.B;
+    const int32_t nrows = ROW1 ? 1 : rows;
+    for (int32_t r = 0; r < nrows; ++r) {
+        f32x4 nA = A, nB = B;
+        if (!ROW1 && r + 1 < nrows) {
+            const float* nrow = g + static_cast<int64_t>(r + 1) * ldg;
+            nA = load_nt(nrow + a_off);
+            nB = load_nt(nrow + a_off + 256);
         }
+        const float v[8] = {A.x, A.y, A.z, A.w, B.x, B.y, B.z, B.w};
+        u16x2 mag[4], sgn[4];
+        tile_mags(v, inv, c.s0x, c.pre, T, w0 + static_cast<uint32_t>(r), key0, key1, mag, sgn);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            h[j] = __builtin_bit_cast(uint32_t, static_cast<u16x2>(mag[j] * sgn[j] + __builtin_bit_cast(u16x2, h[j])));
+        if (++pending == kPairRows) {
+            widen_pairs(h, acc);
+            pending = 0;
+        }
+        A = nA;
+        B = nB;
     }
-    if (blockIdx.x == 0 && threadIdx.x < 64)
-        quant_sum_tail<MULTI, ACC, DEQ, NIB>(g, d, ldg, rows, w0, idx, ntiles, inv_s, inv0, s0, kmax, key0, key1, sum,
-                                        deq_s, out);
+    widen_pairs(h, acc);
+    sa += i32x4{acc[0], acc[1], acc[2], acc[3]};
+    sb += i32x4{acc[4], acc[5], acc[6], acc[7]};
+    store_through<NT>(sum + t_off, 16 * lane, sa);
+    store_through<NT>(sum + t_off, 16 * lane + 1024, sb);
+    if (DEQ) {
+        // the index words again (two registers live instead of eight indices)
+        const auto f = [&](uint32_t word, int j) { return MULTI ? deq_s[min((word >> (8 * j)) & 0xFFu, kmax)] : deq0; };
+        f32x4 oa, ob;
+        oa.x = static_cast<float>(sa.x) * f(in.ka, 0);
+        oa.y = static_cast<float>(sa.y) * f(in.ka, 1);
+        oa.z = static_cast<float>(sa.z) * f(in.ka, 2);
+        oa.w = static_cast<float>(sa.w) * f(in.ka, 3);
+        ob.x = static_cast<float>(sb.x) * f(in.kb, 0);
+        ob.y = static_cast<float>(sb.y) * f(in.kb, 1);
+        ob.z = static_cast<float>(sb.z) * f(in.kb, 2);
+        ob.w = static_cast<float>(sb.w) * f(in.kb, 3);
+        store_through<NT>(out + t_off, 16 * lane, oa);
+        store_through<NT>(out + t_off, 16 * lane + 1024, ob);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1787,88 +1637,6 @@ __device__ __forceinline__ float max3_abs(float m, float x, float y)
     return __builtin_elementwise_maximum(m, __builtin_elementwise_maximum(fabsf(x), fabsf(y)));
 }
 
-// INDEX: form the tile's shared index (several scales) and store it; else
-// one scale, every index 0.  The first `rows` rows are quantised, row r as
-// worker worker0 + r.
-// The shared index of a lane's eight coordinates of one tile (A quad, then B
-// quad) from the largest usable |g| over the ROWS rows it holds: two rows per
-// instruction with the NaN- and infinity-propagating maximum; a result that
-// is not finite means some value was not usable (infinite or NaN), and then
-// the lane forms the largest usable |g| value by value.  Then the exponent
-// table (by_table) or K threshold compares.
-template <int ROWS>
-__device__ __forceinline__ void tile_index(const f32x4 (&A)[ROWS], const f32x4 (&B)[ROWS], const uint2* tab,
-                                           bool by_table, const float* thr, int32_t K, bool zero, uint32_t k[8])
-{
-    float a[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    static_assert(ROWS % 2 == 0, "rows are taken in pairs");
-#pragma unroll
-    for (int r = 0; r < ROWS; r += 2) {
-        a[0] = max3_abs(a[0], A[r].x, A[r + 1].x);
-        a[1] = max3_abs(a[1], A[r].y, A[r + 1].y);
-        a[2] = max3_abs(a[2], A[r].z, A[r + 1].z);
-        a[3] = max3_abs(a[3], A[r].w, A[r + 1].w);
-        a[4] = max3_abs(a[4], B[r].x, B[r + 1].x);
-        a[5] = max3_abs(a[5], B[r].y, B[r + 1].y);
-        a[6] = max3_abs(a[6], B[r].z, B[r + 1].z);
-        a[7] = max3_abs(a[7], B[r].w, B[r + 1].w);
-    }
-    uint32_t worst = 0u;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        worst = max(worst, __float_as_uint(a[j]));
-    if (__builtin_expect(worst >= 0x7F800000u, 0)) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            a[j] = 0.0f;
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            a[0] = fmaxf(a[0], usable_or_zero(A[r].x));
-            a[1] = fmaxf(a[1], usable_or_zero(A[r].y));
-            a[2] = fmaxf(a[2], usable_or_zero(A[r].z));
-            a[3] = fmaxf(a[3], usable_or_zero(A[r].w));
-            a[4] = fmaxf(a[4], usable_or_zero(B[r].x));
-            a[5] = fmaxf(a[5], usable_or_zero(B[r].y));
-            a[6] = fmaxf(a[6], usable_or_zero(B[r].z));
-            a[7] = fmaxf(a[7], usable_or_zero(B[r].w));
-        }
-    }
-    if (by_table) {
-        const uint32_t kzero = static_cast<uint32_t>(K - 1);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint32_t b = __float_as_uint(a[j]);
-            const uint2 t = tab[b >> 23];
-            k[j] = b != 0u ? t.x + (b <= t.y ? 1u : 0u) : kzero;
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            int32_t count = 0;
-            for (int q = 0; q < K; ++q)
-                count += a[j] <= thr[q] ? 1 : 0;
-            k[j] = index_from_count(a[j], count, K, zero);
-        }
-    }
-}
-
-// Stores a lane's eight index bytes of one tile: the A quad's at a_off, the B
-// quad's at a_off + 256.
-template <bool NT>
-__device__ __forceinline__ void store_index(uint8_t* __restrict__ idx, int64_t a_off, const uint32_t k[8])
-{
-    const uint32_t ka = k[0] | (k[1] << 8) | (k[2] << 16) | (k[3] << 24);
-    const uint32_t kb = k[4] | (k[5] << 8) | (k[6] << 16) | (k[7] << 24);
-    uint32_t* ip = reinterpret_cast<uint32_t*>(idx + a_off);
-    if (NT) {
-        __builtin_nontemporal_store(ka, ip);
-        __builtin_nontemporal_store(kb, ip + 64);
-    } else {
-        ip[0] = ka;
-        ip[64] = kb;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // All of up to kFuseRows resident rows quantised, summed and reconstructed in
 // one call (one scale, or several with the shared index formed here).  One
@@ -1894,46 +1662,6 @@ struct RowTables {
     float deq[kMaxScales];  // RN32(W / (M s_k))
     RowKey key[kFuseRows];  // each row's part of its Philox blocks
 };
-
-// The call's constants in one wave: lane k < K forms scale k's entries.
-struct WaveScale {
-    float s0x;       // s_0 * 2^16 when pre, else s_0
-    bool pre;
-    float inv, deq;  // lane k's s_k / W (times 2^16 when pre) and RN32(W / (M s_k)); 0 on the zero path
-};
-
-__device__ __forceinline__ float lane_value(float x, int32_t lane)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
-}
-
-// The scales come to their lanes through scalar loads: a vector load of them
-// here would be waited for behind the rows' loads, which the counter of
-// outstanding loads retires in order, and so would everything formed from
-// it (measured on 4 rows of 25.6 M coordinates with four scales: 113.7 us against 108.1; 8 rows of 11.2 M: 79.5 against 73.3).
-template <bool MULTI>
-__device__ __forceinline__ WaveScale wave_scale(const float* __restrict__ wptr, const ScaleSet& S, int32_t M)
-{
-    WaveScale c;
-    const float W = *wptr;
-    float s = S.s[0];
-    if (MULTI) {
-#pragma unroll
-        for (int k = 1; k < kMaxScales; ++k)
-            __asm__("v_writelane_b32 %0, %1, %2" : "+v"(s) : "s"(S.s[k]), "n"(k));
-    }
-    const float q = div_rn32(s, W);
-    const float s0 = S.s[0];
-    const bool zero = zero_path(W, lane_value(q, 0));
-    // the largest entry is the last scale's; 2^16 times it stays finite
-    c.pre = zero || lane_value(q, MULTI ? S.K - 1 : 0) <= 0x1p100f;
-    const float inv = zero ? 0.0f : q;
-    c.inv = c.pre ? inv * 65536.0f : inv;
-    c.s0x = c.pre ? s0 * 65536.0f : s0;
-    // M * s_k is exactly representable in binary32 (checked on the host)
-    c.deq = zero ? 0.0f : div_rn32(W, static_cast<float>(static_cast<double>(M) * static_cast<double>(s)));
-    return c;
-}
 
 // The shared index of a lane's four coordinates from the largest usable |g|
 // over the ROWS rows it holds: two rows per instruction with the NaN- and
@@ -2028,57 +1756,73 @@ __device__ __forceinline__ void add_pair(const u16x2 mag[4], const u16x2 sgn[4],
     }
 }
 
-template <int ROWS, bool MULTI, bool NT, bool TAIL>
-__device__ __forceinline__ void rows_tile(const f32x4 (&A)[ROWS], const float* __restrict__ g, int64_t ldg,
-                                          int32_t rows, uint32_t worker0, int64_t T, int64_t d, const WaveScale& c, int32_t K, const RowTables& tab,
-                                          uint32_t key0, uint32_t key1, uint8_t* __restrict__ idx,
-                                          int32_t* __restrict__ sum, float* __restrict__ out)
+// The wave's constants, and the tables of a tile's rows (workers worker0 ..)
+// in LDS.
+template <int ROWS, bool MULTI>
+__device__ __forceinline__ WaveScale row_tables(const float* __restrict__ wptr, const ScaleSet& S, int32_t M,
+                                                uint32_t c1, uint32_t worker0, uint32_t key0, RowTables& tab)
+{
+    if (threadIdx.x < ROWS)
+        tab.key[threadIdx.x] = row_key(c1, worker0 + threadIdx.x, key0);
+    const WaveScale c = wave_scale<MULTI>(wptr, S, M);
+    if (MULTI && threadIdx.x < kMaxScales) {
+        tab.inv[threadIdx.x] = c.inv;
+        tab.deq[threadIdx.x] = c.deq;
+    }
+    __syncthreads();
+    return c;
+}
+
+// Stores a lane's four index bytes of tile T (those below d with TAIL).
+template <bool TAIL>
+__device__ __forceinline__ void store_index(uint8_t* __restrict__ idx, int64_t T, int64_t d, const uint32_t k[4])
 {
     const int lane = threadIdx.x & 63;
     const int64_t a_off = T << 8;
     const int64_t left = TAIL ? d - a_off - 4 * lane : 4;
-    uint32_t k[4] = {0u, 0u, 0u, 0u};
-    float inv[4];
-    if (MULTI) {
-        quad_index<ROWS>(A, c, K, k);
-        const uint32_t word = k[0] | (k[1] << 8) | (k[2] << 16) | (k[3] << 24);
-        if (left >= 4) {
-            store_through<false>(idx + a_off, 4 * lane, word);
-        } else {
-            for (int j = 0; j < left; ++j)
-                idx[a_off + 4 * lane + j] = static_cast<uint8_t>(word >> (8 * j));
-        }
+    const uint32_t word = k[0] | (k[1] << 8) | (k[2] << 16) | (k[3] << 24);
+    if (left >= 4) {
+        store_through<false>(idx + a_off, 4 * lane, word);
+    } else {
+        for (int j = 0; j < left; ++j)
+            idx[a_off + 4 * lane + j] = static_cast<uint8_t>(word >> (8 * j));
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        inv[j] = MULTI ? tab.inv[k[j]] : lane_value(c.inv, 0);
+}
+
+// The codes of every row pair of tile T: use(p, mag, sgn, nullptr) for each
+// pair p as the fast form gives it, then use(p, exact, sgn, fast) for the
+// pairs that need the exact form, with what the first call was given.
+template <int ROWS, bool TAIL, typename F>
+__device__ __forceinline__ void for_row_pairs(const f32x4 (&A)[ROWS], const float* __restrict__ g, int64_t ldg,
+                                              int32_t rows, uint32_t worker0, int64_t T, int64_t d,
+                                              const WaveScale& c, const float inv[4], const RowTables& tab,
+                                              uint32_t key0, uint32_t key1, F use)
+{
     const uint32_t c0 = quad_c0(T), c1 = quad_c1(T);
     const uint32_t odd = threadIdx.x & 1u;
     const LaneKey lk = lane_key(c0, 0u, key1);
     const float inv8[8] = {inv[0], inv[1], inv[2], inv[3], inv[0], inv[1], inv[2], inv[3]};
-    u16x2 h0 = {0, 0}, h1 = {0, 0};
-    u16x2 mag[4], sgn[4];
+    u16x2 mag[4] = {}, sgn[4];
     uint32_t bits[4];
     uint32_t redo = 0u;  // row pairs that need the exact form (wave-uniform)
 #pragma unroll
     for (int p = 0; p < ROWS / 2; ++p) {
         if (2 * p < rows) {
             // the pair's row keys are read when its turn comes (the index
-            // depends on the sums so far): read ahead for every pair, they
+            // depends on the pair before): read ahead for every pair, they
             // take 8 registers each and cost waves on the SIMD (8 rows at
             // 11.2 M coordinates, four scales: 78.7 us against 73.3)
             uint32_t row = 2 * p + odd;
-            __asm__ volatile("" : "+v"(row) : "v"(h0));
+            __asm__ volatile("" : "+v"(row) : "v"(mag[0]));
             const float v[8] = {A[2 * p].x,     A[2 * p].y,     A[2 * p].z,     A[2 * p].w,
                                 A[2 * p + 1].x, A[2 * p + 1].y, A[2 * p + 1].z, A[2 * p + 1].w};
             const bool rare = fast_mags(v, inv8, c.s0x, lk, tab.key[row], key0, key1, bits, mag, sgn);
             redo |= rare || !c.pre ? 1u << p : 0u;
-            add_pair(mag, sgn, 2 * p + 1 < rows, h0, h1);
+            use(p, mag, sgn, nullptr);
         }
     }
-    // the pairs that need it once more, from memory: the exact magnitudes in
-    // place of the fast ones (a loop here instead of a branch per pair keeps
-    // the tile's code straight and a third of the size)
+    // the pairs that need it once more, from memory (a loop here instead of a
+    // branch per pair keeps the tile's code straight and a third of the size)
     while (__builtin_expect(redo != 0u, 0)) {
         const int p = __builtin_ctz(redo);
         redo &= redo - 1u;
@@ -2089,11 +1833,39 @@ __device__ __forceinline__ void rows_tile(const f32x4 (&A)[ROWS], const float* _
         fast_mags(v, inv8, c.s0x, lk, tab.key[2 * p + odd], key0, key1, bits, mag, sgn);
         u16x2 ex[4];
         exact_mags(v, inv8, c.s0x, c.pre, c0, c1, worker0 + 2u * p + odd, key0, key1, bits, ex);
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            ex[j] -= mag[j];
-        add_pair(ex, sgn, r0 + 1 < rows, h0, h1);
+        use(p, ex, sgn, mag);
     }
+}
+
+template <int ROWS, bool MULTI, bool NT, bool TAIL>
+__device__ __forceinline__ void rows_tile(const f32x4 (&A)[ROWS], const float* __restrict__ g, int64_t ldg,
+                                          int32_t rows, uint32_t worker0, int64_t T, int64_t d, const WaveScale& c,
+                                          int32_t K, const RowTables& tab, uint32_t key0, uint32_t key1,
+                                          uint8_t* __restrict__ idx, int32_t* __restrict__ sum,
+                                          float* __restrict__ out)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t a_off = T << 8;
+    const int64_t left = TAIL ? d - a_off - 4 * lane : 4;
+    uint32_t k[4] = {0u, 0u, 0u, 0u};
+    if (MULTI) {
+        quad_index<ROWS>(A, c, K, k);
+        store_index<TAIL>(idx, T, d, k);
+    }
+    float inv[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        inv[j] = MULTI ? tab.inv[k[j]] : lane_value(c.inv, 0);
+    // the codes of 16 rows in 16-bit lanes (|sum| <= 16 * 127, exact)
+    u16x2 h0 = {0, 0}, h1 = {0, 0};
+    for_row_pairs<ROWS, TAIL>(A, g, ldg, rows, worker0, T, d, c, inv, tab, key0, key1,
+                              [&](int p, const u16x2 mag[4], const u16x2 sgn[4], const u16x2* fast) {
+                                  u16x2 m[4];
+#pragma unroll
+                                  for (int j = 0; j < 4; ++j)
+                                      m[j] = fast ? static_cast<u16x2>(mag[j] - fast[j]) : mag[j];
+                                  add_pair(m, sgn, 2 * p + 1 < rows, h0, h1);
+                              });
     const i32x4 s = {static_cast<int16_t>(h0.x), static_cast<int16_t>(h0.y), static_cast<int16_t>(h1.x),
                      static_cast<int16_t>(h1.y)};
     const float deq0 = lane_value(c.deq, 0);
@@ -2129,14 +1901,7 @@ __device__ __forceinline__ void rows_block(const float* __restrict__ g, int64_t 
     f32x4 A[ROWS];
     if (whole)
         load_quads<ROWS, false>(g, ldg, rows, T, d, A);
-    if (threadIdx.x < ROWS)
-        tab.key[threadIdx.x] = row_key(quad_c1(T), static_cast<uint32_t>(worker0) + threadIdx.x, key0);
-    const WaveScale c = wave_scale<MULTI>(wptr, S, M);
-    if (MULTI && threadIdx.x < kMaxScales) {
-        tab.inv[threadIdx.x] = c.inv;
-        tab.deq[threadIdx.x] = c.deq;
-    }
-    __syncthreads();
+    const WaveScale c = row_tables<ROWS, MULTI>(wptr, S, M, quad_c1(T), static_cast<uint32_t>(worker0), key0, tab);
     if (whole) {
         rows_tile<ROWS, MULTI, NT, false>(A, g, ldg, rows, static_cast<uint32_t>(worker0), T, d, c, S.K, tab, key0, key1,
                                       idx, sum, out);
@@ -2147,9 +1912,15 @@ __device__ __forceinline__ void rows_block(const float* __restrict__ g, int64_t 
     }
 }
 
+// With more than 12 rows at most two waves per SIMD: 16 rows of VGG-16 size
+// ran in 1.66 ms with two waves and 1.68-1.70 with three (4-bit codes stored:
+// 1.80 and 1.87); 8 rows of 25.6 M in 157-170 us with four or five and 170-195
+// with two.
+#define UQ_ROWS_WAVES(ROWS) __attribute__((amdgpu_waves_per_eu(1, (ROWS) > 12 ? 2 : 8)))
+
 // One scale.
 template <int ROWS, bool NT>
-__global__ __launch_bounds__(64) void k_quant_sum_split(const float* __restrict__ g, int64_t d, int32_t rows,
+__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS) void k_quant_sum_split(const float* __restrict__ g, int64_t d, int32_t rows,
                                                         int64_t ldg, int32_t worker0, const float* __restrict__ wptr,
                                                         ScaleSet S, uint32_t key0, uint32_t key1, int64_t tile0,
                                                         int32_t* __restrict__ sum, int32_t M, float* __restrict__ out)
@@ -2160,7 +1931,7 @@ __global__ __launch_bounds__(64) void k_quant_sum_split(const float* __restrict_
 // Several scales, the shared index formed and stored: all M rows, as workers
 // 0 .. M - 1.
 template <int ROWS, bool NT>
-__global__ __launch_bounds__(64) void k_index_quant_sum(const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg,
+__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS) void k_index_quant_sum(const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg,
                                                         const float* __restrict__ wptr, ScaleSet S, uint32_t key0,
                                                         uint32_t key1, int64_t tile0, uint8_t* __restrict__ idx,
                                                         int32_t* __restrict__ sum, float* __restrict__ out)
@@ -2170,32 +1941,12 @@ __global__ __launch_bounds__(64) void k_index_quant_sum(const float* __restrict_
 
 // ---------------------------------------------------------------------------
 // The shared index formed in the quantiser (several scales, at most 16 rows,
-// codes stored): k_index_quant_sum's tiles, every row of a tile held by one
-// wave and the index formed from their exact maxima and stored, with each
-// row's codes stored (int8, or packed 4- or 2-bit fields) instead of summed.
-// The codes and the index equal uq_shared_scale's index followed by the
-// quantiser's codes, given the same W.  A wave collects its rows' codes of
-// the tile in LDS and stores them as 16-byte pieces: at VGG-16 size with
-// 4-bit codes 1.85 ms against 1.96 for two 2-byte stores per lane and row.
+// codes stored): k_index_quant_sum's tiles, index and codes, with each row's
+// codes stored (int8, or packed 4- or 2-bit fields) instead of summed.  The
+// codes and the index equal uq_shared_scale's index followed by the
+// quantiser's codes, given the same W.  A wave collects its rows' codes of the
+// tile in LDS and stores them as 16-byte pieces.
 // ---------------------------------------------------------------------------
-// Four consecutive codes (16-bit lanes of p01, p23) in the code row's layout:
-// 4, 2 or 1 bytes.
-template <int BITS>
-__device__ __forceinline__ uint32_t pack_quad(uint32_t p01, uint32_t p23)
-{
-    const uint32_t w = __builtin_amdgcn_perm(p23, p01, 0x06040200u);
-    if (BITS == 8)
-        return w;
-    if (BITS == 4) {
-        const uint32_t x = w & 0x0F0F0F0Fu;
-        const uint32_t y = x | (x >> 4);
-        return __builtin_amdgcn_perm(0u, y, 0x0C0C0200u);
-    }
-    const uint32_t x = w & 0x03030303u;
-    const uint32_t y = x | (x >> 6);
-    return (y | (y >> 12)) & 0xFFu;
-}
-
 template <int BITS>
 __device__ __forceinline__ void lds_put(uint8_t* p, uint32_t v)
 {
@@ -2207,220 +1958,94 @@ __device__ __forceinline__ void lds_put(uint8_t* p, uint32_t v)
         *p = static_cast<uint8_t>(v);
 }
 
-template <int ROWS, int BITS, bool PRE, bool NT>
-__device__ __forceinline__ void index_quantise_tile(const f32x4 (&A)[ROWS], const f32x4 (&B)[ROWS], int32_t rows,
-                                                    int64_t T, const uint2* tab, bool by_table, const float* thr,
-                                                    int32_t K, bool zero, const float* inv_t, float s0x,
-                                                    uint32_t key0, uint32_t key1,
+template <int ROWS, int BITS, bool NT, bool TAIL>
+__device__ __forceinline__ void index_quantise_tile(const f32x4 (&A)[ROWS], const float* __restrict__ g, int64_t ldg,
+                                                    int32_t rows, int64_t T, int64_t d, const WaveScale& c, int32_t K,
+                                                    const RowTables& tab, uint32_t key0, uint32_t key1,
                                                     uint8_t* __restrict__ idx, uint8_t* __restrict__ codes,
                                                     int64_t ldc, uint8_t* stage)
 {
+    constexpr int kRowBytes = 32 * BITS;  // one row's codes of a tile
     const int lane = threadIdx.x & 63;
-    const int64_t a_off = (T << 9) + 4 * lane;
-    uint32_t k[8];
-    tile_index<ROWS>(A, B, tab, by_table, thr, K, zero, k);
-    store_index<NT>(idx, a_off, k);
-    float inv[8];
+    uint32_t k[4];
+    quad_index<ROWS>(A, c, K, k);
+    store_index<TAIL>(idx, T, d, k);
+    float inv[4];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-        inv[j] = inv_t[k[j]];
+    for (int j = 0; j < 4; ++j)
+        inv[j] = tab.inv[k[j]];
+    for_row_pairs<ROWS, TAIL>(A, g, ldg, rows, 0u, T, d, c, inv, tab, key0, key1,
+                              [&](int p, const u16x2 mag[4], const u16x2 sgn[4], const u16x2*) {
+                                  uint32_t q[4];
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-        if (r < rows) {
-            const float v[8] = {A[r].x, A[r].y, A[r].z, A[r].w, B[r].x, B[r].y, B[r].z, B[r].w};
-            uint32_t p[4];
-            tile_codes<PRE>(v, inv, s0x, T, static_cast<uint32_t>(r), key0, key1, p);
-            // the row's codes of this tile into the wave's LDS rows
-            uint8_t* srow = stage + r * (64 * BITS);
-            lds_put<BITS>(srow + (4 * lane) * BITS / 8, pack_quad<BITS>(p[0], p[1]));
-            lds_put<BITS>(srow + (256 + 4 * lane) * BITS / 8, pack_quad<BITS>(p[2], p[3]));
-        }
-    }
-    // 16-byte pieces of the wave's rows (64 * BITS bytes per row and tile),
-    // several rows' pieces per store: the wave's own LDS writes above
-    // complete before these reads
-    constexpr int kPieces = 64 * BITS / 16;
-    constexpr int kAll = ROWS * kPieces;
-    __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                                  for (int j = 0; j < 4; ++j)
+                                      q[j] = __builtin_bit_cast(uint32_t, static_cast<u16x2>(mag[j] * sgn[j]));
+                                  uint8_t* srow = stage + 2 * p * kRowBytes + lane * (BITS / 2);
+                                  lds_put<BITS>(srow, pack_quad<BITS>(q[0], q[1]));
+                                  lds_put<BITS>(srow + kRowBytes, pack_quad<BITS>(q[2], q[3]));
+                              });
+    __syncthreads();  // one wave: its LDS writes complete before the reads below
+    if (!TAIL) {
+        // 16-byte pieces, several rows' per store
+        constexpr int kPieces = kRowBytes / 16;
+        constexpr int kAll = ROWS * kPieces;
 #pragma unroll
-    for (int c0 = 0; c0 < kAll; c0 += 64) {
-        const int c = c0 + lane;
-        const int r = c / kPieces;
-        const int off = (c % kPieces) * 16;
-        if (c < kAll && r < rows) {
-            const u32x4 v = *reinterpret_cast<const u32x4*>(stage + r * (64 * BITS) + off);
-            u32x4* dst = reinterpret_cast<u32x4*>(codes + static_cast<int64_t>(r) * ldc + T * (64 * BITS) + off);
-            if (NT)
-                __builtin_nontemporal_store(v, dst);
-            else
-                *dst = v;
-        }
-    }
-}
-
-// The coordinates past the last whole tile (fewer than 512): lane t of one
-// wave takes the 8 contiguous coordinates of group ntiles * 64 + t, forms
-// their indices from the rows' maxima (threshold counts), then quantises and
-// stores every row's codes.  inv_s holds s_k / W (not scaled).
-template <int BITS>
-__device__ __forceinline__ void index_quantise_tail(const float* __restrict__ g, int64_t d, int64_t ldg, int32_t M,
-                                                    int64_t ntiles, const float* thr, int32_t K, bool zero,
-                                                    const float* inv_s, float s0, uint32_t key0, uint32_t key1,
-                                                    uint8_t* __restrict__ idx, uint8_t* __restrict__ codes,
-                                                    int64_t ldc)
-{
-    const int64_t q = (ntiles << 6) + (threadIdx.x & 63);
-    const int64_t base = q << 3;
-    if (base >= d)
-        return;
-    float a[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    for (int32_t r = 0; r < M; ++r) {
-        const float* row = g + static_cast<int64_t>(r) * ldg;
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            a[j] = fmaxf(a[j], usable_or_zero(base + j < d ? row[base + j] : 0.0f));
-    }
-    float inv[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        int32_t count = 0;
-        for (int k = 0; k < K; ++k)
-            count += a[j] <= thr[k] ? 1 : 0;
-        const uint32_t kk = index_from_count(a[j], count, K, zero);
-        inv[j] = inv_s[kk];
-        if (base + j < d)
-            idx[base + j] = static_cast<uint8_t>(kk);
-    }
-    for (int32_t r = 0; r < M; ++r) {
-        const float* row = g + static_cast<int64_t>(r) * ldg;
-        uint8_t* out = codes + static_cast<int64_t>(r) * ldc;
-        float v[8];
-        int32_t code[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-            v[j] = base + j < d ? row[base + j] : 0.0f;
-        quantise_group(v, inv, s0, static_cast<uint64_t>(q), static_cast<uint32_t>(r), key0, key1, code);
-        if (BITS == 8) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (base + j < d)
-                    out[base + j] = static_cast<uint8_t>(code[j]);
-        } else if (BITS == 4) {
-            // the group's 8 codes fill whole bytes of its own (codes past d are 0)
-            *reinterpret_cast<uint32_t*>(out + base / 2) = pack_field<4>(code) | (pack_field<4>(code + 4) << 16);
-        } else {
-            *reinterpret_cast<uint16_t*>(out + base / 4) =
-                static_cast<uint16_t>(pack_field<2>(code) | (pack_field<2>(code + 4) << 8));
-        }
-    }
-}
-
-template <int ROWS, int BITS, bool NT>
-__global__ __launch_bounds__(kBlock) void k_index_quantise(const float* __restrict__ g, int64_t d, int32_t M,
-                                                           int64_t ldg, const float* __restrict__ wptr, ScaleSet S,
-                                                           uint32_t key0, uint32_t key1, uint8_t* __restrict__ idx,
-                                                           uint8_t* __restrict__ codes, int64_t ldc)
-{
-    __shared__ float inv_s[kMaxScales];  // s_k / W
-    __shared__ float inv_p[kMaxScales];  // s_k / W * 2^16 when pre
-    __shared__ float thr_s[kMaxScales];  // T_k
-    __shared__ uint2 tab_s[256];
-    __shared__ __align__(16) uint8_t stage_s[4][ROWS * 64 * BITS];  // each wave's code rows of its tile
-    const int lane = threadIdx.x & 63;
-    const int64_t ntiles = d >> 9;
-    const int32_t wave_in_block = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(threadIdx.x >> 6));
-    const int64_t first = static_cast<int64_t>(blockIdx.x) * (kBlock / 64) + wave_in_block;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * (kBlock / 64);
-    uint8_t* stage = stage_s[wave_in_block];
-
-    // every row of the first tile goes out before W is read and the tables
-    // are formed
-    f32x4 A[ROWS], B[ROWS];
-    const auto load_rows = [&](int64_t T) {
-        const int64_t a_off = (T << 9) + 4 * lane;
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            const float* row = g + static_cast<int64_t>(r < M ? r : M - 1) * ldg;
-            A[r] = load_nt(row + a_off);
-            B[r] = load_nt(row + a_off + 256);
-        }
-    };
-    if (first < ntiles)
-        load_rows(first);
-
-    const float W = *wptr;
-    const float s0 = S.s[0];
-    const int32_t K = S.K;
-    const float q0 = div_rn32(s0, W);
-    const bool zero = zero_path(W, q0);
-    const bool pre = zero || div_rn32(S.s_last, W) <= 0x1p100f;
-    if (threadIdx.x < K) {
-        const float inv = zero ? 0.0f : div_rn32(S.s[threadIdx.x], W);
-        inv_s[threadIdx.x] = inv;
-        inv_p[threadIdx.x] = pre ? inv * 65536.0f : inv;
-        thr_s[threadIdx.x] = zero ? 0.0f : index_threshold(inv, s0);
-    }
-    __syncthreads();
-    // thread e forms the table's entry e, as in k_index_quant_sum
-    int crowded = 0;
-    {
-        const uint32_t e = threadIdx.x;
-        int32_t above = 0, inside = 0;
-        uint32_t tin = 0u;
-        for (int k = 0; k < K; ++k) {
-            const uint32_t tb = __float_as_uint(thr_s[k]);
-            above += (tb >> 23) > e ? 1 : 0;
-            if ((tb >> 23) == e) {
-                ++inside;
-                tin = tb;
+        for (int p0 = 0; p0 < kAll; p0 += 64) {
+            const int p = p0 + lane;
+            const int r = p / kPieces;
+            const int off = (p % kPieces) * 16;
+            if (p < kAll && r < rows) {
+                const u32x4 v = *reinterpret_cast<const u32x4*>(stage + r * kRowBytes + off);
+                u32x4* dst = reinterpret_cast<u32x4*>(codes + static_cast<int64_t>(r) * ldc + T * kRowBytes + off);
+                if (NT)
+                    __builtin_nontemporal_store(v, dst);
+                else
+                    *dst = v;
             }
         }
-        uint2 ent;
-        if (zero) {
-            ent.x = static_cast<uint32_t>(K - 2);
-            ent.y = 0xFFFFFFFFu;
-        } else {
-            crowded = inside > 1 ? 1 : 0;
-            const bool limit = inside > 0 && above > 0;
-            ent.x = static_cast<uint32_t>(above > 0 ? above - 1 : 0) - (limit ? 0u : 1u);
-            ent.y = limit ? tin : 0xFFFFFFFFu;
-        }
-        tab_s[e] = ent;
+    } else {
+        // the row's bytes up to d (int8), or those of every 8-coordinate
+        // group that starts below d (fields past d hold 0)
+        const int64_t left = d - (T << 8);
+        const int64_t n = BITS == 8 ? left : (left + 7) / 8 * BITS;
+        for (int32_t r = 0; r < rows; ++r)
+            for (int64_t i = lane; i < n; i += 64)
+                codes[static_cast<int64_t>(r) * ldc + T * kRowBytes + i] = stage[r * kRowBytes + i];
     }
-    const bool by_table = __syncthreads_or(crowded) == 0;
-    const float s0x = pre ? s0 * 65536.0f : s0;
+}
 
-    for (int64_t T = first; T < ntiles; T += stride) {
-        if (T != first)
-            load_rows(T);
-        if (pre)
-            index_quantise_tile<ROWS, BITS, true, NT>(A, B, M, T, tab_s, by_table, thr_s, K, zero, inv_p, s0x,
-                                                             key0, key1, idx, codes, ldc, stage);
-        else
-            index_quantise_tile<ROWS, BITS, false, NT>(A, B, M, T, tab_s, by_table, thr_s, K, zero, inv_p, s0x,
-                                                              key0, key1, idx, codes, ldc, stage);
+// Block b takes tile tile0 + b, as rows_block.
+template <int ROWS, int BITS, bool NT>
+__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS) void k_index_quantise(const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg,
+                                                       const float* __restrict__ wptr, ScaleSet S, uint32_t key0,
+                                                       uint32_t key1, int64_t tile0, uint8_t* __restrict__ idx,
+                                                       uint8_t* __restrict__ codes, int64_t ldc)
+{
+    __shared__ RowTables tab;
+    __shared__ __align__(16) uint8_t stage[ROWS * 32 * BITS];
+    const int64_t T = tile0 + blockIdx.x;
+    const bool whole = T < d >> 8;
+    f32x4 A[ROWS];
+    if (whole)
+        load_quads<ROWS, false>(g, ldg, M, T, d, A);
+    const WaveScale c = row_tables<ROWS, true>(wptr, S, 1, quad_c1(T), 0u, key0, tab);
+    if (whole) {
+        index_quantise_tile<ROWS, BITS, NT, false>(A, g, ldg, M, T, d, c, S.K, tab, key0, key1, idx, codes, ldc, stage);
+    } else {
+        load_quads<ROWS, true>(g, ldg, M, T, d, A);
+        index_quantise_tile<ROWS, BITS, NT, true>(A, g, ldg, M, T, d, c, S.K, tab, key0, key1, idx, codes, ldc, stage);
     }
-    if (blockIdx.x == 0 && threadIdx.x < 64)
-        index_quantise_tail<BITS>(g, d, ldg, M, ntiles, thr_s, K, zero, inv_s, s0, key0, key1, idx, codes, ldc);
 }
 
 // ---------------------------------------------------------------------------
 // Host-side launchers (called by the ABI layer after validation).
 // ---------------------------------------------------------------------------
-// Tiles per wave for the quantiser.  Launch-shape sweeps on MI355X with cold
-// caches: one tile per wave (a one-shot grid) is fastest for one scale; with
-// several scales two consecutive tiles per wave amortise the per-block table
-// set-up and read the shared index in longer runs.
-// The quantiser stores its codes nontemporally when one launch writes more
-// than this many bytes: measured 3% faster steps at VGG-16 size (2.2 GB of
-// codes), 1.8-2.5% slower at ResNet-18 and ResNet-50 sizes (89 and 204 MB),
-// where the sum then finds the codes in the 256 MB Infinity Cache.
+// The multi-scale quantiser with the index formed in it stores its codes
+// nontemporally when one launch writes more than this many bytes: measured 3%
+// faster steps at VGG-16 size (2.2 GB of codes), 1.8-2.5% slower at ResNet-18
+// and ResNet-50 sizes (89 and 204 MB), where the sum then finds the codes in
+// the 256 MB Infinity Cache.
 constexpr int64_t kCodesNontemporalBytes = int64_t(512) << 20;
-
-static int32_t quantise_tiles_per_wave(int32_t K)
-{
-    return K > 1 ? 2 : 1;
-}
 
 // Enough blocks for every unit to get its own thread / wave / tile (the
 // streaming kernels run fastest as one pass with no grid-stride reuse).  The
@@ -2461,6 +2086,12 @@ constexpr int64_t kMaximaNontemporalBytes = int64_t(128) << 20;
 // The index pass stores the index (one byte per coordinate) nontemporally
 // beyond this many bytes, where the passes that read it back find it in HBM.
 constexpr int64_t kIndexNontemporalBytes = int64_t(256) << 20;
+
+// Write-through stores also carry the nontemporal hint when the sums exceed
+// this many bytes, the Infinity Cache's size (work-free passes): the sums and
+// outputs of 16 rows at VGG-16 size, with the index, 1.64 against 1.72 ms;
+// at ResNet-50 size (102 MB) 167 us with the hint, 157 without.
+constexpr int64_t kThroughNontemporalBytes = int64_t(256) << 20;
 
 hipError_t launch_shared_scale(const float* g, int64_t d, int32_t M, int64_t ldg, const ScaleSet& S,
                                float* w, uint8_t* idx, void* ws, hipStream_t stream, int32_t idx_bits)
@@ -2548,25 +2179,23 @@ hipError_t launch_quantise(const float* g, int64_t d, int32_t rows, int64_t ldg,
         return hipSuccess;
     const uint32_t key0 = static_cast<uint32_t>(seed);
     const uint32_t key1 = static_cast<uint32_t>(seed >> 32);
-    // `tpw` consecutive 512-coordinate tiles per wave, four waves per block
-    const int32_t tpw = quantise_tiles_per_wave(S.K);
-    unsigned tile_blocks = one_shot(d >> 9, (kBlock / 64) * tpw);
-    // keep rows x tile blocks within the grid cap; the waves stride over the rest
-    const int64_t per_row = one_shot_cap() / rows / 8 * 8;
-    if (static_cast<int64_t>(tile_blocks) > per_row)
-        tile_blocks = static_cast<unsigned>(per_row < 8 ? 8 : per_row);
-    dim3 grid(tile_blocks, static_cast<unsigned>(rows));
+    // one block per 512-coordinate tile and row (the last tile partial), rows
+    // x tiles within the grid cap
+    const int64_t ntiles = (d + 511) >> 9;
+    const int64_t per_row = one_shot_cap() / rows < 1 ? 1 : one_shot_cap() / rows;
     uint8_t* out = reinterpret_cast<uint8_t*>(codes);
-    // codes beyond twice the 256 MB Infinity Cache are stored nontemporally
-    const int32_t nt_codes = static_cast<int64_t>(rows) * ((d * bits + 7) / 8) > kCodesNontemporalBytes ? 1 : 0;
-#define UQ_LAUNCH_QUANTISE(MULTI, BITS)                                                                          \
+    const bool nt = static_cast<int64_t>(rows) * ((d * bits + 7) / 8) > kThroughNontemporalBytes;
+    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += per_row) {
+    const int64_t n = ntiles - tile0 < per_row ? ntiles - tile0 : per_row;
+    const dim3 grid(static_cast<unsigned>(n), static_cast<unsigned>(rows));
+#define UQ_LAUNCH_QUANTISE(MULTI, BITS)                                                                            \
     do {                                                                                                           \
-        if (nt_codes)                                                                                              \
-            hipLaunchKernelGGL((k_quantise<MULTI, BITS, true>), grid, dim3(kBlock), 0, stream, g, d, ldg, worker0, \
-                               w, S, idx, key0, key1, out, ldc, tpw);                                               \
+        if (nt)                                                                                                    \
+            hipLaunchKernelGGL((k_quantise<MULTI, BITS, true>), grid, dim3(64), 0, stream, g, d, ldg, worker0, w,  \
+                               S, idx, key0, key1, tile0, out, ldc);                                               \
         else                                                                                                       \
-            hipLaunchKernelGGL((k_quantise<MULTI, BITS, false>), grid, dim3(kBlock), 0, stream, g, d, ldg, worker0,\
-                               w, S, idx, key0, key1, out, ldc, tpw);                                               \
+            hipLaunchKernelGGL((k_quantise<MULTI, BITS, false>), grid, dim3(64), 0, stream, g, d, ldg, worker0, w, \
+                               S, idx, key0, key1, tile0, out, ldc);                                               \
     } while (0)
     const bool multi = S.K > 1;
     if (bits == 8) {
@@ -2576,15 +2205,10 @@ hipError_t launch_quantise(const float* g, int64_t d, int32_t rows, int64_t ldg,
     } else {
         if (multi) UQ_LAUNCH_QUANTISE(true, 2); else UQ_LAUNCH_QUANTISE(false, 2);
     }
+    }
 #undef UQ_LAUNCH_QUANTISE
     return hipGetLastError();
 }
-
-// Write-through stores also carry the nontemporal hint when the sums exceed
-// this many bytes, the Infinity Cache's size (work-free passes): the sums and
-// outputs of 16 rows at VGG-16 size, with the index, 1.64 against 1.72 ms;
-// at ResNet-50 size (102 MB) 167 us with the hint, 157 without.
-constexpr int64_t kThroughNontemporalBytes = int64_t(256) << 20;
 
 // One scale, 5 <= rows <= kFuseRows rows set and reconstructed in one call:
 // one block per 256-coordinate tile (the last one partial), one instance per
@@ -2633,23 +2257,24 @@ hipError_t launch_quant_sum(const float* g, int64_t d, int32_t rows, int64_t ldg
         return hipSuccess;
     const uint32_t key0 = static_cast<uint32_t>(seed);
     const uint32_t key1 = static_cast<uint32_t>(seed >> 32);
-    // one wave per 512-coordinate tile (at least one block for the tail)
-    const dim3 grid(one_shot(d >> 9, kBlock / 64));
-    // sums beyond 64 MiB are loaded and stored nontemporally, as in the fused sum
-    const bool nt = 4 * d > kSumNontemporalBytes;
+    const bool nt = 4 * d > kThroughNontemporalBytes;
     const bool multi = S.K > 1;
     const bool acc = accumulate != 0;
     const bool deq = out != nullptr;
     if (!multi && !acc && deq && rows > 4 && rows <= kFuseRows)
         return launch_quant_sum_split(g, d, rows, ldg, worker0, w, S, key0, key1, sum, M, out, stream);
+    // one block per 512-coordinate tile, the last one partial
+    const int64_t ntiles = (d + 511) >> 9;
+    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
+    const dim3 grid(one_shot(ntiles - tile0, 1));
 #define UQ_LAUNCH_QSUM_(MULTI, ACC, DEQ, NT, NIB)                                                                   \
     do {                                                                                                           \
         if (rows == 1)                                                                                             \
-            hipLaunchKernelGGL((k_quant_sum<MULTI, ACC, DEQ, NT, true, NIB>), grid, dim3(kBlock), 0, stream, g, d,  \
-                               rows, ldg, worker0, w, S, idx, key0, key1, sum, M, out);                            \
+            hipLaunchKernelGGL((k_quant_sum<MULTI, ACC, DEQ, NT, true, NIB>), grid, dim3(64), 0, stream, g, d,      \
+                               rows, ldg, worker0, w, S, idx, key0, key1, tile0, sum, M, out);                     \
         else                                                                                                       \
-            hipLaunchKernelGGL((k_quant_sum<MULTI, ACC, DEQ, NT, false, NIB>), grid, dim3(kBlock), 0, stream, g, d, \
-                               rows, ldg, worker0, w, S, idx, key0, key1, sum, M, out);                            \
+            hipLaunchKernelGGL((k_quant_sum<MULTI, ACC, DEQ, NT, false, NIB>), grid, dim3(64), 0, stream, g, d,     \
+                               rows, ldg, worker0, w, S, idx, key0, key1, tile0, sum, M, out);                     \
     } while (0)
     // the 4-bit index layout only matters with several scales (NIB = MULTI
     // there, so one scale compiles no second instance)
@@ -2678,6 +2303,7 @@ hipError_t launch_quant_sum(const float* g, int64_t d, int32_t rows, int64_t ldg
         if (acc) UQ_LAUNCH_QSUM_DEQ(true, true); else UQ_LAUNCH_QSUM_DEQ(true, false);
     } else {
         if (acc) UQ_LAUNCH_QSUM_DEQ(false, true); else UQ_LAUNCH_QSUM_DEQ(false, false);
+    }
     }
 #undef UQ_LAUNCH_QSUM_DEQ
 #undef UQ_LAUNCH_QSUM_NT
@@ -2723,39 +2349,30 @@ hipError_t launch_index_quantise(const float* g, int64_t d, int32_t M, int64_t l
         return hipSuccess;
     const uint32_t key0 = static_cast<uint32_t>(seed);
     const uint32_t key1 = static_cast<uint32_t>(seed >> 32);
-    const dim3 grid(one_shot(d >> 9, kBlock / 64));
-    // codes stored nontemporally past the quantiser's threshold, the index with them
     const bool nt = static_cast<int64_t>(M) * ((d * bits + 7) / 8) > kCodesNontemporalBytes;
-#define UQ_LAUNCH_IQ_(ROWS, BITS, NT)                                                                             \
-    hipLaunchKernelGGL((k_index_quantise<ROWS, BITS, NT>), grid, dim3(kBlock), 0, stream, g, d, M, ldg, w, S, key0, \
-                       key1, idx, codes, ldc)
-#define UQ_LAUNCH_IQ_B(ROWS, NT)              \
-    do {                                      \
-        if (bits == 8)                        \
-            UQ_LAUNCH_IQ_(ROWS, 8, NT);       \
-        else if (bits == 4)                   \
-            UQ_LAUNCH_IQ_(ROWS, 4, NT);       \
-        else                                  \
-            UQ_LAUNCH_IQ_(ROWS, 2, NT);       \
-    } while (0)
-#define UQ_LAUNCH_IQ(ROWS)                   \
-    do {                                     \
-        if (nt)                              \
-            UQ_LAUNCH_IQ_B(ROWS, true);      \
-        else                                 \
-            UQ_LAUNCH_IQ_B(ROWS, false);     \
-    } while (0)
-    if (M <= 2)
-        UQ_LAUNCH_IQ(2);
-    else if (M <= 4)
-        UQ_LAUNCH_IQ(4);
-    else if (M <= 8)
-        UQ_LAUNCH_IQ(8);
-    else
-        UQ_LAUNCH_IQ(16);
+    const int64_t ntiles = (d + 255) >> 8;
+    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
+        const dim3 grid(one_shot(ntiles - tile0, 1));
+#define UQ_LAUNCH_IQ_(PAIRS, BITS, NT)                                                                             \
+    hipLaunchKernelGGL((k_index_quantise<2 * PAIRS, BITS, NT>), grid, dim3(64), 0, stream, g, d, M, ldg, w, S,     \
+                       key0, key1, tile0, idx, codes, ldc)
+#define UQ_LAUNCH_IQ(PAIRS, NT)                   \
+    case PAIRS:                                   \
+        if (bits == 8)                            \
+            UQ_LAUNCH_IQ_(PAIRS, 8, NT);          \
+        else if (bits == 4)                       \
+            UQ_LAUNCH_IQ_(PAIRS, 4, NT);          \
+        else                                      \
+            UQ_LAUNCH_IQ_(PAIRS, 2, NT);          \
+        break
+        if (nt) {
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, true); }
+        } else {
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, false); }
+        }
 #undef UQ_LAUNCH_IQ
-#undef UQ_LAUNCH_IQ_B
 #undef UQ_LAUNCH_IQ_
+    }
     return hipGetLastError();
 }
 
@@ -2813,11 +2430,14 @@ hipError_t launch_dequant(const int32_t* sum, int64_t d, int32_t M, const float*
 {
     if (d == 0)
         return hipSuccess;
-    const unsigned gx = one_shot((d + 3) / 4, kBlock);
-    if (S.K > 1)
-        hipLaunchKernelGGL(k_dequant<true>, dim3(gx), dim3(kBlock), 0, stream, sum, d, M, w, S, idx, out);
-    else
-        hipLaunchKernelGGL(k_dequant<false>, dim3(gx), dim3(kBlock), 0, stream, sum, d, M, w, S, idx, out);
+    const int64_t ntiles = (d + 511) >> 9;
+    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
+        const dim3 grid(one_shot(ntiles - tile0, 1));
+        if (S.K > 1)
+            hipLaunchKernelGGL(k_dequant<true>, grid, dim3(64), 0, stream, sum, d, M, w, S, idx, tile0, out);
+        else
+            hipLaunchKernelGGL(k_dequant<false>, grid, dim3(64), 0, stream, sum, d, M, w, S, idx, tile0, out);
+    }
     return hipGetLastError();
 }
 
