@@ -303,6 +303,33 @@ int uq_index_quantize(const float* g, int64_t d, int32_t M, int64_t ldg, const f
                       const float* scales, int32_t K, uint64_t seed, int32_t bits, uint8_t* idx,
                       void* codes, int64_t ldc, void* stream);
 
+/*
+ * A whole aggregation step of Algorithm 1 (K = 1) or Algorithm 2 (K > 1) over
+ * M resident workers in one call: uq_shared_scale with K = 1 (W only), then
+ * one pass over the gradients that forms the shared index (K > 1), every
+ * row's codes, their sums and the reconstruction.  Bit for bit the results of
+ * uq_shared_scale followed by uq_index_quantize_sum (bits = 0, K > 1),
+ * uq_quantize_sum (bits = 0, K = 1, worker0 = 0), or the quantiser that stores
+ * `bits`-bit codes (uq_index_quantize, uq_quantize_single or
+ * uq_quantize_packed over all rows, worker0 = 0) and uq_sum_dequantize, given
+ * the same W.  Small steps take fewer launches: one for d <= 4096, two while
+ * the norm has at most 1024 partial sums (M * ceil(d / 8192) of them up to
+ * d = 2^23), three beyond.
+ *   g, d, M, ldg   as for uq_shared_scale, 1 <= M <= 16; row m is worker m
+ *   scales, K      host array of K floats, as for uq_dequantize
+ *   bits           0: codes not stored (codes is ignored); 8: int8; 4 or 2:
+ *                  packed, and the smallest scale must fit the field
+ *   w              one fp32 (written): W
+ *   idx            [d] uint8 (written); must be NULL iff K == 1
+ *   codes, ldc     as for uq_index_quantize (written)
+ *   sum, out       as for uq_index_quantize_sum (written)
+ *   ws, ws_bytes   as for uq_shared_scale
+ * The checks of those calls apply; M > 16 returns UQ_ERANGE.
+ */
+int uq_aggregate(const float* g, int64_t d, int32_t M, int64_t ldg, const float* scales, int32_t K, uint64_t seed,
+                 int32_t bits, float* w, uint8_t* idx, void* codes, int64_t ldc, int32_t* sum, float* out, void* ws,
+                 size_t ws_bytes, void* stream);
+
 /* ------------------------------------------------------------------------
  * Sub-byte codes.  The paper stores every code in 8 bits because its
  * framework had no narrower type, and found bit-packing too slow (Sec. 5,

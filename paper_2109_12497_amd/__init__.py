@@ -66,6 +66,7 @@ def _load() -> ctypes.CDLL:
     L.uq_quantize_sum_idx4.argtypes = [P, i64, i32, i64, i32, P, P, i32, P, u64, i32, P, i32, P, P]
     L.uq_index_quantize_sum.argtypes = [P, i64, i32, i64, P, P, i32, u64, P, P, P, P]
     L.uq_index_quantize.argtypes = [P, i64, i32, i64, P, P, i32, u64, i32, P, P, i64, P]
+    L.uq_aggregate.argtypes = [P, i64, i32, i64, P, i32, u64, i32, P, P, P, i64, P, P, P, sz, P]
     L.uq_sum_packed.argtypes = [P, i64, i32, i64, i32, i32, P, P]
     L.uq_randk_workspace_bytes.argtypes = [i64, i64]
     L.uq_randk_workspace_bytes.restype = sz
@@ -81,7 +82,7 @@ def _load() -> ctypes.CDLL:
     for name in ("uq_shared_scale", "uq_shared_scale_idx4", "uq_shared_scale_noalloc", "uq_quantize_single",
                  "uq_quantize_multi", "uq_sum_codes", "uq_dequantize", "uq_sum_dequantize", "uq_quantize_packed",
                  "uq_sum_packed", "uq_quantize_sum", "uq_quantize_sum_idx4",
-                 "uq_index_quantize_sum", "uq_index_quantize",
+                 "uq_index_quantize_sum", "uq_index_quantize", "uq_aggregate",
                  "uq_randk_select", "uq_gather",
                  "uq_scatter", "uq_set_grid_cap", "uq_set_randk_mode"):
         getattr(L, name).restype = ctypes.c_int
@@ -231,6 +232,12 @@ def uq_index_quantize(g, d, M, ldg, w, scales, K, seed, bits, idx, codes, ldc, s
     hs = _host_scales(scales)
     _check(lib.uq_index_quantize(_ptr(g), d, M, ldg, _ptr(w), hs.ptr, K, seed, bits, _ptr(idx), _ptr(codes), ldc,
                                  _stream(stream)))
+
+
+def uq_aggregate(g, d, M, ldg, scales, K, seed, bits, w, idx, codes, ldc, sum, out, ws, ws_bytes, stream=None) -> None:
+    hs = _host_scales(scales)
+    _check(lib.uq_aggregate(_ptr(g), d, M, ldg, hs.ptr, K, seed, bits, _ptr(w), _ptr(idx), _ptr(codes), ldc, _ptr(sum),
+                            _ptr(out), _ptr(ws), ws_bytes, _stream(stream)))
 
 
 def uq_sum_packed(packed, d, rows, ldp, bits, accumulate, sum, stream=None) -> None:

@@ -527,6 +527,37 @@ int uq_index_quantize(const float* g, int64_t d, int32_t M, int64_t ldg, const f
                                               static_cast<hipStream_t>(stream)));
 }
 
+int uq_aggregate(const float* g, int64_t d, int32_t M, int64_t ldg, const float* scales, int32_t K, uint64_t seed,
+                 int32_t bits, float* w, uint8_t* idx, void* codes, int64_t ldc, int32_t* sum, float* out, void* ws,
+                 size_t ws_bytes, void* stream)
+{
+    if (bits != 0 && bits != 8 && bits != 4 && bits != 2)
+        return fail(UQ_ERANGE, "bits = %d is not 0, 8, 4 or 2", bits);
+    uq::ScaleSet S;
+    UQ_TRY(check_scales(scales, K, &S));
+    if (bits != 0 && bits < 8 && S.s[0] > static_cast<float>((1 << (bits - 1)) - 1))
+        return fail(UQ_ERANGE, "smallest scale %g does not fit a %d-bit code", (double)S.s[0], bits);
+    UQ_TRY(check_dims(d, M, "M"));
+    if (M > uq::kFuseRows)
+        return fail(UQ_ERANGE, "M = %d exceeds the %d rows held in registers", M, uq::kFuseRows);
+    UQ_TRY(check_rows(g, d, M, ldg, 4, "g"));
+    UQ_TRY(check_w(w));
+    if (bits != 0)
+        UQ_TRY(check_rows(codes, (d * bits + 7) / 8, M, ldc, 16, "codes"));
+    UQ_TRY(check_vec(sum, d, "sum"));
+    uq::ScaleSet S2;
+    UQ_TRY(check_reconstruction(d, M, w, scales, K, idx, out, &S2));
+    if (ws == nullptr)
+        return fail(UQ_EINVAL, "ws is NULL");
+    if (!aligned(ws, 16))
+        return fail(UQ_EALIGN, "ws is not 16-byte aligned");
+    if (ws_bytes < uq_workspace_bytes(d, M))
+        return fail(UQ_EWORKSPACE, "workspace of %zu bytes is smaller than the %zu needed", ws_bytes,
+                    uq_workspace_bytes(d, M));
+    return launched(uq::launch_aggregate(g, d, M, ldg, S, seed, bits, w, idx, static_cast<uint8_t*>(codes), ldc, sum,
+                                         out, ws, static_cast<hipStream_t>(stream)));
+}
+
 size_t uq_randk_workspace_bytes(int64_t d, int64_t K)
 {
     (void)d;

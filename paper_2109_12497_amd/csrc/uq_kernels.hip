@@ -1095,10 +1095,9 @@ __device__ __forceinline__ float lane_value(float x, int32_t lane)
 // outstanding loads retires in order, and so would everything formed from
 // it (measured on 4 rows of 25.6 M coordinates with four scales: 113.7 us against 108.1; 8 rows of 11.2 M: 79.5 against 73.3).
 template <bool MULTI>
-__device__ __forceinline__ WaveScale wave_scale(const float* __restrict__ wptr, const ScaleSet& S, int32_t M)
+__device__ __forceinline__ WaveScale wave_scale(float W, const ScaleSet& S, int32_t M)
 {
     WaveScale c;
-    const float W = *wptr;
     float s = S.s[0];
     if (MULTI) {
 #pragma unroll
@@ -1192,7 +1191,7 @@ __global__ __launch_bounds__(64) void k_quantise(const float* __restrict__ g, in
     TileIn in = {};
     if (T < ntiles)
         in = load_tile<MULTI>(row, idx, (T << 9) + 4 * lane);
-    const WaveScale c = wave_scale<MULTI>(wptr, S, 1);
+    const WaveScale c = wave_scale<MULTI>(*wptr, S, 1);
     const uint32_t kmax = static_cast<uint32_t>(S.K - 1);
     if (MULTI && lane < kMaxScales) {
         inv_s[lane] = c.raw;
@@ -1407,7 +1406,7 @@ __global__ __launch_bounds__(64) void k_dequant(const int32_t* __restrict__ sum,
                 kk[h] = *reinterpret_cast<const uint32_t*>(idx + i);
         }
     }
-    const WaveScale c = wave_scale<MULTI>(wptr, S, M);
+    const WaveScale c = wave_scale<MULTI>(*wptr, S, M);
     const float deq0 = lane_value(c.deq, 0);
     const uint32_t kmax = static_cast<uint32_t>(S.K - 1);
     if (MULTI && lane < kMaxScales)
@@ -1548,7 +1547,7 @@ __global__ __launch_bounds__(64) void k_quant_sum(const float* __restrict__ g, i
             sb = load_sum4<NT>(sum + a_off + 256);
         }
     }
-    const WaveScale c = wave_scale<MULTI>(wptr, S, M);
+    const WaveScale c = wave_scale<MULTI>(*wptr, S, M);
     const uint32_t kmax = static_cast<uint32_t>(S.K - 1);
     const float inv0 = lane_value(c.inv, 0), raw0 = lane_value(c.raw, 0), deq0 = DEQ ? lane_value(c.deq, 0) : 0.0f;
     if (lane < kMaxScales) {
@@ -1756,23 +1755,6 @@ __device__ __forceinline__ void add_pair(const u16x2 mag[4], const u16x2 sgn[4],
     }
 }
 
-// The wave's constants, and the tables of a tile's rows (workers worker0 ..)
-// in LDS.
-template <int ROWS, bool MULTI>
-__device__ __forceinline__ WaveScale row_tables(const float* __restrict__ wptr, const ScaleSet& S, int32_t M,
-                                                uint32_t c1, uint32_t worker0, uint32_t key0, RowTables& tab)
-{
-    if (threadIdx.x < ROWS)
-        tab.key[threadIdx.x] = row_key(c1, worker0 + threadIdx.x, key0);
-    const WaveScale c = wave_scale<MULTI>(wptr, S, M);
-    if (MULTI && threadIdx.x < kMaxScales) {
-        tab.inv[threadIdx.x] = c.inv;
-        tab.deq[threadIdx.x] = c.deq;
-    }
-    __syncthreads();
-    return c;
-}
-
 // Stores a lane's four index bytes of tile T (those below d with TAIL).
 template <bool TAIL>
 __device__ __forceinline__ void store_index(uint8_t* __restrict__ idx, int64_t T, int64_t d, const uint32_t k[4])
@@ -1837,116 +1819,6 @@ __device__ __forceinline__ void for_row_pairs(const f32x4 (&A)[ROWS], const floa
     }
 }
 
-template <int ROWS, bool MULTI, bool NT, bool TAIL>
-__device__ __forceinline__ void rows_tile(const f32x4 (&A)[ROWS], const float* __restrict__ g, int64_t ldg,
-                                          int32_t rows, uint32_t worker0, int64_t T, int64_t d, const WaveScale& c,
-                                          int32_t K, const RowTables& tab, uint32_t key0, uint32_t key1,
-                                          uint8_t* __restrict__ idx, int32_t* __restrict__ sum,
-                                          float* __restrict__ out)
-{
-    const int lane = threadIdx.x & 63;
-    const int64_t a_off = T << 8;
-    const int64_t left = TAIL ? d - a_off - 4 * lane : 4;
-    uint32_t k[4] = {0u, 0u, 0u, 0u};
-    if (MULTI) {
-        quad_index<ROWS>(A, c, K, k);
-        store_index<TAIL>(idx, T, d, k);
-    }
-    float inv[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        inv[j] = MULTI ? tab.inv[k[j]] : lane_value(c.inv, 0);
-    // the codes of 16 rows in 16-bit lanes (|sum| <= 16 * 127, exact)
-    u16x2 h0 = {0, 0}, h1 = {0, 0};
-    for_row_pairs<ROWS, TAIL>(A, g, ldg, rows, worker0, T, d, c, inv, tab, key0, key1,
-                              [&](int p, const u16x2 mag[4], const u16x2 sgn[4], const u16x2* fast) {
-                                  u16x2 m[4];
-#pragma unroll
-                                  for (int j = 0; j < 4; ++j)
-                                      m[j] = fast ? static_cast<u16x2>(mag[j] - fast[j]) : mag[j];
-                                  add_pair(m, sgn, 2 * p + 1 < rows, h0, h1);
-                              });
-    const i32x4 s = {static_cast<int16_t>(h0.x), static_cast<int16_t>(h0.y), static_cast<int16_t>(h1.x),
-                     static_cast<int16_t>(h1.y)};
-    const float deq0 = lane_value(c.deq, 0);
-    f32x4 o;
-    o.x = static_cast<float>(s.x) * (MULTI ? tab.deq[k[0]] : deq0);
-    o.y = static_cast<float>(s.y) * (MULTI ? tab.deq[k[1]] : deq0);
-    o.z = static_cast<float>(s.z) * (MULTI ? tab.deq[k[2]] : deq0);
-    o.w = static_cast<float>(s.w) * (MULTI ? tab.deq[k[3]] : deq0);
-    if (left >= 4) {
-        store_through<NT>(sum + a_off, 16 * lane, s);
-        store_through<NT>(out + a_off, 16 * lane, o);
-    } else {
-        const int64_t i = a_off + 4 * lane;
-        if (left > 0) { sum[i] = s.x; out[i] = o.x; }
-        if (left > 1) { sum[i + 1] = s.y; out[i + 1] = o.y; }
-        if (left > 2) { sum[i + 2] = s.z; out[i + 2] = o.z; }
-    }
-}
-
-// Block b takes tile tile0 + b; the tile past the whole ones holds the last
-// coordinates.  There is no loop over tiles: with one, the compiler kept the
-// rows' keys and other loop invariants in registers (155 instead of 101 at 16
-// rows); a call with more tiles than the grid cap is several launches.
-template <int ROWS, bool MULTI, bool NT>
-__device__ __forceinline__ void rows_block(const float* __restrict__ g, int64_t d, int32_t rows, int64_t ldg,
-                                           int32_t worker0, const float* __restrict__ wptr, const ScaleSet& S,
-                                           uint32_t key0, uint32_t key1, int64_t tile0, uint8_t* __restrict__ idx,
-                                           int32_t* __restrict__ sum, int32_t M, float* __restrict__ out)
-{
-    __shared__ RowTables tab;
-    const int64_t T = tile0 + blockIdx.x;
-    const bool whole = T < d >> 8;
-    f32x4 A[ROWS];
-    if (whole)
-        load_quads<ROWS, false>(g, ldg, rows, T, d, A);
-    const WaveScale c = row_tables<ROWS, MULTI>(wptr, S, M, quad_c1(T), static_cast<uint32_t>(worker0), key0, tab);
-    if (whole) {
-        rows_tile<ROWS, MULTI, NT, false>(A, g, ldg, rows, static_cast<uint32_t>(worker0), T, d, c, S.K, tab, key0, key1,
-                                      idx, sum, out);
-    } else {
-        load_quads<ROWS, true>(g, ldg, rows, T, d, A);
-        rows_tile<ROWS, MULTI, NT, true>(A, g, ldg, rows, static_cast<uint32_t>(worker0), T, d, c, S.K, tab, key0, key1,
-                                     idx, sum, out);
-    }
-}
-
-// With more than 12 rows at most two waves per SIMD: 16 rows of VGG-16 size
-// ran in 1.66 ms with two waves and 1.68-1.70 with three (4-bit codes stored:
-// 1.80 and 1.87); 8 rows of 25.6 M in 157-170 us with four or five and 170-195
-// with two.
-#define UQ_ROWS_WAVES(ROWS) __attribute__((amdgpu_waves_per_eu(1, (ROWS) > 12 ? 2 : 8)))
-
-// One scale.
-template <int ROWS, bool NT>
-__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS) void k_quant_sum_split(const float* __restrict__ g, int64_t d, int32_t rows,
-                                                        int64_t ldg, int32_t worker0, const float* __restrict__ wptr,
-                                                        ScaleSet S, uint32_t key0, uint32_t key1, int64_t tile0,
-                                                        int32_t* __restrict__ sum, int32_t M, float* __restrict__ out)
-{
-    rows_block<ROWS, false, NT>(g, d, rows, ldg, worker0, wptr, S, key0, key1, tile0, nullptr, sum, M, out);
-}
-
-// Several scales, the shared index formed and stored: all M rows, as workers
-// 0 .. M - 1.
-template <int ROWS, bool NT>
-__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS) void k_index_quant_sum(const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg,
-                                                        const float* __restrict__ wptr, ScaleSet S, uint32_t key0,
-                                                        uint32_t key1, int64_t tile0, uint8_t* __restrict__ idx,
-                                                        int32_t* __restrict__ sum, float* __restrict__ out)
-{
-    rows_block<ROWS, true, NT>(g, d, M, ldg, 0, wptr, S, key0, key1, tile0, idx, sum, M, out);
-}
-
-// ---------------------------------------------------------------------------
-// The shared index formed in the quantiser (several scales, at most 16 rows,
-// codes stored): k_index_quant_sum's tiles, index and codes, with each row's
-// codes stored (int8, or packed 4- or 2-bit fields) instead of summed.  The
-// codes and the index equal uq_shared_scale's index followed by the
-// quantiser's codes, given the same W.  A wave collects its rows' codes of the
-// tile in LDS and stores them as 16-byte pieces.
-// ---------------------------------------------------------------------------
 template <int BITS>
 __device__ __forceinline__ void lds_put(uint8_t* p, uint32_t v)
 {
@@ -1958,82 +1830,378 @@ __device__ __forceinline__ void lds_put(uint8_t* p, uint32_t v)
         *p = static_cast<uint8_t>(v);
 }
 
-template <int ROWS, int BITS, bool NT, bool TAIL>
-__device__ __forceinline__ void index_quantise_tile(const f32x4 (&A)[ROWS], const float* __restrict__ g, int64_t ldg,
-                                                    int32_t rows, int64_t T, int64_t d, const WaveScale& c, int32_t K,
-                                                    const RowTables& tab, uint32_t key0, uint32_t key1,
-                                                    uint8_t* __restrict__ idx, uint8_t* __restrict__ codes,
-                                                    int64_t ldc, uint8_t* stage)
+// How the sums and outputs of a rows pass are stored (and, unless
+// kStoreThrough, codes nontemporally): through the caches, nontemporally, or
+// both.  Steps in a loop over three sets of buffers, 8 rows: 11.2 M
+// coordinates (45 MB of sums), one scale, through 127.6 us, nontemporal
+// 131.3, both 132.6; four scales 132.9 through, 129.8 with only the sums
+// through, 133.4 nontemporal; 25.6 M (102 MB), four scales, 297.5 through,
+// 292.9 nontemporal, 293.2 both.  A pass of 16 rows of VGG-16 size without
+// work (553 MB): 1.72 ms through, 1.68 nontemporal, 1.64 both.
+constexpr int kStoreThrough = 0, kStoreNontemporal = 1, kStoreBoth = 2;
+
+// What a rows pass writes: the index (several scales), the rows' codes as
+// BITS-bit fields (BITS = 0: not stored), and, unless sum is null, their
+// sums and the reconstruction.
+struct RowsOut {
+    uint8_t* idx;
+    uint8_t* codes;
+    int64_t ldc;
+    int32_t* sum;
+    float* out;
+};
+
+constexpr int rows_stage_bytes(int rows, int bits)
+{
+    return rows * 32 * bits < 16 ? 16 : rows * 32 * bits;
+}
+
+// One tile: the index, every row's codes (collected in the wave's LDS rows
+// `stage` and stored as 16-byte pieces), their sums in 16-bit lanes (|sum| <=
+// 16 * 127, exact) and the reconstruction.
+template <int ROWS, bool MULTI, int BITS, int POL, bool TAIL>
+__device__ __forceinline__ void rows_tile(const f32x4 (&A)[ROWS], const float* __restrict__ g, int64_t ldg,
+                                          int32_t rows, uint32_t worker0, int64_t T, int64_t d, const WaveScale& c,
+                                          int32_t K, const RowTables& tab, uint32_t key0, uint32_t key1,
+                                          const RowsOut& o, uint8_t* stage)
 {
     constexpr int kRowBytes = 32 * BITS;  // one row's codes of a tile
     const int lane = threadIdx.x & 63;
-    uint32_t k[4];
-    quad_index<ROWS>(A, c, K, k);
-    store_index<TAIL>(idx, T, d, k);
+    const int64_t a_off = T << 8;
+    const int64_t left = TAIL ? d - a_off - 4 * lane : 4;
+    uint32_t k[4] = {0u, 0u, 0u, 0u};
+    if (MULTI) {
+        quad_index<ROWS>(A, c, K, k);
+        store_index<TAIL>(o.idx, T, d, k);
+    }
     float inv[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-        inv[j] = tab.inv[k[j]];
-    for_row_pairs<ROWS, TAIL>(A, g, ldg, rows, 0u, T, d, c, inv, tab, key0, key1,
-                              [&](int p, const u16x2 mag[4], const u16x2 sgn[4], const u16x2*) {
-                                  uint32_t q[4];
+        inv[j] = MULTI ? tab.inv[k[j]] : lane_value(c.inv, 0);
+    u16x2 h0 = {0, 0}, h1 = {0, 0};
+    for_row_pairs<ROWS, TAIL>(
+        A, g, ldg, rows, worker0, T, d, c, inv, tab, key0, key1,
+        [&](int p, const u16x2 mag[4], const u16x2 sgn[4], const u16x2* fast) {
+            if (BITS != 0) {
+                uint32_t q[4];
 #pragma unroll
-                                  for (int j = 0; j < 4; ++j)
-                                      q[j] = __builtin_bit_cast(uint32_t, static_cast<u16x2>(mag[j] * sgn[j]));
-                                  uint8_t* srow = stage + 2 * p * kRowBytes + lane * (BITS / 2);
-                                  lds_put<BITS>(srow, pack_quad<BITS>(q[0], q[1]));
-                                  lds_put<BITS>(srow + kRowBytes, pack_quad<BITS>(q[2], q[3]));
-                              });
-    __syncthreads();  // one wave: its LDS writes complete before the reads below
-    if (!TAIL) {
-        // 16-byte pieces, several rows' per store
-        constexpr int kPieces = kRowBytes / 16;
-        constexpr int kAll = ROWS * kPieces;
-#pragma unroll
-        for (int p0 = 0; p0 < kAll; p0 += 64) {
-            const int p = p0 + lane;
-            const int r = p / kPieces;
-            const int off = (p % kPieces) * 16;
-            if (p < kAll && r < rows) {
-                const u32x4 v = *reinterpret_cast<const u32x4*>(stage + r * kRowBytes + off);
-                u32x4* dst = reinterpret_cast<u32x4*>(codes + static_cast<int64_t>(r) * ldc + T * kRowBytes + off);
-                if (NT)
-                    __builtin_nontemporal_store(v, dst);
-                else
-                    *dst = v;
+                for (int j = 0; j < 4; ++j)
+                    q[j] = __builtin_bit_cast(uint32_t, static_cast<u16x2>(mag[j] * sgn[j]));
+                constexpr int B = BITS == 0 ? 8 : BITS;
+                uint8_t* srow = stage + 2 * p * kRowBytes + lane * (B / 2);
+                lds_put<B>(srow, pack_quad<B>(q[0], q[1]));
+                lds_put<B>(srow + kRowBytes, pack_quad<B>(q[2], q[3]));
             }
+            u16x2 m[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                m[j] = fast ? static_cast<u16x2>(mag[j] - fast[j]) : mag[j];
+            add_pair(m, sgn, 2 * p + 1 < rows, h0, h1);
+        });
+    if (BITS != 0) {
+        // the wave's own LDS writes complete before the reads below
+        __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (!TAIL) {
+            // 16-byte pieces, several rows' per store
+            constexpr int kPieces = BITS == 0 ? 1 : kRowBytes / 16;
+            constexpr int kAll = ROWS * kPieces;
+#pragma unroll
+            for (int p0 = 0; p0 < kAll; p0 += 64) {
+                const int p = p0 + lane;
+                const int r = p / kPieces;
+                const int off = (p % kPieces) * 16;
+                if (p < kAll && r < rows) {
+                    const u32x4 v = *reinterpret_cast<const u32x4*>(stage + r * kRowBytes + off);
+                    u32x4* dst = reinterpret_cast<u32x4*>(o.codes + static_cast<int64_t>(r) * o.ldc + T * kRowBytes + off);
+                    if (POL != 0)
+                        __builtin_nontemporal_store(v, dst);
+                    else
+                        *dst = v;
+                }
+            }
+        } else {
+            // the row's bytes up to d (int8), or those of every 8-coordinate
+            // group that starts below d (fields past d hold 0)
+            const int64_t rest = d - a_off;
+            const int64_t n = BITS == 8 ? rest : (rest + 7) / 8 * BITS;
+            for (int32_t r = 0; r < rows; ++r)
+                for (int64_t i = lane; i < n; i += 64)
+                    o.codes[static_cast<int64_t>(r) * o.ldc + T * kRowBytes + i] = stage[r * kRowBytes + i];
+        }
+        if (o.sum == nullptr)
+            return;
+    }
+    const i32x4 s = {static_cast<int16_t>(h0.x), static_cast<int16_t>(h0.y), static_cast<int16_t>(h1.x),
+                     static_cast<int16_t>(h1.y)};
+    const float deq0 = lane_value(c.deq, 0);
+    f32x4 r;
+    r.x = static_cast<float>(s.x) * (MULTI ? tab.deq[k[0]] : deq0);
+    r.y = static_cast<float>(s.y) * (MULTI ? tab.deq[k[1]] : deq0);
+    r.z = static_cast<float>(s.z) * (MULTI ? tab.deq[k[2]] : deq0);
+    r.w = static_cast<float>(s.w) * (MULTI ? tab.deq[k[3]] : deq0);
+    if (left >= 4) {
+        if (POL == kStoreNontemporal) {
+            __builtin_nontemporal_store(s, reinterpret_cast<i32x4*>(o.sum + a_off + 4 * lane));
+            store_nt(o.out + a_off + 4 * lane, r);
+        } else {
+            store_through<POL == kStoreBoth>(o.sum + a_off, 16 * lane, s);
+            if (MULTI && POL == kStoreThrough)
+                store_nt(o.out + a_off + 4 * lane, r);
+            else
+                store_through<POL == kStoreBoth>(o.out + a_off, 16 * lane, r);
         }
     } else {
-        // the row's bytes up to d (int8), or those of every 8-coordinate
-        // group that starts below d (fields past d hold 0)
-        const int64_t left = d - (T << 8);
-        const int64_t n = BITS == 8 ? left : (left + 7) / 8 * BITS;
-        for (int32_t r = 0; r < rows; ++r)
-            for (int64_t i = lane; i < n; i += 64)
-                codes[static_cast<int64_t>(r) * ldc + T * kRowBytes + i] = stage[r * kRowBytes + i];
+        const int64_t i = a_off + 4 * lane;
+        if (left > 0) { o.sum[i] = s.x; o.out[i] = r.x; }
+        if (left > 1) { o.sum[i + 1] = s.y; o.out[i + 1] = r.y; }
+        if (left > 2) { o.sum[i + 2] = s.z; o.out[i + 2] = r.z; }
     }
 }
 
-// Block b takes tile tile0 + b, as rows_block.
-template <int ROWS, int BITS, bool NT>
-__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS) void k_index_quantise(const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg,
-                                                       const float* __restrict__ wptr, ScaleSet S, uint32_t key0,
-                                                       uint32_t key1, int64_t tile0, uint8_t* __restrict__ idx,
-                                                       uint8_t* __restrict__ codes, int64_t ldc)
+// Where a rows pass takes W from: *w, or (part not null) the norm's chunk
+// partials [rows][nchunks], reduced by every wave for itself in k_finish's
+// order; the first block then also stores it to *w.
+struct WSource {
+    float* w;
+    const double* part;
+    int32_t nchunks;
+};
+
+// Partials per row up to which a wave reduces them itself: two loads a lane.
+constexpr int32_t kOwnChunks = 128;
+
+// This lane's part of each row's sum (partials lane and lane + 64).
+template <int ROWS>
+__device__ __forceinline__ void load_partials(const WSource& src, int32_t rows, double (&s)[ROWS])
+{
+    const int lane = threadIdx.x & 63;
+    double x[ROWS], y[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const double* p = src.part + static_cast<int64_t>(r < rows ? r : 0) * src.nchunks;
+        x[r] = lane < src.nchunks ? p[lane] : 0.0;
+        y[r] = lane + 64 < src.nchunks ? p[lane + 64] : 0.0;
+    }
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+        s[r] = r < rows ? x[r] + y[r] : 0.0;
+}
+
+// One step of the rows' butterfly at distance `off` over N registers: row
+// pairs are sent to the two halves that have become equal, so that the next
+// distance works on half the registers.
+template <int N>
+__device__ __forceinline__ void fold_rows(double* s, int off)
+{
+    const bool upper = (threadIdx.x & off) != 0;
+    if (N == 1) {
+        s[0] += __shfl_xor(s[0], off, 64);
+    } else {
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i) {
+            const double keep = upper ? s[2 * i + 1] : s[2 * i];
+            const double send = upper ? s[2 * i] : s[2 * i + 1];
+            s[i] = keep + __shfl_xor(send, off, 64);
+        }
+    }
+}
+
+// W from the rows' lane sums: each row's butterfly over distances 32 .. 1
+// (k_finish's order), several rows at a time, then their largest.
+template <int ROWS>
+__device__ __forceinline__ float reduce_w(const double (&in)[ROWS])
+{
+    constexpr int N0 = ROWS <= 2 ? 2 : ROWS <= 4 ? 4 : ROWS <= 8 ? 8 : 16;
+    double s[N0];
+#pragma unroll
+    for (int r = 0; r < N0; ++r)
+        s[r] = r < ROWS ? in[r < ROWS ? r : 0] : 0.0;
+    fold_rows<N0>(s, 32);
+    fold_rows<(N0 > 2 ? N0 / 2 : 1)>(s, 16);
+    fold_rows<(N0 > 4 ? N0 / 4 : 1)>(s, 8);
+    fold_rows<(N0 > 8 ? N0 / 8 : 1)>(s, 4);
+    fold_rows<1>(s, 2);
+    fold_rows<1>(s, 1);
+    const bool any_nan = __ballot(s[0] != s[0]) != 0;
+    double best = s[0] > 0.0 ? s[0] : 0.0;
+#pragma unroll
+    for (int off = 32; off >= 4; off >>= 1) {
+        const double o = __shfl_xor(best, off, 64);
+        best = o > best ? o : best;
+    }
+    return any_nan ? __builtin_nanf("") : static_cast<float>(sqrt(best));
+}
+
+// Block b takes tile tile0 + b; the tile past the whole ones holds the last
+// coordinates.  There is no loop over tiles: with one, the compiler kept the
+// rows' keys and other loop invariants in registers (155 instead of 101 at 16
+// rows); a call with more tiles than the grid cap is several launches.
+template <int ROWS, bool MULTI, int BITS, int POL>
+__device__ __forceinline__ void rows_block(const float* __restrict__ g, int64_t d, int32_t rows, int64_t ldg,
+                                           int32_t worker0, const WSource& src, const ScaleSet& S, uint32_t key0,
+                                           uint32_t key1, int64_t tile0, int32_t M, const RowsOut& o)
 {
     __shared__ RowTables tab;
-    __shared__ __align__(16) uint8_t stage[ROWS * 32 * BITS];
-    const int64_t T = tile0 + blockIdx.x;
+    __shared__ __align__(16) uint8_t stage[rows_stage_bytes(ROWS, BITS)];
+    int64_t T = tile0 + blockIdx.x;
+    if (BITS == 2) {
+        // a row's codes of a tile are half a 128-byte line: adjacent tiles
+        // to blocks 8 apart, which the same XCD runs, so that its L2 joins
+        // the halves
+        const uint32_t b = blockIdx.x;
+        if ((b | 15u) < gridDim.x)
+            T = tile0 + ((b & ~15u) | ((b & 7u) << 1) | ((b >> 3) & 1u));
+    }
     const bool whole = T < d >> 8;
+    // the partials go out before the rows, whose loads they would wait behind
+    double part[ROWS];
+    if (src.part != nullptr)
+        load_partials<ROWS>(src, rows, part);
     f32x4 A[ROWS];
     if (whole)
-        load_quads<ROWS, false>(g, ldg, M, T, d, A);
-    const WaveScale c = row_tables<ROWS, true>(wptr, S, 1, quad_c1(T), 0u, key0, tab);
-    if (whole) {
-        index_quantise_tile<ROWS, BITS, NT, false>(A, g, ldg, M, T, d, c, S.K, tab, key0, key1, idx, codes, ldc, stage);
+        load_quads<ROWS, false>(g, ldg, rows, T, d, A);
+    if (threadIdx.x < ROWS)
+        tab.key[threadIdx.x] = row_key(quad_c1(T), static_cast<uint32_t>(worker0) + threadIdx.x, key0);
+    float W;
+    if (src.part != nullptr) {
+        W = reduce_w<ROWS>(part);
+        if (T == 0 && threadIdx.x == 0)
+            *src.w = W;
     } else {
-        load_quads<ROWS, true>(g, ldg, M, T, d, A);
-        index_quantise_tile<ROWS, BITS, NT, true>(A, g, ldg, M, T, d, c, S.K, tab, key0, key1, idx, codes, ldc, stage);
+        W = *src.w;
+    }
+    const WaveScale c = wave_scale<MULTI>(W, S, M);
+    if (MULTI && threadIdx.x < kMaxScales) {
+        tab.inv[threadIdx.x] = c.inv;
+        tab.deq[threadIdx.x] = c.deq;
+    }
+    __syncthreads();
+    if (whole) {
+        rows_tile<ROWS, MULTI, BITS, POL, false>(A, g, ldg, rows, static_cast<uint32_t>(worker0), T, d, c, S.K, tab,
+                                                key0, key1, o, stage);
+    } else {
+        load_quads<ROWS, true>(g, ldg, rows, T, d, A);
+        rows_tile<ROWS, MULTI, BITS, POL, true>(A, g, ldg, rows, static_cast<uint32_t>(worker0), T, d, c, S.K, tab,
+                                               key0, key1, o, stage);
+    }
+}
+
+// With more than 12 rows at most two waves per SIMD: 16 rows of VGG-16 size
+// ran in 1.66 ms with two waves and 1.68-1.70 with three (4-bit codes stored:
+// 1.80 and 1.87); 8 rows of 25.6 M in 157-170 us with four or five and 170-195
+// with two.
+#define UQ_ROWS_WAVES(ROWS) __attribute__((amdgpu_waves_per_eu(1, (ROWS) > 12 ? 2 : 8)))
+
+// One scale, no codes stored.
+template <int ROWS, int POL>
+__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS) void k_quant_sum_split(
+    const float* __restrict__ g, int64_t d, int32_t rows, int64_t ldg, int32_t worker0, WSource src, ScaleSet S,
+    uint32_t key0, uint32_t key1, int64_t tile0, int32_t M, RowsOut o)
+{
+    rows_block<ROWS, false, 0, POL>(g, d, rows, ldg, worker0, src, S, key0, key1, tile0, M, o);
+}
+
+// Several scales, no codes stored; the shared index formed and stored: all M
+// rows, as workers 0 .. M - 1.
+template <int ROWS, int POL>
+__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS) void k_index_quant_sum(
+    const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg, WSource src, ScaleSet S, uint32_t key0,
+    uint32_t key1, int64_t tile0, RowsOut o)
+{
+    rows_block<ROWS, true, 0, POL>(g, d, M, ldg, 0, src, S, key0, key1, tile0, M, o);
+}
+
+// The codes stored as BITS-bit fields, and (o.sum not null) summed and
+// reconstructed in the same pass, so that they are not read again.
+template <int ROWS, bool MULTI, int BITS, bool NT>
+__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS) void k_index_quantise(
+    const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg, WSource src, ScaleSet S, uint32_t key0,
+    uint32_t key1, int64_t tile0, RowsOut o)
+{
+    rows_block<ROWS, MULTI, BITS, NT ? kStoreBoth : kStoreThrough>(g, d, M, ldg, 0, src, S, key0, key1, tile0, M, o);
+}
+
+// ---------------------------------------------------------------------------
+// A whole step in one block, for d <= kSmallStep coordinates of at most 16
+// rows: the rows' sums of squares in k_sumsq's order (one chunk a row: 256
+// threads), W by k_finish's rule, then one wave per 256-coordinate tile as
+// above.  At such sizes a step is launches and their latency.
+// 1000 coordinates of 8 rows, codes stored: 24.0 us as four kernels, 11.9 as one.
+// ---------------------------------------------------------------------------
+constexpr int kSmallThreads = 512;
+constexpr int64_t kSmallStep = 4096;
+
+template <int ROWS, bool MULTI, int BITS>
+__global__ __launch_bounds__(kSmallThreads) void k_step_small(const float* __restrict__ g, int64_t d, int32_t M,
+                                                              int64_t ldg, float* __restrict__ w, ScaleSet S,
+                                                              uint32_t key0, uint32_t key1, RowsOut o)
+{
+    __shared__ double wave_part[ROWS][4];
+    __shared__ RowTables tab;
+    __shared__ __align__(16) uint8_t stage_s[kSmallThreads / 64][rows_stage_bytes(ROWS, BITS)];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(threadIdx.x >> 6));
+    // two rows at a time, 256 threads each
+    const int32_t nvec = static_cast<int32_t>(d >> 2);
+    const int t = threadIdx.x & 255;
+    double sq[ROWS / 2];
+#pragma unroll
+    for (int i = 0; i < ROWS / 2; ++i) {
+        const int m = 2 * i + static_cast<int>(threadIdx.x >> 8);
+        const float* row = g + static_cast<int64_t>(m < M ? m : M - 1) * ldg;
+        double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0;
+#pragma unroll
+        for (int u = 0; u < kSmallStep / 1024; ++u) {
+            const int32_t j = t + 256 * u;
+            if (j < nvec) {
+                const f32x4 a = *reinterpret_cast<const f32x4*>(row + 4 * j);
+                acc0 = fma((double)a.x, (double)a.x, acc0); acc1 = fma((double)a.y, (double)a.y, acc1);
+                acc2 = fma((double)a.z, (double)a.z, acc2); acc3 = fma((double)a.w, (double)a.w, acc3);
+            }
+        }
+        const int32_t tail = 4 * nvec + t;
+        if (tail < d) {
+            const double x = row[tail];
+            acc0 = fma(x, x, acc0);
+        }
+        sq[i] = (acc0 + acc1) + (acc2 + acc3);
+    }
+#pragma unroll
+    for (int i = 0; i < ROWS / 2; ++i) {
+        const double s = wave_sum(sq[i]);
+        if (lane == 0)
+            wave_part[2 * i + (wave >> 2)][wave & 3] = s;
+    }
+    __syncthreads();
+    double best = 0.0;
+    bool any_nan = false;
+    for (int32_t m = 0; m < M; ++m) {
+        const double r = (wave_part[m][0] + wave_part[m][1]) + (wave_part[m][2] + wave_part[m][3]);
+        any_nan = any_nan || (r != r);
+        best = r > best ? r : best;
+    }
+    const float W = any_nan ? __builtin_nanf("") : static_cast<float>(sqrt(best));
+    if (threadIdx.x == 0)
+        *w = W;
+    const WaveScale c = wave_scale<MULTI>(W, S, M);
+    if (threadIdx.x < ROWS)
+        tab.key[threadIdx.x] = row_key(0u, threadIdx.x, key0);
+    if (MULTI && threadIdx.x < kMaxScales) {
+        tab.inv[threadIdx.x] = c.inv;
+        tab.deq[threadIdx.x] = c.deq;
+    }
+    __syncthreads();
+    for (int32_t T = wave; T < (d + 255) >> 8; T += kSmallThreads / 64) {
+        f32x4 A[ROWS];
+        if (T < d >> 8) {
+            load_quads<ROWS, false>(g, ldg, M, T, d, A);
+            rows_tile<ROWS, MULTI, BITS, kStoreThrough, false>(A, g, ldg, M, 0u, T, d, c, S.K, tab, key0, key1, o,
+                                                       stage_s[wave]);
+        } else {
+            load_quads<ROWS, true>(g, ldg, M, T, d, A);
+            rows_tile<ROWS, MULTI, BITS, kStoreThrough, true>(A, g, ldg, M, 0u, T, d, c, S.K, tab, key0, key1, o,
+                                                      stage_s[wave]);
+        }
     }
 }
 
@@ -2092,6 +2260,22 @@ constexpr int64_t kIndexNontemporalBytes = int64_t(256) << 20;
 // outputs of 16 rows at VGG-16 size, with the index, 1.64 against 1.72 ms;
 // at ResNet-50 size (102 MB) 167 us with the hint, 157 without.
 constexpr int64_t kThroughNontemporalBytes = int64_t(256) << 20;
+
+// The norm: chunk partials, and W from them unless w is null.
+static hipError_t launch_norm(const float* g, int64_t d, int32_t M, int64_t ldg, const NormPlan& plan, float* w,
+                              double* part, hipStream_t stream)
+{
+    if (plan.nchunks > 0) {
+        // rows beyond the grid cap / nchunks are taken in turn by the same blocks
+        int64_t gy = one_shot_cap() / plan.nchunks;
+        gy = gy < 1 ? 1 : (gy > M ? M : gy);
+        dim3 grid(static_cast<unsigned>(plan.nchunks), static_cast<unsigned>(gy));
+        hipLaunchKernelGGL(k_sumsq, grid, dim3(kBlock), 0, stream, g, d, M, ldg, plan.chunk, plan.nchunks, part);
+    }
+    if (w != nullptr)
+        hipLaunchKernelGGL(k_finish, dim3(1), dim3(kFinishThreads), 0, stream, part, plan.nchunks, M, w);
+    return hipGetLastError();
+}
 
 hipError_t launch_shared_scale(const float* g, int64_t d, int32_t M, int64_t ldg, const ScaleSet& S,
                                float* w, uint8_t* idx, void* ws, hipStream_t stream, int32_t idx_bits)
@@ -2152,15 +2336,9 @@ hipError_t launch_shared_scale(const float* g, int64_t d, int32_t M, int64_t ldg
         return hipGetLastError();
     }
     double* part = static_cast<double*>(ws);
-    const NormPlan plan = norm_plan(d);
-    if (plan.nchunks > 0) {
-        // rows beyond the grid cap / nchunks are taken in turn by the same blocks
-        int64_t gy = one_shot_cap() / plan.nchunks;
-        gy = gy < 1 ? 1 : (gy > M ? M : gy);
-        dim3 grid(static_cast<unsigned>(plan.nchunks), static_cast<unsigned>(gy));
-        hipLaunchKernelGGL(k_sumsq, grid, dim3(kBlock), 0, stream, g, d, M, ldg, plan.chunk, plan.nchunks, part);
-    }
-    hipLaunchKernelGGL(k_finish, dim3(1), dim3(kFinishThreads), 0, stream, part, plan.nchunks, M, w);
+    const hipError_t e = launch_norm(g, d, M, ldg, norm_plan(d), w, part, stream);
+    if (e != hipSuccess)
+        return e;
     if (S.K > 1 && d > 0) {
         const unsigned gx = one_shot((d + 3) / 4, kBlock);
         if (nib)
@@ -2210,38 +2388,45 @@ hipError_t launch_quantise(const float* g, int64_t d, int32_t rows, int64_t ldg,
     return hipGetLastError();
 }
 
-// One scale, 5 <= rows <= kFuseRows rows set and reconstructed in one call:
+// The rows pass's stores by the bytes of its sums (see kStoreThrough).
+static int rows_policy(int64_t d)
+{
+    return 4 * d > kThroughNontemporalBytes ? kStoreBoth : 4 * d > kSumNontemporalBytes ? kStoreNontemporal
+                                                                                       : kStoreThrough;
+}
+
+// One scale, at most kFuseRows rows set and reconstructed in one call:
 // one block per 256-coordinate tile (the last one partial), one instance per
 // row pair count.
-#define UQ_ROW_PAIRS_3_TO_8(LAUNCH, NT) \
+#define UQ_ROW_PAIRS_1_TO_8(LAUNCH, NT) \
+    LAUNCH(1, NT);                      \
+    LAUNCH(2, NT);                      \
     LAUNCH(3, NT);                      \
     LAUNCH(4, NT);                      \
     LAUNCH(5, NT);                      \
     LAUNCH(6, NT);                      \
     LAUNCH(7, NT);                      \
     LAUNCH(8, NT)
-#define UQ_ROW_PAIRS_1_TO_8(LAUNCH, NT) \
-    LAUNCH(1, NT);                      \
-    LAUNCH(2, NT);                      \
-    UQ_ROW_PAIRS_3_TO_8(LAUNCH, NT)
 
 static hipError_t launch_quant_sum_split(const float* g, int64_t d, int32_t rows, int64_t ldg, int32_t worker0,
-                                         const float* w, const ScaleSet& S, uint32_t key0, uint32_t key1,
-                                         int32_t* sum, int32_t M, float* out, hipStream_t stream)
+                                         const WSource& src, const ScaleSet& S, uint32_t key0, uint32_t key1,
+                                         int32_t M, const RowsOut& o, hipStream_t stream)
 {
     const int64_t ntiles = (d + 255) >> 8;
-    const bool nt = 4 * d > kThroughNontemporalBytes;
+    const int policy = rows_policy(d);
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
         const dim3 grid(one_shot(ntiles - tile0, 1));
-#define UQ_LAUNCH_SPLIT(PAIRS, NT)                                                                                 \
+#define UQ_LAUNCH_SPLIT(PAIRS, POL)                                                                                \
     case PAIRS:                                                                                                    \
-        hipLaunchKernelGGL((k_quant_sum_split<2 * PAIRS, NT>), grid, dim3(64), 0, stream, g, d, rows, ldg,         \
-                           worker0, w, S, key0, key1, tile0, sum, M, out);                                         \
+        hipLaunchKernelGGL((k_quant_sum_split<2 * PAIRS, POL>), grid, dim3(64), 0, stream, g, d, rows, ldg,         \
+                           worker0, src, S, key0, key1, tile0, M, o);                                              \
         break
-        if (nt) {
-            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_3_TO_8(UQ_LAUNCH_SPLIT, true); }
+        if (policy == kStoreThrough) {
+            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreThrough); }
+        } else if (policy == kStoreNontemporal) {
+            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreNontemporal); }
         } else {
-            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_3_TO_8(UQ_LAUNCH_SPLIT, false); }
+            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreBoth); }
         }
 #undef UQ_LAUNCH_SPLIT
     }
@@ -2262,7 +2447,8 @@ hipError_t launch_quant_sum(const float* g, int64_t d, int32_t rows, int64_t ldg
     const bool acc = accumulate != 0;
     const bool deq = out != nullptr;
     if (!multi && !acc && deq && rows > 4 && rows <= kFuseRows)
-        return launch_quant_sum_split(g, d, rows, ldg, worker0, w, S, key0, key1, sum, M, out, stream);
+        return launch_quant_sum_split(g, d, rows, ldg, worker0, WSource{const_cast<float*>(w), nullptr, 0}, S, key0,
+                                      key1, M, RowsOut{nullptr, nullptr, 0, sum, out}, stream);
     // one block per 512-coordinate tile, the last one partial
     const int64_t ntiles = (d + 511) >> 9;
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
@@ -2312,50 +2498,65 @@ hipError_t launch_quant_sum(const float* g, int64_t d, int32_t rows, int64_t ldg
     return hipGetLastError();
 }
 
-hipError_t launch_index_quant_sum(const float* g, int64_t d, int32_t M, int64_t ldg, const float* w,
-                                  const ScaleSet& S, uint64_t seed, uint8_t* idx, int32_t* sum, float* out,
-                                  hipStream_t stream)
+// Several scales, no codes stored: one block per 256-coordinate tile (the
+// last one partial), one instance per row pair count.
+static hipError_t launch_index_quant_sum_from(const float* g, int64_t d, int32_t M, int64_t ldg, const WSource& src,
+                                              const ScaleSet& S, uint32_t key0, uint32_t key1, const RowsOut& o,
+                                              hipStream_t stream)
 {
-    if (d == 0)
-        return hipSuccess;
-    const uint32_t key0 = static_cast<uint32_t>(seed);
-    const uint32_t key1 = static_cast<uint32_t>(seed >> 32);
-    // one block per 256-coordinate tile (the last one partial), one instance
-    // per row pair count
     const int64_t ntiles = (d + 255) >> 8;
-    const bool nt = 4 * d > kThroughNontemporalBytes;
+    const int policy = rows_policy(d);
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
         const dim3 grid(one_shot(ntiles - tile0, 1));
-#define UQ_LAUNCH_IQS(PAIRS, NT)                                                                                   \
+#define UQ_LAUNCH_IQS(PAIRS, POL)                                                                                  \
     case PAIRS:                                                                                                    \
-        hipLaunchKernelGGL((k_index_quant_sum<2 * PAIRS, NT>), grid, dim3(64), 0, stream, g, d, M, ldg, w, S,      \
-                           key0, key1, tile0, idx, sum, out);                                                      \
+        hipLaunchKernelGGL((k_index_quant_sum<2 * PAIRS, POL>), grid, dim3(64), 0, stream, g, d, M, ldg, src, S,    \
+                           key0, key1, tile0, o);                                                                  \
         break
-        if (nt) {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, true); }
+        if (policy == kStoreThrough) {
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreThrough); }
+        } else if (policy == kStoreNontemporal) {
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreNontemporal); }
         } else {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, false); }
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreBoth); }
         }
 #undef UQ_LAUNCH_IQS
     }
     return hipGetLastError();
 }
 
-hipError_t launch_index_quantise(const float* g, int64_t d, int32_t M, int64_t ldg, const float* w,
-                                 const ScaleSet& S, uint64_t seed, int32_t bits, uint8_t* idx, uint8_t* codes,
-                                 int64_t ldc, hipStream_t stream)
+hipError_t launch_index_quant_sum(const float* g, int64_t d, int32_t M, int64_t ldg, const float* w,
+                                  const ScaleSet& S, uint64_t seed, uint8_t* idx, int32_t* sum, float* out,
+                                  hipStream_t stream)
 {
     if (d == 0)
         return hipSuccess;
-    const uint32_t key0 = static_cast<uint32_t>(seed);
-    const uint32_t key1 = static_cast<uint32_t>(seed >> 32);
+    return launch_index_quant_sum_from(g, d, M, ldg, WSource{const_cast<float*>(w), nullptr, 0}, S,
+                                       static_cast<uint32_t>(seed), static_cast<uint32_t>(seed >> 32),
+                                       RowsOut{idx, nullptr, 0, sum, out}, stream);
+}
+
+// The codes stored as `bits`-bit fields (one scale or several), and summed
+// and reconstructed too unless o.sum is null.
+static hipError_t launch_stored_from(const float* g, int64_t d, int32_t M, int64_t ldg, const WSource& src,
+                                     const ScaleSet& S, uint32_t key0, uint32_t key1, int32_t bits, const RowsOut& o,
+                                     hipStream_t stream)
+{
     const bool nt = static_cast<int64_t>(M) * ((d * bits + 7) / 8) > kCodesNontemporalBytes;
+    const bool multi = S.K > 1 || o.idx != nullptr;
     const int64_t ntiles = (d + 255) >> 8;
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
         const dim3 grid(one_shot(ntiles - tile0, 1));
-#define UQ_LAUNCH_IQ_(PAIRS, BITS, NT)                                                                             \
-    hipLaunchKernelGGL((k_index_quantise<2 * PAIRS, BITS, NT>), grid, dim3(64), 0, stream, g, d, M, ldg, w, S,     \
-                       key0, key1, tile0, idx, codes, ldc)
+#define UQ_LAUNCH_IQ__(PAIRS, MULTI, BITS, NT)                                                                     \
+    hipLaunchKernelGGL((k_index_quantise<2 * PAIRS, MULTI, BITS, NT>), grid, dim3(64), 0, stream, g, d, M, ldg,    \
+                       src, S, key0, key1, tile0, o)
+#define UQ_LAUNCH_IQ_(PAIRS, BITS, NT)                \
+    do {                                              \
+        if (multi)                                    \
+            UQ_LAUNCH_IQ__(PAIRS, true, BITS, NT);    \
+        else                                          \
+            UQ_LAUNCH_IQ__(PAIRS, false, BITS, NT);   \
+    } while (0)
 #define UQ_LAUNCH_IQ(PAIRS, NT)                   \
     case PAIRS:                                   \
         if (bits == 8)                            \
@@ -2372,8 +2573,87 @@ hipError_t launch_index_quantise(const float* g, int64_t d, int32_t M, int64_t l
         }
 #undef UQ_LAUNCH_IQ
 #undef UQ_LAUNCH_IQ_
+#undef UQ_LAUNCH_IQ__
     }
     return hipGetLastError();
+}
+
+hipError_t launch_index_quantise(const float* g, int64_t d, int32_t M, int64_t ldg, const float* w,
+                                 const ScaleSet& S, uint64_t seed, int32_t bits, uint8_t* idx, uint8_t* codes,
+                                 int64_t ldc, hipStream_t stream)
+{
+    if (d == 0)
+        return hipSuccess;
+    return launch_stored_from(g, d, M, ldg, WSource{const_cast<float*>(w), nullptr, 0}, S, static_cast<uint32_t>(seed),
+                              static_cast<uint32_t>(seed >> 32), bits, RowsOut{idx, codes, ldc, nullptr, nullptr},
+                              stream);
+}
+
+// Partials (all rows') up to which every wave of the rows pass forms W from
+// them itself instead of reading what k_finish formed, which takes a launch and a wait
+// (4 rows of 2^20 coordinates, 512 partials: the step 18.8 us with it, 13.4
+// without; 8 rows, 1024 partials, 2-bit codes stored: 27.0 and 21.3).
+constexpr int64_t kOwnNormPartials = 1024;
+
+static hipError_t launch_step_small(const float* g, int64_t d, int32_t M, int64_t ldg, float* w, const ScaleSet& S,
+                                    uint32_t key0, uint32_t key1, int32_t bits, const RowsOut& o, hipStream_t stream)
+{
+#define UQ_LAUNCH_SMALL_(ROWS, MULTI, BITS)                                                                        \
+    hipLaunchKernelGGL((k_step_small<ROWS, MULTI, BITS>), dim3(1), dim3(kSmallThreads), 0, stream, g, d, M, ldg,   \
+                       w, S, key0, key1, o)
+#define UQ_LAUNCH_SMALL(ROWS, MULTI)                                      \
+    do {                                                                  \
+        if (bits == 8)                                                    \
+            UQ_LAUNCH_SMALL_(ROWS, MULTI, 8);                             \
+        else if (bits == 4)                                               \
+            UQ_LAUNCH_SMALL_(ROWS, MULTI, 4);                             \
+        else if (bits == 2)                                               \
+            UQ_LAUNCH_SMALL_(ROWS, MULTI, 2);                             \
+        else                                                              \
+            UQ_LAUNCH_SMALL_(ROWS, MULTI, 0);                             \
+    } while (0)
+    if (M <= 8) {
+        if (S.K > 1) UQ_LAUNCH_SMALL(8, true); else UQ_LAUNCH_SMALL(8, false);
+    } else {
+        if (S.K > 1) UQ_LAUNCH_SMALL(16, true); else UQ_LAUNCH_SMALL(16, false);
+    }
+#undef UQ_LAUNCH_SMALL
+#undef UQ_LAUNCH_SMALL_
+    return hipGetLastError();
+}
+
+hipError_t launch_aggregate(const float* g, int64_t d, int32_t M, int64_t ldg, const ScaleSet& S, uint64_t seed,
+                            int32_t bits, float* w, uint8_t* idx, uint8_t* codes, int64_t ldc, int32_t* sum,
+                            float* out, void* ws, hipStream_t stream)
+{
+    const uint32_t key0 = static_cast<uint32_t>(seed);
+    const uint32_t key1 = static_cast<uint32_t>(seed >> 32);
+    const RowsOut o{S.K > 1 ? idx : nullptr, codes, ldc, sum, out};
+    const NormPlan plan = norm_plan(d);
+    if (d > 0 && d <= kSmallStep)
+        return launch_step_small(g, d, M, ldg, w, S, key0, key1, bits, o, stream);
+    // one scale with codes stored: beyond what the cache holds, summing them
+    // as they are stored saves reading them back; below, the quantiser and
+    // the sum are faster apart (one scale needs no row of another's):
+    // 8 rows of 25.6 M 297 against 311 us at 2 bits, 332 against 349 at 8;
+    // 16 rows of 60 M 1554 against 1467 us at 8 bits
+    const bool apart = bits != 0 && S.K == 1 && d > 0 && plan.nchunks > kOwnChunks &&
+                       static_cast<int64_t>(M) * ((d * bits + 7) / 8) <= kThroughNontemporalBytes;
+    const bool own = !apart && d > 0 && plan.nchunks <= kOwnChunks && M * plan.nchunks <= kOwnNormPartials;
+    double* part = static_cast<double*>(ws);
+    const hipError_t e = launch_norm(g, d, M, ldg, plan, own ? nullptr : w, part, stream);
+    if (e != hipSuccess || d == 0)
+        return e;
+    if (apart) {
+        const hipError_t q = launch_quantise(g, d, M, ldg, 0, w, S, nullptr, seed, codes, ldc, bits, stream);
+        return q != hipSuccess ? q : launch_sum_dequant(codes, d, M, ldc, bits, 0, sum, M, w, S, nullptr, out, stream);
+    }
+    const WSource src{w, own ? part : nullptr, plan.nchunks};
+    if (bits != 0)
+        return launch_stored_from(g, d, M, ldg, src, S, key0, key1, bits, o, stream);
+    if (S.K > 1)
+        return launch_index_quant_sum_from(g, d, M, ldg, src, S, key0, key1, o, stream);
+    return launch_quant_sum_split(g, d, M, ldg, 0, src, S, key0, key1, M, o, stream);
 }
 
 hipError_t launch_sum(const int8_t* codes, int64_t d, int32_t rows, int64_t ldc, int32_t accumulate,

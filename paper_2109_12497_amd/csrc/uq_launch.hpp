@@ -150,6 +150,12 @@ hipError_t launch_index_quant_sum(const float* g, int64_t d, int32_t M, int64_t 
 hipError_t launch_index_quantise(const float* g, int64_t d, int32_t M, int64_t ldg, const float* w,
                                  const ScaleSet& S, uint64_t seed, int32_t bits, uint8_t* idx, uint8_t* codes,
                                  int64_t ldc, hipStream_t stream);
+// a whole step over M <= 16 resident rows: W, the rows' codes (stored as
+// `bits`-bit fields, bits = 0: not stored), their sums and the
+// reconstruction, and with several scales the shared index
+hipError_t launch_aggregate(const float* g, int64_t d, int32_t M, int64_t ldg, const ScaleSet& S, uint64_t seed,
+                            int32_t bits, float* w, uint8_t* idx, uint8_t* codes, int64_t ldc, int32_t* sum,
+                            float* out, void* ws, hipStream_t stream);
 hipError_t launch_sum_packed(const uint8_t* packed, int64_t d, int32_t rows, int64_t ldp, int32_t bits,
                              int32_t accumulate, int32_t* sum, hipStream_t stream);
 hipError_t launch_sum(const int8_t* codes, int64_t d, int32_t rows, int64_t ldc, int32_t accumulate,

@@ -11,7 +11,7 @@ from __future__ import annotations
 import numpy as np
 import torch
 
-from . import (_stream, uq_dequantize, uq_gather, uq_index_quantize, uq_index_quantize_sum, uq_quantize_multi, uq_quantize_packed,
+from . import (_stream, uq_aggregate, uq_dequantize, uq_gather, uq_index_quantize, uq_index_quantize_sum, uq_quantize_multi, uq_quantize_packed,
                uq_quantize_single, uq_quantize_sum, uq_quantize_sum_idx4, uq_randk_select, uq_randk_workspace_bytes,
                uq_scatter, uq_shared_scale, uq_shared_scale_idx4, uq_sum_codes, uq_sum_dequantize, uq_sum_packed,
                uq_workspace_bytes)
@@ -38,8 +38,10 @@ class Step:
     index is formed inside the call that quantises every row, from the rows
     it holds (uq_index_quantize_sum with quant_sum, else uq_index_quantize,
     which stores the codes), so the shared-scale call forms W only.  The
-    default is True when those conditions hold with quant_sum or with packed
-    codes; int8 codes stored keep the separate index pass unless asked.
+    default is True when those conditions hold.
+    With resident rows, fused=True, M <= 16 and one scale or the index formed
+    in the pass, run() is one call (uq_aggregate), which also adds stored
+    codes into the sum as it stores them.
     index_bits=4 (several scales, quant_sum, index not formed in the pass):
     the shared index is held as 4-bit fields, two coordinates a byte
     (uq_shared_scale_idx4, uq_quantize_sum_idx4), so each call that reads it
@@ -56,11 +58,12 @@ class Step:
         self.scales = [float(s) for s in scales]
         self.K = len(self.scales)
         can = not streamed and self.K > 1 and 1 <= M <= 16
-        default = can and (self.quant_sum or bits != 8)
-        self.index_in_pass = default if index_in_pass is None else index_in_pass
+        self.index_in_pass = can if index_in_pass is None else index_in_pass
         assert not (self.index_in_pass and not can), "index_in_pass needs resident rows, K > 1, M <= 16"
         self.streamed = streamed
         self.bits = bits
+        # the whole step is one library call
+        self.one_call = not streamed and fused and 1 <= M <= 16 and (self.K == 1 or self.index_in_pass)
         assert index_bits in (8, 4), "index_bits is 8 or 4"
         assert index_bits == 8 or (self.quant_sum and self.K > 1 and not self.index_in_pass), \
             "the 4-bit index serves the quantise-and-sum with several scales and a separate index pass"
@@ -156,15 +159,15 @@ class Step:
         assert g.dtype == torch.float32 and g.device == self.device and g.shape[0] == self.M
         assert g.stride(1) == 1 and g.shape[1] >= self.d
         stream = _stream(stream)  # resolved once for the step's calls
+        if self.one_call:
+            codes = self.codes
+            uq_aggregate(g, self.d, self.M, g.stride(0), self.scales, self.K, seed, 0 if codes is None else self.bits,
+                         self.w, self.idx, codes, self.ldc, self.sum, self.out, self.ws, self.ws_bytes, stream)
+            return self.out[:self.d]
         self.shared_scale(g, stream, w_only=self.index_in_pass)
-        if self.index_in_pass and self.quant_sum:
-            self.index_quantize_sum(g, seed, stream=stream)
-        elif self.index_in_pass:
+        if self.index_in_pass:
             self.index_quantize(g, seed, stream=stream)
-            if self.fused:
-                self.sum_dequantize(stream=stream)
-            else:
-                self.sum_codes(stream=stream)
+            self.sum_codes(stream=stream)
         elif self.quant_sum and self.streamed:
             for m in range(self.M):
                 self.quantize_sum(g[m:m + 1], seed, rows=1, worker0=m, accumulate=1 if m > 0 else 0,
