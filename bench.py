@@ -71,7 +71,7 @@ def selection_roofline(d: int, select_ms: float) -> dict:
     more block each, not counted.  Rate over the whole select call."""
     blocks = (d + 3) // 4
     achieved = blocks / (select_ms * 1e-3) / 1e9
-    return {"bound": "alu", "kernel": "k_rk_init+k_rk_collect+k_rk_sort", "stage": "select",
+    return {"bound": "alu", "kernel": "k_rk_bracket+k_rk_sort", "stage": "select",
             "achieved": round(achieved, 1), "peak": round(PHILOX_PEAK_GBLOCKS, 1), "unit": "G Philox blocks/s",
             "frac": round(achieved / PHILOX_PEAK_GBLOCKS, 4), "traffic": None,
             "algorithmic_blocks_per_launch": blocks, "avg_launch_us": round(select_ms * 1e3, 2),

@@ -370,7 +370,7 @@ int uq_sum_packed(const uint8_t* packed, int64_t d, int32_t rows, int64_t ldp, i
  * sampled coordinates (the paper's K), not a number of scales.
  * ------------------------------------------------------------------------ */
 
-/* Workspace bytes uq_randk_select needs (a fixed size, about 4.4 MiB). */
+/* Workspace bytes uq_randk_select needs (a fixed size, about 4.2 MiB). */
 size_t uq_randk_workspace_bytes(int64_t d, int64_t K);
 
 /*
@@ -406,6 +406,17 @@ int uq_gather(const float* g, int64_t d, int32_t M, int64_t ldg, const uint32_t*
  * out[0..d) = 0, then out[sel[j]] = vals[j] for j < K (indices >= d skipped).
  */
 int uq_scatter(const float* vals, const uint32_t* sel, int64_t K, float* out, int64_t d, void* stream);
+
+/*
+ * The two halves of uq_scatter around the step: uq_randk_select that also
+ * zeroes out[0..d) (the key pass is bound by arithmetic, so the stores cost
+ * little there), and out[sel[j]] = vals[j] alone (indices >= d skipped, the
+ * rest of out untouched).  out must not overlap the gradients that are still
+ * to be gathered; 16-byte aligned in both.
+ */
+int uq_randk_select_zero(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, float* out, void* ws, size_t ws_bytes,
+                         void* stream);
+int uq_scatter_into(const float* vals, const uint32_t* sel, int64_t K, float* out, int64_t d, void* stream);
 
 /*
  * Test hook, not part of the aggregation step: caps the grids of the

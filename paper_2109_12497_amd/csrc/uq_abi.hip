@@ -565,7 +565,8 @@ size_t uq_randk_workspace_bytes(int64_t d, int64_t K)
     return uq::randk_workspace_bytes();
 }
 
-int uq_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, void* ws, size_t ws_bytes, void* stream)
+static int randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, float* out, void* ws, size_t ws_bytes,
+                        void* stream)
 {
     if (d < 1 || d >= (int64_t(1) << 32))
         return fail(UQ_EINVAL, "d = %lld is outside [1, 2^32)", (long long)d);
@@ -579,7 +580,20 @@ int uq_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, void* ws
     if (ws_bytes < uq_randk_workspace_bytes(d, K))
         return fail(UQ_EWORKSPACE, "workspace of %zu bytes is smaller than the %zu needed", ws_bytes,
                     uq_randk_workspace_bytes(d, K));
-    return launched(uq::launch_randk_select(d, K, seed, sel, ws, static_cast<hipStream_t>(stream)));
+    return launched(uq::launch_randk_select(d, K, seed, sel, out, ws, static_cast<hipStream_t>(stream)));
+}
+
+int uq_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, void* ws, size_t ws_bytes, void* stream)
+{
+    return randk_select(d, K, seed, sel, nullptr, ws, ws_bytes, stream);
+}
+
+int uq_randk_select_zero(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, float* out, void* ws, size_t ws_bytes,
+                         void* stream)
+{
+    if (d >= 1)
+        UQ_TRY(check_vec(out, d, "out"));
+    return randk_select(d, K, seed, sel, out, ws, ws_bytes, stream);
 }
 
 int uq_gather(const float* g, int64_t d, int32_t M, int64_t ldg, const uint32_t* sel, int64_t K, float* sub,
@@ -594,7 +608,7 @@ int uq_gather(const float* g, int64_t d, int32_t M, int64_t ldg, const uint32_t*
     return launched(uq::launch_gather(g, d, M, ldg, sel, K, sub, lds, static_cast<hipStream_t>(stream)));
 }
 
-int uq_scatter(const float* vals, const uint32_t* sel, int64_t K, float* out, int64_t d, void* stream)
+static int scatter(const float* vals, const uint32_t* sel, int64_t K, float* out, int64_t d, bool zero, void* stream)
 {
     if (d < 1 || d > kMaxElems)
         return fail(UQ_EINVAL, "d = %lld is out of range", (long long)d);
@@ -603,7 +617,17 @@ int uq_scatter(const float* vals, const uint32_t* sel, int64_t K, float* out, in
     UQ_TRY(check_vec(vals, K, "vals"));
     UQ_TRY(check_vec(sel, K, "sel"));
     UQ_TRY(check_vec(out, d, "out"));
-    return launched(uq::launch_scatter(vals, sel, K, out, d, static_cast<hipStream_t>(stream)));
+    return launched(uq::launch_scatter(vals, sel, K, out, d, zero, static_cast<hipStream_t>(stream)));
+}
+
+int uq_scatter(const float* vals, const uint32_t* sel, int64_t K, float* out, int64_t d, void* stream)
+{
+    return scatter(vals, sel, K, out, d, true, stream);
+}
+
+int uq_scatter_into(const float* vals, const uint32_t* sel, int64_t K, float* out, int64_t d, void* stream)
+{
+    return scatter(vals, sel, K, out, d, false, stream);
 }
 
 int uq_set_randk_mode(int32_t mode)

@@ -177,10 +177,12 @@ size_t randk_workspace_bytes();
 constexpr int32_t kRandkBracket = 1, kRandkHistogram = 0, kRandkBracketMiss = 2;
 constexpr int32_t kRandkHistogramNoCandidates = 3, kRandkBracketMissNoCandidates = 4;
 bool set_randk_mode(int32_t mode);
-hipError_t launch_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, void* ws, hipStream_t stream);
+// out (not null): out[0..d) is zeroed in the key pass
+hipError_t launch_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, float* out, void* ws,
+                               hipStream_t stream);
 hipError_t launch_gather(const float* g, int64_t d, int32_t M, int64_t ldg, const uint32_t* sel, int64_t K,
                          float* sub, int64_t lds, hipStream_t stream);
-hipError_t launch_scatter(const float* vals, const uint32_t* sel, int64_t K, float* out, int64_t d,
+hipError_t launch_scatter(const float* vals, const uint32_t* sel, int64_t K, float* out, int64_t d, bool zero,
                           hipStream_t stream);
 hipError_t launch_dequant(const int32_t* sum, int64_t d, int32_t M, const float* w, const ScaleSet& S,
                           const uint8_t* idx, float* out, hipStream_t stream);

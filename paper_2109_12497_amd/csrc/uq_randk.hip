@@ -11,15 +11,13 @@
 // For K <= kRkSortMax the host first brackets the K-th key: hi is uniform, so
 // the count of keys below any x is binomial and an interval [x_lo, x_hi] of hi
 // ten standard deviations either side of K holds the K-th key except with
-// probability below 1e-20.  One pass over the keys appends every key below
-// x_lo to kRkShards staging lists (each wave adds its selections with one
-// atomic, spread over the lists' counters: device-scope atomics on one
-// address serialise) and collects the ~20 sqrt(K) keys inside the interval
-// with their low words; each of the 64 blocks that sort the lists (one slice
-// of the index range each) checks that the interval held the K-th key and
-// picks the smallest candidates itself.  Should the bracket miss, every such
-// block computes the exact selection itself with the steps below, so the
-// result never depends on it.
+// probability below 1e-20.  One pass over the keys (k_rk_bracket) appends
+// every key below x_lo, and the ~20 sqrt(K) keys inside the interval with
+// their low words, to lists of the block's own, counted in LDS; each of the
+// 64 blocks that sort the lists (one slice of the index range each) checks
+// that the interval held the K-th key and picks the smallest candidates
+// itself.  Should the bracket miss, every such block computes the exact
+// selection itself with the steps below, so the result never depends on it.
 //
 // The histogram passes (K > kRkSortMax, or by the test hook):
 //   1. per-block LDS histograms of hi >> 24 (256 bins), merged with atomics;
@@ -56,13 +54,12 @@ constexpr int kRkShards = 64;      // staging lists of the K <= kRkSortMax path
 constexpr int kRkUnroll = 4;       // Philox blocks per thread and iteration
 constexpr int kRkCopies = 16;      // level-1 histogram copies the blocks merge into
 constexpr int kRkLine = 64;        // uint32 per 256-byte line: one atomic counter per line
-constexpr int kRkShardCand = 256;  // bracket candidates per staging list
 
 struct RandkControl {
     uint32_t b1, need1, b2, need2;  // bins found by the two scans
     uint32_t n_cand, cand_cap;      // candidate append counter; candidates kept (<= kRandkCandidates)
     uint32_t thr_hi, thr_lo, thr_idx;
-    uint32_t x_lo, x_hi;            // collection interval of hi (inclusive)
+    uint32_t x_lo, x_hi;            // the histograms' collection interval of hi (inclusive)
     uint32_t exact;                 // 1: the candidates overflowed, the sort takes the exact path
     uint32_t pad[4];
 };
@@ -77,13 +74,18 @@ struct RandkWorkspace {
     uint32_t hist2[kRkBins2];
     RandkControl ctl;
     uint32_t cand[kRandkCandidates][3];  // (hi, lo, index)
-    uint32_t block_count[kRkMaxBlocks];
-    uint32_t block_offset[kRkMaxBlocks];
+    uint32_t block_count[kRkMaxBlocks];   // the bracket's pass: keys below the interval, per block
+    uint32_t block_offset[kRkMaxBlocks];  // the bracket's pass: keys inside it, per block
     uint32_t n_stage[kRkShards][kRkLine];     // staging list lengths (element 0 of each line)
-    uint32_t stage[kRkShards][kRkSortMax];    // unordered selections (K <= kRkSortMax)
-    uint32_t n_bcand[kRkShards][kRkLine];     // bracket candidates per list (element 0 of each line)
-    uint32_t bcand[kRkShards][kRkShardCand][3];  // (hi, lo, index)
+    // Unordered selections (K <= kRkSortMax).  The histogram route has
+    // kRkShards lists here; the bracket's pass an equal share of the first
+    // half per block for its indices, and of the second for its candidates
+    // (hi, lo, index): at 2048 blocks, 256 indices and 85 candidates where at
+    // most 8 and 2 are expected.
+    uint32_t stage[kRkShards * kRkSortMax];
 };
+static_assert(offsetof(RandkWorkspace, stage) % 16 == 0, "16-byte loads of the lists");
+constexpr uint32_t kRkStageHalf = kRkShards * kRkSortMax / 2;
 
 __device__ __forceinline__ uint4 selection_block(uint32_t q, uint32_t purpose, uint32_t key0, uint32_t key1)
 {
@@ -148,26 +150,28 @@ __device__ __forceinline__ void find_bin(const uint32_t* hist, uint32_t need, ui
 }
 
 static_assert(kRkCopies * kRkBins1 == kRkBins2, "one zeroing loop covers both histograms");
-__global__ __launch_bounds__(kBlock) void k_rk_init(RandkWorkspace* __restrict__ ws, uint32_t x_lo, uint32_t x_hi,
-                                                    uint32_t cand_cap)
+__global__ __launch_bounds__(kBlock) void k_rk_init(RandkWorkspace* __restrict__ ws, uint32_t cand_cap)
 {
     for (int b = threadIdx.x; b < kRkBins2; b += kBlock) {
         reinterpret_cast<uint32_t*>(ws->hist1)[b] = 0u;  // kRkCopies * kRkBins1 == kRkBins2
         ws->hist2[b] = 0u;
     }
-    if (threadIdx.x < sizeof(RandkControl) / 4) {
-        uint32_t v = 0u;
-        if (threadIdx.x == offsetof(RandkControl, x_lo) / 4)
-            v = x_lo;
-        if (threadIdx.x == offsetof(RandkControl, x_hi) / 4)
-            v = x_hi;
-        if (threadIdx.x == offsetof(RandkControl, cand_cap) / 4)
-            v = cand_cap;
-        reinterpret_cast<uint32_t*>(&ws->ctl)[threadIdx.x] = v;
-    }
-    if (threadIdx.x < kRkShards) {
+    if (threadIdx.x < sizeof(RandkControl) / 4)
+        reinterpret_cast<uint32_t*>(&ws->ctl)[threadIdx.x] =
+            threadIdx.x == offsetof(RandkControl, cand_cap) / 4 ? cand_cap : 0u;
+    if (threadIdx.x < kRkShards)
         ws->n_stage[threadIdx.x][0] = 0u;
-        ws->n_bcand[threadIdx.x][0] = 0u;
+}
+
+// Zeroes the four coordinates of key group q (those below d).
+__device__ __forceinline__ void zero_group(float* __restrict__ out, int64_t q, int64_t d)
+{
+    const int64_t i = q << 2;
+    if (i + 4 <= d) {
+        store_nt(out + i, f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+    } else {
+        for (int64_t j = i; j < d; ++j)
+            out[j] = 0.0f;
     }
 }
 
@@ -269,22 +273,21 @@ __global__ __launch_bounds__(kBlock) void k_rk_scan2(RandkWorkspace* __restrict_
     }
 }
 
-// Pass 3: collect the keys whose hi lies in [x_lo, x_hi], with low words.
-// With PICK (K <= kRkSortMax) the keys below x_lo are appended to the staging
-// lists in the same pass (all selected when the interval holds the K-th
-// key): each wave adds its selections of a key group to list (wave id mod
-// kRkShards) with one atomic.  SHARDED (the bracket, about 20 sqrt(K)
-// candidates) puts the candidates in per-list arrays, so that their append
-// counters are spread too; otherwise (d / 2^20 expected) they go to one list.
-template <bool PICK, bool SHARDED>
+// Pass 3 of the histogram route: collect the keys whose hi lies in
+// [x_lo, x_hi] (d / 2^20 expected).  With PICK (K <= kRkSortMax) the keys
+// below x_lo are appended to the staging lists in the same pass: each wave
+// adds its selections of a key group to list (wave id mod kRkShards) with one
+// atomic.  out (not null) is zeroed on the way.
+template <bool PICK>
 __global__ __launch_bounds__(kBlock) void k_rk_collect(int64_t d, uint32_t key0, uint32_t key1,
-                                                       RandkWorkspace* __restrict__ ws, uint32_t K)
+                                                       RandkWorkspace* __restrict__ ws, uint32_t K,
+                                                       float* __restrict__ out)
 {
     const uint32_t x_lo = ws->ctl.x_lo, x_hi = ws->ctl.x_hi;
     const int lane = threadIdx.x & 63;
     const uint64_t below_lanes = (uint64_t(1) << lane) - 1u;
     const uint32_t shard = (blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) % kRkShards;
-    uint32_t* list = ws->stage[shard];
+    uint32_t* list = ws->stage + shard * kRkSortMax;
     const int64_t nq = (d + 3) >> 2;
     const int64_t step = static_cast<int64_t>(gridDim.x) * kBlock * kRkUnroll;
     for (int64_t q0 = static_cast<int64_t>(blockIdx.x) * kBlock * kRkUnroll + threadIdx.x; q0 < nq; q0 += step) {
@@ -294,6 +297,8 @@ __global__ __launch_bounds__(kBlock) void k_rk_collect(int64_t d, uint32_t key0,
       for (int u = 0; u < kRkUnroll; ++u) {
         const int64_t q = q0 + static_cast<int64_t>(u) * kBlock;
         const uint4 w = wu[u];
+        if (out != nullptr)
+            zero_group(out, q, d);
         bool any = false;
         uint32_t take = 0u;
 #pragma unroll
@@ -309,20 +314,11 @@ __global__ __launch_bounds__(kBlock) void k_rk_collect(int64_t d, uint32_t key0,
             for (int j = 0; j < 4; ++j) {
                 const int64_t i = (q << 2) + j;
                 if (i < d && word_of(w, j) >= x_lo && word_of(w, j) <= x_hi) {
-                    if (SHARDED) {
-                        const uint32_t slot = atomicAdd(&ws->n_bcand[shard][0], 1u);
-                        if (slot < static_cast<uint32_t>(kRkShardCand)) {
-                            ws->bcand[shard][slot][0] = word_of(w, j);
-                            ws->bcand[shard][slot][1] = word_of(l, j);
-                            ws->bcand[shard][slot][2] = static_cast<uint32_t>(i);
-                        }
-                    } else {
-                        const uint32_t slot = atomicAdd(&ws->ctl.n_cand, 1u);
-                        if (slot < ws->ctl.cand_cap) {
-                            ws->cand[slot][0] = word_of(w, j);
-                            ws->cand[slot][1] = word_of(l, j);
-                            ws->cand[slot][2] = static_cast<uint32_t>(i);
-                        }
+                    const uint32_t slot = atomicAdd(&ws->ctl.n_cand, 1u);
+                    if (slot < ws->ctl.cand_cap) {
+                        ws->cand[slot][0] = word_of(w, j);
+                        ws->cand[slot][1] = word_of(l, j);
+                        ws->cand[slot][2] = static_cast<uint32_t>(i);
                     }
                 }
             }
@@ -351,6 +347,80 @@ __global__ __launch_bounds__(kBlock) void k_rk_collect(int64_t d, uint32_t key0,
             }
         }
       }
+    }
+}
+
+// The bracket's pass: every key with hi < x_lo (selected, if the interval
+// holds the K-th key) and every key with hi in [x_lo, x_hi], with its low
+// word, to the block's own lists, counted in LDS; the counts are stored
+// whatever fits, so that the sort sees an overflow.  Bound by the Philox
+// arithmetic, so out (not null) is zeroed in it: its stores take the memory
+// the pass leaves idle.
+__global__ __launch_bounds__(kBlock) void k_rk_bracket(int64_t d, uint32_t key0, uint32_t key1, uint32_t x_lo,
+                                                       uint32_t x_hi, RandkWorkspace* __restrict__ ws,
+                                                       uint32_t pick_cap, uint32_t cand_cap, float* __restrict__ out)
+{
+    __shared__ uint32_t n_pick, n_cand;
+    if (threadIdx.x == 0) {
+        n_pick = 0u;
+        n_cand = 0u;
+    }
+    __syncthreads();
+    uint32_t* list = ws->stage + blockIdx.x * pick_cap;
+    uint32_t* cand = ws->stage + kRkStageHalf + blockIdx.x * cand_cap * 3u;
+    const int64_t nq = (d + 3) >> 2;
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kBlock * kRkUnroll;
+    for (int64_t q0 = static_cast<int64_t>(blockIdx.x) * kBlock * kRkUnroll + threadIdx.x; q0 < nq; q0 += step) {
+        if (out != nullptr) {
+#pragma unroll
+            for (int u = 0; u < kRkUnroll; ++u)
+                zero_group(out, q0 + static_cast<int64_t>(u) * kBlock, d);
+        }
+        // groups past nq are formed too (no branch between the blocks) and
+        // fall to the test against d
+        uint4 w[kRkUnroll];
+#pragma unroll
+        for (int u = 0; u < kRkUnroll; ++u)
+            w[u] = selection_block(static_cast<uint32_t>(q0 + static_cast<int64_t>(u) * kBlock), 2u, key0, key1);
+#pragma unroll
+        for (int u = 0; u < kRkUnroll; ++u) {
+            if (min(min(w[u].x, w[u].y), min(w[u].z, w[u].w)) > x_hi)
+                continue;
+            const int64_t q = q0 + static_cast<int64_t>(u) * kBlock;
+            bool any = false;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t hi = word_of(w[u], j);
+                const int64_t i = (q << 2) + j;
+                if (i < d && hi < x_lo) {
+                    const uint32_t slot = atomicAdd(&n_pick, 1u);
+                    if (slot < pick_cap)
+                        list[slot] = static_cast<uint32_t>(i);
+                }
+                any = any || (i < d && hi >= x_lo && hi <= x_hi);
+            }
+            if (any) {
+                const uint4 l = selection_block(static_cast<uint32_t>(q), 3u, key0, key1);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t hi = word_of(w[u], j);
+                    const int64_t i = (q << 2) + j;
+                    if (i < d && hi >= x_lo && hi <= x_hi) {
+                        const uint32_t slot = atomicAdd(&n_cand, 1u);
+                        if (slot < cand_cap) {
+                            cand[3u * slot] = hi;
+                            cand[3u * slot + 1u] = word_of(l, j);
+                            cand[3u * slot + 2u] = static_cast<uint32_t>(i);
+                        }
+                    }
+                }
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        ws->block_count[blockIdx.x] = n_pick;
+        ws->block_offset[blockIdx.x] = n_cand;
     }
 }
 
@@ -487,7 +557,7 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_threshold(RandkWorkspace*
         if (PICK && rank <= want) {
             const uint32_t pos = atomicAdd(&ws->n_stage[0][0], 1u);
             if (pos < K)
-                ws->stage[0][pos] = i;
+                ws->stage[pos] = i;
         }
     }
 }
@@ -521,7 +591,7 @@ __device__ __forceinline__ uint32_t selected_mask(int64_t q, int64_t d, uint32_t
 // Binomial(d, x / 2^32), so the host can name an interval [x_lo, x_hi] of hi
 // that holds the K-th key except with probability below 1e-20 (ten standard
 // deviations either side); one collection pass then appends every key below
-// x_lo to the staging lists and gathers the roughly 20 sqrt(K) keys inside
+// x_lo to its blocks' lists and gathers the roughly 20 sqrt(K) keys inside
 // the interval as candidates, and every block of the sort completes the
 // selection for itself: it checks that the interval did hold the K-th key
 // (fewer than K keys below it, at least K at or below its top, every
@@ -551,18 +621,9 @@ __device__ __forceinline__ uint32_t bucket_of(uint32_t i, double scale)
     return b < kRkBuckets ? b : kRkBuckets - 1u;
 }
 
-// The K staged indices in increasing order, by kRkSlices blocks.  The index
-// range is cut into kRkBuckets buckets (a monotone map) and block j owns the
-// contiguous run of buckets j * kRkSliceBuckets .. + kRkSliceBuckets - 1.
-// Every block reads all staged indices (16 threads per staging list), counts
-// those in earlier slices (its output offset) and bins its own through LDS
-// counters (about K / kRkBuckets per bucket); a second read places them by
-// bucket, and each is written at the offset plus its bucket's start plus its
-// rank inside the bucket (the indices are distinct).
 constexpr int kRkSlices = 64;
 constexpr int kRkSliceBuckets = kRkBuckets / kRkSlices;
 static_assert(kRkSliceBuckets == 64, "one wave scans a slice's buckets");
-static_assert(kRkShards * 16 == kRkSortThreads, "16 threads per staging list");
 
 // The selections of one block's slice of the output, in index order, given
 // the threshold (th, tl, ti): one pass in index order that counts the
@@ -718,17 +779,24 @@ __device__ void sort_exact_slice(int64_t d, uint32_t K, uint32_t key0, uint32_t 
 // the bracket's candidates) in increasing order, by kRkSlices blocks.  The
 // index range is cut into kRkBuckets buckets (a monotone map) and block j owns
 // the contiguous run of buckets j * kRkSliceBuckets .. + kRkSliceBuckets - 1.
-// Every block reads all staged indices (16 threads per staging list), counts
-// those in earlier slices (its output offset) and bins its own through LDS
-// counters (about K / kRkBuckets per bucket); a second read places them by
-// bucket, and each is written at the offset plus its bucket's start plus its
-// rank inside the bucket (the indices are distinct).
+// Every block reads all staged indices (2^log_tps threads per list, four
+// indices a load), counts those in earlier slices (its output offset), keeps
+// its own in LDS and counts them per bucket (about K / kRkBuckets each); they
+// are then placed by bucket, and each is written at the offset plus its
+// bucket's start plus its rank inside the bucket (the indices are distinct).
+// The lists: nlists of `cap` entries from ws->stage; with BRACKET also the
+// candidates' lists of `ccap` entries.
 template <bool BRACKET>
 __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace* __restrict__ ws,
                                                             uint32_t* __restrict__ sel, uint32_t K, int64_t d,
-                                                            uint32_t key0, uint32_t key1)
+                                                            uint32_t key0, uint32_t key1, uint32_t nlists,
+                                                            uint32_t log_tps, uint32_t cap, uint32_t ccap,
+                                                            uint32_t x_lo, uint32_t x_hi, uint32_t exact_cap)
 {
+    constexpr uint32_t kMine = BRACKET ? 3u * kRkPickMax : kRkSortMax;
     __shared__ uint32_t buf[kRkSortMax];
+    __shared__ uint32_t mine[kMine];  // the slice's indices; before them the bracket's candidates
+    __shared__ uint32_t n_list[kRkMaxBlocks];
     __shared__ uint32_t count[kRkSliceBuckets];
     __shared__ uint32_t start[kRkSliceBuckets];
     __shared__ uint32_t wave_below[kRkSortThreads / 64];
@@ -736,66 +804,77 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
     const uint32_t t = threadIdx.x;
     const uint32_t slice = blockIdx.x;
     const int lane = t & 63, wave = t >> 6;
-    const uint32_t* list = ws->stage[t >> 4];
-    const uint32_t len = min(ws->n_stage[t >> 4][0], static_cast<uint32_t>(kRkSortMax));
-    const uint32_t sub = t & 15u;
+    const uint32_t tps = 1u << log_tps, sub = t & (tps - 1u);
+    const uint32_t list0 = t >> log_tps, dlist = static_cast<uint32_t>(kRkSortThreads) >> log_tps;
     const double scale = static_cast<double>(kRkBuckets) / static_cast<double>(d);
 
     // BRACKET: this block's picks among the candidates, in h[0 .. n_pick)
     __shared__ uint32_t h[BRACKET ? kRkBins2 : 1];
-    __shared__ uint32_t cl[BRACKET ? kRkPickMax : 1][3];
+    __shared__ uint32_t n_clist[BRACKET ? kRkMaxBlocks : 1];
     __shared__ uint32_t cross[BRACKET ? kRkCross : 1][3];
     __shared__ uint32_t scratch[kRkSortThreads / 64 + 4];
     __shared__ uint32_t found[2];
-    __shared__ uint32_t n_list[kRkShards], list_off[kRkShards];
-    __shared__ uint32_t n_cross, n_pick, overflow;
+    __shared__ uint32_t staged_all, n_cl, n_cross, n_pick, overflow;
+    if (t == 0) {
+        n_mine = 0u;
+        staged_all = 0u;
+        n_cl = 0u;
+        n_cross = 0u;
+        n_pick = 0u;
+        overflow = 0u;
+    }
+    if (t < kRkSliceBuckets)
+        count[t] = 0u;
     uint32_t npick = 0u;
     if (BRACKET) {
-        static_assert(kRkPickBuckets == 2 * kRkSortThreads, "two parts per thread in the scan");
-        const uint32_t x_lo = ws->ctl.x_lo, x_hi = ws->ctl.x_hi;
+        uint32_t (*cl)[3] = reinterpret_cast<uint32_t(*)[3]>(mine);
         const uint64_t width = static_cast<uint64_t>(x_hi - x_lo) + 1u;
-        if (t == 0) {
-            n_cross = 0u;
-            n_pick = 0u;
-            overflow = 0u;
+        uint32_t np[kRkMaxBlocks / kRkSortThreads], nc[kRkMaxBlocks / kRkSortThreads];
+#pragma unroll
+        for (int i = 0; i < kRkMaxBlocks / kRkSortThreads; ++i) {
+            const uint32_t s = t + i * kRkSortThreads;
+            np[i] = s < nlists ? ws->block_count[s] : 0u;
+            nc[i] = s < nlists ? ws->block_offset[s] : 0u;
         }
         for (int b = t; b < kRkPickBuckets; b += kRkSortThreads)
             h[b] = 0u;
-        __syncthreads();
-        uint32_t below = 0u, cands = 0u;
-        if (t < kRkShards) {
-            below = ws->n_stage[t][0];
-            cands = ws->n_bcand[t][0];
-            n_list[t] = cands;
-            if (cands > static_cast<uint32_t>(kRkShardCand))
-                atomicOr(&overflow, 1u);
+        uint32_t below = 0u;
+        bool over = false;
+#pragma unroll
+        for (int i = 0; i < kRkMaxBlocks / kRkSortThreads; ++i) {
+            n_list[t + i * kRkSortThreads] = min(np[i], cap);
+            n_clist[t + i * kRkSortThreads] = min(nc[i], ccap);
+            below += np[i];
+            over = over || np[i] > cap || nc[i] > ccap;
         }
-        const uint32_t ib = block_inclusive_scan<kRkSortThreads>(below, scratch);
-        if (t == kRkSortThreads - 1)
-            found[0] = ib;  // the last thread's inclusive sum is the total
-        const uint32_t ic = block_inclusive_scan<kRkSortThreads>(cands, scratch);
-        if (t == kRkSortThreads - 1)
-            found[1] = ic;
-        if (t < kRkShards)
-            list_off[t] = ic - cands;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1)
+            below += __shfl_xor(below, off, 64);
         __syncthreads();
-        const uint32_t staged = found[0];
-        const uint32_t n_c = found[1];
+        if (lane == 0)
+            atomicAdd(&staged_all, below);
+        if (over)
+            atomicOr(&overflow, 1u);
+        for (uint32_t s = list0; s < nlists; s += dlist) {
+            const uint32_t n = n_clist[s];
+            if (n <= sub)
+                continue;
+            const uint32_t* src = ws->stage + kRkStageHalf + s * ccap * 3u;
+            uint32_t slot = atomicAdd(&n_cl, (n - sub + tps - 1u) >> log_tps);
+            for (uint32_t j = sub; j < n; j += tps, ++slot)
+                if (slot < static_cast<uint32_t>(kRkPickMax)) {
+                    const uint32_t hh = src[3u * j];
+                    cl[slot][0] = hh;
+                    cl[slot][1] = src[3u * j + 1u];
+                    cl[slot][2] = src[3u * j + 2u];
+                    atomicAdd(&h[pick_bucket(hh, x_lo, width)], 1u);
+                }
+        }
+        __syncthreads();
+        const uint32_t staged = staged_all, n_c = n_cl;
         bool valid = overflow == 0u && n_c <= static_cast<uint32_t>(kRkPickMax) && staged < K && staged + n_c >= K;
         uint32_t bstar = 0u, rest = 0u;
         if (valid) {
-            {  // gather: 16 threads per list
-                const uint32_t sh = t >> 4, n = n_list[sh], off = list_off[sh];
-                for (uint32_t j = sub; j < n; j += 16u) {
-                    cl[off + j][0] = ws->bcand[sh][j][0];
-                    cl[off + j][1] = ws->bcand[sh][j][1];
-                    cl[off + j][2] = ws->bcand[sh][j][2];
-                }
-            }
-            __syncthreads();
-            for (uint32_t c = t; c < n_c; c += kRkSortThreads)
-                atomicAdd(&h[pick_bucket(cl[c][0], x_lo, width)], 1u);
-            __syncthreads();
             find_bin<kRkPickBuckets / kRkSortThreads, kRkSortThreads>(h, K - staged, scratch, &found[0], &found[1]);
             __syncthreads();
             bstar = found[0];
@@ -814,7 +893,7 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
         }
         if (!valid) {
             sort_exact_slice(d, K, key0, key1, sel, h, reinterpret_cast<uint32_t(*)[3]>(buf), scratch, found,
-                             ws->ctl.cand_cap);
+                             exact_cap);
             return;
         }
         // the picks, into h (the parts' counts are no longer needed)
@@ -834,40 +913,50 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
                     h[pos] = ii;
             }
         }
-        __syncthreads();
+        __syncthreads();  // and the candidates' memory becomes the slice's
         npick = min(n_pick, static_cast<uint32_t>(kRkBins2));
+    } else {
+        if (ws->ctl.exact != 0u) {
+            // the candidates overflowed: the threshold block found the
+            // threshold exactly (or, failing, wrote the sentinel), but the
+            // selected candidates were not staged, so the slice is written
+            // from the keys themselves
+            if (ws->ctl.exact == 1u)
+                write_slice_in_order(d, K, key0, key1, sel, ws->ctl.thr_hi, ws->ctl.thr_lo, ws->ctl.thr_idx, scratch);
+            return;
+        }
+        if (t < kRkShards)
+            n_list[t] = min(ws->n_stage[t][0], cap);
+        __syncthreads();
     }
 
-    if (!BRACKET && ws->ctl.exact != 0u) {
-        // the histogram route's candidates overflowed: its threshold block
-        // found the threshold exactly (or, failing, wrote the sentinel), but
-        // the selected candidates were not staged, so the slice is written
-        // from the keys themselves
-        if (ws->ctl.exact == 1u)
-            write_slice_in_order(d, K, key0, key1, sel, ws->ctl.thr_hi, ws->ctl.thr_lo, ws->ctl.thr_idx, scratch);
-        return;
-    }
-    if (t < kRkSliceBuckets)
-        count[t] = 0u;
-    __syncthreads();
     uint32_t below = 0u;
-#pragma unroll 4
-    for (uint32_t p = sub; p < len; p += 16u) {
-        const uint32_t b = bucket_of(list[p], scale);
+    const auto place = [&](uint32_t v) {
+        const uint32_t b = bucket_of(v, scale);
         const uint32_t sl = b / kRkSliceBuckets;
-        if (sl < slice)
+        if (sl < slice) {
             ++below;
-        else if (sl == slice)
+        } else if (sl == slice) {
             atomicAdd(&count[b % kRkSliceBuckets], 1u);
+            const uint32_t pos = atomicAdd(&n_mine, 1u);
+            if (pos < kMine)
+                mine[pos] = v;
+        }
+    };
+    for (uint32_t s = list0; s < nlists; s += dlist) {
+        const uint32_t* list = ws->stage + s * cap;
+        const uint32_t n = n_list[s];
+#pragma unroll 2
+        for (uint32_t p = 4u * sub; p < n; p += 4u * tps) {
+            const uint4 v = *reinterpret_cast<const uint4*>(list + p);
+#pragma unroll
+            for (uint32_t j = 0; j < 4u; ++j)
+                if (p + j < n)
+                    place(word_of(v, static_cast<int>(j)));
+        }
     }
-    for (uint32_t p = t; p < npick; p += kRkSortThreads) {
-        const uint32_t b = bucket_of(h[p], scale);
-        const uint32_t sl = b / kRkSliceBuckets;
-        if (sl < slice)
-            ++below;
-        else if (sl == slice)
-            atomicAdd(&count[b % kRkSliceBuckets], 1u);
-    }
+    for (uint32_t p = t; p < npick; p += kRkSortThreads)
+        place(h[p]);
     // indices in earlier slices: the block's output offset
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1)
@@ -875,6 +964,11 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
     if (lane == 0)
         wave_below[wave] = below;
     __syncthreads();
+    const uint32_t n = BRACKET ? n_mine : min(n_mine, kMine);
+    if (BRACKET && n > kMine) {  // block-uniform; not reached by random keys (K / 64 expected)
+        sort_exact_slice(d, K, key0, key1, sel, h, reinterpret_cast<uint32_t(*)[3]>(buf), scratch, found, exact_cap);
+        return;
+    }
     uint32_t offset = 0u;
 #pragma unroll
     for (int v = 0; v < kRkSortThreads / 64; ++v)
@@ -890,36 +984,19 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
                 x += y;
         }
         start[lane] = x - c;
-        if (lane == 63)
-            n_mine = x;
         count[lane] = 0u;  // reused as the bucket's fill cursor
     }
     __syncthreads();
-#pragma unroll 4
-    for (uint32_t p = sub; p < len; p += 16u) {
-        const uint32_t v = list[p];
-        const uint32_t b = bucket_of(v, scale);
-        if (b / kRkSliceBuckets == slice) {
-            const uint32_t lb = b % kRkSliceBuckets;
-            const uint32_t pos = start[lb] + atomicAdd(&count[lb], 1u);
-            if (pos < static_cast<uint32_t>(kRkSortMax))
-                buf[pos] = v;
-        }
-    }
-    for (uint32_t p = t; p < npick; p += kRkSortThreads) {
-        const uint32_t v = h[p];
-        const uint32_t b = bucket_of(v, scale);
-        if (b / kRkSliceBuckets == slice) {
-            const uint32_t lb = b % kRkSliceBuckets;
-            const uint32_t pos = start[lb] + atomicAdd(&count[lb], 1u);
-            if (pos < static_cast<uint32_t>(kRkSortMax))
-                buf[pos] = v;
-        }
+    for (uint32_t p = t; p < n; p += kRkSortThreads) {
+        const uint32_t v = mine[p];
+        const uint32_t lb = bucket_of(v, scale) % kRkSliceBuckets;
+        const uint32_t pos = start[lb] + atomicAdd(&count[lb], 1u);
+        if (pos < static_cast<uint32_t>(kRkSortMax))
+            buf[pos] = v;
     }
     __syncthreads();
     // each of the slice's indices goes to the offset plus its bucket's start
     // plus the number of smaller indices in its bucket
-    const uint32_t n = min(n_mine, static_cast<uint32_t>(kRkSortMax));
     for (uint32_t e = t; e < n; e += kRkSortThreads) {
         const uint32_t v = buf[e];
         const uint32_t lb = bucket_of(v, scale) % kRkSliceBuckets;
@@ -1039,16 +1116,13 @@ __global__ __launch_bounds__(kBlock) void k_gather(const float* __restrict__ g, 
     }
 }
 
+// Four coordinates a thread.
 __global__ __launch_bounds__(kBlock) void k_zero(float* __restrict__ out, int64_t d)
 {
-    const int64_t n4 = d >> 2;
-    const f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
-    for (int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; q < n4;
+    const int64_t nq = (d + 3) >> 2;
+    for (int64_t q = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; q < nq;
          q += static_cast<int64_t>(gridDim.x) * kBlock)
-        store_nt(out + (q << 2), z);
-    const int64_t t = (n4 << 2) + static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    if (blockIdx.x == 0 && t < d)
-        out[t] = 0.0f;
+        zero_group(out, q, d);
 }
 
 // (an index >= d is skipped)
@@ -1069,12 +1143,12 @@ size_t randk_workspace_bytes()
 }
 
 // Persistent grid for the key passes: kBlock * kRkUnroll key groups per block
-// and iteration, at most eight blocks per compute unit.
+// and iteration, at most eight blocks per compute unit and one list each.
 static unsigned key_grid(int64_t d)
 {
     const int64_t groups = (d + 3) >> 2;
     int64_t blocks = (groups + kBlock * kRkUnroll - 1) / (kBlock * kRkUnroll);
-    const int64_t cap = grid_cap() / 8;
+    const int64_t cap = grid_cap() / 8 < kRkMaxBlocks ? grid_cap() / 8 : kRkMaxBlocks;
     blocks = blocks < 1 ? 1 : (blocks > cap ? cap : blocks);
     return static_cast<unsigned>(blocks);
 }
@@ -1112,7 +1186,8 @@ static bool randk_bracket(int64_t d, int64_t K, uint32_t* x_lo, uint32_t* x_hi)
     return true;
 }
 
-hipError_t launch_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, void* ws_raw, hipStream_t stream)
+hipError_t launch_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, float* out, void* ws_raw,
+                               hipStream_t stream)
 {
     RandkWorkspace* ws = static_cast<RandkWorkspace*>(ws_raw);
     const uint32_t key0 = static_cast<uint32_t>(seed);
@@ -1128,14 +1203,18 @@ hipError_t launch_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* se
     if (K <= kRkSortMax && !histogram && randk_bracket(d, K, &x_lo, &x_hi)) {
         if (mode == kRandkBracketMiss || mode == kRandkBracketMissNoCandidates)
             x_lo = x_hi = 0u;  // an interval that cannot hold the K-th key: the exact fallback runs
-        hipLaunchKernelGGL(k_rk_init, dim3(1), dim3(kBlock), 0, stream, ws, x_lo, x_hi, cand_cap);
-        hipLaunchKernelGGL((k_rk_collect<true, true>), dim3(gx), dim3(kBlock), 0, stream, d, key0, key1, ws,
-                           static_cast<uint32_t>(K));
+        const uint32_t pick_cap = kRkStageHalf / gx & ~3u, key_cap = kRkStageHalf / 3u / gx;
+        uint32_t log_tps = 0u;  // threads per list in the sort
+        while ((gx << (log_tps + 1u)) <= static_cast<unsigned>(kRkSortThreads))
+            ++log_tps;
+        hipLaunchKernelGGL(k_rk_bracket, dim3(gx), dim3(kBlock), 0, stream, d, key0, key1, x_lo, x_hi, ws, pick_cap,
+                           key_cap, out);
         hipLaunchKernelGGL((k_rk_sort<true>), dim3(kRkSlices), dim3(kRkSortThreads), 0, stream, ws, sel,
-                           static_cast<uint32_t>(K), d, key0, key1);
+                           static_cast<uint32_t>(K), d, key0, key1, gx, log_tps, pick_cap, key_cap, x_lo, x_hi,
+                           cand_cap);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_rk_init, dim3(1), dim3(kBlock), 0, stream, ws, 0u, 0u, cand_cap);
+    hipLaunchKernelGGL(k_rk_init, dim3(1), dim3(kBlock), 0, stream, ws, cand_cap);
     // the first histogram merges its LDS bins into global memory: few,
     // long-lived blocks keep those atomics to a few per bin
     int64_t hist_blocks = grid_cap() / 32;  // two blocks per compute unit
@@ -1147,16 +1226,17 @@ hipError_t launch_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* se
     if (K <= kRkSortMax) {
         // the collection pass also appends the keys below the boundary
         // prefix; the threshold block appends the selected candidates
-        hipLaunchKernelGGL((k_rk_collect<true, false>), dim3(gx), dim3(kBlock), 0, stream, d, key0, key1, ws,
-                           static_cast<uint32_t>(K));
+        hipLaunchKernelGGL(k_rk_collect<true>, dim3(gx), dim3(kBlock), 0, stream, d, key0, key1, ws,
+                           static_cast<uint32_t>(K), out);
         hipLaunchKernelGGL(k_rk_threshold<true>, dim3(1), dim3(kRkSortThreads), 0, stream, ws,
                            static_cast<uint32_t>(K), d, key0, key1, sel);
         hipLaunchKernelGGL((k_rk_sort<false>), dim3(kRkSlices), dim3(kRkSortThreads), 0, stream, ws, sel,
-                           static_cast<uint32_t>(K), d, key0, key1);
+                           static_cast<uint32_t>(K), d, key0, key1, static_cast<uint32_t>(kRkShards), 4u,
+                           static_cast<uint32_t>(kRkSortMax), 0u, 0u, 0u, 0u);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((k_rk_collect<false, false>), dim3(gx), dim3(kBlock), 0, stream, d, key0, key1, ws,
-                       static_cast<uint32_t>(K));
+    hipLaunchKernelGGL(k_rk_collect<false>, dim3(gx), dim3(kBlock), 0, stream, d, key0, key1, ws,
+                       static_cast<uint32_t>(K), out);
     hipLaunchKernelGGL(k_rk_threshold<false>, dim3(1), dim3(kRkSortThreads), 0, stream, ws,
                        static_cast<uint32_t>(K), d, key0, key1, sel);
     // ordered compaction over contiguous chunks (a multiple of 1024 coordinates)
@@ -1181,13 +1261,15 @@ hipError_t launch_gather(const float* g, int64_t d, int32_t M, int64_t ldg, cons
     return hipGetLastError();
 }
 
-hipError_t launch_scatter(const float* vals, const uint32_t* sel, int64_t K, float* out, int64_t d,
+hipError_t launch_scatter(const float* vals, const uint32_t* sel, int64_t K, float* out, int64_t d, bool zero,
                           hipStream_t stream)
 {
-    int64_t zb = ((d + 3) / 4 + kBlock - 1) / kBlock;
-    const int64_t cap = grid_cap();
-    zb = zb < 1 ? 1 : (zb > cap ? cap : zb);
-    hipLaunchKernelGGL(k_zero, dim3(static_cast<unsigned>(zb)), dim3(kBlock), 0, stream, out, d);
+    if (zero) {
+        int64_t zb = ((d + 3) / 4 + kBlock - 1) / kBlock;
+        const int64_t cap = grid_cap();
+        zb = zb < 1 ? 1 : (zb > cap ? cap : zb);
+        hipLaunchKernelGGL(k_zero, dim3(static_cast<unsigned>(zb)), dim3(kBlock), 0, stream, out, d);
+    }
     int64_t sb = (K + kBlock - 1) / kBlock;
     sb = sb < 1 ? 1 : sb;
     hipLaunchKernelGGL(k_scatter, dim3(static_cast<unsigned>(sb)), dim3(kBlock), 0, stream, vals, sel, K, out, d);

@@ -12,8 +12,8 @@ import numpy as np
 import torch
 
 from . import (_stream, uq_aggregate, uq_dequantize, uq_gather, uq_index_quantize, uq_index_quantize_sum, uq_quantize_multi, uq_quantize_packed,
-               uq_quantize_single, uq_quantize_sum, uq_quantize_sum_idx4, uq_randk_select, uq_randk_workspace_bytes,
-               uq_scatter, uq_shared_scale, uq_shared_scale_idx4, uq_sum_codes, uq_sum_dequantize, uq_sum_packed,
+               uq_quantize_single, uq_quantize_sum, uq_quantize_sum_idx4, uq_randk_select, uq_randk_select_zero, uq_randk_workspace_bytes,
+               uq_scatter, uq_scatter_into, uq_shared_scale, uq_shared_scale_idx4, uq_sum_codes, uq_sum_dequantize, uq_sum_packed,
                uq_workspace_bytes)
 
 
@@ -220,10 +220,19 @@ class RandKStep:
     def run(self, g, seed: int, stream=None):
         assert g.dtype == torch.float32 and g.shape[0] == self.M and g.stride(1) == 1
         stream = _stream(stream)  # resolved once for the step's calls
-        self.select(seed, stream)
+        # out is zeroed in the selection's key pass, unless g lies in out's
+        # memory: then only after the gather
+        apart = g.untyped_storage().data_ptr() != self.out.untyped_storage().data_ptr()
+        if apart:
+            uq_randk_select_zero(self.d, self.k, seed, self.sel, self.out, self.rk_ws, self.rk_ws_bytes, stream)
+        else:
+            self.select(seed, stream)
         self.gather(g, stream)
         self.inner.run(self.sub, seed, stream)
-        self.scatter(stream)
+        if apart:
+            uq_scatter_into(self.inner.out, self.sel, self.k, self.out, self.d, stream)
+        else:
+            self.scatter(stream)
         return self.out[:self.d]
 
 

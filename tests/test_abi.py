@@ -383,6 +383,18 @@ def test_randk_select_rejects(kw, want):
 
 
 @pytest.mark.parametrize("kw,want", [
+    (dict(out=None), "inval"), (dict(out=A + 4), "align"), (dict(d=0), "inval"), (dict(K=1001), "range"),
+    (dict(ws=None), "inval"),
+])
+def test_zeroing_select_and_scatter_into_reject(kw, want):
+    args = dict(d=1000, K=10, out=A, ws=A)
+    args.update(kw)
+    assert L.uq_randk_select_zero(args["d"], args["K"], 7, A, args["out"], args["ws"], 1 << 23, None) == E[want]
+    if "ws" not in kw:
+        assert L.uq_scatter_into(A, A, args["K"], args["out"], args["d"], None) == E[want]
+
+
+@pytest.mark.parametrize("kw,want", [
     (dict(g=None), "inval"), (dict(M=0), "inval"), (dict(K=0), "range"), (dict(K=101), "range"),
     (dict(ldg=50), "inval"), (dict(lds=10), "inval"), (dict(lds=30), "align"), (dict(sel=None), "inval"),
     (dict(sub=A + 4), "align"),

@@ -164,3 +164,41 @@ def test_random_selections(d, K, seed, mode):
     finally:
         uq.uq_set_randk_mode(1)
     assert np.array_equal(got, O.randk_select(d, K, seed))
+
+
+@pytest.mark.parametrize("mode", [1, 0, 2], ids=["bracket", "histograms", "bracket-missed"])
+@pytest.mark.parametrize("d,K", [(1, 1), (6, 2), (4096, 100), (4097, 4000), (5 * 4096 + 3, 9000),
+                                 (1024 * 4096 + 1, 1000), (2048 * 4096 - 3, 16_384), (2048 * 4096 + 5, 3000),
+                                 (100_001, 20_000)])
+def test_zeroing_selection_and_scatter_into(d, K, mode):
+    """The key pass that also zeroes the output, at one list, one per 4096
+    coordinates, more than a sort block's threads, and the most; nothing past
+    d is touched."""
+    if mode == 2 and d > 100_000:
+        pytest.skip("the slow fallback, covered at small sizes")
+    uq.uq_set_randk_mode(mode)
+    try:
+        st = RandKStep(d, 1, K, [127.0], device=DEV)
+        out = torch.full((d + 64,), 3.0, device=DEV)
+        vals = torch.arange(1, K + 1, dtype=torch.float32, device=DEV)
+        uq.uq_randk_select_zero(d, K, 31, st.sel, out, st.rk_ws, st.rk_ws_bytes)
+        assert not out[:d].any() and bool((out[d:] == 3.0).all())
+        uq.uq_scatter_into(vals, st.sel, K, out, d)
+        torch.cuda.synchronize()
+    finally:
+        uq.uq_set_randk_mode(1)
+    sel = O.randk_select(d, K, 31)
+    assert np.array_equal(st.sel[:K].cpu().numpy().view(np.uint32), sel)
+    full = np.zeros(d, dtype=np.float32)
+    full[sel.astype(np.int64)] = np.arange(1, K + 1, dtype=np.float32)
+    assert np.array_equal(out[:d].cpu().numpy(), full)
+
+
+def test_gradients_in_the_steps_own_output():
+    d, K = 50_003, 2000
+    host = synth.gaussian_rows(1, d, seed=5, ldg=synth.round_up(d, 64))
+    a, b = RandKStep(d, 1, K, [127.0], device=DEV), RandKStep(d, 1, K, [127.0], device=DEV)
+    a.out[:d].copy_(torch.from_numpy(host[0, :d]))
+    got = a.run(a.out.unsqueeze(0), 4)
+    want = b.run(torch.from_numpy(host).to(DEV), 4)
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))
