@@ -408,14 +408,15 @@ int uq_gather(const float* g, int64_t d, int32_t M, int64_t ldg, const uint32_t*
 int uq_scatter(const float* vals, const uint32_t* sel, int64_t K, float* out, int64_t d, void* stream);
 
 /*
- * The two halves of uq_scatter around the step: uq_randk_select that also
- * zeroes out[0..d) (the key pass is bound by arithmetic, so the stores cost
- * little there), and out[sel[j]] = vals[j] alone (indices >= d skipped, the
- * rest of out untouched).  out must not overlap the gradients that are still
- * to be gathered; 16-byte aligned in both.
+ * The calls around a step with less memory traffic and fewer launches.
+ * uq_randk_select_gather: uq_randk_select and uq_gather, and, unless out is
+ * NULL, out[0..d) = 0 on the way (the key pass is bound by arithmetic, so the
+ * stores cost little there).  out (16-byte aligned) must not overlap g.
+ * uq_scatter_into: out[sel[j]] = vals[j] alone (indices >= d skipped), the
+ * rest of out untouched.
  */
-int uq_randk_select_zero(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, float* out, void* ws, size_t ws_bytes,
-                         void* stream);
+int uq_randk_select_gather(const float* g, int64_t d, int32_t M, int64_t ldg, int64_t K, uint64_t seed, uint32_t* sel,
+                           float* sub, int64_t lds, float* out, void* ws, size_t ws_bytes, void* stream);
 int uq_scatter_into(const float* vals, const uint32_t* sel, int64_t K, float* out, int64_t d, void* stream);
 
 /*

@@ -71,7 +71,7 @@ def _load() -> ctypes.CDLL:
     L.uq_randk_workspace_bytes.argtypes = [i64, i64]
     L.uq_randk_workspace_bytes.restype = sz
     L.uq_randk_select.argtypes = [i64, i64, u64, P, P, sz, P]
-    L.uq_randk_select_zero.argtypes = [i64, i64, u64, P, P, P, sz, P]
+    L.uq_randk_select_gather.argtypes = [P, i64, i32, i64, i64, u64, P, P, i64, P, P, sz, P]
     L.uq_gather.argtypes = [P, i64, i32, i64, P, i64, P, i64, P]
     L.uq_scatter.argtypes = L.uq_scatter_into.argtypes = [P, P, i64, P, i64, P]
     L.uq_set_grid_cap.argtypes = [i64]
@@ -84,7 +84,7 @@ def _load() -> ctypes.CDLL:
                  "uq_quantize_multi", "uq_sum_codes", "uq_dequantize", "uq_sum_dequantize", "uq_quantize_packed",
                  "uq_sum_packed", "uq_quantize_sum", "uq_quantize_sum_idx4",
                  "uq_index_quantize_sum", "uq_index_quantize", "uq_aggregate",
-                 "uq_randk_select", "uq_randk_select_zero", "uq_gather",
+                 "uq_randk_select", "uq_randk_select_gather", "uq_gather",
                  "uq_scatter", "uq_scatter_into", "uq_set_grid_cap", "uq_set_randk_mode"):
         getattr(L, name).restype = ctypes.c_int
     return L
@@ -261,8 +261,9 @@ def uq_scatter(vals, sel, K, out, d, stream=None) -> None:
     _check(lib.uq_scatter(_ptr(vals), _ptr(sel), K, _ptr(out), d, _stream(stream)))
 
 
-def uq_randk_select_zero(d, K, seed, sel, out, ws, ws_bytes, stream=None) -> None:
-    _check(lib.uq_randk_select_zero(d, K, seed, _ptr(sel), _ptr(out), _ptr(ws), ws_bytes, _stream(stream)))
+def uq_randk_select_gather(g, d, M, ldg, K, seed, sel, sub, lds, out, ws, ws_bytes, stream=None) -> None:
+    _check(lib.uq_randk_select_gather(_ptr(g), d, M, ldg, K, seed, _ptr(sel), _ptr(sub), lds, _ptr(out), _ptr(ws),
+                                      ws_bytes, _stream(stream)))
 
 
 def uq_scatter_into(vals, sel, K, out, d, stream=None) -> None:

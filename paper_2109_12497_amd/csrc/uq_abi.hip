@@ -566,7 +566,7 @@ size_t uq_randk_workspace_bytes(int64_t d, int64_t K)
 }
 
 static int randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, float* out, void* ws, size_t ws_bytes,
-                        void* stream)
+                        const float* g, int32_t M, int64_t ldg, float* sub, int64_t lds, void* stream)
 {
     if (d < 1 || d >= (int64_t(1) << 32))
         return fail(UQ_EINVAL, "d = %lld is outside [1, 2^32)", (long long)d);
@@ -580,20 +580,26 @@ static int randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, floa
     if (ws_bytes < uq_randk_workspace_bytes(d, K))
         return fail(UQ_EWORKSPACE, "workspace of %zu bytes is smaller than the %zu needed", ws_bytes,
                     uq_randk_workspace_bytes(d, K));
-    return launched(uq::launch_randk_select(d, K, seed, sel, out, ws, static_cast<hipStream_t>(stream)));
+    return launched(uq::launch_randk_select(d, K, seed, sel, out, ws, g, M, ldg, sub, lds,
+                                            static_cast<hipStream_t>(stream)));
 }
 
 int uq_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, void* ws, size_t ws_bytes, void* stream)
 {
-    return randk_select(d, K, seed, sel, nullptr, ws, ws_bytes, stream);
+    return randk_select(d, K, seed, sel, nullptr, ws, ws_bytes, nullptr, 0, 0, nullptr, 0, stream);
 }
 
-int uq_randk_select_zero(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, float* out, void* ws, size_t ws_bytes,
-                         void* stream)
+int uq_randk_select_gather(const float* g, int64_t d, int32_t M, int64_t ldg, int64_t K, uint64_t seed, uint32_t* sel,
+                           float* sub, int64_t lds, float* out, void* ws, size_t ws_bytes, void* stream)
 {
-    if (d >= 1)
+    UQ_TRY(check_dims(d, M, "M"));
+    if (K < 1 || K > d)
+        return fail(UQ_ERANGE, "K = %lld is outside [1, d]", (long long)K);
+    UQ_TRY(check_rows(g, d, M, ldg, 1, "g"));
+    UQ_TRY(check_rows(sub, K, M, lds, 4, "sub"));
+    if (out != nullptr)
         UQ_TRY(check_vec(out, d, "out"));
-    return randk_select(d, K, seed, sel, out, ws, ws_bytes, stream);
+    return randk_select(d, K, seed, sel, out, ws, ws_bytes, g, M, ldg, sub, lds, stream);
 }
 
 int uq_gather(const float* g, int64_t d, int32_t M, int64_t ldg, const uint32_t* sel, int64_t K, float* sub,

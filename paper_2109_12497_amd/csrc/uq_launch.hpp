@@ -177,9 +177,10 @@ size_t randk_workspace_bytes();
 constexpr int32_t kRandkBracket = 1, kRandkHistogram = 0, kRandkBracketMiss = 2;
 constexpr int32_t kRandkHistogramNoCandidates = 3, kRandkBracketMissNoCandidates = 4;
 bool set_randk_mode(int32_t mode);
-// out (not null): out[0..d) is zeroed in the key pass
+// out (not null): out[0..d) is zeroed in the key pass; g (not null): the
+// selected coordinates of its M rows are gathered into sub
 hipError_t launch_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, float* out, void* ws,
-                               hipStream_t stream);
+                               const float* g, int32_t M, int64_t ldg, float* sub, int64_t lds, hipStream_t stream);
 hipError_t launch_gather(const float* g, int64_t d, int32_t M, int64_t ldg, const uint32_t* sel, int64_t K,
                          float* sub, int64_t lds, hipStream_t stream);
 hipError_t launch_scatter(const float* vals, const uint32_t* sel, int64_t K, float* out, int64_t d, bool zero,

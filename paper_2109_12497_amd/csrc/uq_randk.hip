@@ -65,6 +65,12 @@ struct RandkControl {
 };
 
 constexpr int kRkMaxBlocks = 2048;  // ordered-compaction blocks
+// The bracket's key pass: 1024-thread blocks, two per compute unit, each with
+// a list of its own.  With 2048 256-thread blocks the sort blocks read 2048
+// lists of about five entries, mostly a cache line each, and took 19.6 us.
+constexpr int kRkKeyThreads = 1024;
+constexpr int kRkLists = 512;
+constexpr int kRkKeyUnroll = 2;
 
 // Device-scope atomics execute at the memory side and serialise per cache
 // line, so counters that many waves hit live on lines of their own and the
@@ -74,14 +80,14 @@ struct RandkWorkspace {
     uint32_t hist2[kRkBins2];
     RandkControl ctl;
     uint32_t cand[kRandkCandidates][3];  // (hi, lo, index)
-    uint32_t block_count[kRkMaxBlocks];   // the bracket's pass: keys below the interval, per block
-    uint32_t block_offset[kRkMaxBlocks];  // the bracket's pass: keys inside it, per block
+    uint32_t block_count[kRkMaxBlocks];   // the bracket's pass: keys below the interval, per list
+    uint32_t block_offset[kRkMaxBlocks];  // the bracket's pass: keys inside it, per list
     uint32_t n_stage[kRkShards][kRkLine];     // staging list lengths (element 0 of each line)
     // Unordered selections (K <= kRkSortMax).  The histogram route has
     // kRkShards lists here; the bracket's pass an equal share of the first
     // half per block for its indices, and of the second for its candidates
-    // (hi, lo, index): at 2048 blocks, 256 indices and 85 candidates where at
-    // most 8 and 2 are expected.
+    // (hi, lo, index): at 512 blocks, 1024 indices and 341 candidates where at
+    // most 32 and 8 are expected.
     uint32_t stage[kRkShards * kRkSortMax];
 };
 static_assert(offsetof(RandkWorkspace, stage) % 16 == 0, "16-byte loads of the lists");
@@ -356,7 +362,7 @@ __global__ __launch_bounds__(kBlock) void k_rk_collect(int64_t d, uint32_t key0,
 // whatever fits, so that the sort sees an overflow.  Bound by the Philox
 // arithmetic, so out (not null) is zeroed in it: its stores take the memory
 // the pass leaves idle.
-__global__ __launch_bounds__(kBlock) void k_rk_bracket(int64_t d, uint32_t key0, uint32_t key1, uint32_t x_lo,
+__global__ __launch_bounds__(kRkKeyThreads) void k_rk_bracket(int64_t d, uint32_t key0, uint32_t key1, uint32_t x_lo,
                                                        uint32_t x_hi, RandkWorkspace* __restrict__ ws,
                                                        uint32_t pick_cap, uint32_t cand_cap, float* __restrict__ out)
 {
@@ -369,24 +375,24 @@ __global__ __launch_bounds__(kBlock) void k_rk_bracket(int64_t d, uint32_t key0,
     uint32_t* list = ws->stage + blockIdx.x * pick_cap;
     uint32_t* cand = ws->stage + kRkStageHalf + blockIdx.x * cand_cap * 3u;
     const int64_t nq = (d + 3) >> 2;
-    const int64_t step = static_cast<int64_t>(gridDim.x) * kBlock * kRkUnroll;
-    for (int64_t q0 = static_cast<int64_t>(blockIdx.x) * kBlock * kRkUnroll + threadIdx.x; q0 < nq; q0 += step) {
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kRkKeyThreads * kRkKeyUnroll;
+    for (int64_t q0 = static_cast<int64_t>(blockIdx.x) * kRkKeyThreads * kRkKeyUnroll + threadIdx.x; q0 < nq; q0 += step) {
         if (out != nullptr) {
 #pragma unroll
-            for (int u = 0; u < kRkUnroll; ++u)
-                zero_group(out, q0 + static_cast<int64_t>(u) * kBlock, d);
+            for (int u = 0; u < kRkKeyUnroll; ++u)
+                zero_group(out, q0 + static_cast<int64_t>(u) * kRkKeyThreads, d);
         }
         // groups past nq are formed too (no branch between the blocks) and
         // fall to the test against d
-        uint4 w[kRkUnroll];
+        uint4 w[kRkKeyUnroll];
 #pragma unroll
-        for (int u = 0; u < kRkUnroll; ++u)
-            w[u] = selection_block(static_cast<uint32_t>(q0 + static_cast<int64_t>(u) * kBlock), 2u, key0, key1);
+        for (int u = 0; u < kRkKeyUnroll; ++u)
+            w[u] = selection_block(static_cast<uint32_t>(q0 + static_cast<int64_t>(u) * kRkKeyThreads), 2u, key0, key1);
 #pragma unroll
-        for (int u = 0; u < kRkUnroll; ++u) {
+        for (int u = 0; u < kRkKeyUnroll; ++u) {
             if (min(min(w[u].x, w[u].y), min(w[u].z, w[u].w)) > x_hi)
                 continue;
-            const int64_t q = q0 + static_cast<int64_t>(u) * kBlock;
+            const int64_t q = q0 + static_cast<int64_t>(u) * kRkKeyThreads;
             bool any = false;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -625,12 +631,32 @@ constexpr int kRkSlices = 64;
 constexpr int kRkSliceBuckets = kRkBuckets / kRkSlices;
 static_assert(kRkSliceBuckets == 64, "one wave scans a slice's buckets");
 
+// Where the selected coordinates' values go as they are found:
+// sub[m][j] = g[m][sel[j]] (g null: nowhere).
+struct GatherTo {
+    const float* g;
+    int64_t ldg;
+    float* sub;
+    int64_t lds;
+    int32_t M;
+};
+
+// sel[pos] = i, and its values (0 for the sentinel index).
+__device__ __forceinline__ void put_selected(uint32_t* __restrict__ sel, uint32_t pos, uint32_t i, int64_t d,
+                                             const GatherTo& to)
+{
+    sel[pos] = i;
+    if (to.g != nullptr)
+        for (int32_t m = 0; m < to.M; ++m)
+            to.sub[m * to.lds + pos] = i < d ? to.g[m * to.ldg + i] : 0.0f;
+}
+
 // The selections of one block's slice of the output, in index order, given
 // the threshold (th, tl, ti): one pass in index order that counts the
 // selections of earlier slices (the slice's offset) and writes the slice's
 // own at their places.
 __device__ void write_slice_in_order(int64_t d, uint32_t K, uint32_t key0, uint32_t key1, uint32_t* __restrict__ sel,
-                                     uint32_t th, uint32_t tl, uint32_t ti, uint32_t* scratch)
+                                     uint32_t th, uint32_t tl, uint32_t ti, uint32_t* scratch, const GatherTo& to)
 {
     constexpr int T = kRkSortThreads;
     const int64_t nq = (d + 3) >> 2;
@@ -665,7 +691,7 @@ __device__ void write_slice_in_order(int64_t d, uint32_t K, uint32_t key0, uint3
         for (int j = 0; j < 4; ++j)
             if ((mm >> j) & 1u) {
                 if (pos < K)
-                    sel[pos] = static_cast<uint32_t>((q << 2) + j);
+                    put_selected(sel, pos, static_cast<uint32_t>((q << 2) + j), d, to);
                 ++pos;
             }
         if (t == T - 1)
@@ -684,7 +710,8 @@ __device__ void write_slice_in_order(int64_t d, uint32_t K, uint32_t key0, uint3
 // candidates (about d / 2^20 are expected, at most 4096 on average for
 // d < 2^32).  Should refine_threshold fail, every output entry is 0xFFFFFFFF.
 __device__ void sort_exact_slice(int64_t d, uint32_t K, uint32_t key0, uint32_t key1, uint32_t* __restrict__ sel,
-                                 uint32_t* h, uint32_t (*cand)[3], uint32_t* scratch, uint32_t* found, uint32_t cap)
+                                 uint32_t* h, uint32_t (*cand)[3], uint32_t* scratch, uint32_t* found, uint32_t cap,
+                                 const GatherTo& to)
 {
     constexpr int T = kRkSortThreads;
     constexpr uint32_t kCap = kRkSortMax / 3;
@@ -767,12 +794,12 @@ __device__ void sort_exact_slice(int64_t d, uint32_t K, uint32_t key0, uint32_t 
     } else if (!refine_threshold<T>(d, key0, key1, prefix, need2, h, cand, kRkRefineCap, scratch, found, &thr[0],
                                     &thr[1], &thr[2])) {
         for (uint32_t j = t; j < K; j += T)
-            sel[j] = 0xFFFFFFFFu;
+            put_selected(sel, j, 0xFFFFFFFFu, d, to);
         return;
     }
     const uint32_t th = thr[0], tl = thr[1], ti = thr[2];
     __syncthreads();
-    write_slice_in_order(d, K, key0, key1, sel, th, tl, ti, scratch);
+    write_slice_in_order(d, K, key0, key1, sel, th, tl, ti, scratch, to);
 }
 
 // The staged indices (and, with BRACKET, the picks this block makes among
@@ -791,12 +818,12 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
                                                             uint32_t* __restrict__ sel, uint32_t K, int64_t d,
                                                             uint32_t key0, uint32_t key1, uint32_t nlists,
                                                             uint32_t log_tps, uint32_t cap, uint32_t ccap,
-                                                            uint32_t x_lo, uint32_t x_hi, uint32_t exact_cap)
+                                                            uint32_t x_lo, uint32_t x_hi, uint32_t exact_cap,
+                                                            GatherTo to)
 {
     constexpr uint32_t kMine = BRACKET ? 3u * kRkPickMax : kRkSortMax;
     __shared__ uint32_t buf[kRkSortMax];
     __shared__ uint32_t mine[kMine];  // the slice's indices; before them the bracket's candidates
-    __shared__ uint32_t n_list[kRkMaxBlocks];
     __shared__ uint32_t count[kRkSliceBuckets];
     __shared__ uint32_t start[kRkSliceBuckets];
     __shared__ uint32_t wave_below[kRkSortThreads / 64];
@@ -805,12 +832,12 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
     const uint32_t slice = blockIdx.x;
     const int lane = t & 63, wave = t >> 6;
     const uint32_t tps = 1u << log_tps, sub = t & (tps - 1u);
-    const uint32_t list0 = t >> log_tps, dlist = static_cast<uint32_t>(kRkSortThreads) >> log_tps;
+    const uint32_t my_list = t >> log_tps;  // a thread reads one list: nlists * tps <= kRkSortThreads
     const double scale = static_cast<double>(kRkBuckets) / static_cast<double>(d);
 
     // BRACKET: this block's picks among the candidates, in h[0 .. n_pick)
     __shared__ uint32_t h[BRACKET ? kRkBins2 : 1];
-    __shared__ uint32_t n_clist[BRACKET ? kRkMaxBlocks : 1];
+    __shared__ uint32_t n_list[kRkLists], n_clist[kRkLists];
     __shared__ uint32_t cross[BRACKET ? kRkCross : 1][3];
     __shared__ uint32_t scratch[kRkSortThreads / 64 + 4];
     __shared__ uint32_t found[2];
@@ -825,50 +852,52 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
     }
     if (t < kRkSliceBuckets)
         count[t] = 0u;
+    // the thread's first two quads of its list, loaded before the picks are made
+    uint32_t n = 0u;
+    const uint32_t* list = ws->stage + my_list * cap;
+    uint4 first[2] = {};
+    const auto load_first = [&] {
+#pragma unroll
+        for (uint32_t i = 0; i < 2u; ++i)
+            if (4u * (sub + i * tps) < n)
+                first[i] = *reinterpret_cast<const uint4*>(list + 4u * (sub + i * tps));
+    };
     uint32_t npick = 0u;
     if (BRACKET) {
         uint32_t (*cl)[3] = reinterpret_cast<uint32_t(*)[3]>(mine);
         const uint64_t width = static_cast<uint64_t>(x_hi - x_lo) + 1u;
-        uint32_t np[kRkMaxBlocks / kRkSortThreads], nc[kRkMaxBlocks / kRkSortThreads];
-#pragma unroll
-        for (int i = 0; i < kRkMaxBlocks / kRkSortThreads; ++i) {
-            const uint32_t s = t + i * kRkSortThreads;
-            np[i] = s < nlists ? ws->block_count[s] : 0u;
-            nc[i] = s < nlists ? ws->block_offset[s] : 0u;
-        }
+        const uint32_t np = t < nlists ? ws->block_count[t] : 0u, nc = t < nlists ? ws->block_offset[t] : 0u;
         for (int b = t; b < kRkPickBuckets; b += kRkSortThreads)
             h[b] = 0u;
-        uint32_t below = 0u;
-        bool over = false;
-#pragma unroll
-        for (int i = 0; i < kRkMaxBlocks / kRkSortThreads; ++i) {
-            n_list[t + i * kRkSortThreads] = min(np[i], cap);
-            n_clist[t + i * kRkSortThreads] = min(nc[i], ccap);
-            below += np[i];
-            over = over || np[i] > cap || nc[i] > ccap;
+        if (t < nlists) {
+            n_list[t] = min(np, cap);
+            n_clist[t] = min(nc, ccap);
         }
+        uint32_t below = np;
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1)
             below += __shfl_xor(below, off, 64);
         __syncthreads();
         if (lane == 0)
             atomicAdd(&staged_all, below);
-        if (over)
+        if (np > cap || nc > ccap)
             atomicOr(&overflow, 1u);
-        for (uint32_t s = list0; s < nlists; s += dlist) {
-            const uint32_t n = n_clist[s];
-            if (n <= sub)
-                continue;
-            const uint32_t* src = ws->stage + kRkStageHalf + s * ccap * 3u;
-            uint32_t slot = atomicAdd(&n_cl, (n - sub + tps - 1u) >> log_tps);
-            for (uint32_t j = sub; j < n; j += tps, ++slot)
-                if (slot < static_cast<uint32_t>(kRkPickMax)) {
-                    const uint32_t hh = src[3u * j];
-                    cl[slot][0] = hh;
-                    cl[slot][1] = src[3u * j + 1u];
-                    cl[slot][2] = src[3u * j + 2u];
-                    atomicAdd(&h[pick_bucket(hh, x_lo, width)], 1u);
-                }
+        if (my_list < nlists) {
+            n = n_list[my_list];
+            load_first();
+            const uint32_t n_c = n_clist[my_list];
+            const uint32_t* src = ws->stage + kRkStageHalf + my_list * ccap * 3u;
+            if (n_c > sub) {
+                uint32_t slot = atomicAdd(&n_cl, (n_c - sub + tps - 1u) >> log_tps);
+                for (uint32_t j = sub; j < n_c; j += tps, ++slot)
+                    if (slot < static_cast<uint32_t>(kRkPickMax)) {
+                        const uint32_t hh = src[3u * j], ll = src[3u * j + 1u], ii = src[3u * j + 2u];
+                        cl[slot][0] = hh;
+                        cl[slot][1] = ll;
+                        cl[slot][2] = ii;
+                        atomicAdd(&h[pick_bucket(hh, x_lo, width)], 1u);
+                    }
+            }
         }
         __syncthreads();
         const uint32_t staged = staged_all, n_c = n_cl;
@@ -893,7 +922,7 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
         }
         if (!valid) {
             sort_exact_slice(d, K, key0, key1, sel, h, reinterpret_cast<uint32_t(*)[3]>(buf), scratch, found,
-                             exact_cap);
+                             exact_cap, to);
             return;
         }
         // the picks, into h (the parts' counts are no longer needed)
@@ -922,11 +951,14 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
             // selected candidates were not staged, so the slice is written
             // from the keys themselves
             if (ws->ctl.exact == 1u)
-                write_slice_in_order(d, K, key0, key1, sel, ws->ctl.thr_hi, ws->ctl.thr_lo, ws->ctl.thr_idx, scratch);
+                write_slice_in_order(d, K, key0, key1, sel, ws->ctl.thr_hi, ws->ctl.thr_lo, ws->ctl.thr_idx, scratch,
+                                     to);
             return;
         }
-        if (t < kRkShards)
-            n_list[t] = min(ws->n_stage[t][0], cap);
+        if (my_list < nlists) {
+            n = min(ws->n_stage[my_list][0], cap);
+            load_first();
+        }
         __syncthreads();
     }
 
@@ -943,18 +975,17 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
                 mine[pos] = v;
         }
     };
-    for (uint32_t s = list0; s < nlists; s += dlist) {
-        const uint32_t* list = ws->stage + s * cap;
-        const uint32_t n = n_list[s];
-#pragma unroll 2
-        for (uint32_t p = 4u * sub; p < n; p += 4u * tps) {
-            const uint4 v = *reinterpret_cast<const uint4*>(list + p);
+    const auto place_quad = [&](uint32_t p, const uint4& v) {
 #pragma unroll
-            for (uint32_t j = 0; j < 4u; ++j)
-                if (p + j < n)
-                    place(word_of(v, static_cast<int>(j)));
-        }
-    }
+        for (uint32_t j = 0; j < 4u; ++j)
+            if (p + j < n)
+                place(word_of(v, static_cast<int>(j)));
+    };
+    place_quad(4u * sub, first[0]);
+    place_quad(4u * (sub + tps), first[1]);
+#pragma unroll 2
+    for (uint32_t p = 4u * (sub + 2u * tps); p < n; p += 4u * tps)
+        place_quad(p, *reinterpret_cast<const uint4*>(list + p));
     for (uint32_t p = t; p < npick; p += kRkSortThreads)
         place(h[p]);
     // indices in earlier slices: the block's output offset
@@ -964,9 +995,9 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
     if (lane == 0)
         wave_below[wave] = below;
     __syncthreads();
-    const uint32_t n = BRACKET ? n_mine : min(n_mine, kMine);
-    if (BRACKET && n > kMine) {  // block-uniform; not reached by random keys (K / 64 expected)
-        sort_exact_slice(d, K, key0, key1, sel, h, reinterpret_cast<uint32_t(*)[3]>(buf), scratch, found, exact_cap);
+    const uint32_t n_own = BRACKET ? n_mine : min(n_mine, kMine);
+    if (BRACKET && n_own > kMine) {  // block-uniform; not reached by random keys (K / 64 expected)
+        sort_exact_slice(d, K, key0, key1, sel, h, reinterpret_cast<uint32_t(*)[3]>(buf), scratch, found, exact_cap, to);
         return;
     }
     uint32_t offset = 0u;
@@ -987,7 +1018,7 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
         count[lane] = 0u;  // reused as the bucket's fill cursor
     }
     __syncthreads();
-    for (uint32_t p = t; p < n; p += kRkSortThreads) {
+    for (uint32_t p = t; p < n_own; p += kRkSortThreads) {
         const uint32_t v = mine[p];
         const uint32_t lb = bucket_of(v, scale) % kRkSliceBuckets;
         const uint32_t pos = start[lb] + atomicAdd(&count[lb], 1u);
@@ -995,9 +1026,9 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
             buf[pos] = v;
     }
     __syncthreads();
-    // each of the slice's indices goes to the offset plus its bucket's start
-    // plus the number of smaller indices in its bucket
-    for (uint32_t e = t; e < n; e += kRkSortThreads) {
+    // each of the slice's indices goes to its bucket's start plus the number
+    // of smaller indices in its bucket
+    for (uint32_t e = t; e < n_own; e += kRkSortThreads) {
         const uint32_t v = buf[e];
         const uint32_t lb = bucket_of(v, scale) % kRkSliceBuckets;
         const uint32_t s0 = start[lb];
@@ -1005,11 +1036,23 @@ __global__ __launch_bounds__(kRkSortThreads) void k_rk_sort(const RandkWorkspace
         uint32_t rank = 0u;
         for (uint32_t a = 0; a < m; ++a)
             rank += buf[s0 + a] < v ? 1u : 0u;
-        const uint32_t pos = offset + s0 + rank;
-        if (pos < K)
-            sel[pos] = v;
+        // in order into the memory of the unordered ones, no longer needed
+        if (s0 + rank < kMine)
+            mine[s0 + rank] = v;
     }
+    __syncthreads();
+    const uint32_t n_out = offset < K ? min(n_own, K - offset) : 0u;
+    for (uint32_t e = t; e < n_out; e += kRkSortThreads)
+        sel[offset + e] = mine[e];
+    // their values here, not in a launch of their own: one load in flight per
+    // thread, K / 64 of them per row
+    if (to.g != nullptr)
+        for (uint32_t p = t; p < n_out * static_cast<uint32_t>(to.M); p += kRkSortThreads) {
+            const uint32_t m = p / n_out, e = p % n_out;
+            to.sub[m * to.lds + offset + e] = to.g[m * to.ldg + mine[e]];
+        }
 }
+
 
 
 // K > kRkSortMax: block b owns coordinates [b * chunk, (b + 1) * chunk); one
@@ -1143,12 +1186,12 @@ size_t randk_workspace_bytes()
 }
 
 // Persistent grid for the key passes: kBlock * kRkUnroll key groups per block
-// and iteration, at most eight blocks per compute unit and one list each.
+// and iteration, at most eight blocks per compute unit.
 static unsigned key_grid(int64_t d)
 {
     const int64_t groups = (d + 3) >> 2;
     int64_t blocks = (groups + kBlock * kRkUnroll - 1) / (kBlock * kRkUnroll);
-    const int64_t cap = grid_cap() / 8 < kRkMaxBlocks ? grid_cap() / 8 : kRkMaxBlocks;
+    const int64_t cap = grid_cap() / 8;
     blocks = blocks < 1 ? 1 : (blocks > cap ? cap : blocks);
     return static_cast<unsigned>(blocks);
 }
@@ -1187,12 +1230,13 @@ static bool randk_bracket(int64_t d, int64_t K, uint32_t* x_lo, uint32_t* x_hi)
 }
 
 hipError_t launch_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* sel, float* out, void* ws_raw,
-                               hipStream_t stream)
+                               const float* g, int32_t M, int64_t ldg, float* sub, int64_t lds, hipStream_t stream)
 {
+    const GatherTo none{nullptr, 0, nullptr, 0, 0};
     RandkWorkspace* ws = static_cast<RandkWorkspace*>(ws_raw);
     const uint32_t key0 = static_cast<uint32_t>(seed);
     const uint32_t key1 = static_cast<uint32_t>(seed >> 32);
-    const unsigned gx = key_grid(d);  // persistent grid for the key passes
+    const unsigned gx = key_grid(d);  // persistent grid for the histogram route's key passes
     const int32_t mode = g_randk_mode.load(std::memory_order_relaxed);
     // the test modes keep no candidates, so that the exact refinement runs
     const uint32_t cand_cap = (mode == kRandkHistogramNoCandidates || mode == kRandkBracketMissNoCandidates)
@@ -1203,15 +1247,18 @@ hipError_t launch_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* se
     if (K <= kRkSortMax && !histogram && randk_bracket(d, K, &x_lo, &x_hi)) {
         if (mode == kRandkBracketMiss || mode == kRandkBracketMissNoCandidates)
             x_lo = x_hi = 0u;  // an interval that cannot hold the K-th key: the exact fallback runs
-        const uint32_t pick_cap = kRkStageHalf / gx & ~3u, key_cap = kRkStageHalf / 3u / gx;
+        const int64_t blocks = (((d + 3) >> 2) + kRkKeyThreads - 1) / kRkKeyThreads;
+        const int64_t most = grid_cap() / 32 < kRkLists ? grid_cap() / 32 : kRkLists;
+        const unsigned nl = static_cast<unsigned>(blocks < most ? blocks : most);
+        const uint32_t pick_cap = kRkStageHalf / nl & ~3u, key_cap = kRkStageHalf / 3u / nl;
         uint32_t log_tps = 0u;  // threads per list in the sort
-        while ((gx << (log_tps + 1u)) <= static_cast<unsigned>(kRkSortThreads))
+        while ((nl << (log_tps + 1u)) <= static_cast<unsigned>(kRkSortThreads))
             ++log_tps;
-        hipLaunchKernelGGL(k_rk_bracket, dim3(gx), dim3(kBlock), 0, stream, d, key0, key1, x_lo, x_hi, ws, pick_cap,
+        hipLaunchKernelGGL(k_rk_bracket, dim3(nl), dim3(kRkKeyThreads), 0, stream, d, key0, key1, x_lo, x_hi, ws, pick_cap,
                            key_cap, out);
         hipLaunchKernelGGL((k_rk_sort<true>), dim3(kRkSlices), dim3(kRkSortThreads), 0, stream, ws, sel,
-                           static_cast<uint32_t>(K), d, key0, key1, gx, log_tps, pick_cap, key_cap, x_lo, x_hi,
-                           cand_cap);
+                           static_cast<uint32_t>(K), d, key0, key1, nl, log_tps, pick_cap, key_cap, x_lo, x_hi,
+                           cand_cap, GatherTo{g, ldg, sub, lds, M});
         return hipGetLastError();
     }
     hipLaunchKernelGGL(k_rk_init, dim3(1), dim3(kBlock), 0, stream, ws, cand_cap);
@@ -1232,8 +1279,8 @@ hipError_t launch_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* se
                            static_cast<uint32_t>(K), d, key0, key1, sel);
         hipLaunchKernelGGL((k_rk_sort<false>), dim3(kRkSlices), dim3(kRkSortThreads), 0, stream, ws, sel,
                            static_cast<uint32_t>(K), d, key0, key1, static_cast<uint32_t>(kRkShards), 4u,
-                           static_cast<uint32_t>(kRkSortMax), 0u, 0u, 0u, 0u);
-        return hipGetLastError();
+                           static_cast<uint32_t>(kRkSortMax), 0u, 0u, 0u, 0u, none);
+        return g != nullptr ? launch_gather(g, d, M, ldg, sel, K, sub, lds, stream) : hipGetLastError();
     }
     hipLaunchKernelGGL(k_rk_collect<false>, dim3(gx), dim3(kBlock), 0, stream, d, key0, key1, ws,
                        static_cast<uint32_t>(K), out);
@@ -1248,7 +1295,7 @@ hipError_t launch_randk_select(int64_t d, int64_t K, uint64_t seed, uint32_t* se
     hipLaunchKernelGGL(k_rk_offsets, dim3(1), dim3(kBlock), 0, stream, ws, nblocks);
     hipLaunchKernelGGL(k_rk_write, dim3(nblocks), dim3(kBlock), 0, stream, d, chunk, key0, key1, ws, sel,
                        static_cast<uint32_t>(K));
-    return hipGetLastError();
+    return g != nullptr ? launch_gather(g, d, M, ldg, sel, K, sub, lds, stream) : hipGetLastError();
 }
 
 hipError_t launch_gather(const float* g, int64_t d, int32_t M, int64_t ldg, const uint32_t* sel, int64_t K,

@@ -12,7 +12,7 @@ import numpy as np
 import torch
 
 from . import (_stream, uq_aggregate, uq_dequantize, uq_gather, uq_index_quantize, uq_index_quantize_sum, uq_quantize_multi, uq_quantize_packed,
-               uq_quantize_single, uq_quantize_sum, uq_quantize_sum_idx4, uq_randk_select, uq_randk_select_zero, uq_randk_workspace_bytes,
+               uq_quantize_single, uq_quantize_sum, uq_quantize_sum_idx4, uq_randk_select, uq_randk_select_gather, uq_randk_workspace_bytes,
                uq_scatter, uq_scatter_into, uq_shared_scale, uq_shared_scale_idx4, uq_sum_codes, uq_sum_dequantize, uq_sum_packed,
                uq_workspace_bytes)
 
@@ -223,11 +223,8 @@ class RandKStep:
         # out is zeroed in the selection's key pass, unless g lies in out's
         # memory: then only after the gather
         apart = g.untyped_storage().data_ptr() != self.out.untyped_storage().data_ptr()
-        if apart:
-            uq_randk_select_zero(self.d, self.k, seed, self.sel, self.out, self.rk_ws, self.rk_ws_bytes, stream)
-        else:
-            self.select(seed, stream)
-        self.gather(g, stream)
+        uq_randk_select_gather(g, self.d, self.M, g.stride(0), self.k, seed, self.sel, self.sub, self.sub.stride(0),
+                               self.out if apart else None, self.rk_ws, self.rk_ws_bytes, stream)
         self.inner.run(self.sub, seed, stream)
         if apart:
             uq_scatter_into(self.inner.out, self.sel, self.k, self.out, self.d, stream)

@@ -383,15 +383,26 @@ def test_randk_select_rejects(kw, want):
 
 
 @pytest.mark.parametrize("kw,want", [
-    (dict(out=None), "inval"), (dict(out=A + 4), "align"), (dict(d=0), "inval"), (dict(K=1001), "range"),
-    (dict(ws=None), "inval"),
+    (dict(out=A + 4), "align"), (dict(d=-1), "inval"), (dict(K=1001), "range"), (dict(K=0), "range"),
+    (dict(ws=None), "inval"), (dict(ws=A + 8), "align"), (dict(g=None), "inval"), (dict(M=0), "inval"),
+    (dict(ldg=50), "inval"), (dict(lds=8), "inval"), (dict(lds=14), "align"), (dict(sub=A + 4), "align"),
+    (dict(sel=None), "inval"), (dict(ws_bytes=64), "ws"),
 ])
-def test_zeroing_select_and_scatter_into_reject(kw, want):
-    args = dict(d=1000, K=10, out=A, ws=A)
+def test_select_gather_rejects(kw, want):
+    a = dict(g=A, d=1000, M=2, ldg=1024, K=10, sel=A, sub=A, lds=16, out=A, ws=A, ws_bytes=1 << 23)
+    a.update(kw)
+    assert L.uq_randk_select_gather(a["g"], a["d"], a["M"], a["ldg"], a["K"], 7, a["sel"], a["sub"], a["lds"],
+                                    a["out"], a["ws"], a["ws_bytes"], None) == E[want]
+
+
+@pytest.mark.parametrize("kw,want", [
+    (dict(vals=None), "inval"), (dict(sel=None), "inval"), (dict(out=None), "inval"), (dict(K=0), "range"),
+    (dict(K=101), "range"), (dict(d=0), "inval"), (dict(out=A + 4), "align"),
+])
+def test_scatter_into_rejects(kw, want):
+    args = dict(vals=A, sel=A, K=20, out=A, d=100)
     args.update(kw)
-    assert L.uq_randk_select_zero(args["d"], args["K"], 7, A, args["out"], args["ws"], 1 << 23, None) == E[want]
-    if "ws" not in kw:
-        assert L.uq_scatter_into(A, A, args["K"], args["out"], args["d"], None) == E[want]
+    assert L.uq_scatter_into(args["vals"], args["sel"], args["K"], args["out"], args["d"], None) == E[want]
 
 
 @pytest.mark.parametrize("kw,want", [

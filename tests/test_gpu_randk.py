@@ -167,30 +167,41 @@ def test_random_selections(d, K, seed, mode):
 
 
 @pytest.mark.parametrize("mode", [1, 0, 2], ids=["bracket", "histograms", "bracket-missed"])
-@pytest.mark.parametrize("d,K", [(1, 1), (6, 2), (4096, 100), (4097, 4000), (5 * 4096 + 3, 9000),
-                                 (1024 * 4096 + 1, 1000), (2048 * 4096 - 3, 16_384), (2048 * 4096 + 5, 3000),
-                                 (100_001, 20_000)])
-def test_zeroing_selection_and_scatter_into(d, K, mode):
-    """The key pass that also zeroes the output, at one list, one per 4096
-    coordinates, more than a sort block's threads, and the most; nothing past
-    d is touched."""
+@pytest.mark.parametrize("d,K,M", [(1, 1, 1), (6, 2, 3), (4096, 100, 2), (4097, 4000, 5), (16_384, 16_384, 1),
+                                   (20_483, 9000, 4), (512 * 4096 - 3, 16_384, 2), (512 * 4096 + 1, 1000, 3),
+                                   (2048 * 4096 + 5, 3000, 2), (100_001, 20_000, 2), (70_000, 10_000, 17)])
+def test_select_gather_and_scatter_into(d, K, M, mode):
+    """Selection, gather and the output's zeroing in one call, from one list
+    of the key pass to the most and past one iteration of each; nothing past
+    d or K is touched."""
     if mode == 2 and d > 100_000:
         pytest.skip("the slow fallback, covered at small sizes")
+    host = synth.gaussian_rows(M, d, seed=d, ldg=synth.round_up(d, 64))
+    g = torch.from_numpy(host).to(DEV)
+    st = RandKStep(d, M, K, [127.0], device=DEV)
+    out = torch.full((d + 64,), 3.0, device=DEV)
+    sub = torch.full_like(st.sub, 5.0)
+    vals = torch.arange(1, K + 1, dtype=torch.float32, device=DEV)
     uq.uq_set_randk_mode(mode)
     try:
-        st = RandKStep(d, 1, K, [127.0], device=DEV)
-        out = torch.full((d + 64,), 3.0, device=DEV)
-        vals = torch.arange(1, K + 1, dtype=torch.float32, device=DEV)
-        uq.uq_randk_select_zero(d, K, 31, st.sel, out, st.rk_ws, st.rk_ws_bytes)
+        uq.uq_randk_select_gather(g, d, M, g.stride(0), K, 31, st.sel, sub, sub.stride(0), out, st.rk_ws,
+                                  st.rk_ws_bytes)
         assert not out[:d].any() and bool((out[d:] == 3.0).all())
+        out.fill_(2.0)
+        uq.uq_randk_select_gather(g, d, M, g.stride(0), K, 31, st.sel, sub, sub.stride(0), None, st.rk_ws,
+                                  st.rk_ws_bytes)
+        assert bool((out == 2.0).all())
         uq.uq_scatter_into(vals, st.sel, K, out, d)
         torch.cuda.synchronize()
     finally:
         uq.uq_set_randk_mode(1)
     sel = O.randk_select(d, K, 31)
     assert np.array_equal(st.sel[:K].cpu().numpy().view(np.uint32), sel)
-    full = np.zeros(d, dtype=np.float32)
-    full[sel.astype(np.int64)] = np.arange(1, K + 1, dtype=np.float32)
+    at = sel.astype(np.int64)
+    assert np.array_equal(sub[:, :K].cpu().numpy().view(np.int32), host[:, at].view(np.int32))
+    assert bool((sub[:, K:] == 5.0).all())
+    full = np.full(d, 2.0, dtype=np.float32)
+    full[at] = np.arange(1, K + 1, dtype=np.float32)
     assert np.array_equal(out[:d].cpu().numpy(), full)
 
 
