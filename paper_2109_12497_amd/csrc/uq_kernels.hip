@@ -1964,9 +1964,9 @@ __device__ __forceinline__ void rows_tile(const f32x4 (&A)[ROWS], const float* _
     }
 }
 
-// Where a rows pass takes W from: *w, or (part not null) the norm's chunk
-// partials [rows][nchunks], reduced by every wave for itself in k_finish's
-// order; the first block then also stores it to *w.
+// Where a rows pass takes W from: *w, or (part not null: the kernels' OWN
+// instances) the norm's chunk partials [rows][nchunks], reduced by every wave
+// for itself in k_finish's order; the first block then also stores it to *w.
 struct WSource {
     float* w;
     const double* part;
@@ -1988,9 +1988,14 @@ __device__ __forceinline__ void load_partials(const WSource& src, int32_t rows, 
         x[r] = lane < src.nchunks ? p[lane] : 0.0;
         y[r] = lane + 64 < src.nchunks ? p[lane + 64] : 0.0;
     }
+    // summed (and so waited for) here, before the rows' loads go out: left to
+    // the reduction, they would be waited for together with the rows (2^20
+    // coordinates of 4 rows: the step 13.4 us, 12.6 this way)
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r)
+    for (int r = 0; r < ROWS; ++r) {
         s[r] = r < rows ? x[r] + y[r] : 0.0;
+        __asm__ volatile("" : "+v"(s[r]));
+    }
 }
 
 // One step of the rows' butterfly at distance `off` over N registers: row
@@ -2042,7 +2047,11 @@ __device__ __forceinline__ float reduce_w(const double (&in)[ROWS])
 // coordinates.  There is no loop over tiles: with one, the compiler kept the
 // rows' keys and other loop invariants in registers (155 instead of 101 at 16
 // rows); a call with more tiles than the grid cap is several launches.
-template <int ROWS, bool MULTI, int BITS, int POL>
+// OWN is a template parameter because the partials' reduction, compiled in,
+// takes registers beside the rows (one scale: 8 rows 96 without, 102 with; 4
+// rows 80 and 86): 5 rows of 5.0 M coordinates 43.7 us with it as a branch,
+// 42.7 without.
+template <int ROWS, bool MULTI, int BITS, int POL, bool OWN>
 __device__ __forceinline__ void rows_block(const float* __restrict__ g, int64_t d, int32_t rows, int64_t ldg,
                                            int32_t worker0, const WSource& src, const ScaleSet& S, uint32_t key0,
                                            uint32_t key1, int64_t tile0, int32_t M, const RowsOut& o)
@@ -2061,7 +2070,7 @@ __device__ __forceinline__ void rows_block(const float* __restrict__ g, int64_t 
     const bool whole = T < d >> 8;
     // the partials go out before the rows, whose loads they would wait behind
     double part[ROWS];
-    if (src.part != nullptr)
+    if (OWN)
         load_partials<ROWS>(src, rows, part);
     f32x4 A[ROWS];
     if (whole)
@@ -2069,7 +2078,7 @@ __device__ __forceinline__ void rows_block(const float* __restrict__ g, int64_t 
     if (threadIdx.x < ROWS)
         tab.key[threadIdx.x] = row_key(quad_c1(T), static_cast<uint32_t>(worker0) + threadIdx.x, key0);
     float W;
-    if (src.part != nullptr) {
+    if (OWN) {
         W = reduce_w<ROWS>(part);
         if (T == 0 && threadIdx.x == 0)
             *src.w = W;
@@ -2092,39 +2101,44 @@ __device__ __forceinline__ void rows_block(const float* __restrict__ g, int64_t 
     }
 }
 
-// With more than 12 rows at most two waves per SIMD: 16 rows of VGG-16 size
-// ran in 1.66 ms with two waves and 1.68-1.70 with three (4-bit codes stored:
-// 1.80 and 1.87); 8 rows of 25.6 M in 157-170 us with four or five and 170-195
-// with two.
-#define UQ_ROWS_WAVES(ROWS) __attribute__((amdgpu_waves_per_eu(1, (ROWS) > 12 ? 2 : 8)))
+// With many rows fewer waves per SIMD than fit.  More than 12 rows: two (16
+// rows of VGG-16 size ran in 1.66 ms with two waves and 1.68-1.70 with three;
+// 4-bit codes stored: 1.80 and 1.87); one scale from 11 rows (12 rows, steps
+// in a loop over three sets of buffers: 7.0 M coordinates 119.2 us with four
+// waves, 117.2 with two; 11.2 M 186.4 and 181.8; 3.0 M 56.0 and 56.6).  7 to
+// 12 rows: four (8 rows of 11.2 M: 128.4 us with five, 127.4 with four; of
+// 25.6 M 157-170 with four or five and 170-195 with two).
+#define UQ_ROWS_WAVES(ROWS, TWO) \
+    __attribute__((amdgpu_waves_per_eu(1, (ROWS) >= (TWO) ? 2 : (ROWS) > 6 ? 4 : 8)))
 
 // One scale, no codes stored.
-template <int ROWS, int POL>
-__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS) void k_quant_sum_split(
+template <int ROWS, int POL, bool OWN>
+__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS, 11) void k_quant_sum_split(
     const float* __restrict__ g, int64_t d, int32_t rows, int64_t ldg, int32_t worker0, WSource src, ScaleSet S,
     uint32_t key0, uint32_t key1, int64_t tile0, int32_t M, RowsOut o)
 {
-    rows_block<ROWS, false, 0, POL>(g, d, rows, ldg, worker0, src, S, key0, key1, tile0, M, o);
+    rows_block<ROWS, false, 0, POL, OWN>(g, d, rows, ldg, worker0, src, S, key0, key1, tile0, M, o);
 }
 
 // Several scales, no codes stored; the shared index formed and stored: all M
 // rows, as workers 0 .. M - 1.
-template <int ROWS, int POL>
-__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS) void k_index_quant_sum(
+template <int ROWS, int POL, bool OWN>
+__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS, 13) void k_index_quant_sum(
     const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg, WSource src, ScaleSet S, uint32_t key0,
     uint32_t key1, int64_t tile0, RowsOut o)
 {
-    rows_block<ROWS, true, 0, POL>(g, d, M, ldg, 0, src, S, key0, key1, tile0, M, o);
+    rows_block<ROWS, true, 0, POL, OWN>(g, d, M, ldg, 0, src, S, key0, key1, tile0, M, o);
 }
 
 // The codes stored as BITS-bit fields, and (o.sum not null) summed and
 // reconstructed in the same pass, so that they are not read again.
-template <int ROWS, bool MULTI, int BITS, bool NT>
-__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS) void k_index_quantise(
+template <int ROWS, bool MULTI, int BITS, bool NT, bool OWN>
+__global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS, 13) void k_index_quantise(
     const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg, WSource src, ScaleSet S, uint32_t key0,
     uint32_t key1, int64_t tile0, RowsOut o)
 {
-    rows_block<ROWS, MULTI, BITS, NT ? kStoreBoth : kStoreThrough>(g, d, M, ldg, 0, src, S, key0, key1, tile0, M, o);
+    rows_block<ROWS, MULTI, BITS, NT ? kStoreBoth : kStoreThrough, OWN>(g, d, M, ldg, 0, src, S, key0, key1, tile0, M,
+                                                                        o);
 }
 
 // ---------------------------------------------------------------------------
@@ -2404,15 +2418,15 @@ static int rows_policy(int64_t d)
 // One scale, at most kFuseRows rows set and reconstructed in one call:
 // one block per 256-coordinate tile (the last one partial), one instance per
 // row pair count.
-#define UQ_ROW_PAIRS_1_TO_8(LAUNCH, NT) \
-    LAUNCH(1, NT);                      \
-    LAUNCH(2, NT);                      \
-    LAUNCH(3, NT);                      \
-    LAUNCH(4, NT);                      \
-    LAUNCH(5, NT);                      \
-    LAUNCH(6, NT);                      \
-    LAUNCH(7, NT);                      \
-    LAUNCH(8, NT)
+#define UQ_ROW_PAIRS_1_TO_8(LAUNCH, STORES, OWN) \
+    LAUNCH(1, STORES, OWN);                      \
+    LAUNCH(2, STORES, OWN);                      \
+    LAUNCH(3, STORES, OWN);                      \
+    LAUNCH(4, STORES, OWN);                      \
+    LAUNCH(5, STORES, OWN);                      \
+    LAUNCH(6, STORES, OWN);                      \
+    LAUNCH(7, STORES, OWN);                      \
+    LAUNCH(8, STORES, OWN)
 
 static hipError_t launch_quant_sum_split(const float* g, int64_t d, int32_t rows, int64_t ldg, int32_t worker0,
                                          const WSource& src, const ScaleSet& S, uint32_t key0, uint32_t key1,
@@ -2422,17 +2436,19 @@ static hipError_t launch_quant_sum_split(const float* g, int64_t d, int32_t rows
     const int policy = rows_policy(d);
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
         const dim3 grid(one_shot(ntiles - tile0, 1));
-#define UQ_LAUNCH_SPLIT(PAIRS, POL)                                                                                \
+#define UQ_LAUNCH_SPLIT(PAIRS, POL, OWN)                                                                           \
     case PAIRS:                                                                                                    \
-        hipLaunchKernelGGL((k_quant_sum_split<2 * PAIRS, POL>), grid, dim3(64), 0, stream, g, d, rows, ldg,         \
+        hipLaunchKernelGGL((k_quant_sum_split<2 * PAIRS, POL, OWN>), grid, dim3(64), 0, stream, g, d, rows, ldg,         \
                            worker0, src, S, key0, key1, tile0, M, o);                                              \
         break
-        if (policy == kStoreThrough) {
-            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreThrough); }
+        if (src.part != nullptr) {
+            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreThrough, true); }
+        } else if (policy == kStoreThrough) {
+            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreThrough, false); }
         } else if (policy == kStoreNontemporal) {
-            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreNontemporal); }
+            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreNontemporal, false); }
         } else {
-            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreBoth); }
+            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreBoth, false); }
         }
 #undef UQ_LAUNCH_SPLIT
     }
@@ -2514,17 +2530,19 @@ static hipError_t launch_index_quant_sum_from(const float* g, int64_t d, int32_t
     const int policy = rows_policy(d);
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
         const dim3 grid(one_shot(ntiles - tile0, 1));
-#define UQ_LAUNCH_IQS(PAIRS, POL)                                                                                  \
+#define UQ_LAUNCH_IQS(PAIRS, POL, OWN)                                                                             \
     case PAIRS:                                                                                                    \
-        hipLaunchKernelGGL((k_index_quant_sum<2 * PAIRS, POL>), grid, dim3(64), 0, stream, g, d, M, ldg, src, S,    \
+        hipLaunchKernelGGL((k_index_quant_sum<2 * PAIRS, POL, OWN>), grid, dim3(64), 0, stream, g, d, M, ldg, src, S,    \
                            key0, key1, tile0, o);                                                                  \
         break
-        if (policy == kStoreThrough) {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreThrough); }
+        if (src.part != nullptr) {
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreThrough, true); }
+        } else if (policy == kStoreThrough) {
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreThrough, false); }
         } else if (policy == kStoreNontemporal) {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreNontemporal); }
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreNontemporal, false); }
         } else {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreBoth); }
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreBoth, false); }
         }
 #undef UQ_LAUNCH_IQS
     }
@@ -2553,29 +2571,31 @@ static hipError_t launch_stored_from(const float* g, int64_t d, int32_t M, int64
     const int64_t ntiles = (d + 255) >> 8;
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
         const dim3 grid(one_shot(ntiles - tile0, 1));
-#define UQ_LAUNCH_IQ__(PAIRS, MULTI, BITS, NT)                                                                     \
-    hipLaunchKernelGGL((k_index_quantise<2 * PAIRS, MULTI, BITS, NT>), grid, dim3(64), 0, stream, g, d, M, ldg,    \
-                       src, S, key0, key1, tile0, o)
-#define UQ_LAUNCH_IQ_(PAIRS, BITS, NT)                \
-    do {                                              \
-        if (multi)                                    \
-            UQ_LAUNCH_IQ__(PAIRS, true, BITS, NT);    \
-        else                                          \
-            UQ_LAUNCH_IQ__(PAIRS, false, BITS, NT);   \
+#define UQ_LAUNCH_IQ__(PAIRS, MULTI, BITS, NT, OWN)                                                                \
+    hipLaunchKernelGGL((k_index_quantise<2 * PAIRS, MULTI, BITS, NT, OWN>), grid, dim3(64), 0, stream, g, d, M,    \
+                       ldg, src, S, key0, key1, tile0, o)
+#define UQ_LAUNCH_IQ_(PAIRS, BITS, NT, OWN)                \
+    do {                                                   \
+        if (multi)                                         \
+            UQ_LAUNCH_IQ__(PAIRS, true, BITS, NT, OWN);    \
+        else                                               \
+            UQ_LAUNCH_IQ__(PAIRS, false, BITS, NT, OWN);   \
     } while (0)
-#define UQ_LAUNCH_IQ(PAIRS, NT)                   \
+#define UQ_LAUNCH_IQ(PAIRS, NT, OWN)              \
     case PAIRS:                                   \
         if (bits == 8)                            \
-            UQ_LAUNCH_IQ_(PAIRS, 8, NT);          \
+            UQ_LAUNCH_IQ_(PAIRS, 8, NT, OWN);     \
         else if (bits == 4)                       \
-            UQ_LAUNCH_IQ_(PAIRS, 4, NT);          \
+            UQ_LAUNCH_IQ_(PAIRS, 4, NT, OWN);     \
         else                                      \
-            UQ_LAUNCH_IQ_(PAIRS, 2, NT);          \
+            UQ_LAUNCH_IQ_(PAIRS, 2, NT, OWN);     \
         break
-        if (nt) {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, true); }
+        if (src.part != nullptr) {
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, false, true); }
+        } else if (nt) {
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, true, false); }
         } else {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, false); }
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, false, false); }
         }
 #undef UQ_LAUNCH_IQ
 #undef UQ_LAUNCH_IQ_
