@@ -2149,7 +2149,15 @@ __global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS, 13) void k_index_quantise(
 // 1000 coordinates of 8 rows, codes stored: 24.0 us as four kernels, 11.9 as one.
 // ---------------------------------------------------------------------------
 constexpr int kSmallThreads = 512;
+// The one block codes its rows in turn, so more rows leave it fewer
+// coordinates before norm and rows pass over many blocks (12.3 us, 8 to 16
+// rows) are faster: 8 rows of 4096 9.9 us (four scales 11.6); 16 rows of 2048
+// 12.1 (12.9), of 3072 14.6 (15.9), of 4096 18.6 (20.2).
 constexpr int64_t kSmallStep = 4096;
+constexpr int64_t small_step(int32_t rows)
+{
+    return rows <= 8 ? kSmallStep : kSmallStep / 2;
+}
 
 template <int ROWS, bool MULTI, int BITS>
 __global__ __launch_bounds__(kSmallThreads) void k_step_small(const float* __restrict__ g, int64_t d, int32_t M,
@@ -2171,7 +2179,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_step_small(const float* __res
         const float* row = g + static_cast<int64_t>(m < M ? m : M - 1) * ldg;
         double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0;
 #pragma unroll
-        for (int u = 0; u < kSmallStep / 1024; ++u) {
+        for (int u = 0; u < small_step(ROWS) / 1024; ++u) {
             const int32_t j = t + 256 * u;
             if (j < nvec) {
                 const f32x4 a = *reinterpret_cast<const f32x4*>(row + 4 * j);
@@ -2656,7 +2664,7 @@ hipError_t launch_aggregate(const float* g, int64_t d, int32_t M, int64_t ldg, c
     const uint32_t key1 = static_cast<uint32_t>(seed >> 32);
     const RowsOut o{S.K > 1 ? idx : nullptr, codes, ldc, sum, out};
     const NormPlan plan = norm_plan(d);
-    if (d > 0 && d <= kSmallStep)
+    if (d > 0 && d <= small_step(M))
         return launch_step_small(g, d, M, ldg, w, S, key0, key1, bits, o, stream);
     // one scale with codes stored: beyond what the cache holds, summing them
     // as they are stored saves reading them back; below, the quantiser and
