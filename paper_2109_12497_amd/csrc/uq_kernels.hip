@@ -2236,11 +2236,10 @@ __global__ __launch_bounds__(kSmallThreads) void k_step_small(const float* __res
 // ---------------------------------------------------------------------------
 // Host-side launchers (called by the ABI layer after validation).
 // ---------------------------------------------------------------------------
-// The multi-scale quantiser with the index formed in it stores its codes
-// nontemporally when one launch writes more than this many bytes: measured 3%
-// faster steps at VGG-16 size (2.2 GB of codes), 1.8-2.5% slower at ResNet-18
-// and ResNet-50 sizes (89 and 204 MB), where the sum then finds the codes in
-// the 256 MB Infinity Cache.
+// A launch that stores codes stores them nontemporally when it writes more
+// than this many bytes: measured 3% faster steps at VGG-16 size (2.2 GB of
+// codes), 1.8-2.5% slower at ResNet-18 and ResNet-50 sizes (89 and 204 MB),
+// where the sum then finds the codes in the 256 MB Infinity Cache.
 constexpr int64_t kCodesNontemporalBytes = int64_t(512) << 20;
 
 // Enough blocks for every unit to get its own thread / wave / tile (the
@@ -2390,7 +2389,9 @@ hipError_t launch_quantise(const float* g, int64_t d, int32_t rows, int64_t ldg,
     const int64_t ntiles = (d + 511) >> 9;
     const int64_t per_row = one_shot_cap() / rows < 1 ? 1 : one_shot_cap() / rows;
     uint8_t* out = reinterpret_cast<uint8_t*>(codes);
-    const bool nt = static_cast<int64_t>(rows) * ((d * bits + 7) / 8) > kThroughNontemporalBytes;
+    // (from 256 MB on, 16 rows of 25.6 M coordinates, 409 MB of codes, then
+    // their sum, took 667 us; from 512 MB 641)
+    const bool nt = static_cast<int64_t>(rows) * ((d * bits + 7) / 8) > kCodesNontemporalBytes;
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += per_row) {
     const int64_t n = ntiles - tile0 < per_row ? ntiles - tile0 : per_row;
     const dim3 grid(static_cast<unsigned>(n), static_cast<unsigned>(rows));

@@ -57,3 +57,17 @@ def test_one_row_takes_the_one_row_kernel():
     block would be drawn for nothing (25.6 M coordinates: 72.9 us, 60.5 here)."""
     assert names(1_200_000, 1, [127.0], quant_sum=True) == ["k_sumsq", "k_finish", "k_quant_sum"]
     assert names(1 << 20, 1, [127.0], quant_sum=True) == ["k_sumsq", "k_quant_sum_split"]  # W formed in it
+
+
+# k_quantise<several scales, bits, nontemporal>: codes up to 512 MB are left to
+# the Infinity Cache, where their sum follows at once.
+@pytest.mark.parametrize("rows,nontemporal", [(10, 0), (15, 0), (16, 0), (17, 1)])
+def test_stored_codes_leave_nontemporally_beyond_512_mb(rows, nontemporal):
+    d = 32_000_000
+    st = Step(256, 1, [127.0], device=DEV)  # its W; the rows below are only captured, never run
+    g = torch.empty((1, 64), device=DEV)
+    codes = torch.empty((1, 64), dtype=torch.int8, device=DEV)
+    import paper_2109_12497_amd as uq
+
+    ks = launched(lambda: uq.uq_quantize_single(g, d, rows, d, 0, st.w, 127, 1, codes, d))
+    assert [(k, a) for k, a, _ in ks] == [("k_quantise", (0, 8, nontemporal))]
