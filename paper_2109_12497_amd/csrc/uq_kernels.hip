@@ -1383,10 +1383,18 @@ __global__ __launch_bounds__(kBlock) void k_sum(const uint8_t* __restrict__ code
 // ---------------------------------------------------------------------------
 // Reconstruction: out_i = RN32(sum_i * deq_k), deq_k = RN32(W / (M s_k)).
 // ---------------------------------------------------------------------------
-// One wave per block and 512 coordinates (the last block: fewer).  NT: the
-// outputs leave nontemporally, beyond kSumNontemporalBytes of them as the
-// sums do: one rank's calls at 25.6 M coordinates (102 MB of outputs) 78.1 us
-// written through, 75.2 nontemporal.
+// One wave per block; a lane takes one quad with one scale, two (256
+// coordinates apart) with several, where the index lookups then overlap (one
+// quad and two, 138 M coordinates: one scale 164 and 175 us, four scales 195
+// and 178; 25.6 M: 31.5 and 33.7, 38.0 and 34.6).  NT: the outputs leave
+// nontemporally, beyond kSumNontemporalBytes of them as the sums do: one
+// rank's calls at 25.6 M coordinates (102 MB of outputs) 78.1 us written
+// through, 75.2 nontemporal.
+constexpr int dequant_quads(bool multi)
+{
+    return multi ? 2 : 1;
+}
+
 template <bool MULTI, bool NT>
 __global__ __launch_bounds__(64) void k_dequant(const int32_t* __restrict__ sum, int64_t d, int32_t M,
                                                 const float* __restrict__ wptr, ScaleSet S,
@@ -1396,13 +1404,14 @@ __global__ __launch_bounds__(64) void k_dequant(const int32_t* __restrict__ sum,
     __shared__ float deq_s[kMaxScales];
     const int lane = threadIdx.x;
     const int64_t T = tile0 + blockIdx.x;
-    const int64_t t_off = T << 9;
-    const bool whole = T < d >> 9;
-    i32x4 s[2] = {};
-    uint32_t kk[2] = {0u, 0u};
+    constexpr int kQuads = dequant_quads(MULTI);
+    const int64_t t_off = T * (256 * kQuads);
+    const bool whole = T < d / (256 * kQuads);
+    i32x4 s[kQuads] = {};
+    uint32_t kk[kQuads] = {};
     if (whole) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < kQuads; ++h) {
             const int64_t i = t_off + 256 * h + 4 * lane;
             s[h] = load_nt(sum + i);
             if (MULTI)
@@ -1417,7 +1426,7 @@ __global__ __launch_bounds__(64) void k_dequant(const int32_t* __restrict__ sum,
     __syncthreads();
     if (whole) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
+        for (int h = 0; h < kQuads; ++h) {
             const auto f = [&](int j) { return MULTI ? deq_s[min((kk[h] >> (8 * j)) & 0xFFu, kmax)] : deq0; };
             f32x4 o;
             o.x = static_cast<float>(s[h].x) * f(0);
@@ -2751,7 +2760,8 @@ hipError_t launch_dequant(const int32_t* sum, int64_t d, int32_t M, const float*
 {
     if (d == 0)
         return hipSuccess;
-    const int64_t ntiles = (d + 511) >> 9;
+    const int64_t tile = 256 * dequant_quads(S.K > 1);
+    const int64_t ntiles = (d + tile - 1) / tile;
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
         const dim3 grid(one_shot(ntiles - tile0, 1));
 #define UQ_LAUNCH_DEQUANT(MULTI, NT) \

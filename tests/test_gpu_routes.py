@@ -71,3 +71,27 @@ def test_stored_codes_leave_nontemporally_beyond_512_mb(rows, nontemporal):
 
     ks = launched(lambda: uq.uq_quantize_single(g, d, rows, d, 0, st.w, 127, 1, codes, d))
     assert [(k, a) for k, a, _ in ks] == [("k_quantise", (0, 8, nontemporal))]
+
+
+# One quad a lane with one scale (256 coordinates a block), two with several.
+@pytest.mark.parametrize("d", [1, 255, 256, 257, 511, 512, 513, 1025, 100_003])
+def test_reconstruction_blocks(d):
+    import numpy as np
+
+    for scales, tile in (([127.0], 256), ([127.0, 2032.0], 512)):
+        st = Step(d, 3, scales, device=DEV, fused=False, **({"index_in_pass": False} if len(scales) > 1 else {}))
+        (k, a, grid), = launched(lambda: st.dequantize())
+        assert k == "k_dequant" and a == (len(scales) > 1, 0) and grid[0] == -(-d // tile)
+        rng = np.random.default_rng(d)
+        s = rng.integers(-381, 382, size=d).astype(np.int32)
+        idx = rng.integers(0, len(scales), size=d)
+        st.sum[:d] = torch.from_numpy(s).to(DEV)
+        if st.idx is not None:
+            st.idx[:d] = torch.from_numpy(idx.astype(np.uint8)).to(DEV)
+        W = np.float32(0.37)
+        st.w[0] = float(W)
+        st.out.fill_(-1.0)
+        st.dequantize()
+        deq = np.array([W / np.float32(3 * x) for x in scales], dtype=np.float32)
+        assert np.array_equal(st.out[:d].cpu().numpy(), s.astype(np.float32) * deq[idx])
+        assert bool((st.out[d:] == -1.0).all())
