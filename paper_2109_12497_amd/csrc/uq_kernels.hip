@@ -1846,14 +1846,17 @@ __device__ __forceinline__ void lds_put(uint8_t* p, uint32_t v)
 }
 
 // How the sums and outputs of a rows pass are stored (and, unless
-// kStoreThrough, codes nontemporally): through the caches, nontemporally, or
-// both.  Steps in a loop over three sets of buffers, 8 rows: 11.2 M
-// coordinates (45 MB of sums), one scale, through 127.6 us, nontemporal
-// 131.3, both 132.6; four scales 132.9 through, 129.8 with only the sums
-// through, 133.4 nontemporal; 25.6 M (102 MB), four scales, 297.5 through,
-// 292.9 nontemporal, 293.2 both.  A pass of 16 rows of VGG-16 size without
-// work (553 MB): 1.72 ms through, 1.68 nontemporal, 1.64 both.
-constexpr int kStoreThrough = 0, kStoreNontemporal = 1, kStoreBoth = 2;
+// kStoreThrough, codes nontemporally): through the caches, nontemporally,
+// both, or the sums through and the outputs nontemporally.  Steps in a loop
+// over three sets of buffers, 8 rows, one scale: 11.2 M coordinates (45 MB of
+// sums) 128.4 us through, 129.2 with only the sums through, 132.3
+// nontemporal; 12.5 M 147.7, 143.5 and 146.5; 16.0 M 190.0, 184.1 and 188.9;
+// 20.0 M sums through 228.0, nontemporal 234.5; 25.6 M 301.4 and 295.9.  Four
+// scales (kStoreThrough there stores the outputs nontemporally): 11.2 M 131.3
+// sums through, 134.8 nontemporal; 25.6 M (102 MB) 297.5 through, 292.9
+// nontemporal, 293.2 both.  A pass of 16 rows of VGG-16 size without work
+// (553 MB): 1.72 ms through, 1.68 nontemporal, 1.64 both.
+constexpr int kStoreThrough = 0, kStoreNontemporal = 1, kStoreBoth = 2, kStoreSumsThrough = 3;
 
 // What a rows pass writes: the index (several scales), the rows' codes as
 // BITS-bit fields (BITS = 0: not stored), and, unless sum is null, their
@@ -1960,7 +1963,7 @@ __device__ __forceinline__ void rows_tile(const f32x4 (&A)[ROWS], const float* _
             store_nt(o.out + a_off + 4 * lane, r);
         } else {
             store_through<POL == kStoreBoth>(o.sum + a_off, 16 * lane, s);
-            if (MULTI && POL == kStoreThrough)
+            if (POL == kStoreSumsThrough || (MULTI && POL == kStoreThrough))
                 store_nt(o.out + a_off + 4 * lane, r);
             else
                 store_through<POL == kStoreBoth>(o.out + a_off, 16 * lane, r);
@@ -2291,6 +2294,11 @@ constexpr int64_t kMaximaNontemporalBytes = int64_t(128) << 20;
 // beyond this many bytes, where the passes that read it back find it in HBM.
 constexpr int64_t kIndexNontemporalBytes = int64_t(256) << 20;
 
+// One scale's rows pass stores its outputs nontemporally beyond this many
+// bytes of them (between 11.2 M and 12.5 M coordinates) and its sums beyond
+// kSumsThroughBytes (between 20.0 M and 25.6 M; see kStoreThrough).
+constexpr int64_t kOutNontemporalBytes = int64_t(46) << 20;
+constexpr int64_t kSumsThroughBytes = int64_t(88) << 20;
 // Write-through stores also carry the nontemporal hint when the sums exceed
 // this many bytes, the Infinity Cache's size (work-free passes): the sums and
 // outputs of 16 rows at VGG-16 size, with the index, 1.64 against 1.72 ms;
@@ -2426,11 +2434,20 @@ hipError_t launch_quantise(const float* g, int64_t d, int32_t rows, int64_t ldg,
     return hipGetLastError();
 }
 
-// The rows pass's stores by the bytes of its sums (see kStoreThrough).
+// The rows pass's stores by the bytes of its sums (see kStoreThrough), with
+// several scales and with one.
 static int rows_policy(int64_t d)
 {
     return 4 * d > kThroughNontemporalBytes ? kStoreBoth : 4 * d > kSumNontemporalBytes ? kStoreNontemporal
                                                                                        : kStoreThrough;
+}
+
+static int one_scale_policy(int64_t d)
+{
+    return 4 * d > kThroughNontemporalBytes ? kStoreBoth
+           : 4 * d > kSumsThroughBytes      ? kStoreNontemporal
+           : 4 * d > kOutNontemporalBytes   ? kStoreSumsThrough
+                                            : kStoreThrough;
 }
 
 // One scale, at most kFuseRows rows set and reconstructed in one call:
@@ -2451,7 +2468,7 @@ static hipError_t launch_quant_sum_split(const float* g, int64_t d, int32_t rows
                                          int32_t M, const RowsOut& o, hipStream_t stream)
 {
     const int64_t ntiles = (d + 255) >> 8;
-    const int policy = rows_policy(d);
+    const int policy = one_scale_policy(d);
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
         const dim3 grid(one_shot(ntiles - tile0, 1));
 #define UQ_LAUNCH_SPLIT(PAIRS, POL, OWN)                                                                           \
@@ -2463,6 +2480,8 @@ static hipError_t launch_quant_sum_split(const float* g, int64_t d, int32_t rows
             switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreThrough, true); }
         } else if (policy == kStoreThrough) {
             switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreThrough, false); }
+        } else if (policy == kStoreSumsThrough) {
+            switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreSumsThrough, false); }
         } else if (policy == kStoreNontemporal) {
             switch ((rows + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_SPLIT, kStoreNontemporal, false); }
         } else {

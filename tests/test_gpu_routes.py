@@ -95,3 +95,16 @@ def test_reconstruction_blocks(d):
         deq = np.array([W / np.float32(3 * x) for x in scales], dtype=np.float32)
         assert np.array_equal(st.out[:d].cpu().numpy(), s.astype(np.float32) * deq[idx])
         assert bool((st.out[d:] == -1.0).all())
+
+
+# k_quant_sum_split<rows, stores, W from partials>: stores 0 through, 3 the
+# sums through and the outputs nontemporally, 1 both nontemporally, 2 both hints.
+@pytest.mark.parametrize("d,stores", [(11_173_962, 0), (12_058_624, 0), (12_058_625, 3), (16_000_001, 3),
+                                      (23_068_672, 3), (23_068_673, 1), (67_108_864, 1), (67_108_865, 2)])
+def test_stores_of_the_one_scale_rows_pass(d, stores):
+    import paper_2109_12497_amd as uq
+
+    st = Step(256, 6, [127.0], device=DEV)  # buffers of a small step: captured only, never run
+    ks = launched(lambda: uq.uq_quantize_sum(st.out, d, 6, -(-d // 64) * 64, 0, st.w, [127.0], 1, None, 1, 0, st.sum,
+                                             6, st.out, None))
+    assert [(k, a) for k, a, _ in ks] == [("k_quant_sum_split", (6, stores, 0))]
