@@ -1530,6 +1530,21 @@ __device__ __forceinline__ void quant_sum_tail(const float* __restrict__ g, int6
     }
 }
 
+// How the sums and outputs of a rows pass, or of the one-row form of
+// k_quant_sum (kStorePlain: its sums into the L2s), are stored (and, unless
+// kStoreThrough, codes nontemporally): through the caches, nontemporally,
+// both, or the sums through and the outputs nontemporally.  Steps in a loop
+// over three sets of buffers, 8 rows, one scale: 11.2 M coordinates (45 MB of
+// sums) 128.4 us through, 129.2 with only the sums through, 132.3
+// nontemporal; 12.5 M 147.7, 143.5 and 146.5; 16.0 M 190.0, 184.1 and 188.9;
+// 20.0 M sums through 228.0, nontemporal 234.5; 25.6 M 301.4 and 295.9.  Four
+// scales (kStoreThrough there stores the outputs nontemporally): 11.2 M 131.3
+// sums through, 134.8 nontemporal; 25.6 M (102 MB) 297.5 through, 292.9
+// nontemporal, 293.2 both.  A pass of 16 rows of VGG-16 size without work
+// (553 MB): 1.72 ms through, 1.68 nontemporal, 1.64 both.
+constexpr int kStoreThrough = 0, kStoreNontemporal = 1, kStoreBoth = 2, kStoreSumsThrough = 3,
+              kStorePlain = 4;
+
 // ROW1: the one-row form (a streamed worker), compiled apart so that it does
 // not carry the row loop's registers.  NIB: the index as 4-bit fields.  NT:
 // the old sums loaded, and the sums and outputs stored, nontemporally too.
@@ -1539,7 +1554,7 @@ __global__ __launch_bounds__(64) void k_quant_sum(const float* __restrict__ g, i
                                                   int32_t worker0, const float* __restrict__ wptr, ScaleSet S,
                                                   const uint8_t* __restrict__ idx, uint32_t key0, uint32_t key1,
                                                   int64_t tile0, int32_t* __restrict__ sum, int32_t M,
-                                                  float* __restrict__ out)
+                                                  float* __restrict__ out, int32_t stores)
 {
     __shared__ float inv_s[kMaxScales];  // s_k / W
     __shared__ float inv_p[kMaxScales];  // s_k / W * 2^16 when pre
@@ -1607,8 +1622,13 @@ __global__ __launch_bounds__(64) void k_quant_sum(const float* __restrict__ g, i
     widen_pairs(h, acc);
     sa += i32x4{acc[0], acc[1], acc[2], acc[3]};
     sb += i32x4{acc[4], acc[5], acc[6], acc[7]};
-    store_through<NT>(sum + t_off, 16 * lane, sa);
-    store_through<NT>(sum + t_off, 16 * lane + 1024, sb);
+    if (ROW1 && !NT && stores == kStorePlain) {
+        *reinterpret_cast<i32x4*>(sum + a_off) = sa;
+        *reinterpret_cast<i32x4*>(sum + a_off + 256) = sb;
+    } else {
+        store_through<NT>(sum + t_off, 16 * lane, sa);
+        store_through<NT>(sum + t_off, 16 * lane + 1024, sb);
+    }
     if (DEQ) {
         // the index words again (two registers live instead of eight indices)
         const auto f = [&](uint32_t word, int j) { return MULTI ? deq_s[min((word >> (8 * j)) & 0xFFu, kmax)] : deq0; };
@@ -1621,8 +1641,13 @@ __global__ __launch_bounds__(64) void k_quant_sum(const float* __restrict__ g, i
         ob.y = static_cast<float>(sb.y) * f(in.kb, 1);
         ob.z = static_cast<float>(sb.z) * f(in.kb, 2);
         ob.w = static_cast<float>(sb.w) * f(in.kb, 3);
-        store_through<NT>(out + t_off, 16 * lane, oa);
-        store_through<NT>(out + t_off, 16 * lane + 1024, ob);
+        if (ROW1 && !NT && stores == kStoreSumsThrough) {
+            store_nt(out + a_off, oa);
+            store_nt(out + a_off + 256, ob);
+        } else {
+            store_through<NT>(out + t_off, 16 * lane, oa);
+            store_through<NT>(out + t_off, 16 * lane + 1024, ob);
+        }
     }
 }
 
@@ -1844,19 +1869,6 @@ __device__ __forceinline__ void lds_put(uint8_t* p, uint32_t v)
     else
         *p = static_cast<uint8_t>(v);
 }
-
-// How the sums and outputs of a rows pass are stored (and, unless
-// kStoreThrough, codes nontemporally): through the caches, nontemporally,
-// both, or the sums through and the outputs nontemporally.  Steps in a loop
-// over three sets of buffers, 8 rows, one scale: 11.2 M coordinates (45 MB of
-// sums) 128.4 us through, 129.2 with only the sums through, 132.3
-// nontemporal; 12.5 M 147.7, 143.5 and 146.5; 16.0 M 190.0, 184.1 and 188.9;
-// 20.0 M sums through 228.0, nontemporal 234.5; 25.6 M 301.4 and 295.9.  Four
-// scales (kStoreThrough there stores the outputs nontemporally): 11.2 M 131.3
-// sums through, 134.8 nontemporal; 25.6 M (102 MB) 297.5 through, 292.9
-// nontemporal, 293.2 both.  A pass of 16 rows of VGG-16 size without work
-// (553 MB): 1.72 ms through, 1.68 nontemporal, 1.64 both.
-constexpr int kStoreThrough = 0, kStoreNontemporal = 1, kStoreBoth = 2, kStoreSumsThrough = 3;
 
 // What a rows pass writes: the index (several scales), the rows' codes as
 // BITS-bit fields (BITS = 0: not stored), and, unless sum is null, their
@@ -2299,6 +2311,13 @@ constexpr int64_t kIndexNontemporalBytes = int64_t(256) << 20;
 // kSumsThroughBytes (between 20.0 M and 25.6 M; see kStoreThrough).
 constexpr int64_t kOutNontemporalBytes = int64_t(46) << 20;
 constexpr int64_t kSumsThroughBytes = int64_t(88) << 20;
+// The one-row quantise-and-sum leaves its sums in the XCDs' L2s (4 MB each)
+// up to this many bytes of them, where the next worker's call finds them: 8
+// streamed workers, one scale, 4.2 M coordinates 99.9 us written through, 89.3
+// plain; 6.3 M 140.4 and 123.9; 8.4 M 173.1 and 174.9 (four scales 213 and
+// 221).  Its outputs leave nontemporally beyond kOutNontemporalBytes: one
+// worker of 16.0 M coordinates 48.4 us through, 41.7.
+constexpr int64_t kSumsInL2Bytes = int64_t(28) << 20;
 // Write-through stores also carry the nontemporal hint when the sums exceed
 // this many bytes, the Infinity Cache's size (work-free passes): the sums and
 // outputs of 16 rows at VGG-16 size, with the index, 1.64 against 1.72 ms;
@@ -2505,6 +2524,8 @@ hipError_t launch_quant_sum(const float* g, int64_t d, int32_t rows, int64_t ldg
     const bool multi = S.K > 1;
     const bool acc = accumulate != 0;
     const bool deq = out != nullptr;
+    const int32_t stores = 4 * d <= kSumsInL2Bytes ? kStorePlain : 4 * d > kOutNontemporalBytes ? kStoreSumsThrough
+                                                                                               : kStoreThrough;
     if (!multi && !acc && deq && rows > 4 && rows <= kFuseRows)
         return launch_quant_sum_split(g, d, rows, ldg, worker0, WSource{const_cast<float*>(w), nullptr, 0}, S, key0,
                                       key1, M, RowsOut{nullptr, nullptr, 0, sum, out}, stream);
@@ -2516,10 +2537,10 @@ hipError_t launch_quant_sum(const float* g, int64_t d, int32_t rows, int64_t ldg
     do {                                                                                                           \
         if (rows == 1)                                                                                             \
             hipLaunchKernelGGL((k_quant_sum<MULTI, ACC, DEQ, NT, true, NIB>), grid, dim3(64), 0, stream, g, d,      \
-                               rows, ldg, worker0, w, S, idx, key0, key1, tile0, sum, M, out);                     \
+                               rows, ldg, worker0, w, S, idx, key0, key1, tile0, sum, M, out, stores);                     \
         else                                                                                                       \
             hipLaunchKernelGGL((k_quant_sum<MULTI, ACC, DEQ, NT, false, NIB>), grid, dim3(64), 0, stream, g, d,     \
-                               rows, ldg, worker0, w, S, idx, key0, key1, tile0, sum, M, out);                     \
+                               rows, ldg, worker0, w, S, idx, key0, key1, tile0, sum, M, out, stores);                     \
     } while (0)
     // the 4-bit index layout only matters with several scales (NIB = MULTI
     // there, so one scale compiles no second instance)
