@@ -2041,10 +2041,11 @@ __device__ __forceinline__ void fold_rows(double* s, int off)
     }
 }
 
-// W from the rows' lane sums: each row's butterfly over distances 32 .. 1
-// (k_finish's order), several rows at a time, then their largest.
+// The largest sum of squares of the rows from their lane sums (NaN if a row's
+// is): each row's butterfly over distances 32 .. 1 (k_finish's order), several
+// rows at a time, then their largest.
 template <int ROWS>
-__device__ __forceinline__ float reduce_w(const double (&in)[ROWS])
+__device__ __forceinline__ double largest_row(const double (&in)[ROWS])
 {
     constexpr int N0 = ROWS <= 2 ? 2 : ROWS <= 4 ? 4 : ROWS <= 8 ? 8 : 16;
     double s[N0];
@@ -2064,7 +2065,7 @@ __device__ __forceinline__ float reduce_w(const double (&in)[ROWS])
         const double o = __shfl_xor(best, off, 64);
         best = o > best ? o : best;
     }
-    return any_nan ? __builtin_nanf("") : static_cast<float>(sqrt(best));
+    return any_nan ? __builtin_nan("") : best;
 }
 
 // Block b takes tile tile0 + b; the tile past the whole ones holds the last
@@ -2103,7 +2104,7 @@ __device__ __forceinline__ void rows_block(const float* __restrict__ g, int64_t 
         tab.key[threadIdx.x] = row_key(quad_c1(T), static_cast<uint32_t>(worker0) + threadIdx.x, key0);
     float W;
     if (OWN) {
-        W = reduce_w<ROWS>(part);
+        W = static_cast<float>(sqrt(largest_row<ROWS>(part)));
         if (T == 0 && threadIdx.x == 0)
             *src.w = W;
     } else {
@@ -2142,6 +2143,116 @@ __global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS, 11) void k_quant_sum_split(
     uint32_t key0, uint32_t key1, int64_t tile0, int32_t M, RowsOut o)
 {
     rows_block<ROWS, false, 0, POL, OWN>(g, d, rows, ldg, worker0, src, S, key0, key1, tile0, M, o);
+}
+
+// The same for few coordinates, a tile's rows split over the block's four
+// waves: wave w codes rows w * RPW .. + RPW - 1 (and with OWN reduces their
+// partials), the waves' sums meet in LDS, wave 0 stores the tile's sums and
+// wave 1 its outputs.  One wave holding every row leaves a SIMD two waves at
+// 11 rows and more, and few tiles fill those unevenly: 16 rows of 262,144
+// coordinates 13.9 us with one wave, 12.0 with four; 524,288 21.3 and 19.9;
+// 2^20 34.4 and 33.6; 12 rows 2^20 27.1 and 25.9; from 2^21 on the two are
+// equal, and with 10 rows and fewer one wave is faster (0.8 M 17.4 and 19.5).
+template <int RPW, bool OWN>
+__global__ __launch_bounds__(256) void k_quant_sum_waves(
+    const float* __restrict__ g, int64_t d, int32_t rows, int64_t ldg, int32_t worker0, WSource src, ScaleSet S,
+    uint32_t key0, uint32_t key1, int64_t tile0, int32_t M, RowsOut o)
+{
+    __shared__ RowTables tab_s[4];
+    __shared__ uint2 part_s[4][64];
+    __shared__ double best_s[4];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int32_t>(threadIdx.x >> 6));
+    const int64_t T = tile0 + blockIdx.x;
+    const bool whole = T < d >> 8;
+    // the wave's rows r0 .. r0 + n - 1 (none: it reads the last row and adds nothing)
+    const int32_t r0 = wave * RPW < rows ? wave * RPW : rows - 1;
+    const int32_t n = wave * RPW < rows ? (rows - r0 < RPW ? rows - r0 : RPW) : 0;
+    const int32_t n_read = n > 0 ? n : 1;
+    const float* mine = g + static_cast<int64_t>(r0) * ldg;
+    const uint32_t first = static_cast<uint32_t>(worker0) + static_cast<uint32_t>(r0);
+    double part[RPW];
+    if (OWN)
+        load_partials<RPW>(WSource{nullptr, src.part + static_cast<int64_t>(r0) * src.nchunks, src.nchunks}, n_read,
+                           part);
+    f32x4 A[RPW];
+    if (whole)
+        load_quads<RPW, false>(mine, ldg, n_read, T, d, A);
+    else
+        load_quads<RPW, true>(mine, ldg, n_read, T, d, A);
+    RowTables& tab = tab_s[wave];
+    if (lane < RPW)
+        tab.key[lane] = row_key(quad_c1(T), first + static_cast<uint32_t>(lane), key0);
+    float W;
+    if (OWN) {
+        const double best = largest_row<RPW>(part);
+        if (lane == 0)
+            best_s[wave] = best;
+        __syncthreads();
+        bool any_nan = false;
+        double most = 0.0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            any_nan = any_nan || best_s[w] != best_s[w];
+            most = best_s[w] > most ? best_s[w] : most;
+        }
+        W = any_nan ? __builtin_nanf("") : static_cast<float>(sqrt(most));
+        if (T == 0 && threadIdx.x == 0)
+            *src.w = W;
+    } else {
+        W = *src.w;
+    }
+    const WaveScale c = wave_scale<false>(W, S, M);
+    const float inv0 = lane_value(c.inv, 0);
+    const float inv[4] = {inv0, inv0, inv0, inv0};
+    // the wave's own keys are in LDS before it reads them
+    __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    u16x2 h0 = {0, 0}, h1 = {0, 0};
+    const auto add = [&](int p, const u16x2 mag[4], const u16x2 sgn[4], const u16x2* fast) {
+        u16x2 m[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            m[j] = fast ? static_cast<u16x2>(mag[j] - fast[j]) : mag[j];
+        add_pair(m, sgn, 2 * p + 1 < n, h0, h1);
+    };
+    if (whole)
+        for_row_pairs<RPW, false>(A, mine, ldg, n, first, T, d, c, inv, tab, key0, key1, add);
+    else
+        for_row_pairs<RPW, true>(A, mine, ldg, n, first, T, d, c, inv, tab, key0, key1, add);
+    part_s[wave][lane] = make_uint2(__builtin_bit_cast(uint32_t, h0), __builtin_bit_cast(uint32_t, h1));
+    __syncthreads();
+    if (wave > 1)
+        return;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        if (w != wave) {
+            const uint2 q = part_s[w][lane];
+            h0 += __builtin_bit_cast(u16x2, q.x);
+            h1 += __builtin_bit_cast(u16x2, q.y);
+        }
+    }
+    const i32x4 s = {static_cast<int16_t>(h0.x), static_cast<int16_t>(h0.y), static_cast<int16_t>(h1.x),
+                     static_cast<int16_t>(h1.y)};
+    const float deq0 = lane_value(c.deq, 0);
+    const f32x4 r = {static_cast<float>(s.x) * deq0, static_cast<float>(s.y) * deq0, static_cast<float>(s.z) * deq0,
+                     static_cast<float>(s.w) * deq0};
+    const int64_t i = (T << 8) + 4 * lane;
+    const int64_t left = d - i;
+    if (left >= 4) {
+        if (wave == 0)
+            store_through<false>(o.sum + (T << 8), 16 * lane, s);
+        else
+            store_through<false>(o.out + (T << 8), 16 * lane, r);
+    } else {
+        for (int j = 0; j < 3; ++j) {
+            if (j < left) {
+                if (wave == 0)
+                    o.sum[i + j] = s[j];
+                else
+                    o.out[i + j] = r[j];
+            }
+        }
+    }
 }
 
 // Several scales, no codes stored; the shared index formed and stored: all M
@@ -2482,11 +2593,26 @@ static int one_scale_policy(int64_t d)
     LAUNCH(7, STORES, OWN);                      \
     LAUNCH(8, STORES, OWN)
 
+// Tiles up to which 11 to 16 rows of one scale are split over four waves.
+constexpr int64_t kWavesTiles = int64_t(1) << 13;
+
 static hipError_t launch_quant_sum_split(const float* g, int64_t d, int32_t rows, int64_t ldg, int32_t worker0,
                                          const WSource& src, const ScaleSet& S, uint32_t key0, uint32_t key1,
                                          int32_t M, const RowsOut& o, hipStream_t stream)
 {
     const int64_t ntiles = (d + 255) >> 8;
+    if (rows > 10 && ntiles <= kWavesTiles) {
+        const int64_t cap = one_shot_cap();
+        for (int64_t tile0 = 0; tile0 < ntiles; tile0 += cap) {
+            const dim3 grid(static_cast<unsigned>(ntiles - tile0 < cap ? ntiles - tile0 : cap));
+#define UQ_LAUNCH_WAVES(OWN)                                                                                      \
+    hipLaunchKernelGGL((k_quant_sum_waves<4, OWN>), grid, dim3(256), 0, stream, g, d, rows, ldg, worker0, src, S, \
+                       key0, key1, tile0, M, o)
+            if (src.part != nullptr) UQ_LAUNCH_WAVES(true); else UQ_LAUNCH_WAVES(false);
+#undef UQ_LAUNCH_WAVES
+        }
+        return hipGetLastError();
+    }
     const int policy = one_scale_policy(d);
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
         const dim3 grid(one_shot(ntiles - tile0, 1));

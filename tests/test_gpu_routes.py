@@ -108,3 +108,10 @@ def test_stores_of_the_one_scale_rows_pass(d, stores):
     ks = launched(lambda: uq.uq_quantize_sum(st.out, d, 6, -(-d // 64) * 64, 0, st.w, [127.0], 1, None, 1, 0, st.sum,
                                              6, st.out, None))
     assert [(k, a) for k, a, _ in ks] == [("k_quant_sum_split", (6, stores, 0))]
+
+
+# 11 to 16 rows of one scale: a tile's rows split over four waves up to 8192 tiles.
+@pytest.mark.parametrize("d,M,kernel", [(100_003, 10, "k_quant_sum_split"), (100_003, 11, "k_quant_sum_waves"),
+                                        (1 << 21, 16, "k_quant_sum_waves"), ((1 << 21) + 1, 16, "k_quant_sum_split")])
+def test_many_rows_split_over_waves(d, M, kernel):
+    assert names(d, M, [127.0], quant_sum=True)[-1] == kernel
