@@ -2846,10 +2846,13 @@ hipError_t launch_aggregate(const float* g, int64_t d, int32_t M, int64_t ldg, c
     // as they are stored saves reading them back; below, the quantiser and
     // the sum are faster apart (one scale needs no row of another's):
     // 8 rows of 25.6 M 297 against 311 us at 2 bits, 332 against 349 at 8;
-    // 16 rows of 60 M 1554 against 1467 us at 8 bits
-    const bool apart = bits != 0 && S.K == 1 && d > 0 && plan.nchunks > kOwnChunks &&
+    // 16 rows of 60 M 1554 against 1467 us at 8 bits; with at most kOwnChunks
+    // partials a row (but too many for every wave to reduce) that is so from 13
+    // rows, where the pass has two waves a SIMD: 16 rows of 2^20, 8 bits 40.8 us
+    // against 35.0, 12 rows of 0.8 M 24.4 against 25.6
+    const bool own = d > 0 && plan.nchunks <= kOwnChunks && M * plan.nchunks <= kOwnNormPartials;
+    const bool apart = bits != 0 && S.K == 1 && d > 0 && !own && (plan.nchunks > kOwnChunks || M > 12) &&
                        static_cast<int64_t>(M) * ((d * bits + 7) / 8) <= kThroughNontemporalBytes;
-    const bool own = !apart && d > 0 && plan.nchunks <= kOwnChunks && M * plan.nchunks <= kOwnNormPartials;
     double* part = static_cast<double*>(ws);
     const hipError_t e = launch_norm(g, d, M, ldg, plan, own ? nullptr : w, part, stream);
     if (e != hipSuccess || d == 0)

@@ -115,3 +115,15 @@ def test_stores_of_the_one_scale_rows_pass(d, stores):
                                         (1 << 21, 16, "k_quant_sum_waves"), ((1 << 21) + 1, 16, "k_quant_sum_split")])
 def test_many_rows_split_over_waves(d, M, kernel):
     assert names(d, M, [127.0], quant_sum=True)[-1] == kernel
+
+
+# Stored codes of one scale: quantiser and sum apart, or summed as they are stored.
+@pytest.mark.parametrize("d,M,ks", [
+    (1 << 19, 16, ["k_sumsq", "k_index_quantise"]),                        # 1024 partials: W formed in the pass
+    ((1 << 19) + 1, 16, ["k_sumsq", "k_finish", "k_quantise", "k_sum"]),
+    (1 << 20, 13, ["k_sumsq", "k_finish", "k_quantise", "k_sum"]),
+    (1 << 20, 12, ["k_sumsq", "k_finish", "k_index_quantise"]),
+    ((1 << 20) + 1, 4, ["k_sumsq", "k_finish", "k_quantise", "k_sum"]),    # more than 128 partials a row
+])
+def test_stored_codes_of_one_scale(d, M, ks):
+    assert names(d, M, [127.0]) == ks
