@@ -423,9 +423,10 @@ int uq_scatter_into(const float* vals, const uint32_t* sel, int64_t K, float* ou
  * Test hook, not part of the aggregation step: caps the grids of the
  * streaming passes (norm, index, quantise, sum, reconstruction) at `blocks`
  * blocks, 8 <= blocks <= 2^22; 0 restores the default 2^22 (the dispatch
- * packet counts work-items in 32 bits).  The passes cover whatever their grid
- * does not with grid-stride loops, which the default reaches only past about
- * 2^33 coordinates; a lower cap lets tests run those loops at small sizes.
+ * packet counts work-items in 32 bits).  What one grid does not cover is taken
+ * by further launches (the passes with a one-wave block per tile: from 2^30
+ * coordinates, the quantiser from rows * d = 2^31) or by grid-stride loops (the
+ * others, past about 2^33); a lower cap lets tests reach both at small sizes.
  * Outputs do not depend on the cap.  Process-wide: set it only while no other
  * thread issues library calls.  UQ_EINVAL for a value out of range.
  */

@@ -2380,8 +2380,10 @@ constexpr int64_t kCodesNontemporalBytes = int64_t(512) << 20;
 // Enough blocks for every unit to get its own thread / wave / tile (the
 // streaming kernels run fastest as one pass with no grid-stride reuse).  The
 // dispatch packet counts work-items in 32 bits, so the grid is capped at 2^22
-// blocks; every kernel strides over whatever the grid does not cover.  Tests
-// lower the cap to reach those strides at small sizes.
+// blocks.  What one grid does not cover, the one-wave kernels (one block per
+// tile) take in further launches, past 2^30 coordinates at the earliest, and
+// the others in grid-stride loops.  Tests lower the cap to reach both at small
+// sizes.
 constexpr int64_t kMaxBlocks = int64_t(1) << 22;
 static std::atomic<int64_t> g_one_shot_cap{kMaxBlocks};
 
@@ -2398,6 +2400,12 @@ bool set_one_shot_cap(int64_t blocks)
 static int64_t one_shot_cap()
 {
     return g_one_shot_cap.load(std::memory_order_relaxed);
+}
+
+// One launch's share of `units` one-unit blocks from `first` on, at most `cap`.
+static unsigned blocks_from(int64_t units, int64_t first, int64_t cap)
+{
+    return static_cast<unsigned>(units - first < cap ? units - first : cap);
 }
 
 static unsigned one_shot(int64_t units, int64_t per_block)
@@ -2534,14 +2542,14 @@ hipError_t launch_quantise(const float* g, int64_t d, int32_t rows, int64_t ldg,
     // one block per 512-coordinate tile and row (the last tile partial), rows
     // x tiles within the grid cap
     const int64_t ntiles = (d + 511) >> 9;
-    const int64_t per_row = one_shot_cap() / rows < 1 ? 1 : one_shot_cap() / rows;
+    const int64_t share = one_shot_cap() / rows;
+    const int64_t per_row = share < 1 ? 1 : share;
     uint8_t* out = reinterpret_cast<uint8_t*>(codes);
     // (from 256 MB on, 16 rows of 25.6 M coordinates, 409 MB of codes, then
     // their sum, took 667 us; from 512 MB 641)
     const bool nt = static_cast<int64_t>(rows) * ((d * bits + 7) / 8) > kCodesNontemporalBytes;
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += per_row) {
-    const int64_t n = ntiles - tile0 < per_row ? ntiles - tile0 : per_row;
-    const dim3 grid(static_cast<unsigned>(n), static_cast<unsigned>(rows));
+        const dim3 grid(blocks_from(ntiles, tile0, per_row), static_cast<unsigned>(rows));
 #define UQ_LAUNCH_QUANTISE(MULTI, BITS)                                                                            \
     do {                                                                                                           \
         if (nt)                                                                                                    \
@@ -2551,14 +2559,14 @@ hipError_t launch_quantise(const float* g, int64_t d, int32_t rows, int64_t ldg,
             hipLaunchKernelGGL((k_quantise<MULTI, BITS, false>), grid, dim3(64), 0, stream, g, d, ldg, worker0, w, \
                                S, idx, key0, key1, tile0, out, ldc);                                               \
     } while (0)
-    const bool multi = S.K > 1;
-    if (bits == 8) {
-        if (multi) UQ_LAUNCH_QUANTISE(true, 8); else UQ_LAUNCH_QUANTISE(false, 8);
-    } else if (bits == 4) {
-        if (multi) UQ_LAUNCH_QUANTISE(true, 4); else UQ_LAUNCH_QUANTISE(false, 4);
-    } else {
-        if (multi) UQ_LAUNCH_QUANTISE(true, 2); else UQ_LAUNCH_QUANTISE(false, 2);
-    }
+        const bool multi = S.K > 1;
+        if (bits == 8) {
+            if (multi) UQ_LAUNCH_QUANTISE(true, 8); else UQ_LAUNCH_QUANTISE(false, 8);
+        } else if (bits == 4) {
+            if (multi) UQ_LAUNCH_QUANTISE(true, 4); else UQ_LAUNCH_QUANTISE(false, 4);
+        } else {
+            if (multi) UQ_LAUNCH_QUANTISE(true, 2); else UQ_LAUNCH_QUANTISE(false, 2);
+        }
     }
 #undef UQ_LAUNCH_QUANTISE
     return hipGetLastError();
@@ -2604,7 +2612,7 @@ static hipError_t launch_quant_sum_split(const float* g, int64_t d, int32_t rows
     if (rows > 10 && ntiles <= kWavesTiles) {
         const int64_t cap = one_shot_cap();
         for (int64_t tile0 = 0; tile0 < ntiles; tile0 += cap) {
-            const dim3 grid(static_cast<unsigned>(ntiles - tile0 < cap ? ntiles - tile0 : cap));
+            const dim3 grid(blocks_from(ntiles, tile0, cap));
 #define UQ_LAUNCH_WAVES(OWN)                                                                                      \
     hipLaunchKernelGGL((k_quant_sum_waves<4, OWN>), grid, dim3(256), 0, stream, g, d, rows, ldg, worker0, src, S, \
                        key0, key1, tile0, M, o)
@@ -2614,8 +2622,9 @@ static hipError_t launch_quant_sum_split(const float* g, int64_t d, int32_t rows
         return hipGetLastError();
     }
     const int policy = one_scale_policy(d);
-    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
-        const dim3 grid(one_shot(ntiles - tile0, 1));
+    const int64_t cap = one_shot_cap();
+    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += cap) {
+        const dim3 grid(blocks_from(ntiles, tile0, cap));
 #define UQ_LAUNCH_SPLIT(PAIRS, POL, OWN)                                                                           \
     case PAIRS:                                                                                                    \
         hipLaunchKernelGGL((k_quant_sum_split<2 * PAIRS, POL, OWN>), grid, dim3(64), 0, stream, g, d, rows, ldg,         \
@@ -2657,8 +2666,9 @@ hipError_t launch_quant_sum(const float* g, int64_t d, int32_t rows, int64_t ldg
                                       key1, M, RowsOut{nullptr, nullptr, 0, sum, out}, stream);
     // one block per 512-coordinate tile, the last one partial
     const int64_t ntiles = (d + 511) >> 9;
-    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
-    const dim3 grid(one_shot(ntiles - tile0, 1));
+    const int64_t cap = one_shot_cap();
+    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += cap) {
+        const dim3 grid(blocks_from(ntiles, tile0, cap));
 #define UQ_LAUNCH_QSUM_(MULTI, ACC, DEQ, NT, NIB)                                                                   \
     do {                                                                                                           \
         if (rows == 1)                                                                                             \
@@ -2691,11 +2701,11 @@ hipError_t launch_quant_sum(const float* g, int64_t d, int32_t rows, int64_t ldg
         else                                     \
             UQ_LAUNCH_QSUM_NT(MULTI, ACC, false);\
     } while (0)
-    if (multi) {
-        if (acc) UQ_LAUNCH_QSUM_DEQ(true, true); else UQ_LAUNCH_QSUM_DEQ(true, false);
-    } else {
-        if (acc) UQ_LAUNCH_QSUM_DEQ(false, true); else UQ_LAUNCH_QSUM_DEQ(false, false);
-    }
+        if (multi) {
+            if (acc) UQ_LAUNCH_QSUM_DEQ(true, true); else UQ_LAUNCH_QSUM_DEQ(true, false);
+        } else {
+            if (acc) UQ_LAUNCH_QSUM_DEQ(false, true); else UQ_LAUNCH_QSUM_DEQ(false, false);
+        }
     }
 #undef UQ_LAUNCH_QSUM_DEQ
 #undef UQ_LAUNCH_QSUM_NT
@@ -2712,8 +2722,9 @@ static hipError_t launch_index_quant_sum_from(const float* g, int64_t d, int32_t
 {
     const int64_t ntiles = (d + 255) >> 8;
     const int policy = rows_policy(d);
-    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
-        const dim3 grid(one_shot(ntiles - tile0, 1));
+    const int64_t cap = one_shot_cap();
+    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += cap) {
+        const dim3 grid(blocks_from(ntiles, tile0, cap));
 #define UQ_LAUNCH_IQS(PAIRS, POL, OWN)                                                                             \
     case PAIRS:                                                                                                    \
         hipLaunchKernelGGL((k_index_quant_sum<2 * PAIRS, POL, OWN>), grid, dim3(64), 0, stream, g, d, M, ldg, src, S,    \
@@ -2753,8 +2764,9 @@ static hipError_t launch_stored_from(const float* g, int64_t d, int32_t M, int64
     const bool nt = static_cast<int64_t>(M) * ((d * bits + 7) / 8) > kCodesNontemporalBytes;
     const bool multi = S.K > 1 || o.idx != nullptr;
     const int64_t ntiles = (d + 255) >> 8;
-    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
-        const dim3 grid(one_shot(ntiles - tile0, 1));
+    const int64_t cap = one_shot_cap();
+    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += cap) {
+        const dim3 grid(blocks_from(ntiles, tile0, cap));
 #define UQ_LAUNCH_IQ__(PAIRS, MULTI, BITS, NT, OWN)                                                                \
     hipLaunchKernelGGL((k_index_quantise<2 * PAIRS, MULTI, BITS, NT, OWN>), grid, dim3(64), 0, stream, g, d, M,    \
                        ldg, src, S, key0, key1, tile0, o)
@@ -2931,8 +2943,9 @@ hipError_t launch_dequant(const int32_t* sum, int64_t d, int32_t M, const float*
         return hipSuccess;
     const int64_t tile = 256 * dequant_quads(S.K > 1);
     const int64_t ntiles = (d + tile - 1) / tile;
-    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += one_shot_cap()) {
-        const dim3 grid(one_shot(ntiles - tile0, 1));
+    const int64_t cap = one_shot_cap();
+    for (int64_t tile0 = 0; tile0 < ntiles; tile0 += cap) {
+        const dim3 grid(blocks_from(ntiles, tile0, cap));
 #define UQ_LAUNCH_DEQUANT(MULTI, NT) \
     hipLaunchKernelGGL((k_dequant<MULTI, NT>), grid, dim3(64), 0, stream, sum, d, M, w, S, idx, tile0, out)
         const bool nt = 4 * d > kSumNontemporalBytes;
