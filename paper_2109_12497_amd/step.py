@@ -162,7 +162,8 @@ class Step:
         if self.one_call:
             codes = self.codes
             uq_aggregate(g, self.d, self.M, g.stride(0), self.scales, self.K, seed, 0 if codes is None else self.bits,
-                         self.w, self.idx, codes, self.ldc, self.sum, self.out, self.ws, self.ws_bytes, stream)
+                         self.w, self.idx, codes, self.ldc if codes is None else codes.stride(0), self.sum, self.out,
+                         self.ws, self.ws_bytes, stream)
             return self.out[:self.d]
         self.shared_scale(g, stream, w_only=self.index_in_pass)
         if self.index_in_pass:

@@ -117,3 +117,20 @@ def test_invalid_calls_are_refused():
                dict(ws_bytes=16), dict(scales=(0.5,))):
         with pytest.raises(uq.UQError):
             call(**kw)
+
+
+@pytest.mark.parametrize("bits", [8, 4])
+def test_codes_go_to_the_buffer_the_step_holds(bits):
+    """A wider codes buffer put in the step's place (one allocation for several
+    layers): its own row stride counts, not the one the step was made with."""
+    d, M = 5000, 6
+    host = synth.mixed_rows(M, d, seed=8, ldg=synth.round_up(d, 64))
+    g = torch.from_numpy(host).to(DEV)
+    scales = [127.0 if bits == 8 else 7.0]
+    a, b = (Step(d, M, scales, device=DEV, bits=bits) for _ in range(2))
+    b.codes = torch.zeros((M, a.ldc + 512), dtype=torch.int8, device=DEV)
+    a.run(g, 4)
+    b.run(g, 4)
+    n = (d * bits + 7) // 8
+    assert torch.equal(a.codes[:, :n], b.codes[:, :n])
+    assert not b.codes[:, a.ldc:].any()
