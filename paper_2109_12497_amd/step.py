@@ -21,6 +21,17 @@ def round_up(x: int, m: int) -> int:
     return (x + m - 1) // m * m
 
 
+def overlap(a, b) -> bool:
+    """Whether the memory spanned by two strided tensors overlaps (whatever
+    storage objects they are views of)."""
+    def span(t):
+        last = sum((n - 1) * st for n, st in zip(t.shape, t.stride()))
+        return t.data_ptr(), t.data_ptr() + (last + 1) * t.element_size()
+
+    (a0, a1), (b0, b1) = span(a), span(b)
+    return a.numel() > 0 and b.numel() > 0 and a0 < b1 and b0 < a1
+
+
 class Step:
     """Buffers and call sequence for M workers' gradients g [M, ldg] fp32.
 
@@ -223,7 +234,7 @@ class RandKStep:
         stream = _stream(stream)  # resolved once for the step's calls
         # out is zeroed in the selection's key pass, unless g lies in out's
         # memory: then only after the gather
-        apart = g.untyped_storage().data_ptr() != self.out.untyped_storage().data_ptr()
+        apart = not overlap(g, self.out)
         uq_randk_select_gather(g, self.d, self.M, g.stride(0), self.k, seed, self.sel, self.sub, self.sub.stride(0),
                                self.out if apart else None, self.rk_ws, self.rk_ws_bytes, stream)
         self.inner.run(self.sub, seed, stream)

@@ -213,3 +213,21 @@ def test_gradients_in_the_steps_own_output():
     got = a.run(a.out.unsqueeze(0), 4)
     want = b.run(torch.from_numpy(host).to(DEV), 4)
     assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+
+
+def test_gradients_inside_the_output_under_another_storage():
+    """The output may not be zeroed before the gather where the gradients lie
+    in its memory, also when they come through an exchange that gives the same
+    memory a storage of its own."""
+    from paper_2109_12497_amd.step import RandKStep
+
+    d, M, k, ldg = 30_000, 4, 500, 30_016
+    host = synth.gaussian_rows(M, d, seed=12, ldg=ldg)
+    want = RandKStep(d, M, k, [127.0], device=DEV)
+    ref = want.run(torch.from_numpy(host).to(DEV), 9).clone()
+    st = RandKStep(d, M, k, [127.0], device=DEV)
+    st.out = torch.zeros(64 + M * ldg, dtype=torch.float32, device=DEV)
+    g = torch.from_dlpack(st.out[64:]).view(M, ldg)
+    assert g.untyped_storage().data_ptr() != st.out.untyped_storage().data_ptr()
+    g.copy_(torch.from_numpy(host))
+    assert torch.equal(st.run(g, 9), ref)
