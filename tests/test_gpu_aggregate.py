@@ -1,8 +1,6 @@
 """uq_aggregate (a whole step in one call) against the separate calls and the
-oracle, bit for bit, at the sizes where its routes and tiles change: one block
-up to 4096 coordinates, W formed by the rows pass itself while the norm has at
-most 1024 partials, 256-coordinate tiles with a partial last one, and each
-number of row pairs."""
+oracle, bit for bit, at the sizes where its routes and tiles change (SIZES),
+256-coordinate tiles with a partial last one, and each number of row pairs."""
 import numpy as np
 import pytest
 
@@ -19,9 +17,14 @@ import paper_2109_12497_amd as uq  # noqa: E402
 from paper_2109_12497_amd.step import Step  # noqa: E402
 
 DEV = torch.device("cuda:0")
-# (d, M): tile and route edges; M * ceil(d / 8192) = 1024 and 1025 partials
+# (d, M): tile and route edges: one block up to 4096 coordinates of 8 rows and
+# 2048 of more; W formed by the rows pass (its partials reduced by every wave,
+# two a lane from 65 a row on) up to 128 partials a row and 1024 in all; a
+# tile's rows split over four waves from 11 rows on
 SIZES = [(1, 1), (3, 2), (255, 3), (256, 5), (257, 8), (1000, 8), (2049, 16), (4095, 9), (4096, 4), (4097, 16),
-         (8193, 7), (65_537, 13), (100_003, 6), (64 * 8192, 16), (64 * 8192 + 5, 16), (300_001, 1)]
+         (8193, 7), (65_537, 13), (100_003, 6), (64 * 8192, 16), (64 * 8192 + 5, 16), (300_001, 1),
+         (2048, 11), (4096, 9), (20_001, 11), (64 * 8192 + 1, 4), (65 * 8192, 15), (128 * 8192, 8), (128 * 8192, 1),
+         (128 * 8192 + 1, 3), (128 * 8192, 13)]
 SCALES = {"s127": [127.0], "K4": synth.scales_for(8, 4), "crowded": [1.0, 2.0, 3.0, 127.0]}
 
 
@@ -134,3 +137,55 @@ def test_codes_go_to_the_buffer_the_step_holds(bits):
     n = (d * bits + 7) // 8
     assert torch.equal(a.codes[:, :n], b.codes[:, :n])
     assert not b.codes[:, a.ldc:].any()
+
+
+@pytest.mark.parametrize("M", [11, 16])
+@pytest.mark.parametrize("d", [1 << 21, (1 << 21) + 1])
+def test_rows_split_over_waves_at_its_last_size(M, d):
+    """One scale, 11 to 16 rows: up to 8192 tiles a tile's rows are split over
+    four waves, beyond one wave holds them all."""
+    g = torch.empty((M, synth.round_up(d, 64)), device=DEV)
+    g.normal_(0.0, 1e-3, generator=torch.Generator(device=DEV).manual_seed(d + M))
+    a, b = (Step(d, M, [127.0], device=DEV, quant_sum=True) for _ in range(2))
+    a.run(g, 21)
+    b.shared_scale(g, w_only=True)
+    for m in range(M):
+        b.quantize_sum(g[m:m + 1], 21, rows=1, worker0=m, accumulate=int(m > 0), reconstruct=m == M - 1)
+    assert torch.equal(a.w[:1].view(torch.int32), b.w[:1].view(torch.int32))
+    assert torch.equal(a.sum, b.sum) and torch.equal(a.out.view(torch.int32), b.out.view(torch.int32))
+
+
+# W given, not formed from the rows: the codes of finite values stay, and
+# infinite or NaN ones are 0 and do not raise a coordinate's index
+@pytest.mark.parametrize("W", [1.0, 1e-33])
+@pytest.mark.parametrize("d,M", [(700, 2), (5003, 5), (5003, 8), (20_001, 11), (20_001, 16)])
+@pytest.mark.parametrize("call", ["index_quantize", "index_quantize4", "index_quantize_sum", "quantize_sum"])
+def test_non_finite_values_under_a_finite_scale(call, d, M, W):
+    scales = [127.0] if call == "quantize_sum" else [7.0, 112.0, 1792.0]
+    host = synth.mixed_rows(M, d, seed=d * M, ldg=synth.round_up(d, 64))
+    host[:, :d] *= np.float32(0.3 * W) / np.abs(host[:, :d]).max()
+    rng = np.random.default_rng(d)
+    for value in (np.inf, -np.inf, np.nan):  # alone, in both rows of a pair, and in the last, ragged tile
+        for m, i in [(0, int(rng.integers(d))), (M - 1, int(rng.integers(d))), (M - 1, d - 1), (M // 2, d - 2),
+                     (min(1, M - 1), d - 1)]:
+            host[m, i] = value
+    host[:, d // 2] = np.nan  # no usable value in the coordinate
+    g = torch.from_numpy(host).to(DEV)
+    bits = 4 if call.endswith("4") else 8
+    st = Step(d, M, scales, device=DEV, bits=bits, quant_sum=call.endswith("sum"))
+    st.w[0] = W
+    getattr(st, call.rstrip("4"))(g, 31)
+    torch.cuda.synchronize()
+    ref = O.pipeline(host, scales, seed=31, d=d, W=np.float32(W))
+    assert np.abs(ref["codes"]).max() > 0
+    if len(scales) > 1:
+        assert np.array_equal(st.index_host(), ref["idx"])
+        assert len(np.unique(ref["idx"])) > 1
+    if call.endswith("sum"):
+        assert np.array_equal(st.sum[:d].cpu().numpy(), ref["sum"])
+        assert np.array_equal(st.out[:d].cpu().numpy().view(np.int32), ref["out"].view(np.int32))
+    else:
+        codes = st.codes.cpu().numpy()
+        got = codes[:, :d] if bits == 8 else np.stack([O.unpack_codes(codes[m].view(np.uint8)[:(d + 1) // 2], d, 4)
+                                                       for m in range(M)])
+        assert np.array_equal(got, ref["codes"])
