@@ -11,21 +11,23 @@ the 8 TB/s HBM peak the step's algorithmic bytes reach.
 The default workload is the largest that fits one GPU: d = 2^30 heavy-tailed
 (Student-t) coordinates, 16 workers streamed one at a time through a resident
 int32 sum, eight scales (Algorithm 2), each worker quantised and added into
-the sum in one fused call (with resident workers, one call quantises and sums
-all rows, and with several scales and at most 16 workers it also forms the
-shared scale index from the rows it holds, so the shared-scale call forms W
-only; workloads with packed codes store them, then sum them).
+the sum in one fused call (with at most 16 resident workers the whole step is
+one call, uq_aggregate: the norm, then one pass that quantises and sums all
+rows and with several scales forms the shared index from the rows it holds;
+workloads with packed codes store them too).
 
 Prints one JSON line: the step's rate, its stages' times and shares, the
 roofline of the stage with the largest share, the oracle's rate on one core
 and on all cores over a bounded sample, and the device's results on that
 sample checked against the oracle's.  Extra modes:
   --workload NAME       another workload of synth.WORKLOADS
-  --composed            codes stored, then summed (separate calls)
+  --composed            codes stored (streamed workers: then summed by a
+                        second call; resident workers: one call a step, which
+                        sums them as it stores them, or with one scale and
+                        codes the cache holds, after it)
   --index-pass          resident workers, several scales: the shared index
                         from the shared-scale call's own pass, not formed
-                        inside the quantise-and-sum (or, with packed codes,
-                        inside the quantiser)
+                        inside the pass that quantises every row
   --byte-index          the shared index as bytes, not 4-bit fields, where the
                         quantise-and-sum reads a separately formed one
   --graph               time replays of the step captured in a HIP graph
@@ -181,6 +183,73 @@ def plan_stages(d: int, M: int, K: int, bits: int = 8, streamed: bool = False, q
         st.append(dict(name="quantize", kernels=[qk], calls=1, bytes=quantize_bytes_per_launch(d, M, K, bits)))
         st.append(dict(name="sum_dequantize", kernels=["k_sum_dequant"], calls=1, bytes=M * cb + 4 * d + 4 * d + ib))
     return st
+
+
+# The limits of uq_aggregate's routes (launch_aggregate in uq_kernels.hip).
+BLOCK_STEP = {8: 4096, FUSED_MAX_ROWS: 2048}  # coordinates of a one-block step, by rows up to
+OWN_CHUNKS, OWN_PARTIALS = 128, 1024          # norm partials a row and in all that the rows pass reduces itself
+APART_BYTES, APART_ROWS = 256 << 20, 12
+
+
+def aggregate_route(d: int, M: int, K: int, bits: int) -> str:
+    """How one uq_aggregate call runs (bits = 0: no codes stored): "block",
+    one block; "own", the norm's partials, then a rows pass that forms W from
+    them; "pass", the norm, then a rows pass; "apart" (stored codes of one
+    scale), the norm, the quantiser and the sum."""
+    if d <= BLOCK_STEP[8 if M <= 8 else FUSED_MAX_ROWS]:
+        return "block"
+    chunk = 8192 * max(1, -(-d // (8192 * 1024)))
+    chunks = -(-d // chunk)
+    if chunks <= OWN_CHUNKS and M * chunks <= OWN_PARTIALS:
+        return "own"
+    if bits and K == 1 and (chunks > OWN_CHUNKS or M > APART_ROWS) and M * code_bytes(d, bits) <= APART_BYTES:
+        return "apart"
+    return "pass"
+
+
+def plan_one_call(d: int, M: int, K: int, bits: int = 8, quant_sum: bool = False) -> list:
+    """The stages of a step that is one uq_aggregate call, as plan_stages
+    gives them.  A stage with fn=None has no call of its own: its time is the
+    whole call's less the other stages'."""
+    route = aggregate_route(d, M, K, 0 if quant_sum else bits)
+    if route == "apart":
+        return plan_stages(d, M, K, bits)
+    rows_bytes = 4 * M * d + (d if K > 1 else 0) + (0 if quant_sum else M * code_bytes(d, bits)) + 4 * d + 4 * d
+    if quant_sum:
+        kernel = "k_index_quant_sum" if K > 1 else "k_quant_sum_split"
+        if K == 1 and M > 10 and d <= 256 << 13:
+            kernel = "k_quant_sum_waves"
+        elif K == 1 and M == 1 and route == "pass":
+            kernel = "k_quant_sum_set_deq"
+    else:
+        kernel = "k_index_quantise" + ("" if bits == 8 else f"_{bits}bit")
+    norm = shared_scale_bytes(d, M, 1)
+    if route == "block":
+        return [dict(name="aggregate", kernels=["k_step_small"], calls=1, bytes=norm + rows_bytes, fn=None)]
+    if route == "own":
+        return [dict(name="aggregate", kernels=["k_sumsq", kernel], calls=1, bytes=norm + rows_bytes, fn=None)]
+    # the call of its own that launches the same kernel, where there is one
+    fn = None
+    if quant_sum and K > 1:
+        fn = "index_quant_sum"
+    elif quant_sum and (M > 4 or M == 1):
+        fn = "quant_sum"
+    name = fn or ("rows_pass" if quant_sum else "quantize_and_sum")
+    return [dict(name="shared_scale", kernels=scale_kernels(M, 1), calls=1, bytes=norm),
+            dict(name=name, kernels=[kernel], calls=1, bytes=rows_bytes, fn=fn)]
+
+
+def step_path(step, d: int, M: int, K: int, bits: int) -> str:
+    """What the timed step does with its codes, for the line's config."""
+    if step.one_call:
+        route = aggregate_route(d, M, K, 0 if step.quant_sum else bits)
+        if route == "apart":
+            return "codes stored, then summed"
+        return (("quantise-and-sum fused" if step.quant_sum else "codes stored and summed in one pass")
+                + (", index formed in it" if K > 1 else ""))
+    if step.quant_sum:
+        return "quantise-and-sum fused"
+    return "codes stored, then summed"
 
 
 def algorithmic_bytes(d: int, M: int, K: int, streamed: bool, bits: int = 8, quant_sum: bool = False,
@@ -451,6 +520,7 @@ def bench_randk(args, g, cfg) -> int:
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
         "config": {"workload": args.workload, "d": d, "M": M, "scales": scales, "seed": seed, "randk": k,
                    "quantizer": "multi" if len(scales) > 1 else "single",
+                   "path": "gather and zeroing inside the selection's call; stages timed as calls of their own",
                    "launch": "hip graph replay per step" if args.graph else "host launches",
                    "parallelism": "one GPU, M workers simulated"},
         "stage_ms": stage_ms, "roofline": selection_roofline(d, stage_ms["select"]), "cpu_baseline": base}
@@ -529,11 +599,11 @@ def main() -> int:
     ap.add_argument("--warmup", type=int, default=20)
     ap.add_argument("--workload", default="student-t")
     ap.add_argument("--composed", action="store_true",
-                    help="quantise and sum in separate calls (the codes through HBM) instead of the fused "
-                         "quantise-and-sum (packed-code workloads always store their codes)")
+                    help="store the codes (the codes through HBM) instead of only adding them into the sum "
+                         "(packed-code workloads always store theirs)")
     ap.add_argument("--index-pass", action="store_true",
                     help="resident workers with several scales: the shared index from the shared-scale call's own "
-                         "pass instead of formed inside the quantise-and-sum or, with packed codes, the quantiser")
+                         "pass instead of formed inside the pass that quantises every row")
     ap.add_argument("--byte-index", action="store_true",
                     help="the quantise-and-sum reads a separately formed shared index as one byte per coordinate "
                          "instead of 4-bit fields")
@@ -605,17 +675,23 @@ def main() -> int:
     # -- per-stage times: each stage's call repeated back to back between two
     # events on the stream (mean over rounds), so host launch overhead does
     # not enter them; a stage's share of the step is calls x time per call
-    stages = plan_stages(d, M, K, bits, streamed, quant_sum, step.index_in_pass, step.index_bits)
+    # (a stage without a call of its own: the step's less the others')
+    if step.one_call:
+        stages = plan_one_call(d, M, K, bits, quant_sum)
+    else:
+        stages = plan_stages(d, M, K, bits, streamed, quant_sum, step.index_in_pass, step.index_bits)
     fns = stage_fns(step, g, seed, M)
     reps = stage_reps(args.steps, elapsed / args.steps)
+    rest = None
     for st in stages:
-        st["ms"] = stage_ms_per_call(torch, stream, fns[st["name"]], reps)
+        if st.get("fn", st["name"]) is None:
+            rest = st
+        else:
+            st["ms"] = stage_ms_per_call(torch, stream, fns[st["name"]], reps)
+    if rest is not None:
+        whole = stage_ms_per_call(torch, stream, replay, reps)
+        rest["ms"] = whole - sum(st["calls"] * st["ms"] for st in stages if st is not rest)
     step_bytes = sum(st["calls"] * st["bytes"] for st in stages)
-    # a step that is one call sums stored codes as it stores them (with one
-    # scale only when they exceed the 256 MB cache): they, and the index, are
-    # not read back as the separate calls timed above read them
-    if step.one_call and step.codes is not None and (K > 1 or M * code_bytes(d, bits) > 256 << 20):
-        step_bytes -= M * code_bytes(d, bits) + (d if K > 1 else 0)
     progress("stages timed: " + ", ".join(f"{st['name']} {st['ms']:.4f} ms x {st['calls']}" for st in stages))
 
     # -- the roofline of the stage with the largest share of the step: its
@@ -644,10 +720,7 @@ def main() -> int:
         "data": "synthetic",
         "config": {"workload": args.workload, "d": d, "M": M, "scales": scales, "seed": seed,
                    "quantizer": "multi" if K > 1 else "single", "streamed": streamed, "code_bits": bits,
-                   "path": ("quantise-and-sum fused, index formed in it" if step.index_in_pass and quant_sum
-                            else "quantise-and-sum fused" if quant_sum
-                            else "codes stored with the index formed in the quantiser, then summed"
-                            if step.index_in_pass else "codes stored, then summed"),
+                   "path": step_path(step, d, M, K, bits),
                    "index_bits": step.index_bits if K > 1 else None,
                    "launch": "hip graph replay per step" if args.graph else "host launches",
                    "parallelism": "one GPU, M workers simulated"},

@@ -123,6 +123,43 @@ def test_stage_plan_names_the_kernels():
         assert sum(s["calls"] for s in st[1:]) == M
 
 
+@pytest.mark.parametrize("d,M,K,bits,route", [
+    (4096, 8, 1, 8, "block"), (4097, 8, 1, 8, "own"), (2048, 16, 4, 0, "block"), (2049, 9, 4, 0, "own"),
+    (1 << 20, 8, 1, 8, "own"), ((1 << 20) + 1, 8, 1, 8, "apart"), ((1 << 20) + 1, 1, 4, 8, "pass"),
+    (1 << 19, 16, 1, 0, "own"), ((1 << 19) + 1, 16, 1, 0, "pass"),
+    (1 << 20, 12, 1, 8, "pass"), (1 << 20, 13, 1, 8, "apart"), (1 << 20, 16, 4, 8, "pass"),
+    (1 << 25, 8, 1, 8, "apart"), ((1 << 25) + 16, 8, 1, 8, "pass"), (1 << 26, 8, 1, 4, "apart"),
+    ((1 << 26) + 16, 8, 1, 4, "pass"), (1 << 25, 8, 1, 0, "pass")])
+def test_one_call_routes(d, M, K, bits, route):
+    assert bench.aggregate_route(d, M, K, bits) == route
+
+
+def test_one_call_stages():
+    """A resident step of at most 16 workers is one call: its stages are the
+    kernels that call launches, and stored codes are read back only where the
+    sum is a launch of its own."""
+    d = 25_557_032
+    for M, bits in ((8, 8), (16, 4)):
+        cb = bench.code_bytes(d, bits)
+        st = bench.plan_one_call(d, M, 4, bits)  # four scales: summed as they are stored
+        assert [s["name"] for s in st] == ["shared_scale", "quantize_and_sum"] and st[1]["fn"] is None
+        assert st[0]["kernels"] == ["k_sumsq", "k_finish"]
+        assert sum(s["bytes"] for s in st) == 8 * M * d + 9 * d + M * cb
+    # one scale: apart while the cache holds the codes, in one pass beyond
+    assert bench.plan_one_call(d, 8, 1, 8) == bench.plan_stages(d, 8, 1, 8)
+    st = bench.plan_one_call(d, 16, 1, 8)
+    assert st[1]["kernels"] == ["k_index_quantise"] and st[1]["bytes"] == 16 * 5 * d + 8 * d
+    # no codes stored: the call that launches the same kernel is timed
+    assert [(s["name"], s["kernels"]) for s in bench.plan_one_call(d, 8, 4, 8, True)[1:]] == \
+        [("index_quant_sum", ["k_index_quant_sum"])]
+    assert bench.plan_one_call(d, 8, 1, 8, True)[1]["fn"] == "quant_sum"
+    assert bench.plan_one_call(d, 4, 1, 8, True)[1]["fn"] is None
+    # small steps are one or two launches that no other call makes
+    assert [s["kernels"] for s in bench.plan_one_call(1000, 8, 1)] == [["k_step_small"]]
+    assert [s["kernels"] for s in bench.plan_one_call(1 << 20, 4, 1, 8, True)] == [["k_sumsq", "k_quant_sum_split"]]
+    assert bench.plan_one_call(1 << 20, 4, 1, 8, True)[0]["bytes"] == (8 * 4 + 8) << 20
+
+
 def test_stage_reps():
     assert bench.stage_reps(200, 0.163e-3) == 200
     assert bench.stage_reps(200, 66e-3) == 10

@@ -103,3 +103,18 @@ def test_randk_bench_line():
     assert base["kind"] == "oracle" and base["cores"] >= 1 and base["value"] > 0
     assert base["sample"].startswith("full workload")
     assert j["parity_vs_oracle"] == "bit-exact"
+
+
+@pytest.mark.parametrize("workload,extra,path,stages", [
+    ("resnet18-2bit", (), "codes stored, then summed", {"shared_scale", "quantize", "sum_dequantize"}),
+    ("vgg16-multi-4bit", (), "codes stored and summed in one pass, index formed in it",
+     {"shared_scale", "quantize_and_sum"}),
+    ("resnet50", ("--composed",), "codes stored and summed in one pass, index formed in it",
+     {"shared_scale", "quantize_and_sum"}),
+    ("resnet18", (), "quantise-and-sum fused", {"shared_scale", "quant_sum"})])
+def test_stages_of_one_call_steps(workload, extra, path, stages):
+    """The stages are those the timed step runs: their shares add up to it."""
+    j = run_bench(*extra, workload=workload, steps=30, warmup=10)
+    assert j["config"]["path"] == path and set(j["stage_ms"]) == stages
+    check_roofline(j, 0.85, 1.15)
+    assert j["pct_hbm_peak"] < 100 and j["parity_vs_oracle"] == "bit-exact"
