@@ -306,15 +306,17 @@ int uq_index_quantize(const float* g, int64_t d, int32_t M, int64_t ldg, const f
 /*
  * A whole aggregation step of Algorithm 1 (K = 1) or Algorithm 2 (K > 1) over
  * M resident workers in one call: uq_shared_scale with K = 1 (W only), then
- * one pass over the gradients that forms the shared index (K > 1), every
- * row's codes, their sums and the reconstruction.  Bit for bit the results of
+ * the shared index (K > 1), every row's codes, their sums and the
+ * reconstruction, in one pass over the gradients (but see Launches).  Bit for bit the results of
  * uq_shared_scale followed by uq_index_quantize_sum (bits = 0, K > 1),
  * uq_quantize_sum (bits = 0, K = 1, worker0 = 0), or the quantiser that stores
  * `bits`-bit codes (uq_index_quantize, uq_quantize_single or
  * uq_quantize_packed over all rows, worker0 = 0) and uq_sum_dequantize, given
- * the same W.  Small steps take fewer launches: one for d <= 4096, two while
- * the norm has at most 1024 partial sums (M * ceil(d / 8192) of them up to
- * d = 2^23), three beyond.
+ * the same W.  Launches: one for d <= 4096 with M <= 8, d <= 2048 with more
+ * rows; two while the norm has at most 128 partial sums a row and 1024 in all
+ * (ceil(d / 8192) a row up to d = 2^23); else three, or, for stored codes of
+ * one scale up to 256 MB (with at most 128 partial sums a row: from 13 rows),
+ * four, the codes then being read back by their sum.
  *   g, d, M, ldg   as for uq_shared_scale, 1 <= M <= 16; row m is worker m
  *   scales, K      host array of K floats, as for uq_dequantize
  *   bits           0: codes not stored (codes is ignored); 8: int8; 4 or 2:

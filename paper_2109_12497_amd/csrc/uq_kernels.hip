@@ -22,8 +22,12 @@
 //   k_index_quant_sum  all of up to 16 rows held at once: the     (Eq. (11) +
 //                shared index from their exact maxima, then        sharing, (12),
 //                k_quant_sum's codes, sums and reconstruction      sum, (13))
-//   k_quant_sum_split  one scale, 5 to 16 rows: the same with     (Eq. (8),
-//                no index                                          sum, (9))
+//   k_quant_sum_split  one scale, up to 16 rows: the same with    (Eq. (8),
+//                no index; k_quant_sum_waves: few coordinates      sum, (9))
+//                of 11 to 16 rows, a tile's rows over four waves
+//   k_index_quantise  either with the codes stored, and summed    (the same)
+//                and reconstructed as they are stored
+//   k_step_small a whole step of few coordinates in one block     (Alg. 1 / 2)
 //   k_dequant    int32 (+ index) -> fp32                          (Eq. (9)/(13))
 //
 // Every per-coordinate result is a pure function of its inputs and the
@@ -1651,22 +1655,6 @@ __global__ __launch_bounds__(64) void k_quant_sum(const float* __restrict__ g, i
     }
 }
 
-// ---------------------------------------------------------------------------
-// The shared scale index formed inside the quantise-and-sum over all M <=
-// kFuseRows rows (Sec. 3.2: Eq. (11) with scale sharing, then Eq. (12), the
-// sum and Eq. (13)).  One wave per 512-coordinate tile, as k_quant_sum, but
-// every row of the tile is loaded at once and held in registers: a
-// coordinate's index comes from its exact largest usable |g| over the rows,
-// and the rows are then quantised from registers, so neither the rows'
-// maxima nor an index pass over them is needed.  The index uses the
-// thresholds T_k of k_index_max (#{k : a <= T_k} - 1): when no binade holds
-// two thresholds, a table over the exponent field gives, for binade e, the
-// count above it and the bits of the one threshold inside it, and since the
-// bits of non-negative binary32 values order like the values, a coordinate
-// costs one lookup and one integer compare, exact with no ties to resolve.
-// ROWS is M rounded up to a power of two; rows past M re-read row M - 1
-// (no change to the maximum, no branch on the loads) and are not quantised.
-// ---------------------------------------------------------------------------
 // max(m, |x|, |y|) in one instruction (v_maximum3_f32, the absolute values
 // by source modifiers).  This maximum propagates NaN: the result is NaN if
 // any operand is, else infinite if any operand is, else the largest finite
@@ -1692,9 +1680,10 @@ __device__ __forceinline__ float max3_abs(float m, float x, float y)
 // words per coordinate without any work took 1.86 ms with four-wave blocks
 // and nontemporal stores, 1.61 ms with one-wave blocks, and 1.59 ms with
 // those and write-through stores (1.25 ms for the reads alone).  One quad per
-// lane and row keeps 16 rows in 64 registers, so four waves share a SIMD (two
-// with 512-coordinate tiles).  The tables are formed by the wave's first K
-// lanes and kept in LDS; a one-wave block has no barrier to wait at.
+// lane and row keeps 16 rows in 64 registers of 157 to 167 in all
+// (UQ_ROWS_WAVES: how many waves share a SIMD).  The tables are formed by the
+// wave's first K lanes and kept in LDS; a one-wave block has no barrier to
+// wait at.
 // ---------------------------------------------------------------------------
 struct RowTables {
     float inv[kMaxScales];  // s_k / W, times 2^16 when pre
@@ -2070,8 +2059,8 @@ __device__ __forceinline__ double largest_row(const double (&in)[ROWS])
 
 // Block b takes tile tile0 + b; the tile past the whole ones holds the last
 // coordinates.  There is no loop over tiles: with one, the compiler kept the
-// rows' keys and other loop invariants in registers (155 instead of 101 at 16
-// rows); a call with more tiles than the grid cap is several launches.
+// rows' keys and other loop invariants in registers and held far more of them;
+// a call with more tiles than the grid cap is several launches.
 // OWN is a template parameter because the partials' reduction, compiled in,
 // takes registers beside the rows (one scale: 8 rows 96 without, 102 with; 4
 // rows 80 and 86): 5 rows of 5.0 M coordinates 43.7 us with it as a branch,
@@ -2277,7 +2266,7 @@ __global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS, 13) void k_index_quantise(
 }
 
 // ---------------------------------------------------------------------------
-// A whole step in one block, for d <= kSmallStep coordinates of at most 16
+// A whole step in one block, for d <= small_step(M) coordinates of at most 16
 // rows: the rows' sums of squares in k_sumsq's order (one chunk a row: 256
 // threads), W by k_finish's rule, then one wave per 256-coordinate tile as
 // above.  At such sizes a step is launches and their latency.
@@ -2812,9 +2801,12 @@ hipError_t launch_index_quantise(const float* g, int64_t d, int32_t M, int64_t l
 }
 
 // Partials (all rows') up to which every wave of the rows pass forms W from
-// them itself instead of reading what k_finish formed, which takes a launch and a wait
-// (4 rows of 2^20 coordinates, 512 partials: the step 18.8 us with it, 13.4
-// without; 8 rows, 1024 partials, 2-bit codes stored: 27.0 and 21.3).
+// them itself instead of reading what k_finish formed, which takes a launch
+// and a wait: with the partials and with k_finish, 4 rows of 128 each 12.3
+// and 14.7 us, 8 rows of 64 13.1 and 15.0, of 128 (1024 in all) 19.8 and
+// 20.5, 16 rows of 64 21.3 and 22.4.  The gain shrinks towards both limits;
+// beyond them nothing was measured (more than 128 a row would take more than
+// two loads a lane).
 constexpr int64_t kOwnNormPartials = 1024;
 
 static hipError_t launch_step_small(const float* g, int64_t d, int32_t M, int64_t ldg, float* w, const ScaleSet& S,

@@ -52,7 +52,11 @@ class Step:
     default is True when those conditions hold.
     With resident rows, fused=True, M <= 16 and one scale or the index formed
     in the pass, run() is one call (uq_aggregate), which also adds stored
-    codes into the sum as it stores them.
+    codes into the sum as it stores them (with one scale and codes that the
+    cache holds it may sum them after).  Where the index is formed in the
+    pass, run() forms W as the one-scale norm does; shared_scale(g) with
+    several scales sums it in another order, so its W, and codes that depend
+    on it, can differ by one ulp (shared_scale(g, w_only=True) gives run()'s).
     index_bits=4 (several scales, quant_sum, index not formed in the pass):
     the shared index is held as 4-bit fields, two coordinates a byte
     (uq_shared_scale_idx4, uq_quantize_sum_idx4), so each call that reads it

@@ -122,8 +122,8 @@ def test_index_at_scale_limits(scales, crowded, M):
     """Coordinates at, and one ulp either side of, every scale's limit (the
     largest |g| with RN32(|g| s_k / W) <= s_0), in rows other than the one
     that sets W, plus magnitudes spread over many binades and denormals:
-    the table path (one limit per binade) and the count path (limits sharing
-    a binade), against the oracle."""
+    with one limit per binade and with several sharing one, against the
+    oracle."""
     Wv = np.float32(0.9)
     limits = []
     for k in range(1, len(scales)):

@@ -345,7 +345,7 @@ def test_many_maxima_in_a_thresholds_key_bucket(M, cap):
     host[0, :] = 0.0
     host[0, 0] = Wv  # a one-hot row: its norm is W
     assert np.sqrt((host.astype(np.float64) ** 2).sum(axis=1)).max() == np.float64(Wv)
-    uq.uq_set_grid_cap(cap)  # 8 blocks: the passes' grid-stride loops
+    uq.uq_set_grid_cap(cap)  # 8 blocks: the passes' grid-stride loops and further launches
     try:
         res, _, _ = gpu_step(host, d, scales, seed=9)
     finally:

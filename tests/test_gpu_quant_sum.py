@@ -203,8 +203,8 @@ def test_rows_split_over_waves_from_a_worker_offset():
 @pytest.mark.parametrize("cap", [8, 24])
 @pytest.mark.parametrize("M", [7, 16])
 def test_rows_split_over_waves_capped_grids(cap, M):
-    """Blocks striding over several tiles (their LDS sums alternate between
-    two buffers by tile); the results must not depend on the grid."""
+    """The rows pass as several launches (the grid capped far below one block
+    per tile); the results must not depend on the grid."""
     d = 100_003
     host = synth.mixed_rows(M, d, seed=cap + M, ldg=synth.round_up(d, 64))
     uq.uq_set_grid_cap(cap)
