@@ -1977,9 +1977,9 @@ __device__ __forceinline__ void rows_tile(const f32x4 (&A)[ROWS], const float* _
     }
 }
 
-// Where a rows pass takes W from: *w, or (part not null: the kernels' OWN
-// instances) the norm's chunk partials [rows][nchunks], reduced by every wave
-// for itself in k_finish's order; the first block then also stores it to *w.
+// Where a rows pass takes W from: *w, or (part not null) the norm's chunk
+// partials [rows][nchunks], reduced by every wave for itself in k_finish's
+// order; the first block then also stores it to *w.
 struct WSource {
     float* w;
     const double* part;
@@ -2001,14 +2001,21 @@ __device__ __forceinline__ void load_partials(const WSource& src, int32_t rows, 
         x[r] = lane < src.nchunks ? p[lane] : 0.0;
         y[r] = lane + 64 < src.nchunks ? p[lane + 64] : 0.0;
     }
-    // summed (and so waited for) here, before the rows' loads go out: left to
-    // the reduction, they would be waited for together with the rows (2^20
-    // coordinates of 4 rows: the step 13.4 us, 12.6 this way)
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
+    for (int r = 0; r < ROWS; ++r)
         s[r] = r < rows ? x[r] + y[r] : 0.0;
+}
+
+// Has the lane sums formed (and so their loads waited for) where it stands,
+// before the rows' loads go out: left to the reduction, they would be waited
+// for together with the rows (2^20 coordinates of 4 rows: the step 13.4 us,
+// 12.6 this way).
+template <int ROWS>
+__device__ __forceinline__ void settle(double (&s)[ROWS])
+{
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
         __asm__ volatile("" : "+v"(s[r]));
-    }
 }
 
 // One step of the rows' butterfly at distance `off` over N registers: row
@@ -2061,11 +2068,14 @@ __device__ __forceinline__ double largest_row(const double (&in)[ROWS])
 // coordinates.  There is no loop over tiles: with one, the compiler kept the
 // rows' keys and other loop invariants in registers and held far more of them;
 // a call with more tiles than the grid cap is several launches.
-// OWN is a template parameter because the partials' reduction, compiled in,
-// takes registers beside the rows (one scale: 8 rows 96 without, 102 with; 4
-// rows 80 and 86): 5 rows of 5.0 M coordinates 43.7 us with it as a branch,
-// 42.7 without.
-template <int ROWS, bool MULTI, int BITS, int POL, bool OWN>
+// NORM: W from memory, from the partials, or by a run-time branch.  With one
+// scale and no codes stored the two are compiled apart, because the partials'
+// reduction takes registers beside the rows (8 rows 96 without, 102 with; 4
+// rows 80 and 86): 5 rows of 5.0 M coordinates 43.7 us with the branch, 42.7
+// without.  Several scales and stored codes keep the branch: apart they were
+// no faster, 16 rows of VGG-16 size 0.3% slower, with 4-bit codes 0.7%.
+constexpr int kNormRead = 0, kNormOwn = 1, kNormEither = 2;
+template <int ROWS, bool MULTI, int BITS, int POL, int NORM>
 __device__ __forceinline__ void rows_block(const float* __restrict__ g, int64_t d, int32_t rows, int64_t ldg,
                                            int32_t worker0, const WSource& src, const ScaleSet& S, uint32_t key0,
                                            uint32_t key1, int64_t tile0, int32_t M, const RowsOut& o)
@@ -2082,17 +2092,20 @@ __device__ __forceinline__ void rows_block(const float* __restrict__ g, int64_t 
             T = tile0 + ((b & ~15u) | ((b & 7u) << 1) | ((b >> 3) & 1u));
     }
     const bool whole = T < d >> 8;
+    const bool own = NORM == kNormOwn || (NORM == kNormEither && src.part != nullptr);
     // the partials go out before the rows, whose loads they would wait behind
     double part[ROWS];
-    if (OWN)
+    if (own)
         load_partials<ROWS>(src, rows, part);
+    if (NORM == kNormOwn)
+        settle<ROWS>(part);
     f32x4 A[ROWS];
     if (whole)
         load_quads<ROWS, false>(g, ldg, rows, T, d, A);
     if (threadIdx.x < ROWS)
         tab.key[threadIdx.x] = row_key(quad_c1(T), static_cast<uint32_t>(worker0) + threadIdx.x, key0);
     float W;
-    if (OWN) {
+    if (own) {
         W = static_cast<float>(sqrt(largest_row<ROWS>(part)));
         if (T == 0 && threadIdx.x == 0)
             *src.w = W;
@@ -2131,7 +2144,7 @@ __global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS, 11) void k_quant_sum_split(
     const float* __restrict__ g, int64_t d, int32_t rows, int64_t ldg, int32_t worker0, WSource src, ScaleSet S,
     uint32_t key0, uint32_t key1, int64_t tile0, int32_t M, RowsOut o)
 {
-    rows_block<ROWS, false, 0, POL, OWN>(g, d, rows, ldg, worker0, src, S, key0, key1, tile0, M, o);
+    rows_block<ROWS, false, 0, POL, OWN ? kNormOwn : kNormRead>(g, d, rows, ldg, worker0, src, S, key0, key1, tile0, M, o);
 }
 
 // The same for few coordinates, a tile's rows split over the block's four
@@ -2161,9 +2174,11 @@ __global__ __launch_bounds__(256) void k_quant_sum_waves(
     const float* mine = g + static_cast<int64_t>(r0) * ldg;
     const uint32_t first = static_cast<uint32_t>(worker0) + static_cast<uint32_t>(r0);
     double part[RPW];
-    if (OWN)
+    if (OWN) {
         load_partials<RPW>(WSource{nullptr, src.part + static_cast<int64_t>(r0) * src.nchunks, src.nchunks}, n_read,
                            part);
+        settle<RPW>(part);
+    }
     f32x4 A[RPW];
     if (whole)
         load_quads<RPW, false>(mine, ldg, n_read, T, d, A);
@@ -2246,23 +2261,23 @@ __global__ __launch_bounds__(256) void k_quant_sum_waves(
 
 // Several scales, no codes stored; the shared index formed and stored: all M
 // rows, as workers 0 .. M - 1.
-template <int ROWS, int POL, bool OWN>
+template <int ROWS, int POL>
 __global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS, 13) void k_index_quant_sum(
     const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg, WSource src, ScaleSet S, uint32_t key0,
     uint32_t key1, int64_t tile0, RowsOut o)
 {
-    rows_block<ROWS, true, 0, POL, OWN>(g, d, M, ldg, 0, src, S, key0, key1, tile0, M, o);
+    rows_block<ROWS, true, 0, POL, kNormEither>(g, d, M, ldg, 0, src, S, key0, key1, tile0, M, o);
 }
 
 // The codes stored as BITS-bit fields, and (o.sum not null) summed and
 // reconstructed in the same pass, so that they are not read again.
-template <int ROWS, bool MULTI, int BITS, bool NT, bool OWN>
+template <int ROWS, bool MULTI, int BITS, bool NT>
 __global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS, 13) void k_index_quantise(
     const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg, WSource src, ScaleSet S, uint32_t key0,
     uint32_t key1, int64_t tile0, RowsOut o)
 {
-    rows_block<ROWS, MULTI, BITS, NT ? kStoreBoth : kStoreThrough, OWN>(g, d, M, ldg, 0, src, S, key0, key1, tile0, M,
-                                                                        o);
+    rows_block<ROWS, MULTI, BITS, NT ? kStoreBoth : kStoreThrough, kNormEither>(g, d, M, ldg, 0, src, S, key0, key1,
+                                                                                tile0, M, o);
 }
 
 // ---------------------------------------------------------------------------
@@ -2580,15 +2595,15 @@ static int one_scale_policy(int64_t d)
 // One scale, at most kFuseRows rows set and reconstructed in one call:
 // one block per 256-coordinate tile (the last one partial), one instance per
 // row pair count.
-#define UQ_ROW_PAIRS_1_TO_8(LAUNCH, STORES, OWN) \
-    LAUNCH(1, STORES, OWN);                      \
-    LAUNCH(2, STORES, OWN);                      \
-    LAUNCH(3, STORES, OWN);                      \
-    LAUNCH(4, STORES, OWN);                      \
-    LAUNCH(5, STORES, OWN);                      \
-    LAUNCH(6, STORES, OWN);                      \
-    LAUNCH(7, STORES, OWN);                      \
-    LAUNCH(8, STORES, OWN)
+#define UQ_ROW_PAIRS_1_TO_8(LAUNCH, ...) \
+    LAUNCH(1, __VA_ARGS__);              \
+    LAUNCH(2, __VA_ARGS__);              \
+    LAUNCH(3, __VA_ARGS__);              \
+    LAUNCH(4, __VA_ARGS__);              \
+    LAUNCH(5, __VA_ARGS__);              \
+    LAUNCH(6, __VA_ARGS__);              \
+    LAUNCH(7, __VA_ARGS__);              \
+    LAUNCH(8, __VA_ARGS__)
 
 // Tiles up to which 11 to 16 rows of one scale are split over four waves.
 constexpr int64_t kWavesTiles = int64_t(1) << 13;
@@ -2714,19 +2729,17 @@ static hipError_t launch_index_quant_sum_from(const float* g, int64_t d, int32_t
     const int64_t cap = one_shot_cap();
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += cap) {
         const dim3 grid(blocks_from(ntiles, tile0, cap));
-#define UQ_LAUNCH_IQS(PAIRS, POL, OWN)                                                                             \
+#define UQ_LAUNCH_IQS(PAIRS, POL)                                                                                  \
     case PAIRS:                                                                                                    \
-        hipLaunchKernelGGL((k_index_quant_sum<2 * PAIRS, POL, OWN>), grid, dim3(64), 0, stream, g, d, M, ldg, src, S,    \
+        hipLaunchKernelGGL((k_index_quant_sum<2 * PAIRS, POL>), grid, dim3(64), 0, stream, g, d, M, ldg, src, S,    \
                            key0, key1, tile0, o);                                                                  \
         break
-        if (src.part != nullptr) {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreThrough, true); }
-        } else if (policy == kStoreThrough) {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreThrough, false); }
+        if (policy == kStoreThrough) {
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreThrough); }
         } else if (policy == kStoreNontemporal) {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreNontemporal, false); }
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreNontemporal); }
         } else {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreBoth, false); }
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQS, kStoreBoth); }
         }
 #undef UQ_LAUNCH_IQS
     }
@@ -2756,31 +2769,29 @@ static hipError_t launch_stored_from(const float* g, int64_t d, int32_t M, int64
     const int64_t cap = one_shot_cap();
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += cap) {
         const dim3 grid(blocks_from(ntiles, tile0, cap));
-#define UQ_LAUNCH_IQ__(PAIRS, MULTI, BITS, NT, OWN)                                                                \
-    hipLaunchKernelGGL((k_index_quantise<2 * PAIRS, MULTI, BITS, NT, OWN>), grid, dim3(64), 0, stream, g, d, M,    \
-                       ldg, src, S, key0, key1, tile0, o)
-#define UQ_LAUNCH_IQ_(PAIRS, BITS, NT, OWN)                \
-    do {                                                   \
-        if (multi)                                         \
-            UQ_LAUNCH_IQ__(PAIRS, true, BITS, NT, OWN);    \
-        else                                               \
-            UQ_LAUNCH_IQ__(PAIRS, false, BITS, NT, OWN);   \
+#define UQ_LAUNCH_IQ__(PAIRS, MULTI, BITS, NT)                                                                     \
+    hipLaunchKernelGGL((k_index_quantise<2 * PAIRS, MULTI, BITS, NT>), grid, dim3(64), 0, stream, g, d, M, ldg,    \
+                       src, S, key0, key1, tile0, o)
+#define UQ_LAUNCH_IQ_(PAIRS, BITS, NT)                \
+    do {                                              \
+        if (multi)                                    \
+            UQ_LAUNCH_IQ__(PAIRS, true, BITS, NT);    \
+        else                                          \
+            UQ_LAUNCH_IQ__(PAIRS, false, BITS, NT);   \
     } while (0)
-#define UQ_LAUNCH_IQ(PAIRS, NT, OWN)              \
+#define UQ_LAUNCH_IQ(PAIRS, NT)                   \
     case PAIRS:                                   \
         if (bits == 8)                            \
-            UQ_LAUNCH_IQ_(PAIRS, 8, NT, OWN);     \
+            UQ_LAUNCH_IQ_(PAIRS, 8, NT);          \
         else if (bits == 4)                       \
-            UQ_LAUNCH_IQ_(PAIRS, 4, NT, OWN);     \
+            UQ_LAUNCH_IQ_(PAIRS, 4, NT);          \
         else                                      \
-            UQ_LAUNCH_IQ_(PAIRS, 2, NT, OWN);     \
+            UQ_LAUNCH_IQ_(PAIRS, 2, NT);          \
         break
-        if (src.part != nullptr) {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, false, true); }
-        } else if (nt) {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, true, false); }
+        if (nt) {
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, true); }
         } else {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, false, false); }
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, false); }
         }
 #undef UQ_LAUNCH_IQ
 #undef UQ_LAUNCH_IQ_
