@@ -217,7 +217,7 @@ def plan_one_call(d: int, M: int, K: int, bits: int = 8, quant_sum: bool = False
     rows_bytes = 4 * M * d + (d if K > 1 else 0) + (0 if quant_sum else M * code_bytes(d, bits)) + 4 * d + 4 * d
     if quant_sum:
         kernel = "k_index_quant_sum" if K > 1 else "k_quant_sum_split"
-        if K == 1 and M > 10 and d <= 256 << 13:
+        if K == 1 and ((M > 10 and d <= 256 << 13) or (M == 8 and 256 << 14 < d and 4 * d <= 46 << 20)):
             kernel = "k_quant_sum_waves"
         elif K == 1 and M == 1 and route == "pass":
             kernel = "k_quant_sum_set_deq"

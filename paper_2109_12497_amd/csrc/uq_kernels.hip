@@ -2147,14 +2147,17 @@ __global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS, 11) void k_quant_sum_split(
     rows_block<ROWS, false, 0, POL, OWN ? kNormOwn : kNormRead>(g, d, rows, ldg, worker0, src, S, key0, key1, tile0, M, o);
 }
 
-// The same for few coordinates, a tile's rows split over the block's four
-// waves: wave w codes rows w * RPW .. + RPW - 1 (and with OWN reduces their
+// The same with a tile's rows split over the block's four waves: wave w codes rows w * RPW .. + RPW - 1 (and with OWN reduces their
 // partials), the waves' sums meet in LDS, wave 0 stores the tile's sums and
 // wave 1 its outputs.  One wave holding every row leaves a SIMD two waves at
 // 11 rows and more, and few tiles fill those unevenly: 16 rows of 262,144
 // coordinates 13.9 us with one wave, 12.0 with four; 524,288 21.3 and 19.9;
 // 2^20 34.4 and 33.6; 12 rows 2^20 27.1 and 25.9; from 2^21 on the two are
-// equal, and with 10 rows and fewer one wave is faster (0.8 M 17.4 and 19.5).
+// equal, and with 9 or 10 rows one wave is faster (0.8 M 17.4 and 19.5).
+// 8 rows, two a wave: 5.0 M coordinates 62.7 and 61.8 us, 9.0 M 104.0 and
+// 101.7, 11.2 M 128.3 and 125.5 (3.1 M 43.0 and 43.5; fewer rows leave a wave
+// a single one: 7 rows' pass alone, in cache, 62.0 and 64.0, 5 rows' step 85.0
+// and 91.0).
 template <int RPW, bool OWN>
 __global__ __launch_bounds__(256) void k_quant_sum_waves(
     const float* __restrict__ g, int64_t d, int32_t rows, int64_t ldg, int32_t worker0, WSource src, ScaleSet S,
@@ -2605,22 +2608,28 @@ static int one_scale_policy(int64_t d)
     LAUNCH(7, __VA_ARGS__);              \
     LAUNCH(8, __VA_ARGS__)
 
-// Tiles up to which 11 to 16 rows of one scale are split over four waves.
+// Tiles up to which 11 to 16 rows of one scale are split over four waves, and
+// beyond which 8 are (up to kOutNontemporalBytes of outputs).
 constexpr int64_t kWavesTiles = int64_t(1) << 13;
+constexpr int64_t kPairTiles = int64_t(1) << 14;
 
 static hipError_t launch_quant_sum_split(const float* g, int64_t d, int32_t rows, int64_t ldg, int32_t worker0,
                                          const WSource& src, const ScaleSet& S, uint32_t key0, uint32_t key1,
                                          int32_t M, const RowsOut& o, hipStream_t stream)
 {
     const int64_t ntiles = (d + 255) >> 8;
-    if (rows > 10 && ntiles <= kWavesTiles) {
+    const bool few = rows > 10 && ntiles <= kWavesTiles;
+    if (few || (rows == 8 && ntiles > kPairTiles && 4 * d <= kOutNontemporalBytes)) {
         const int64_t cap = one_shot_cap();
         for (int64_t tile0 = 0; tile0 < ntiles; tile0 += cap) {
             const dim3 grid(blocks_from(ntiles, tile0, cap));
-#define UQ_LAUNCH_WAVES(OWN)                                                                                      \
-    hipLaunchKernelGGL((k_quant_sum_waves<4, OWN>), grid, dim3(256), 0, stream, g, d, rows, ldg, worker0, src, S, \
+#define UQ_LAUNCH_WAVES(RPW, OWN)                                                                                   \
+    hipLaunchKernelGGL((k_quant_sum_waves<RPW, OWN>), grid, dim3(256), 0, stream, g, d, rows, ldg, worker0, src, S, \
                        key0, key1, tile0, M, o)
-            if (src.part != nullptr) UQ_LAUNCH_WAVES(true); else UQ_LAUNCH_WAVES(false);
+            // (the norm has too many partials for OWN where 8 rows come here)
+            if (!few) UQ_LAUNCH_WAVES(2, false);
+            else if (src.part != nullptr) UQ_LAUNCH_WAVES(4, true);
+            else UQ_LAUNCH_WAVES(4, false);
 #undef UQ_LAUNCH_WAVES
         }
         return hipGetLastError();

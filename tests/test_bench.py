@@ -153,6 +153,7 @@ def test_one_call_stages():
     assert [(s["name"], s["kernels"]) for s in bench.plan_one_call(d, 8, 4, 8, True)[1:]] == \
         [("index_quant_sum", ["k_index_quant_sum"])]
     assert bench.plan_one_call(d, 8, 1, 8, True)[1]["fn"] == "quant_sum"
+    assert bench.plan_one_call(11_173_962, 8, 1, 8, True)[1]["kernels"] == ["k_quant_sum_waves"]
     assert bench.plan_one_call(d, 4, 1, 8, True)[1]["fn"] is None
     # small steps are one or two launches that no other call makes
     assert [s["kernels"] for s in bench.plan_one_call(1000, 8, 1)] == [["k_step_small"]]

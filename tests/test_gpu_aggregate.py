@@ -139,11 +139,13 @@ def test_codes_go_to_the_buffer_the_step_holds(bits):
     assert not b.codes[:, a.ldc:].any()
 
 
-@pytest.mark.parametrize("M", [11, 16])
-@pytest.mark.parametrize("d", [1 << 21, (1 << 21) + 1])
-def test_rows_split_over_waves_at_its_last_size(M, d):
-    """One scale, 11 to 16 rows: up to 8192 tiles a tile's rows are split over
-    four waves, beyond one wave holds them all."""
+@pytest.mark.parametrize("d,M", [(1 << 21, 11), ((1 << 21) + 1, 11), (1 << 21, 16), ((1 << 21) + 1, 16),
+                                 (1 << 22, 8), ((1 << 22) + 1, 8), ((1 << 22) + 255, 8), (12_058_624, 8),
+                                 (12_058_625, 8)])
+def test_rows_split_over_waves_at_its_edges(d, M):
+    """One scale: a tile's rows are split over four waves with 11 to 16 rows of
+    up to 8192 tiles, and with 8 rows beyond 16384 tiles up to 46 MB of
+    outputs; otherwise one wave holds them all."""
     g = torch.empty((M, synth.round_up(d, 64)), device=DEV)
     g.normal_(0.0, 1e-3, generator=torch.Generator(device=DEV).manual_seed(d + M))
     a, b = (Step(d, M, [127.0], device=DEV, quant_sum=True) for _ in range(2))
@@ -152,6 +154,12 @@ def test_rows_split_over_waves_at_its_last_size(M, d):
     for m in range(M):
         b.quantize_sum(g[m:m + 1], 21, rows=1, worker0=m, accumulate=int(m > 0), reconstruct=m == M - 1)
     assert torch.equal(a.w[:1].view(torch.int32), b.w[:1].view(torch.int32))
+    assert torch.equal(a.sum, b.sum) and torch.equal(a.out.view(torch.int32), b.out.view(torch.int32))
+    g[1, d - 1] = float("nan")  # under the same W, in the last tile
+    g[M - 1, 5] = float("inf")
+    a.quantize_sum(g, 21)
+    for m in range(M):
+        b.quantize_sum(g[m:m + 1], 21, rows=1, worker0=m, accumulate=int(m > 0), reconstruct=m == M - 1)
     assert torch.equal(a.sum, b.sum) and torch.equal(a.out.view(torch.int32), b.out.view(torch.int32))
 
 

@@ -110,9 +110,13 @@ def test_stores_of_the_one_scale_rows_pass(d, stores):
     assert [(k, a) for k, a, _ in ks] == [("k_quant_sum_split", (6, stores, 0))]
 
 
-# 11 to 16 rows of one scale: a tile's rows split over four waves up to 8192 tiles.
+# A tile's rows split over four waves (one scale): 11 to 16 rows up to 8192
+# tiles, 8 rows beyond 16384 tiles up to 46 MB of outputs.
 @pytest.mark.parametrize("d,M,kernel", [(100_003, 10, "k_quant_sum_split"), (100_003, 11, "k_quant_sum_waves"),
-                                        (1 << 21, 16, "k_quant_sum_waves"), ((1 << 21) + 1, 16, "k_quant_sum_split")])
+                                        (1 << 21, 16, "k_quant_sum_waves"), ((1 << 21) + 1, 16, "k_quant_sum_split"),
+                                        (1 << 22, 8, "k_quant_sum_split"), ((1 << 22) + 1, 8, "k_quant_sum_waves"),
+                                        ((1 << 22) + 1, 7, "k_quant_sum_split"), (11_173_962, 8, "k_quant_sum_waves"),
+                                        (12_058_624, 8, "k_quant_sum_waves"), (12_058_625, 8, "k_quant_sum_split")])
 def test_many_rows_split_over_waves(d, M, kernel):
     assert names(d, M, [127.0], quant_sum=True)[-1] == kernel
 
