@@ -2072,8 +2072,10 @@ __device__ __forceinline__ double largest_row(const double (&in)[ROWS])
 // scale and no codes stored the two are compiled apart, because the partials'
 // reduction takes registers beside the rows (8 rows 96 without, 102 with; 4
 // rows 80 and 86): 5 rows of 5.0 M coordinates 43.7 us with the branch, 42.7
-// without.  Several scales and stored codes keep the branch: apart they were
-// no faster, 16 rows of VGG-16 size 0.3% slower, with 4-bit codes 0.7%.
+// without.  So are up to 4 rows of stored codes (25.6 M coordinates, four
+// scales: one row 46.3 us with the branch, 44.9 without, 3 rows 80.5 and
+// 78.1).  The rest keep the branch: apart they were no faster, 16 rows of
+// VGG-16 size 0.3% slower, with 4-bit codes 0.7%.
 constexpr int kNormRead = 0, kNormOwn = 1, kNormEither = 2;
 template <int ROWS, bool MULTI, int BITS, int POL, int NORM>
 __device__ __forceinline__ void rows_block(const float* __restrict__ g, int64_t d, int32_t rows, int64_t ldg,
@@ -2273,14 +2275,16 @@ __global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS, 13) void k_index_quant_sum(
 }
 
 // The codes stored as BITS-bit fields, and (o.sum not null) summed and
-// reconstructed in the same pass, so that they are not read again.
-template <int ROWS, bool MULTI, int BITS, bool NT>
+// reconstructed in the same pass, so that they are not read again.  OWN (up to
+// 4 rows only): W from the partials; beyond, either way (see NORM).
+template <int ROWS, bool MULTI, int BITS, bool NT, bool OWN>
 __global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS, 13) void k_index_quantise(
     const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg, WSource src, ScaleSet S, uint32_t key0,
     uint32_t key1, int64_t tile0, RowsOut o)
 {
-    rows_block<ROWS, MULTI, BITS, NT ? kStoreBoth : kStoreThrough, kNormEither>(g, d, M, ldg, 0, src, S, key0, key1,
-                                                                                tile0, M, o);
+    constexpr int kNorm = ROWS > 4 ? kNormEither : OWN ? kNormOwn : kNormRead;
+    rows_block<ROWS, MULTI, BITS, NT ? kStoreBoth : kStoreThrough, kNorm>(g, d, M, ldg, 0, src, S, key0, key1, tile0,
+                                                                          M, o);
 }
 
 // ---------------------------------------------------------------------------
@@ -2778,29 +2782,32 @@ static hipError_t launch_stored_from(const float* g, int64_t d, int32_t M, int64
     const int64_t cap = one_shot_cap();
     for (int64_t tile0 = 0; tile0 < ntiles; tile0 += cap) {
         const dim3 grid(blocks_from(ntiles, tile0, cap));
-#define UQ_LAUNCH_IQ__(PAIRS, MULTI, BITS, NT)                                                                     \
-    hipLaunchKernelGGL((k_index_quantise<2 * PAIRS, MULTI, BITS, NT>), grid, dim3(64), 0, stream, g, d, M, ldg,    \
-                       src, S, key0, key1, tile0, o)
-#define UQ_LAUNCH_IQ_(PAIRS, BITS, NT)                \
-    do {                                              \
-        if (multi)                                    \
-            UQ_LAUNCH_IQ__(PAIRS, true, BITS, NT);    \
-        else                                          \
-            UQ_LAUNCH_IQ__(PAIRS, false, BITS, NT);   \
+#define UQ_LAUNCH_IQ__(PAIRS, MULTI, BITS, NT, OWN)                                                                \
+    hipLaunchKernelGGL((k_index_quantise<2 * PAIRS, MULTI, BITS, NT, OWN && (PAIRS <= 2)>), grid, dim3(64), 0,     \
+                       stream, g, d, M, ldg, src, S, key0, key1, tile0, o)
+#define UQ_LAUNCH_IQ_(PAIRS, BITS, NT, OWN)                \
+    do {                                                   \
+        if (multi)                                         \
+            UQ_LAUNCH_IQ__(PAIRS, true, BITS, NT, OWN);    \
+        else                                               \
+            UQ_LAUNCH_IQ__(PAIRS, false, BITS, NT, OWN);   \
     } while (0)
-#define UQ_LAUNCH_IQ(PAIRS, NT)                   \
+#define UQ_LAUNCH_IQ(PAIRS, NT, OWN)              \
     case PAIRS:                                   \
         if (bits == 8)                            \
-            UQ_LAUNCH_IQ_(PAIRS, 8, NT);          \
+            UQ_LAUNCH_IQ_(PAIRS, 8, NT, OWN);     \
         else if (bits == 4)                       \
-            UQ_LAUNCH_IQ_(PAIRS, 4, NT);          \
+            UQ_LAUNCH_IQ_(PAIRS, 4, NT, OWN);     \
         else                                      \
-            UQ_LAUNCH_IQ_(PAIRS, 2, NT);          \
+            UQ_LAUNCH_IQ_(PAIRS, 2, NT, OWN);     \
         break
-        if (nt) {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, true); }
+        if (src.part != nullptr) {
+            // (at most 1024 partials: never codes of 512 MB)
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, false, true); }
+        } else if (nt) {
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, true, false); }
         } else {
-            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, false); }
+            switch ((M + 1) / 2) { UQ_ROW_PAIRS_1_TO_8(UQ_LAUNCH_IQ, false, false); }
         }
 #undef UQ_LAUNCH_IQ
 #undef UQ_LAUNCH_IQ_

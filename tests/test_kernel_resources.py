@@ -42,3 +42,13 @@ def test_one_scale_rows_pass_holds_only_its_rows(kernels, rows, at_most):
     plain = {n: r for n, r in kernels.items() if re.search(rf"k_quant_sum_splitILi{rows}ELi\dELb0E", n)}
     assert len(plain) >= 3
     assert all(r <= at_most for r in plain.values()), plain
+
+
+@pytest.mark.parametrize("rows,at_most", [(2, 66), (4, 90)])
+def test_few_rows_of_stored_codes_hold_only_their_rows(kernels, rows, at_most):
+    """The same for up to 4 rows of stored codes (mangled as <rows, several
+    scales, bits, nontemporal, W from partials>): one row of 25.6 M
+    coordinates 46.3 us with the reduction's registers, 44.9 without."""
+    plain = {n: r for n, r in kernels.items() if re.search(rf"k_index_quantiseILi{rows}ELb\dELi\dELb\dELb0E", n)}
+    assert len(plain) == 12
+    assert all(r <= at_most for r in plain.values()), plain
