@@ -2282,7 +2282,7 @@ __global__ __launch_bounds__(64) UQ_ROWS_WAVES(ROWS, 13) void k_index_quantise(
     const float* __restrict__ g, int64_t d, int32_t M, int64_t ldg, WSource src, ScaleSet S, uint32_t key0,
     uint32_t key1, int64_t tile0, RowsOut o)
 {
-    constexpr int kNorm = ROWS > 4 ? kNormEither : OWN ? kNormOwn : kNormRead;
+    constexpr int kNorm = ROWS > 4 || OWN ? kNormEither : kNormRead;
     rows_block<ROWS, MULTI, BITS, NT ? kStoreBoth : kStoreThrough, kNorm>(g, d, M, ldg, 0, src, S, key0, key1, tile0,
                                                                           M, o);
 }
